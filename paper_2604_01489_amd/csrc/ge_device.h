@@ -16,6 +16,11 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2_t;
 
 #define GE_LDS __attribute__((address_space(3)))
 
+// 8 and 16 bytes at any address their element type allows: the compiler makes one vector access of it
+// (unaligned accesses to global memory are on for this target).
+struct __attribute__((packed, aligned(2))) u32x2_any_t { u32x2_t v; };
+struct __attribute__((packed, aligned(2))) i32x4_any_t { i32x4_t v; };
+
 enum { ACT_NONE = 0, ACT_RELU = 1, ACT_GELU_TANH = 2 };
 enum { DT_F32 = 0, DT_BF16 = 1 };
 
@@ -341,7 +346,8 @@ __device__ __forceinline__ void act_clamp_row_block(const GemmParams &p, f32x4_t
 
 // What row block (row m of this lane) needs from memory: its row scale and, per column block, the
 // lane's 4 residual elements as raw words (RES_BF16: two words of packed pairs; RES_F32: four).
-template <int RES, int TN, bool EDGE>
+// RAGGED: rows of any length at any address their type allows, so a lane's 4 columns may hang over p.N one by one.
+template <int RES, int TN, bool EDGE, bool RAGGED = false>
 __device__ __forceinline__ void fetch_row_block_t(const GemmParams &p, int b, int m, int colLane, float &rs, unsigned (&raw)[TN][4])
 {
     const bool rowOk = !EDGE || m < p.M;
@@ -352,7 +358,32 @@ __device__ __forceinline__ void fetch_row_block_t(const GemmParams &p, int b, in
         for (int j = 0; j < TN; ++j) {
             const int n = colLane + j * 16;
             const bool inside = !EDGE || (rowOk && n < p.N);
-            if constexpr (RES == RES_BF16) {
+            if constexpr (RAGGED) {
+                const bool whole = rowOk && n + 4 <= p.N;
+                if constexpr (RES == RES_BF16) {
+                    const unsigned short *src = (const unsigned short *)p.R + rowAt + n;
+                    u32x2_t t = {0u, 0u};
+                    if (whole) t = ((const u32x2_any_t *)src)->v;
+                    else if (inside) {
+                        t[0] = src[0];
+                        if (n + 1 < p.N) t[0] |= (unsigned)src[1] << 16;
+                        if (n + 2 < p.N) t[1] = src[2];
+                    }
+                    raw[j][0] = t[0];
+                    raw[j][1] = t[1];
+                } else {
+                    const unsigned *src = (const unsigned *)p.R + rowAt + n;
+                    i32x4_t t = {0, 0, 0, 0};
+                    if (whole) t = ((const i32x4_any_t *)src)->v;
+                    else if (inside) {
+#pragma unroll
+                        for (int r = 0; r < 3; ++r)
+                            if (n + r < p.N) t[r] = (int)src[r];
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) raw[j][r] = (unsigned)t[r];
+                }
+            } else if constexpr (RES == RES_BF16) {
                 u32x2_t t = {0u, 0u};
                 if (inside) t = *(const u32x2_t *)((const unsigned short *)p.R + rowAt + n);
                 raw[j][0] = t[0];
@@ -409,7 +440,7 @@ __device__ __forceinline__ void apply_row_block_t(const GemmParams &p, int b, f3
 
 // The lane's bias values for the swapped product: 4 consecutive columns from colLane + 16 j per
 // column block (colLane is a multiple of 4), in one piece where the pointer allows.
-template <int TN, bool EDGE>
+template <int TN, bool EDGE, bool RAGGED = false>
 __device__ __forceinline__ void fetch_bias_t(const GemmParams &p, int colLane, float (&bv)[TN][4])
 {
     const bool biasVec = (((unsigned long long)p.bias) & 15ull) == 0ull;
@@ -417,7 +448,10 @@ __device__ __forceinline__ void fetch_bias_t(const GemmParams &p, int colLane, f
     for (int j = 0; j < TN; ++j) {
         const int n = colLane + j * 16;
         const bool ok = p.bias != nullptr && (!EDGE || n < p.N);
-        if (biasVec) {
+        if (RAGGED) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) bv[j][r] = (ok && n + r < p.N) ? p.bias[n + r] : 0.0f;
+        } else if (biasVec) {
             f32x4_t t = {0.0f, 0.0f, 0.0f, 0.0f};
             if (ok) t = *(const f32x4_t *)(p.bias + n);
 #pragma unroll
@@ -431,7 +465,7 @@ __device__ __forceinline__ void fetch_bias_t(const GemmParams &p, int colLane, f
 
 // The chain over all row blocks of a wave tile and the parking of the results, as bf16, in the
 // row-major LDS image of the block tile.
-template <int RES, int BN, int TM, int TN, bool EDGE, int MODE = CHAIN_ANY>
+template <int RES, int BN, int TM, int TN, bool EDGE, int MODE = CHAIN_ANY, bool RAGGED = false>
 __device__ __forceinline__ void chain_and_park_t(const GemmParams &p, int b, f32x4_t (&acc)[TM][TN], const float (&bv)[TN][4],
                                         GE_LDS char *lds, int m0, int colLane, int tileRow, int tileCol)
 {
@@ -449,12 +483,12 @@ __device__ __forceinline__ void chain_and_park_t(const GemmParams &p, int b, f32
     unsigned raw[PF][TN][4];
 #pragma unroll
     for (int d = 0; d < PF - 1; ++d)
-        if (d < TM) fetch_row_block_t<RESF, TN, EDGE>(p, b, m0 + tileRow + d * 16, colLane, rs[d], raw[d]);
+        if (d < TM) fetch_row_block_t<RESF, TN, EDGE, RAGGED>(p, b, m0 + tileRow + d * 16, colLane, rs[d], raw[d]);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int row = tileRow + i * 16;
         if (i + PF - 1 < TM)
-            fetch_row_block_t<RESF, TN, EDGE>(p, b, m0 + row + (PF - 1) * 16, colLane, rs[(i + PF - 1) % PF], raw[(i + PF - 1) % PF]);
+            fetch_row_block_t<RESF, TN, EDGE, RAGGED>(p, b, m0 + row + (PF - 1) * 16, colLane, rs[(i + PF - 1) % PF], raw[(i + PF - 1) % PF]);
         if constexpr (RES == RES_BF16_LDS) {
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
@@ -490,10 +524,12 @@ __device__ __forceinline__ void chain_and_park_t(const GemmParams &p, int b, f32
 // waited for its own copies; the barrier below makes them visible, and each lane reads the pieces it replaces.
 // (tileRow, tileCol): row of this lane and first of its 4 columns in block (0, 0) of the wave
 // tile, relative to the block tile.
+// RAGGED (EDGE too): N, ldc, ldr and the pointers are anything their types allow; a row piece that hangs over
+// N leaves element by element.
 // NT: the row pieces leave with the non-temporal hint (C is not read back).  Measured at 8192^3 on the
 // four-wave kernel: 0.826 -> 0.811 ms; on the eight-wave kernel no gain (short-K batched shape, 8192^3
 // with A stored K x M) or a loss (3 x 3 convolution, 0.132 -> 0.135 ms), so only the former asks for it.
-template <int BM, int BN, int NW, int LDS_BYTES, int TM, int TN, bool EDGE, bool NT = false>
+template <int BM, int BN, int NW, int LDS_BYTES, int TM, int TN, bool EDGE, bool NT = false, bool RAGGED = false>
 __device__ __forceinline__ void fused_epilogue_bf16_through_lds(const GemmParams &p, int b, f32x4_t (&acc)[TM][TN], GE_LDS char *lds,
                                                        int m0, int n0, int tileRow, int tileCol, int w, int lane,
                                                        bool resInLds = false)
@@ -502,10 +538,10 @@ __device__ __forceinline__ void fused_epilogue_bf16_through_lds(const GemmParams
     static_assert(BM * PITCH <= LDS_BYTES, "bf16 image of the tile fits the stages");
     const int colLane = n0 + tileCol;
     float bv[TN][4];
-    fetch_bias_t<TN, EDGE>(p, colLane, bv);
+    fetch_bias_t<TN, EDGE, RAGGED>(p, colLane, bv);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // every wave is done with the stages
     // the case of activation and clamp, then the way the residual is read, each a uniform branch around the whole walk
-#define GE_PARK(RES_, MODE_) chain_and_park_t<RES_, BN, TM, TN, EDGE, MODE_>(p, b, acc, bv, lds, m0, colLane, tileRow, tileCol)
+#define GE_PARK(RES_, MODE_) chain_and_park_t<RES_, BN, TM, TN, EDGE, MODE_, RAGGED>(p, b, acc, bv, lds, m0, colLane, tileRow, tileCol)
 #define GE_PARK_BY_MODE(RES_)                                              \
     do {                                                                   \
         if (mode == CHAIN_RELU) GE_PARK(RES_, CHAIN_RELU);                 \
@@ -515,6 +551,10 @@ __device__ __forceinline__ void fused_epilogue_bf16_through_lds(const GemmParams
     } while (0)
     const int mode = chain_mode(p);
     if (p.R == nullptr) GE_PARK_BY_MODE(RES_NONE);
+    else if constexpr (RAGGED) {
+        if (p.rType == DT_BF16) GE_PARK_BY_MODE(RES_BF16);
+        else GE_PARK_BY_MODE(RES_F32);
+    }
     else if (resInLds) GE_PARK_BY_MODE(RES_BF16_LDS);
     else if (p.rVec && p.rType == DT_BF16) GE_PARK_BY_MODE(RES_BF16);
     else if (p.rVec) GE_PARK_BY_MODE(RES_F32);
@@ -530,7 +570,16 @@ __device__ __forceinline__ void fused_epilogue_bf16_through_lds(const GemmParams
         const int row = (it * NW + w) * ROWS_PER_INSTR + rowInGroup;
         const i32x4_t v = *(const GE_LDS i32x4_t *)(lds + row * PITCH + ((chunk ^ (row & (CHUNKS - 1))) << 4));
         const int m = m0 + row, n = n0 + chunk * 8;
-        if (!EDGE || (m < p.M && n < p.N)) {
+        if constexpr (RAGGED) {
+            if (m >= p.M) continue;
+            unsigned short *dst = cBase + (long long)m * p.ldc + n;
+            if (n + 8 <= p.N) ((i32x4_any_t *)dst)->v = v;
+            else {
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    if (n + e < p.N) dst[e] = (unsigned short)((unsigned)v[e >> 1] >> (16 * (e & 1)));
+            }
+        } else if (!EDGE || (m < p.M && n < p.N)) {
             if (NT) __builtin_nontemporal_store(v, (i32x4_t *)(cBase + (long long)m * p.ldc + n));
             else *(i32x4_t *)(cBase + (long long)m * p.ldc + n) = v;
         }

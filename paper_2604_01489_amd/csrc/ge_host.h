@@ -20,7 +20,7 @@ constexpr int kNumCU = 256;          // MI355X
 inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 
 // ---- shape -> plan -------------------------------------------------------
-enum TileKind { TILE_256 = 0, TILE_128 = 1, TILE_GENERIC = 2, TILE_SKINNY = 3 };
+enum TileKind { TILE_256 = 0, TILE_128 = 1, TILE_GENERIC = 2, TILE_SKINNY = 3, TILE_RAGGED_128 = 4, TILE_RAGGED_64 = 5 };
 
 struct Plan {
     TileKind tile;
@@ -77,9 +77,13 @@ enum { HALO_AUTO = 0, HALO_OFF = 1, HALO_ON = 2, HALO_VARIANT0 = 3 };
 int opt_conv_halo();
 
 int choose_split(long long tiles, int K, int minSlice);
-// skinny: the caller can launch the tall-skinny kernel (the plain operator only), so the plan may name it
+// Whether the kernel for operands of any alignment (gemm_ragged.h) takes a product the direct-to-LDS kernels do not:
+// rows of 8 elements or more, panels within 31-bit byte offsets, and enough work.
+bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bool transB);
+// skinny: the caller can launch the tall-skinny kernel (the plain operator only), so the plan may name it; ragged:
+// likewise the kernel for operands of any alignment, where `fast` is not given
 ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t plan, int split_k, Plan *out,
-                           bool skinny = false);
+                           bool skinny = false, bool ragged = false);
 size_t partial_bytes(int M, int N, int batch, int splitK);
 int choose_group_m(int tilesM, int tilesN);
 // The four-wave kernel (gemm_bf16_w4.h) takes launches of 256 x 256 tiles whose blocks walk a K range

@@ -10,6 +10,7 @@
 #include "../../include/gemm_epilogue.h"
 #include "gemm_fused.h"
 #include "gemm_fused_launch.h"
+#include "gemm_ragged_launch.h"
 #include "ge_host.h"
 
 namespace {
@@ -72,6 +73,11 @@ bool fast_ok(const ge_fused_args_t &a)
     return true;
 }
 
+bool ragged(const ge_fused_args_t &a)
+{
+    return !is_symmetric(a) && ragged_ok(a.M, a.N, a.K, a.batch, a.lda, a.transA != 0, a.ldb, a.transB != 0);
+}
+
 // 64 k per load phase (see the kernel) where both operands' rows run along k: measured at 8192^3
 // with bf16 output, 0.85 -> 0.81 ms for that layout and 0.75 -> 0.81 ms for each of the other three,
 // whose k-strided operands are fetched in whole lines anyway and only lose the deeper ring.
@@ -109,7 +115,7 @@ extern "C" size_t gemm_epilogue_fused_workspace_bytes(const ge_fused_args_t *arg
     Plan pl;
     const bool triangular = a.a_structure == GE_A_LOWER || a.a_structure == GE_A_UPPER;
     const bool fast = fast_ok(a) && !is_symmetric(a);
-    if (make_plan_bf16(a.M, a.N, a.K, a.batch, fast, triangular ? GE_PLAN_DIRECT : a.plan, a.split_k, &pl) != GE_OK) return 0;
+    if (make_plan_bf16(a.M, a.N, a.K, a.batch, fast, triangular ? GE_PLAN_DIRECT : a.plan, a.split_k, &pl, false, ragged(a)) != GE_OK) return 0;
     return partial_bytes(a.M, a.N, a.batch, pl.splitK);
 }
 
@@ -131,7 +137,7 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
     // unless the kernel for few output columns takes the call (below)
     const bool triangular = a.a_structure == GE_A_LOWER || a.a_structure == GE_A_UPPER;
     const ge_plan_t plan = triangular ? GE_PLAN_DIRECT : a.plan;
-    st = make_plan_bf16(a.M, a.N, a.K, a.batch, fast_ok(a) && !is_symmetric(a), plan, a.split_k, &pl);
+    st = make_plan_bf16(a.M, a.N, a.K, a.batch, fast_ok(a) && !is_symmetric(a), plan, a.split_k, &pl, false, ragged(a));
     if (st != GE_OK) return st;
 
     GemmParams p{};
@@ -201,6 +207,14 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
     case TILE_128:
         if (launch_tile<128>(pg, pl.edge, raw, grid, hs)) set_config("128x128x64_w4", a.transA, a.transB, raw);
         else set_config("128x128x32_w4", a.transA, a.transB, raw);
+        break;
+    case TILE_RAGGED_128:
+        launch_ragged_128(pg, raw, grid, hs);
+        set_config("ragged_128x128x64", a.transA, a.transB, raw);
+        break;
+    case TILE_RAGGED_64:
+        launch_ragged_64(pg, raw, grid, hs);
+        set_config("ragged_64x64x64", a.transA, a.transB, raw);
         break;
     default:
         if (raw) GE_LAUNCH(ge::gemm_bf16_fused_generic_kernel<true>, grid, dim3(256), 0, hs, pg);

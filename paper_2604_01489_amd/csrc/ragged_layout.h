@@ -1,0 +1,69 @@
+// Which 16-byte chunk of an operand of any alignment each lane brings in (gemm_ragged.h: bf16, gemm_f32_ragged.h: fp32), as
+// plain index functions that are compiled into the kernels and into the host-side model test.  The LDS layouts are
+// bf16_layout.h's.  E: elements of a 16-byte chunk, 8 or 4.
+//
+// bf16: a 64-k step of a tile BX wide is BX * 128 bytes, BX / 32 chunks of 8 elements per lane of the four waves.  STRIDED: the
+// operand's memory rows run along the tile's rows (M or N), and a step is two images of 32 k; else they run along k, and
+// a step is one image of 128-byte rows.  Offsets are in elements from the step's first one.
+#pragma once
+#include "bf16_layout.h"
+
+namespace ge {
+
+// chunk j of a lane: its row (k row if STRIDED) and chunk along it, and the 1 KB slab of LDS that it lands in (at 16 * lane)
+template <int BX, bool STRIDED>
+GE_HD constexpr void ragged_place(int j, int w, int lane, int &r, int &c, int &slab)
+{
+    if constexpr (STRIDED) {
+        constexpr int PER = BX / 64;
+        const int h = j / PER, wl = (j % PER) * 4 + w;
+        r = 32 * h + b_slot_k<BX>(wl, lane);
+        c = b_slot_chunk<BX>(wl, lane);
+        slab = h * (BX / 16) + wl;
+    } else {
+        slab = j * 4 + w;
+        r = a64_slot_row(slab, lane);
+        c = a64_slot_chunk(slab, lane);
+    }
+}
+
+// fp32: a 32-k step of a tile BX wide, BX / 32 chunks per lane, is two images of 16 k: 64-byte rows of A (along k), B in
+// rows of BX floats.
+template <int BX, bool STRIDED>
+GE_HD constexpr void ragged_place_f32(int j, int w, int lane, int &r, int &c, int &slab)
+{
+    constexpr int PER = BX / 64;
+    const int h = j / PER, wl = (j % PER) * 4 + w;
+    r = STRIDED ? 16 * h + b_slot_k<2 * BX>(wl, lane) : a_slot_row(wl, lane);
+    c = STRIDED ? b_slot_chunk<2 * BX>(wl, lane) : 4 * h + a_slot_chunk(lane);
+    slab = h * (BX / 16) + wl;
+}
+
+// A step that is not the block's last: `left` is the number of the operand's rows (columns if STRIDED) from the tile's
+// first.  Rows beyond are the last one again, chunks beyond the end of a row along M or N the tile's first; a chunk that
+// hangs over such an end reads on into the row after it, which exists: the step is not the last, and the rows (hence the
+// leading dimension) are at least E elements long.
+template <bool STRIDED, int E>
+GE_HD constexpr unsigned ragged_offset(int r, int c, int ld, int left)
+{
+    return STRIDED ? (unsigned)r * (unsigned)ld + (c * E < left ? (unsigned)(c * E) : 0u)
+                   : (unsigned)(r < left ? r : left - 1) * (unsigned)ld + (unsigned)(c * E);
+}
+
+// The last step, kLeft (at least 1) k of it inside: the chunk is pulled back until it ends inside its row, and what was read
+// is shifted down by sh elements (E or more: nothing of it is wanted), which puts zeros beyond the end.
+template <bool STRIDED, int E>
+GE_HD constexpr void ragged_last(int r, int c, int ld, int left, int kLeft, long long &off, int &sh)
+{
+    if constexpr (STRIDED) {
+        const int start = c * E < left ? c * E : 0, avail = left - start, back = avail < E ? E - avail : 0;
+        off = (long long)(r < kLeft ? r : kLeft - 1) * ld + start - back;
+        sh = r < kLeft ? back : E;
+    } else {
+        const int first = c * E <= kLeft - E ? c * E : kLeft - E;
+        off = (long long)(r < left ? r : left - 1) * ld + first;
+        sh = c * E - first;
+    }
+}
+
+}  // namespace ge

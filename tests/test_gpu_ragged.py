@@ -1,0 +1,76 @@
+"""The bf16 kernel for operands of any alignment (csrc/gemm_ragged.h) against the CPU oracles, on sizes around its tiles
+(64 and 128) and its 64-k steps, with rows that start at any 2-byte address, in every operand storage, output type and
+slicing of K.  Small products stay on the guarded kernel, so every case here has at least 2^24 multiply-adds.  The padding
+of the operands holds huge finite values and the last row ends where the allocation's payload ends (gpu_util)."""
+import os
+import subprocess
+
+import pytest
+
+from gpu_util import run_case, run_fused_case
+
+LAYOUTS = [(False, False), (False, True), (True, False), (True, True)]
+NAME = {(False, False): "nn", (False, True): "nt", (True, False): "tn", (True, True): "tt"}
+
+
+def test_ragged_layout_model(tmp_path):
+    """Host model of the loads and the LDS image, from the kernel's own index header."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    exe = str(tmp_path / "ragged_layout_check")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-o", exe, os.path.join(root, "tests", "ragged_layout_check.cpp")], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout[-2000:]
+    assert "ragged layout ok" in res.stdout
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,tile", [
+    (257, 259, 257, "64x64"),         # one over the tiles and the steps
+    (321, 383, 191, "64x64"),         # full tiles but for the last, one short of three steps
+    (9, 4099, 513, "64x64"),          # a sliver of one tile row
+    (4099, 9, 513, "64x64"),          # B's rows barely a chunk long
+    (2049, 2047, 9, "128x128"),       # one step, a chunk and one element
+    (2175, 2050, 67, "128x128"),      # one element over two tiles and a step
+])
+def test_ragged_plain(oracle, M, N, K, tile):
+    _, _, _, cfg = run_case(oracle, "bf16", M, N, K, alpha=0.5, act="gelu_tanh", seed=M + N + K)
+    assert cfg.replace("_splitk", "") == f"bf16_ragged_{tile}x64"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
+def test_ragged_layouts(oracle, transA, transB):
+    for M, N, K, kw in [(300, 301, 259, dict(pad=(1, 3, 2, 5), residual="f32", beta=0.5, clamp=(-0.1, 2.0), act="gelu_tanh")),
+                        (263, 519, 129, dict(out="bf16", residual="bf16", beta=-0.5, act="relu", pad=(0, 0, 1, 3), misalign=1)),
+                        (256, 512, 128, dict(out="bf16", residual="f32", misalign=3, pad=(0, 8, 1, 0))),
+                        (136, 137, 301, dict(batch=3, out="bf16", act="gelu_tanh", misalign=1))]:
+        _, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=transB, alpha=0.75, with_row_scale=True, plan="direct",
+                                      seed=M + N, **kw)
+        assert cfg == f"bf16_fused_ragged_64x64x64_{NAME[transA, transB]}"
+    for M, N, K, out in [(2063, 2049, 65, "bf16"), (2048, 2051, 70, "f32")]:
+        _, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=transB, with_row_scale=True, act="relu", out=out, plan="direct",
+                                      seed=M + K)
+        assert cfg == f"bf16_fused_ragged_128x128x64_{NAME[transA, transB]}"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("transA,transB", LAYOUTS)
+def test_ragged_k_slices(oracle, transA, transB):
+    """Slices that end inside a step, in slice order, bit for bit the same twice."""
+    outs = []
+    for _ in range(2):
+        got, _, _, cfg = run_fused_case(oracle, 131, 67, 2051, transA=transA, transB=transB, alpha=1.0 / 32, with_row_scale=True,
+                                        act="relu", out="bf16", plan="splitk", split_k=3, seed=7)
+        assert cfg == f"bf16_fused_ragged_64x64x64_{NAME[transA, transB]}_splitk"
+        outs.append(got.tobytes())
+    assert outs[0] == outs[1]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("structure", ["lower", "upper"])
+def test_ragged_triangular(oracle, structure):
+    """Blocks whose K range ends at, or starts inside, their own tile; some of them empty."""
+    for M, N, K in [(331, 197, 331), (131, 401, 517), (517, 401, 131)]:
+        for transA in (False, True):
+            _, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=True, alpha=0.5, act="relu", seed=M, a_structure=structure, plan="direct")
+            assert "ragged" in cfg
