@@ -74,3 +74,23 @@ def test_ragged_triangular(oracle, structure):
         for transA in (False, True):
             _, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=True, alpha=0.5, act="relu", seed=M, a_structure=structure, plan="direct")
             assert "ragged" in cfg
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,cfg", [
+    (257, 513, 33, "f32_generic_64x64x16"),            # one over the tiles and a 32-k step
+    (323, 517, 31, "f32_generic_64x64x16"),            # one step, not full
+    (321, 518, 95, "f32_generic_64x64x16"),            # three steps
+    (1000, 130, 5, "f32_generic_64x64x16"),            # barely more than a chunk of k
+    (2047, 1922, 33, "f32_generic_128x128x16"),
+    (1921, 2046, 66, "f32_generic_128x128x16"),
+    (300, 3, 50, "f32_generic_64x64x16"),              # rows of B shorter than a chunk
+    (130, 515, 3, "f32_generic_64x64x16"),             # rows of A shorter than a chunk
+    (70, 3, 1100, "f32_generic_64x64x16_splitk"),
+    (257, 515, 1061, "f32_generic_64x64x16_splitk"),   # slices that end inside a step
+])
+def test_f32_any_alignment(oracle, M, N, K, cfg):
+    """fp32 operands of any alignment (csrc/gemm_f32_ragged.h): odd sizes, odd leading dimensions, pointers off by 4 bytes."""
+    for kw in [dict(), dict(misalign=1, lda=K + 1, ldb=N + 3, ldc=N + 2)]:
+        _, _, _, got = run_case(oracle, "f32", M, N, K, alpha=0.5, act="gelu_tanh", seed=M + N + K, **kw)
+        assert got == cfg
