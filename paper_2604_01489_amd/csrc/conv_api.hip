@@ -31,14 +31,14 @@ void launch_conv(const GemmParams &p, bool edge, bool raw, dim3 grid, hipStream_
     constexpr int threads = WM * WN * 64;
     const bool h = p.cType == ge::DT_BF16;
     if (raw) {
-        if (edge) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, true, true, ge::ACT_NONE, false, true, false, false, true>), grid, dim3(threads), 0, st, p);
-        else      GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, false, true, ge::ACT_NONE, false, true, false, false, true>), grid, dim3(threads), 0, st, p);
+        if (edge) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 1, true, ge::ACT_NONE, false, true, false, false, true>), grid, dim3(threads), 0, st, p);
+        else      GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 0, true, ge::ACT_NONE, false, true, false, false, true>), grid, dim3(threads), 0, st, p);
     } else if (edge) {
-        if (h) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, true, false, ge::ACT_NONE, false, true, true, true, true>), grid, dim3(threads), 0, st, p);
-        else   GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, true, false, ge::ACT_NONE, false, true, true, false, true>), grid, dim3(threads), 0, st, p);
+        if (h) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 1, false, ge::ACT_NONE, false, true, true, true, true>), grid, dim3(threads), 0, st, p);
+        else   GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 1, false, ge::ACT_NONE, false, true, true, false, true>), grid, dim3(threads), 0, st, p);
     } else {
-        if (h) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, false, false, ge::ACT_NONE, false, true, true, true, true>), grid, dim3(threads), 0, st, p);
-        else   GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, false, false, ge::ACT_NONE, false, true, true, false, true>), grid, dim3(threads), 0, st, p);
+        if (h) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 0, false, ge::ACT_NONE, false, true, true, true, true>), grid, dim3(threads), 0, st, p);
+        else   GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 0, false, ge::ACT_NONE, false, true, true, false, true>), grid, dim3(threads), 0, st, p);
     }
 }
 
@@ -119,7 +119,7 @@ ge_status_t plan_conv(const ge_conv_args_t &a, ConvPlan *out)
 
     // gathering kernel: a K step is 32 channels of one tap, chunks of 8 channels are 16 aligned
     // bytes, byte offsets into the input fit 31 bits; bf16 output leaves in 16-byte row pieces
-    bool fast = !((((uintptr_t)a.X) | ((uintptr_t)a.Wt)) & 15u) && (a.Cin % 32 == 0) && (a.Cout % 8 == 0) &&
+    bool fast = !((((uintptr_t)a.X) | ((uintptr_t)a.Wt)) & 15u) && (a.Cin % 32 == 0) && (a.Cout % 8 == 0) && a.Cout < ge::EDGE_LDC_MAX &&
                 xElems * 2 < (1ll << 31) - (1 << 20) && K * 2 * 256 + 1024 < (1ll << 31);
     if (a.y_type == GE_DTYPE_BF16 && (((uintptr_t)a.Y) & 15u)) fast = false;
     out->OH = OH; out->OW = OW; out->M = M; out->K = K; out->xElems = xElems;

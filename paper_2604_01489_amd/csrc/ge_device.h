@@ -139,6 +139,36 @@ __device__ inline TileCoord map_block(const GemmParams &p)
     return c;
 }
 
+// Masked fp32 stores of a tile on the edge of C, without a branch per store: a raw-buffer resource that ends where the
+// row block's part of C ends drops what lies below it, and the lane offset of a column beyond N is out of any range.
+// (Under an exec mask each store is a basic block of its own: a wave of a 128 x 128 tile on the edge walked 6 KB of
+// code that no other block had brought into the instruction cache, 5 to 8 us: 576 x 3456 x 544 14.8 -> 8.4 us, 2040 x
+// 2040 x 2048 28.7 -> 23.0, the full 2048^3 21.9.)  ldc < EDGE_LDC_MAX, the host checks.
+constexpr int EDGE_LDC_MAX = 1 << 24;
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+
+// rows [row, row + BLOCK_ROWS) of C, columns from col on; row and col are wave-uniform
+template <int BLOCK_ROWS>
+__device__ __forceinline__ buffer_t edge_rows(float *c, long long ldc, int row, int M, int col, int N)
+{
+    row = __builtin_amdgcn_readfirstlane(row);
+    col = __builtin_amdgcn_readfirstlane(col);
+    const int rows = M - row < BLOCK_ROWS ? M - row : BLOCK_ROWS, cols = N - col;
+    const int bytes = rows > 0 && cols > 0 ? ((rows - 1) * (int)ldc + cols) * 4 : 0;
+    return __builtin_amdgcn_make_buffer_rsrc(c + (long long)row * ldc + col, 0, bytes, 0x00020000);
+}
+
+// byte offset of (laneRow, laneCol) in such a block, or out of range
+__device__ __forceinline__ unsigned edge_offset(int laneRow, int laneCol, long long ldc, int col, int N)
+{
+    return col + laneCol < N ? (unsigned)(laneRow * (int)ldc + laneCol) * 4u : 0x80000000u;
+}
+
+__device__ __forceinline__ void edge_store(buffer_t rows, unsigned offset, int row, long long ldc, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rows, (int)(offset + (unsigned)row * (unsigned)((int)ldc * 4)), 0, 0);
+}
+
 // gelu_tanh(v) = 0.5 v (1 + tanh u) with u = sqrt(2/pi) (v + 0.044715 v^3).
 // Since 0.5 (1 + tanh u) = 1 / (1 + exp(-2u)) this is v / (1 + exp(-2u)): one
 // exponential and one division, finite for every finite v (exp overflow gives
@@ -206,6 +236,43 @@ __device__ inline float epilogue_value_rt(float acc, float alpha, float bias, in
     if (act == ACT_RELU) return epilogue_value<ACT_RELU>(acc, alpha, bias);
     if (act == ACT_GELU_TANH) return epilogue_value<ACT_GELU_TANH>(acc, alpha, bias);
     return epilogue_value<ACT_NONE>(acc, alpha, bias);
+}
+
+// The plain operator's result, or (RAW) the fp32 partial sums of a K slice, of one wave tile straight from the
+// accumulators of the 16 x 16 blocks (register r of lane l: row 4*(l/16) + r, column l%16): row by row across the column
+// blocks.  MASK: the tile hangs over M or N.
+template <bool RAW, int ACT, bool MASK, int TM, int TN>
+__device__ __forceinline__ void store_plain_tile(const float *bias, float alpha, float *c, long long ldc, int M, int N, const f32x4_t (&acc)[TM][TN],
+                                                 int rowLane, int colLane)
+{
+    const int laneRow = 4 * (((int)threadIdx.x & 63) >> 4), laneCol = (int)threadIdx.x & 15;
+    float bv[TN];
+    unsigned at[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int n = !MASK || colLane + j * 16 < N ? colLane + j * 16 : N - 1;
+        bv[j] = !RAW && bias != nullptr ? bias[n] : 0.0f;
+        if (MASK) at[j] = edge_offset(laneRow, laneCol + 16 * j, ldc, colLane - laneCol, N);
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        buffer_t rows;
+        if constexpr (MASK) rows = edge_rows<16>(c, ldc, rowLane - laneRow + i * 16, M, colLane - laneCol, N);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float *rowPtr = c + (long long)(rowLane + i * 16 + r) * ldc + colLane;
+            // the row's values first, stage by stage over the column blocks, then its stores
+            float v[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) v[j] = acc[i][j][r];
+            if (!RAW) epilogue_values<ACT, TN>(v, alpha, bv);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if constexpr (MASK) edge_store(rows, at[j], r, ldc, v[j]);
+                else rowPtr[j * 16] = v[j];
+            }
+        }
+    }
 }
 
 // Nearest-even bf16 of an fp32 value, as its 16-bit pattern (the hardware conversion of gfx950).
@@ -350,10 +417,12 @@ __device__ __forceinline__ void act_clamp_row_block(const GemmParams &p, f32x4_t
 template <int RES, int TN, bool EDGE, bool RAGGED = false>
 __device__ __forceinline__ void fetch_row_block_t(const GemmParams &p, int b, int m, int colLane, float &rs, unsigned (&raw)[TN][4])
 {
+    // what lies beyond M or N is never stored: those lanes fetch the last row's (piece's) values, without a branch
     const bool rowOk = !EDGE || m < p.M;
-    rs = (p.rowScale != nullptr && rowOk) ? p.rowScale[m] : 1.0f;
+    const int mc = rowOk ? m : p.M - 1;
+    rs = p.rowScale != nullptr ? p.rowScale[mc] : 1.0f;
     if constexpr (RES == RES_BF16 || RES == RES_F32) {
-        const long long rowAt = (long long)b * p.strideR + (long long)m * p.ldr;
+        const long long rowAt = (long long)b * p.strideR + (long long)mc * p.ldr;
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int n = colLane + j * 16;
@@ -383,16 +452,17 @@ __device__ __forceinline__ void fetch_row_block_t(const GemmParams &p, int b, in
 #pragma unroll
                     for (int r = 0; r < 4; ++r) raw[j][r] = (unsigned)t[r];
                 }
-            } else if constexpr (RES == RES_BF16) {
-                u32x2_t t = {0u, 0u};
-                if (inside) t = *(const u32x2_t *)((const unsigned short *)p.R + rowAt + n);
-                raw[j][0] = t[0];
-                raw[j][1] = t[1];
             } else {
-                i32x4_t t = {0, 0, 0, 0};
-                if (inside) t = *(const i32x4_t *)((const float *)p.R + rowAt + n);
+                const int nc = !EDGE || n < p.N ? n : p.N - 4;
+                if constexpr (RES == RES_BF16) {
+                    const u32x2_t t = *(const u32x2_t *)((const unsigned short *)p.R + rowAt + nc);
+                    raw[j][0] = t[0];
+                    raw[j][1] = t[1];
+                } else {
+                    const i32x4_t t = *(const i32x4_t *)((const float *)p.R + rowAt + nc);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) raw[j][r] = (unsigned)t[r];
+                    for (int r = 0; r < 4; ++r) raw[j][r] = (unsigned)t[r];
+                }
             }
         }
     }
@@ -594,27 +664,22 @@ template <int RES, int TN, bool EDGE>
 __device__ __forceinline__ void fetch_row_block_n(const GemmParams &p, int b, int mFirst, int colLane, float (&rs)[4],
                                          unsigned (&raw)[4][TN])
 {
+    // (beyond M or N: the last row's and column's values, which are never stored)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int m = mFirst + r;
-        rs[r] = (p.rowScale != nullptr && (!EDGE || m < p.M)) ? p.rowScale[m] : 1.0f;
+        const int m = !EDGE || mFirst + r < p.M ? mFirst + r : p.M - 1;
+        rs[r] = p.rowScale != nullptr ? p.rowScale[m] : 1.0f;
     }
     if constexpr (RES != RES_NONE) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int m = mFirst + r;
-            const long long rowAt = (long long)b * p.strideR + (long long)m * p.ldr + colLane;
+            const int m = !EDGE || mFirst + r < p.M ? mFirst + r : p.M - 1;
+            const long long rowAt = (long long)b * p.strideR + (long long)m * p.ldr;
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const bool inside = !EDGE || (m < p.M && colLane + j * 16 < p.N);
-                unsigned t = 0u;
-                if constexpr (RES == RES_BF16) {
-                    if (inside) t = (unsigned)((const unsigned short *)p.R)[rowAt + j * 16];
-                    raw[r][j] = t << 16;
-                } else {
-                    if (inside) t = ((const unsigned *)p.R)[rowAt + j * 16];
-                    raw[r][j] = t;
-                }
+                const int n = !EDGE || colLane + j * 16 < p.N ? colLane + j * 16 : p.N - 1;
+                if constexpr (RES == RES_BF16) raw[r][j] = (unsigned)((const unsigned short *)p.R)[rowAt + n] << 16;
+                else raw[r][j] = ((const unsigned *)p.R)[rowAt + n];
             }
         }
     }
@@ -631,6 +696,12 @@ __device__ __forceinline__ void chain_and_store_n(const GemmParams &p, int b, f3
                                          int rowLane, int colLane)
 {
     float *cBase = p.C + (long long)b * p.strideC;
+    const int laneRow = 4 * (((int)threadIdx.x & 63) >> 4), laneCol = (int)threadIdx.x & 15;
+    unsigned at[TN];
+    if constexpr (EDGE) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) at[j] = edge_offset(laneRow, laneCol + 16 * j, p.ldc, colLane - laneCol, p.N);
+    }
     float rs[2][4];
     unsigned raw[2][4][TN];
     fetch_row_block_n<RES, TN, EDGE>(p, b, rowLane, colLane, rs[0], raw[0]);
@@ -651,13 +722,19 @@ __device__ __forceinline__ void chain_and_store_n(const GemmParams &p, int b, f3
                 for (int j = 0; j < TN; ++j) v[j][r] = __builtin_fmaf(p.beta, __uint_as_float(raw[i & 1][r][j]), v[j][r]);
         }
         act_clamp_row_block<TN, MODE>(p, v);
+        if constexpr (EDGE) {
+            const buffer_t rows = edge_rows<16>(cBase, p.ldc, rowLane - laneRow + i * 16, p.M, colLane - laneCol, p.N);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int m = rowLane + i * 16 + r;
-            float *rowPtr = cBase + (long long)m * p.ldc + colLane;
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                if (!EDGE || (m < p.M && colLane + j * 16 < p.N)) rowPtr[j * 16] = v[j][r];
+                for (int j = 0; j < TN; ++j) edge_store(rows, at[j], r, p.ldc, v[j][r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float *rowPtr = cBase + (long long)(rowLane + i * 16 + r) * p.ldc + colLane;
+#pragma unroll
+                for (int j = 0; j < TN; ++j) rowPtr[j * 16] = v[j][r];
+            }
         }
     }
 }
@@ -672,8 +749,8 @@ __device__ __forceinline__ void fused_epilogue_f32_direct(const GemmParams &p, i
     float bv[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-        const int n = colLane + j * 16;
-        bv[j] = (p.bias != nullptr && (!EDGE || n < p.N)) ? p.bias[n] : 0.0f;
+        const int n = !EDGE || colLane + j * 16 < p.N ? colLane + j * 16 : p.N - 1;
+        bv[j] = p.bias != nullptr ? p.bias[n] : 0.0f;
     }
 #define GE_STORE_BY_MODE(RES_)                                                                                          \
     do {                                                                                                               \

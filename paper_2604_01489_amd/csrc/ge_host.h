@@ -26,9 +26,10 @@ struct Plan {
     TileKind tile;
     int bm, bn, bk;
     int tilesM, tilesN;
+    bool edgeMN;     // tiles hang over M or N
     int splitK;      // >= 1
     int kPerSlice;
-    bool edge;
+    bool edge;       // tiles hang over M or N, or K ends inside a K step
 };
 
 extern thread_local const char *g_last_config;
@@ -78,8 +79,8 @@ int opt_conv_halo();
 
 int choose_split(long long tiles, int K, int minSlice);
 // Whether the kernel for operands of any alignment (gemm_ragged.h) takes a product the direct-to-LDS kernels do not:
-// rows of 8 elements or more, panels within 31-bit byte offsets, and enough work.
-bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bool transB);
+// rows of 8 elements or more, panels (and row blocks of C) within 31-bit byte offsets, and enough work.
+bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bool transB, int ldc);
 // skinny: the caller can launch the tall-skinny kernel (the plain operator only), so the plan may name it; ragged:
 // likewise the kernel for operands of any alignment, where `fast` is not given
 ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t plan, int split_k, Plan *out,
@@ -92,6 +93,8 @@ int choose_group_m(int tilesM, int tilesN);
 // kernel, for timing and for its tests.
 int four_wave_edge(const Plan &pl, int K);
 bool four_wave_ok(const Plan &pl, int K);
+// The same for the other tiled kernels, whose blocks advance `step` k per load phase (gemm_bf16_fast.h).
+int tile_edge(const Plan &pl, int K, int step);
 // The buffer for `need` bytes of partial results of a call on `stream`: the caller's, if it gave one
 // (checked for size and alignment), else the library's buffer for (current device, stream), grown by
 // hipMalloc when a larger one is first needed -- never while the stream is capturing (GE_ERR_WORKSPACE)

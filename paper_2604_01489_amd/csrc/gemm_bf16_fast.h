@@ -133,8 +133,11 @@ struct Bf16Tile {
     static_assert(2 * LOADS <= 63, "vmcnt range");
 };
 
-// EDGE: the tile may hang over M, N or the K range (loads are zero filled through
-// the buffer bounds check, stores are masked).  RAW: write fp32 partial sums for
+// EDGE: 0 full tiles; 1 the tile may hang over M or N (loads are zero filled through the buffer bounds check: the rows
+// and column chunks beyond are masked at the lane offsets, once, at no cost to the loop; stores are masked); 2 the K
+// range may also end inside a step, which masks every load by its k and recomputes the extents of the resources step by
+// step (scalar instructions between the barrier and the first MFMAs: 3064 x 1024 on the 128 x 128 tile takes 31.6 us at
+// K = 3008 and 38.9 at K = 3016).  RAW: write fp32 partial sums for
 // the split-K reduction (no scale, bias or activation) instead of C.
 //
 // TA / TB: the operand is stored transposed (A as K x M, B as N x K).  Only the staging differs:
@@ -158,8 +161,8 @@ struct Bf16Tile {
 // less slack than the three-of-four ring, which the full lines more than repay when both operands
 // are k-contiguous (measured: 8192^3 with both operands k-contiguous 0.85 -> 0.81 ms; with one
 // or none 0.75 -> 0.81 ms; the 3x3 convolution over 256 channels 0.139 -> 0.147 ms, so it is used
-// for the first only).  The K range of a block must be a multiple of 64 unless EDGE.
-template <int BM, int BN, int WM, int WN, bool EDGE, bool RAW, int ACT, bool TA = false, bool TB = false,
+// for the first only).  The K range of a block must be a multiple of 64 unless EDGE is 2.
+template <int BM, int BN, int WM, int WN, int EDGE, bool RAW, int ACT, bool TA = false, bool TB = false,
           bool FUSED = false, bool OUTBF16 = false, bool CONV = false, bool K64 = false>
 __global__ void __launch_bounds__(WM * WN * 64)
 gemm_bf16_kernel(const GemmParams p)
@@ -167,6 +170,7 @@ gemm_bf16_kernel(const GemmParams p)
     using T = Bf16Tile<BM, BN, WM, WN>;
     constexpr int BK = T::BK, NW = T::NW, TM = T::TM, TN = T::TN, LOADS = T::LOADS;
     constexpr bool PINGPONG = T::PINGPONG;
+    constexpr bool KEDGE = EDGE == 2;
     constexpr bool A64 = K64 && !TA, B64 = K64 && TB;     // operands staged in 128-byte rows
     static_assert(!(RAW && FUSED) && (FUSED || !OUTBF16), "partial tiles carry no epilogue; bf16 output is the fused one's");
     static_assert(!CONV || (!TA && TB && (FUSED || RAW) && !K64), "convolution: gathered k-contiguous A, filters as N x K, 32 k per step");
@@ -266,18 +270,18 @@ gemm_bf16_kernel(const GemmParams p)
     // issue_prep(kt) sets up tile kt (resource words, K-edge limit, tap offsets); issue_one(l, ...) then
     // issues its load l (A's first, then B's); issue() is both for all loads.
     rsrc_words_t rA, rB;
-    int kLeft = 0, dIh = 0, dIw = 0;                 // valid k in the tile (EDGE only); tap displacement (CONV only)
+    int kLeft = 0, dIh = 0, dIw = 0;                 // valid k in the tile (KEDGE only); tap displacement (CONV only)
     unsigned tapOff = 0u;
     auto issue_prep = [&](int kt) {
         const long long stepA = CONV ? 0ll : TA ? (long long)kt * BK * p.lda * 2 : (long long)kt * (BK * 2);
         const long long stepB = TB ? (long long)kt * (BK * 2) : (long long)kt * BK * p.ldb * 2;
         // Full tiles: every offset lies inside the operand by construction, and the exact extent
         // (ten scalar instructions per step, measured at 1-3 % of the 8192^3 run) is skipped.
-        // Edge tiles: the resource ends where the operand ends, so a lane that is not masked for
+        // K edges: the resource ends where the operand ends, so a lane that is not masked for
         // whatever reason reads zeros instead of memory beyond the allocation.  Computed
         // unconditionally, then selected: a conditional around it would be a scalar branch.
-        const unsigned leftA = (EDGE || CONV) ? records_left(p.bytesA, offA + stepA) : RSRC_RECORDS;
-        const unsigned leftB = EDGE ? records_left(p.bytesB, offB + stepB) : RSRC_RECORDS;
+        const unsigned leftA = (KEDGE || CONV) ? records_left(p.bytesA, offA + stepA) : RSRC_RECORDS;
+        const unsigned leftB = KEDGE ? records_left(p.bytesB, offB + stepB) : RSRC_RECORDS;
         rA = make_rsrc(gA + stepA, kt < nk ? leftA : 0u);
         rB = make_rsrc(gB + stepB, kt < nk ? leftB : 0u);
         kLeft = kLen - kt * BK;
@@ -298,12 +302,12 @@ gemm_bf16_kernel(const GemmParams p)
                 const bool inside = (unsigned)(ih0[CONV ? j : 0] + dIh) < (unsigned)p.convH && (unsigned)(iw0[CONV ? j : 0] + dIw) < (unsigned)p.convW;
                 v = inside ? v + tapOff : OOB_OFFSET;
             }
-            if (EDGE && kA[j] >= kLeft) v = OOB_OFFSET;
+            if (KEDGE && kA[j] >= kLeft) v = OOB_OFFSET;
             lds_dma16(rA, (unsigned)(size_t)(dA + (j * NW + w) * 1024), v);
         } else {
             const int j = l < T::A_LOADS ? 0 : l - T::A_LOADS;
             unsigned v = voffB[j];
-            if (EDGE && kB[j] >= kLeft) v = OOB_OFFSET;
+            if (KEDGE && kB[j] >= kLeft) v = OOB_OFFSET;
             lds_dma16(rB, (unsigned)(size_t)(dB + (j * NW + w) * 1024), v);
         }
     };
@@ -319,53 +323,53 @@ gemm_bf16_kernel(const GemmParams p)
     auto issue64 = [&](int t64, int stage) {
         GE_LDS char *dA = (GE_LDS char *)smem + stage * 2 * T::A_BYTES;
         GE_LDS char *dB = (GE_LDS char *)smem + 4 * T::A_BYTES + stage * 2 * T::B_BYTES;
-        const int kLeft = kLen - t64 * 64;           // valid k in this tile (EDGE only)
+        const int kLeft = kLen - t64 * 64;           // valid k in this tile (KEDGE only)
         if constexpr (A64) {
             const long long stepA = (long long)t64 * 128;
-            const unsigned leftA = EDGE ? records_left(p.bytesA, offA + stepA) : RSRC_RECORDS;
+            const unsigned leftA = KEDGE ? records_left(p.bytesA, offA + stepA) : RSRC_RECORDS;
             const rsrc_words_t rA = make_rsrc(gA + stepA, t64 < nk64 ? leftA : 0u);
 #pragma unroll
             for (int j = 0; j < NLA; ++j) {
                 unsigned v = voffA[j];
-                if (EDGE && kA[j] >= kLeft) v = OOB_OFFSET;
+                if (KEDGE && kA[j] >= kLeft) v = OOB_OFFSET;
                 lds_dma16(rA, (unsigned)(size_t)(dA + (j * NW + w) * 1024), v);
             }
         } else {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const long long stepA = (long long)(t64 * 64 + h * 32) * p.lda * 2;
-                const bool live = t64 < nk64 && (h == 0 || !EDGE || kLeft > 32);
-                const unsigned leftA = (EDGE && live) ? records_left(p.bytesA, offA + stepA) : RSRC_RECORDS;
+                const bool live = t64 < nk64 && (h == 0 || !KEDGE || kLeft > 32);
+                const unsigned leftA = (KEDGE && live) ? records_left(p.bytesA, offA + stepA) : RSRC_RECORDS;
                 const rsrc_words_t rA = make_rsrc(gA + stepA, live ? leftA : 0u);
 #pragma unroll
                 for (int j = 0; j < NLA; ++j) {
                     unsigned v = voffA[j];
-                    if (EDGE && kA[j] + 32 * h >= kLeft) v = OOB_OFFSET;
+                    if (KEDGE && kA[j] + 32 * h >= kLeft) v = OOB_OFFSET;
                     lds_dma16(rA, (unsigned)(size_t)(dA + h * T::A_BYTES + (j * NW + w) * 1024), v);
                 }
             }
         }
         if constexpr (B64) {
             const long long stepB = (long long)t64 * 128;
-            const unsigned leftB = EDGE ? records_left(p.bytesB, offB + stepB) : RSRC_RECORDS;
+            const unsigned leftB = KEDGE ? records_left(p.bytesB, offB + stepB) : RSRC_RECORDS;
             const rsrc_words_t rB = make_rsrc(gB + stepB, t64 < nk64 ? leftB : 0u);
 #pragma unroll
             for (int j = 0; j < NLB; ++j) {
                 unsigned v = voffB[j];
-                if (EDGE && kB[j] >= kLeft) v = OOB_OFFSET;
+                if (KEDGE && kB[j] >= kLeft) v = OOB_OFFSET;
                 lds_dma16(rB, (unsigned)(size_t)(dB + (j * NW + w) * 1024), v);
             }
         } else {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const long long stepB = (long long)(t64 * 64 + h * 32) * p.ldb * 2;
-                const bool live = t64 < nk64 && (h == 0 || !EDGE || kLeft > 32);
-                const unsigned leftB = (EDGE && live) ? records_left(p.bytesB, offB + stepB) : RSRC_RECORDS;
+                const bool live = t64 < nk64 && (h == 0 || !KEDGE || kLeft > 32);
+                const unsigned leftB = (KEDGE && live) ? records_left(p.bytesB, offB + stepB) : RSRC_RECORDS;
                 const rsrc_words_t rB = make_rsrc(gB + stepB, live ? leftB : 0u);
 #pragma unroll
                 for (int j = 0; j < NLB; ++j) {
                     unsigned v = voffB[j];
-                    if (EDGE && kB[j] + 32 * h >= kLeft) v = OOB_OFFSET;
+                    if (KEDGE && kB[j] + 32 * h >= kLeft) v = OOB_OFFSET;
                     lds_dma16(rB, (unsigned)(size_t)(dB + h * T::B_BYTES + (j * NW + w) * 1024), v);
                 }
             }
@@ -378,8 +382,8 @@ gemm_bf16_kernel(const GemmParams p)
     int kLeft64 = 0;
     auto issue64_prep = [&](int t64) {
         const long long step = (long long)t64 * 128;
-        const unsigned leftA = EDGE ? records_left(p.bytesA, offA + step) : RSRC_RECORDS;
-        const unsigned leftB = EDGE ? records_left(p.bytesB, offB + step) : RSRC_RECORDS;
+        const unsigned leftA = KEDGE ? records_left(p.bytesA, offA + step) : RSRC_RECORDS;
+        const unsigned leftB = KEDGE ? records_left(p.bytesB, offB + step) : RSRC_RECORDS;
         rA64 = make_rsrc(gA + step, t64 < nk64 ? leftA : 0u);
         rB64 = make_rsrc(gB + step, t64 < nk64 ? leftB : 0u);
         kLeft64 = kLen - t64 * 64;
@@ -388,12 +392,12 @@ gemm_bf16_kernel(const GemmParams p)
         if (l < NLA) {
             const int j = l < NLA ? l : 0;
             unsigned v = voffA[j];
-            if (EDGE && kA[j] >= kLeft64) v = OOB_OFFSET;
+            if (KEDGE && kA[j] >= kLeft64) v = OOB_OFFSET;
             lds_dma16(rA64, (unsigned)(size_t)((GE_LDS char *)smem + stage * 2 * T::A_BYTES + (j * NW + w) * 1024), v);
         } else {
             const int j = l < NLA ? 0 : l - NLA;
             unsigned v = voffB[j];
-            if (EDGE && kB[j] >= kLeft64) v = OOB_OFFSET;
+            if (KEDGE && kB[j] >= kLeft64) v = OOB_OFFSET;
             lds_dma16(rB64, (unsigned)(size_t)((GE_LDS char *)smem + 4 * T::A_BYTES + stage * 2 * T::B_BYTES + (j * NW + w) * 1024), v);
         }
     };
@@ -664,13 +668,13 @@ gemm_bf16_kernel(const GemmParams p)
             int laneE = lane, waveE = (int)(threadIdx.x >> 6);
             asm volatile("" : "+v"(laneE), "+v"(waveE));
             const bool resInLds = stage_residual_bf16<BM, BN, NW>(p, tc.b, (GE_LDS char *)smem, m0, n0, p.M, waveE, laneE);
-            fused_epilogue_bf16_through_lds<BM, BN, NW, T::LDS_BYTES, TM, TN, EDGE>(
+            fused_epilogue_bf16_through_lds<BM, BN, NW, T::LDS_BYTES, TM, TN, EDGE != 0>(
                 p, tc.b, acc, (GE_LDS char *)smem, m0, n0, (waveE / WN) * T::WTM + (laneE & 15),
                 (waveE % WN) * T::WTN + 4 * (laneE >> 4), waveE, laneE, resInLds);
         } else {
             // only the tiles that hang over M or N pay for masked stores (a uniform branch)
             if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) fused_epilogue_f32_direct<TM, TN, false>(p, tc.b, acc, rowLane, colLane);
-            else fused_epilogue_f32_direct<TM, TN, EDGE>(p, tc.b, acc, rowLane, colLane);
+            else fused_epilogue_f32_direct<TM, TN, EDGE != 0>(p, tc.b, acc, rowLane, colLane);
         }
     } else {
         float *cBase;
@@ -682,33 +686,9 @@ gemm_bf16_kernel(const GemmParams p)
             ldc = p.ldc;
             cBase = p.C + (long long)tc.b * p.strideC;
         }
-        auto store_tile = [&](auto masked) {
-            constexpr bool MASK = decltype(masked)::value;
-            float bv[TN];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int n = colLane + j * 16;
-                bv[j] = (!RAW && p.bias != nullptr && (!MASK || n < p.N)) ? p.bias[n] : 0.0f;
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = rowLane + i * 16 + r;
-                    float *rowPtr = cBase + (long long)m * ldc + colLane;
-                    // the row's values first, stage by stage over the column blocks, then its stores
-                    float v[TN];
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) v[j] = acc[i][j][r];
-                    if (!RAW) epilogue_values<ACT, TN>(v, p.alpha, bv);
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        if (!MASK || (m < p.M && colLane + j * 16 < p.N)) rowPtr[j * 16] = v[j];
-                }
-        };
         // only the tiles that hang over M or N pay for masked stores (a uniform branch)
-        if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) store_tile(std::false_type{});
-        else store_tile(std::true_type{});
+        if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) store_plain_tile<RAW, ACT, false>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
+        else store_plain_tile<RAW, ACT, EDGE != 0>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
     }
 }
 

@@ -330,30 +330,9 @@ gemm_bf16_w4_kernel(const GemmParams p)
             ldc = p.ldc;
             cBase = p.C + (long long)tc.b * p.strideC;
         }
-        auto store_tile = [&](auto masked) {
-            constexpr bool MASK = decltype(masked)::value;
-            float bv[TN];
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                bv[j] = (!RAW && p.bias != nullptr && (!MASK || colLane + j * 16 < p.N)) ? p.bias[colLane + j * 16] : 0.0f;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = rowLane + i * 16 + r;
-                    float *rowPtr = cBase + (long long)m * ldc + colLane;
-                    // the row's values first, stage by stage over the column blocks, then its stores
-                    float v[TN];
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) v[j] = acc[i][j][r];
-                    if (!RAW) epilogue_values<ACT, TN>(v, p.alpha, bv);
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        if (!MASK || (m < p.M && colLane + j * 16 < p.N)) rowPtr[j * 16] = v[j];
-                }
-        };
-        if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) store_tile(std::false_type{});
-        else store_tile(std::true_type{});
+        // only the tiles that hang over M or N pay for masked stores (a uniform branch)
+        if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) store_plain_tile<RAW, ACT, false>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
+        else store_plain_tile<RAW, ACT, EDGE != 0>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
     }
 }
 

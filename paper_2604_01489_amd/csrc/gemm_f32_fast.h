@@ -179,24 +179,45 @@ gemm_f32_fast_kernel(const GemmParams p)
     float *cBase = p.C + (long long)tc.b * p.strideC + (RAW ? (long long)tc.s * p.sliceStride : 0ll);
     const int rowLane = m0 + wm * T::WTM + 4 * g;
     const int colLane = n0 + wn * T::WTN + l32;
-    float bv[TN];
+    auto store_tile = [&](auto masked, auto actC) {
+        constexpr bool MASK = decltype(masked)::value;
+        constexpr int ACT = decltype(actC)::value;
+        float bv[TN];
+        unsigned at[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int n = colLane + j * 32;
-        bv[j] = (!RAW && p.bias != nullptr && (!EDGE || n < p.N)) ? p.bias[n] : 0.0f;
-    }
+        for (int j = 0; j < TN; ++j) {
+            const int n = !MASK || colLane + j * 32 < p.N ? colLane + j * 32 : p.N - 1;
+            bv[j] = !RAW && p.bias != nullptr ? p.bias[n] : 0.0f;
+            if (MASK) at[j] = edge_offset(4 * g, l32 + 32 * j, p.ldc, colLane - l32, p.N);
+        }
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
+            buffer_t rows;
+            if constexpr (MASK) rows = edge_rows<32>(cBase, p.ldc, rowLane - 4 * g + i * 32, p.M, colLane - l32, p.N);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int m = rowLane + i * 32 + 8 * (r >> 2) + (r & 3);
-            float *rowPtr = cBase + (long long)m * p.ldc + colLane;
+            for (int r = 0; r < 16; ++r) {
+                const int inBlock = 8 * (r >> 2) + (r & 3);
+                float *rowPtr = cBase + (long long)(rowLane + i * 32 + inBlock) * p.ldc + colLane;
+                float v[TN];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const float v = RAW ? acc[i][j][r] : epilogue_value_rt(acc[i][j][r], p.alpha, bv[j], p.act);
-                if (!EDGE || (m < p.M && colLane + j * 32 < p.N)) rowPtr[j * 32] = v;
+                for (int j = 0; j < TN; ++j) v[j] = acc[i][j][r];
+                if (!RAW) epilogue_values<ACT, TN>(v, p.alpha, bv);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    if constexpr (MASK) edge_store(rows, at[j], inBlock, p.ldc, v[j]);
+                    else rowPtr[j * 32] = v[j];
+                }
             }
         }
+    };
+    // the case of the activation, then the mask of a tile on the edge: uniform branches around the whole tile
+    auto store_by_mask = [&](auto actC) {
+        if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) store_tile(std::false_type{}, actC);
+        else store_tile(std::bool_constant<EDGE>{}, actC);
+    };
+    if (RAW || p.act == ACT_NONE) store_by_mask(std::integral_constant<int, ACT_NONE>{});
+    else if (p.act == ACT_RELU) store_by_mask(std::integral_constant<int, ACT_RELU>{});
+    else store_by_mask(std::integral_constant<int, ACT_GELU_TANH>{});
 }
 
 }  // namespace ge

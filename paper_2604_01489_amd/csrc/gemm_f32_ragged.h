@@ -16,7 +16,8 @@ namespace ge {
 
 struct __attribute__((packed, aligned(4))) f32x4_any_t { f32x4_t v; };
 
-// ELEMENTWISE: every element is fetched under its own test (rows shorter than a chunk, panels beyond 31-bit offsets).
+// ELEMENTWISE: every element is fetched under its own test (rows shorter than a chunk, panels or a C
+// beyond 31-bit offsets).
 template <int BX, bool STRIDED, bool ELEMENTWISE>
 struct RaggedChunksF32 {
     static constexpr int NL = BX / 32;
@@ -223,24 +224,36 @@ gemm_f32_ragged_kernel(const GemmParams p)
 
     // accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32
     const int rowLane = m0 + wm * WT + 4 * g, colLane = n0 + wn * WT + l32;
-    float *cBase = p.C + (long long)tc.b * p.strideC + (RAW ? (long long)tc.s * p.sliceStride : 0ll) + colLane;
+    float *cBase = p.C + (long long)tc.b * p.strideC + (RAW ? (long long)tc.s * p.sliceStride : 0ll);
     auto store_tile = [&](auto masked, auto actC) {
         constexpr bool MASK = decltype(masked)::value;
         constexpr int ACT = decltype(actC)::value;
         float bv[T];
+        unsigned at[T];
 #pragma unroll
-        for (int j = 0; j < T; ++j) bv[j] = (!RAW && p.bias != nullptr && (!MASK || colLane + j * 32 < p.N)) ? p.bias[colLane + j * 32] : 0.0f;
+        for (int j = 0; j < T; ++j) {
+            const int n = !MASK || colLane + j * 32 < p.N ? colLane + j * 32 : p.N - 1;
+            bv[j] = !RAW && p.bias != nullptr ? p.bias[n] : 0.0f;
+            if (MASK && !ELEMENTWISE) at[j] = edge_offset(4 * g, l32 + 32 * j, p.ldc, colLane - l32, p.N);
+        }
 #pragma unroll
-        for (int i = 0; i < T; ++i)
+        for (int i = 0; i < T; ++i) {
+            buffer_t rows;
+            if constexpr (MASK && !ELEMENTWISE) rows = edge_rows<32>(cBase, p.ldc, m0 + wm * WT + i * 32, p.M, colLane - l32, p.N);
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int m = rowLane + i * 32 + 8 * (r >> 2) + (r & 3);
+                const int inBlock = 8 * (r >> 2) + (r & 3), m = rowLane + i * 32 + inBlock;
+                float v[T];
+#pragma unroll
+                for (int j = 0; j < T; ++j) v[j] = acc[i][j][r];
+                if (!RAW) epilogue_values<ACT, T>(v, p.alpha, bv);
 #pragma unroll
                 for (int j = 0; j < T; ++j) {
-                    const float v = RAW ? acc[i][j][r] : epilogue_value<ACT>(acc[i][j][r], p.alpha, bv[j]);
-                    if (!MASK || (m < p.M && colLane + j * 32 < p.N)) cBase[(long long)m * p.ldc + j * 32] = v;
+                    if constexpr (MASK && !ELEMENTWISE) edge_store(rows, at[j], inBlock, p.ldc, v[j]);
+                    else if (!MASK || (m < p.M && colLane + j * 32 < p.N)) cBase[(long long)m * p.ldc + colLane + j * 32] = v[j];
                 }
             }
+        }
     };
     // the case of the activation, then the mask of a tile on the edge: uniform branches around the whole tile
     auto store_by_mask = [&](auto actC) {

@@ -62,6 +62,7 @@ bool fast_ok(const ge_fused_args_t &a)
 {
     if ((((uintptr_t)a.A) | ((uintptr_t)a.B)) & 15u) return false;
     if ((a.lda | a.ldb) & 7) return false;
+    if (a.ldc >= ge::EDGE_LDC_MAX) return false;
     if ((a.transA ? a.M : a.K) & 7) return false;
     if ((a.K | a.N) & 7) return false;            // B's row payload; N also for the 16-byte pieces of a bf16 C
     // bf16 output leaves the kernel in 16-byte row pieces
@@ -75,7 +76,7 @@ bool fast_ok(const ge_fused_args_t &a)
 
 bool ragged(const ge_fused_args_t &a)
 {
-    return !is_symmetric(a) && ragged_ok(a.M, a.N, a.K, a.batch, a.lda, a.transA != 0, a.ldb, a.transB != 0);
+    return !is_symmetric(a) && ragged_ok(a.M, a.N, a.K, a.batch, a.lda, a.transA != 0, a.ldb, a.transB != 0, a.ldc);
 }
 
 // 64 k per load phase (see the kernel) where both operands' rows run along k: measured at 8192^3
@@ -88,17 +89,23 @@ bool stage_k64(bool transA, bool transB)
     return !transA && transB;
 }
 
-// A 64-k stage needs the K range of every block to be a multiple of 64, or the edge variant.
 template <int BM>
-bool launch_tile(const GemmParams &p, bool edge, bool raw, dim3 grid, hipStream_t st)
+bool launch_tile(const GemmParams &p, const Plan &pl, bool raw, dim3 grid, hipStream_t st)
 {
     // 128 x 128 blocks: only where more than one block shares a CU (measured with both operands along
     // k, bf16 out: 4096x2048x2048, 512 blocks, 33 us with 64 k per load phase against 44 us with 32;
     // 2048^3, 256 blocks, 27 against 22 us; 2048x2048x8192 81 against 66 us)
     const bool k64 = stage_k64(p.transA != 0, p.transB != 0) && (BM == 256 || grid.x > (unsigned)kNumCU);
-    if (k64) edge = edge || (p.K % 64) || (p.kPerSlice % 64);
-    if (BM == 256) { if (edge) fused_tile_256_edge(p, k64, raw, grid, st); else fused_tile_256_full(p, k64, raw, grid, st); }
-    else           { if (edge) fused_tile_128_edge(p, k64, raw, grid, st); else fused_tile_128_full(p, k64, raw, grid, st); }
+    const int edge = tile_edge(pl, p.K, k64 ? 64 : 32);
+    if (BM == 256) {
+        if (edge == 2) fused_tile_256_kedge(p, k64, raw, grid, st);
+        else if (edge == 1) fused_tile_256_edge(p, k64, raw, grid, st);
+        else fused_tile_256_full(p, k64, raw, grid, st);
+    } else {
+        if (edge == 2) fused_tile_128_kedge(p, k64, raw, grid, st);
+        else if (edge == 1) fused_tile_128_edge(p, k64, raw, grid, st);
+        else fused_tile_128_full(p, k64, raw, grid, st);
+    }
     return k64;
 }
 
@@ -201,11 +208,11 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
             else if (mode == 1) fused_four_wave_e1(pg, raw, grid, hs);
             else fused_four_wave_e0(pg, raw, grid, hs);
             set_config("256x256x64_w4", a.transA, a.transB, raw);
-        } else if (launch_tile<256>(pg, pl.edge, raw, grid, hs)) set_config("256x256x64_w8", a.transA, a.transB, raw);
+        } else if (launch_tile<256>(pg, pl, raw, grid, hs)) set_config("256x256x64_w8", a.transA, a.transB, raw);
         else set_config("256x256x32_w8", a.transA, a.transB, raw);
         break;
     case TILE_128:
-        if (launch_tile<128>(pg, pl.edge, raw, grid, hs)) set_config("128x128x64_w4", a.transA, a.transB, raw);
+        if (launch_tile<128>(pg, pl, raw, grid, hs)) set_config("128x128x64_w4", a.transA, a.transB, raw);
         else set_config("128x128x32_w4", a.transA, a.transB, raw);
         break;
     case TILE_RAGGED_128:

@@ -5,7 +5,7 @@ namespace ge_host {
 
 void fused_tile_256_full(const ge::GemmParams &p, bool k64, bool raw, dim3 grid, hipStream_t st)
 {
-    launch_tile_mode<256, 256, 2, 4, false>(p, k64, raw, grid, st);
+    launch_tile_mode<256, 256, 2, 4, 0>(p, k64, raw, grid, st);
 }
 
 }  // namespace ge_host

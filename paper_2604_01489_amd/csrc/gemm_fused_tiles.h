@@ -8,7 +8,7 @@
 namespace ge_host {
 
 // MODE: 0 = fp32 partial tiles (split-K), 1 = fused epilogue with fp32 output, 2 = with bf16 output
-template <int BM, int BN, int WM, int WN, bool EDGE, int MODE, bool K64>
+template <int BM, int BN, int WM, int WN, int EDGE, int MODE, bool K64>
 void launch_layout(const GemmParams &p, dim3 grid, hipStream_t st)
 {
     constexpr int threads = WM * WN * 64;
@@ -24,7 +24,7 @@ void launch_layout(const GemmParams &p, dim3 grid, hipStream_t st)
     }
 }
 
-template <int BM, int BN, int WM, int WN, bool EDGE>
+template <int BM, int BN, int WM, int WN, int EDGE>
 void launch_tile_mode(const GemmParams &p, bool k64, bool raw, dim3 grid, hipStream_t st)
 {
     const int mode = raw ? 0 : p.cType == ge::DT_BF16 ? 2 : 1;

@@ -236,21 +236,9 @@ gemm_bf16_ragged_kernel(const GemmParams p)
             if (m0 + BT <= p.M && n0 + BT <= p.N) fused_epilogue_f32_direct<T, T, false>(p, tc.b, acc, rowLane, colLane);
             else fused_epilogue_f32_direct<T, T, true>(p, tc.b, acc, rowLane, colLane);
         } else {
-            float *cBase = p.C + (long long)tc.s * p.sliceStride + (long long)tc.b * p.M * p.N + colLane;
-            auto store_partial = [&](auto masked) {
-                constexpr bool MASK = decltype(masked)::value;
-#pragma unroll
-                for (int i = 0; i < T; ++i)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int m = rowLane + i * 16 + r;
-#pragma unroll
-                        for (int j = 0; j < T; ++j)
-                            if (!MASK || (m < p.M && colLane + j * 16 < p.N)) cBase[(long long)m * p.N + j * 16] = acc[i][j][r];
-                    }
-            };
-            if (m0 + BT <= p.M && n0 + BT <= p.N) store_partial(std::false_type{});
-            else store_partial(std::true_type{});
+            float *cBase = p.C + (long long)tc.s * p.sliceStride + (long long)tc.b * p.M * p.N;
+            if (m0 + BT <= p.M && n0 + BT <= p.N) store_plain_tile<true, ACT_NONE, false>(nullptr, 1.0f, cBase, p.N, p.M, p.N, acc, rowLane, colLane);
+            else store_plain_tile<true, ACT_NONE, true>(nullptr, 1.0f, cBase, p.N, p.M, p.N, acc, rowLane, colLane);
         }
     }
 }
