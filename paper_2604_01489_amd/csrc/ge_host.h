@@ -78,6 +78,7 @@ enum { HALO_AUTO = 0, HALO_OFF = 1, HALO_ON = 2, HALO_VARIANT0 = 3 };
 int opt_conv_halo();
 
 int choose_split(long long tiles, int K, int minSlice);
+void slice_k(int K, int bk, int want, int *splitK, int *kPerSlice);
 // Whether the kernel for operands of any alignment (gemm_ragged.h) takes a product the direct-to-LDS kernels do not:
 // rows of 8 elements or more, panels (and row blocks of C) within 31-bit byte offsets, and enough work.
 bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bool transB, int ldc);

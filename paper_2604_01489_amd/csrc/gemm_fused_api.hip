@@ -8,6 +8,7 @@
 #include <cstring>
 
 #include "../../include/gemm_epilogue.h"
+#include "gemm_few_rows.h"
 #include "gemm_fused.h"
 #include "gemm_fused_launch.h"
 #include "gemm_ragged_launch.h"
@@ -89,6 +90,19 @@ bool stage_k64(bool transA, bool transB)
     return !transA && transB;
 }
 
+// A few rows through weights stored N x K: the kernel that streams the weights (gemm_few_rows.h), where their 32-row pieces
+// cover three of four CUs, or the walk over K is short.  (Fewer pieces and a long K are a stream that few CUs cannot
+// draw: 16 x 2048 x 8192 18.1 us, on the tiles with K slices 13.5; 12 x 2808 x 2880 10.5 / 13.5.)
+bool few_rows_ok(const ge_fused_args_t &a)
+{
+    if (a.transA || !a.transB || a.M > 32 || a.a_structure != GE_A_GENERAL || a.plan != GE_PLAN_AUTO || opt_force_config() != FORCE_NONE) return false;
+    // 16-byte pieces along k; a panel of 32 rows, or the rows of A, within 31-bit byte offsets
+    if ((((uintptr_t)a.A | (uintptr_t)a.B) & 15u) || ((a.lda | a.ldb | a.K) & 7) || a.batch > 65535) return false;
+    if ((long long)a.lda * 64 + 1024 >= (1ll << 31) || (long long)a.ldb * 64 + 1024 >= (1ll << 31)) return false;
+    if ((double)a.N * a.K < 512.0 * 1024) return false;                      // a megabyte of weights
+    return (long long)ceil_div(a.N, 32) * a.batch >= kNumCU * 3 / 4 || a.K <= 3072;
+}
+
 template <int BM>
 bool launch_tile(const GemmParams &p, const Plan &pl, bool raw, dim3 grid, hipStream_t st)
 {
@@ -119,6 +133,7 @@ extern "C" size_t gemm_epilogue_fused_workspace_bytes(const ge_fused_args_t *arg
         const SymmPlan sp = plan_symm(a);
         if (sp.fast) return sp.bytes;
     }
+    if (few_rows_ok(a)) return 0;
     Plan pl;
     const bool triangular = a.a_structure == GE_A_LOWER || a.a_structure == GE_A_UPPER;
     const bool fast = fast_ok(a) && !is_symmetric(a);
@@ -146,6 +161,8 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
     const ge_plan_t plan = triangular ? GE_PLAN_DIRECT : a.plan;
     st = make_plan_bf16(a.M, a.N, a.K, a.batch, fast_ok(a) && !is_symmetric(a), plan, a.split_k, &pl, false, ragged(a));
     if (st != GE_OK) return st;
+    const bool fewRows = few_rows_ok(a);
+    if (fewRows) pl.splitK = 1;
 
     GemmParams p{};
     p.A = a.A; p.B = a.B; p.bias = a.bias; p.C = (float *)a.C;
@@ -198,7 +215,20 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
     }
     const dim3 grid((unsigned)((long long)pl.tilesM * pl.tilesN * a.batch * pl.splitK));
     hipStream_t hs = (hipStream_t)stream;
-    switch (pl.tile) {
+    if (fewRows) {
+        const dim3 fgrid((unsigned)ceil_div(a.N, ge_skinny::BM), (unsigned)a.batch);
+        // one workgroup to a CU: a deep ring; more: a shallow one, so that two or three share a CU (3 x 13120 x 9088, 410
+        // workgroups: 42.1 us deep, 38.9 shallow)
+        const bool deep = fgrid.x * fgrid.y <= (unsigned)kNumCU;
+        if (a.M <= 16) {
+            if (deep) GE_LAUNCH((ge::gemm_few_rows_kernel<16, 8>), fgrid, dim3(256), 0, hs, p);
+            else      GE_LAUNCH((ge::gemm_few_rows_kernel<16, 4>), fgrid, dim3(256), 0, hs, p);
+        } else {
+            if (deep) GE_LAUNCH((ge::gemm_few_rows_kernel<32, 8>), fgrid, dim3(256), 0, hs, p);
+            else      GE_LAUNCH((ge::gemm_few_rows_kernel<32, 4>), fgrid, dim3(256), 0, hs, p);
+        }
+        set_config(a.M <= 16 ? "few_rows_16_k128" : "few_rows_32_k128", a.transA, a.transB, false);
+    } else switch (pl.tile) {
     case TILE_256:
         // both operands k-strided: every request is a whole line already and the four-wave
         // kernel has nothing to gain (measured at 8192^3: 0.812 against 0.806 ms)

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from paper_2604_01489_amd import binding
+
 from gpu_util import run_case, run_fused_case
 
 LAYOUTS = [(False, False), (False, True), (True, False), (True, True)]
@@ -94,3 +96,16 @@ def test_f32_any_alignment(oracle, M, N, K, cfg):
     for kw in [dict(), dict(misalign=1, lda=K + 1, ldb=N + 3, ldc=N + 2)]:
         _, _, _, got = run_case(oracle, "f32", M, N, K, alpha=0.5, act="gelu_tanh", seed=M + N + K, **kw)
         assert got == cfg
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,out", [(520, 776, 384, "f32"), (264, 1032, 456, "bf16"), (72, 1096, 1160, "bf16")])
+def test_small_tiles_of_aligned_operands(oracle, M, N, K, out):
+    """Few tiles and K of 384 or more: the 64 x 64 tiles, with the same sums as the larger ones in the same order."""
+    outs = []
+    for option in (None, "128x128"):
+        binding.set_option("force_config", option)
+        got, _, _, cfg = run_fused_case(oracle, M, N, K, transB=True, act="gelu_tanh", residual="bf16", out=out, plan="auto" if option is None else "direct", seed=M)
+        outs.append(got)
+        assert ("ragged_64x64x64" in cfg) == (option is None), cfg
+    assert (outs[0] == outs[1]).all()
