@@ -276,11 +276,7 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
     }
     if (ge_host::take_launch_error() != hipSuccess) return GE_ERR_LAUNCH;
     if (raw) {
-        const long long total = M * a.Cout;
-        long long blocks = (total + 255) / 256;
-        if (blocks > 16 * kNumCU) blocks = 16 * kNumCU;
-        GE_LAUNCH(ge::splitk_reduce_fused_kernel, dim3((unsigned)blocks), dim3(256), 0, hs, p, (const float *)ws);
-        if (ge_host::take_launch_error() != hipSuccess) return GE_ERR_LAUNCH;
+        if (launch_reduce(p, ws, false, hs) != hipSuccess) return GE_ERR_LAUNCH;
     }
     return GE_OK;
 }

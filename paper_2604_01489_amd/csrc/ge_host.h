@@ -103,6 +103,10 @@ int tile_edge(const Plan &pl, int K, int step);
 // ge_release_workspace).
 ge_status_t acquire_workspace(size_t need, void *user, size_t user_bytes, hipStream_t stream, void **out);
 
+// The second pass over p.splitK partial tiles at ws (splitk_reduce.h): p is the call's, its C the result; plain: scale, bias
+// and activation only, fp32 out.
+hipError_t launch_reduce(const GemmParams &p, const void *ws, bool plain, hipStream_t st);
+
 // A symmetric A given by one triangle with few output columns (gemm_symm_api.hip): whether the kernel
 // that fetches every stored element once takes the call, with which super-tile width, and the bytes
 // of its partial results; run_symm launches it and the second pass (p: the call's launch parameters).

@@ -1,9 +1,6 @@
 // Kernels of the widened operator that are not the main kernel: a guarded GEMM for argument
 // lists the direct-to-LDS kernel does not take (odd sizes, unaligned pointers, odd leading
-// dimensions), with operands stored either way round, and the second pass of split-K with
-// the run-time epilogue.  Every global access is predicated (Debugging guide, checklist "Edges").
-// (The kernel that is not a template has internal linkage: this header is included by more than
-// one translation unit.)
+// dimensions), with operands stored either way round.  Every global access is predicated (Debugging guide, checklist "Edges").
 #pragma once
 #include "ge_device.h"
 
@@ -184,33 +181,6 @@ conv_bf16_generic_kernel(const GemmParams p)
         if (m >= p.M) continue;
         if (RAW) p.C[(long long)tc.s * p.sliceStride + (long long)m * p.N + n] = acc[r];
         else fused_store(p, 0, m, n, acc[r]);
-    }
-}
-
-// Split-K second pass of the widened operator: slices added in ascending order by one thread
-// per output (no atomics: bitwise repeatable), then the run-time epilogue.  W holds
-// [slice][batch][M][N] fp32 partial sums.
-static __global__ void __launch_bounds__(256)
-splitk_reduce_fused_kernel(const GemmParams p, const float *__restrict__ W)
-{
-    const long long total = (long long)p.batch * p.M * p.N;
-    for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (long long)gridDim.x * blockDim.x) {
-        const int n = (int)(e % p.N);
-        const long long bm = e / p.N;
-        const int m = (int)(bm % p.M);
-        const long long b = bm / p.M;
-        // the slices in ascending order, eight loads in flight at a time (one by one, behind the loop's test,
-        // a sum of 22 terms was a chain of 22 round trips to memory: 8.4 us for a 1 MB result)
-        float s = 0.0f;
-        for (int i0 = 0; i0 < p.splitK; i0 += 8) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = i0 + u < p.splitK ? W[e + (long long)(i0 + u) * p.sliceStride] : 0.0f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
-        }
-        fused_store(p, b, m, n, s);
     }
 }
 

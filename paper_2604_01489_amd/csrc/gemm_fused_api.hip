@@ -261,11 +261,7 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
     }
     if (ge_host::take_launch_error() != hipSuccess) return GE_ERR_LAUNCH;
     if (raw) {
-        const long long total = (long long)a.batch * a.M * a.N;
-        long long blocks = (total + 255) / 256;
-        if (blocks > 16 * kNumCU) blocks = 16 * kNumCU;
-        GE_LAUNCH(ge::splitk_reduce_fused_kernel, dim3((unsigned)blocks), dim3(256), 0, hs, p, (const float *)ws);
-        if (ge_host::take_launch_error() != hipSuccess) return GE_ERR_LAUNCH;
+        if (launch_reduce(p, ws, false, hs) != hipSuccess) return GE_ERR_LAUNCH;
     }
     return GE_OK;
 }

@@ -88,54 +88,4 @@ gemm_bf16_generic_kernel(const GemmParams p)
     }
 }
 
-// ---------------------------------------------------------------------------
-// Split-K second pass: C[b][m,n] = act(alpha * sum_{s=0}^{S-1} W[s][b][m,n] + bias[n]),
-// slices added in ascending s by one thread per output: no atomics, so the
-// result is bitwise repeatable (optimisation prompt, GEMM list item 7).
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-splitk_reduce_kernel(const float *__restrict__ W, long long sliceStride, int S,
-                     int M, int N, int batch, const float *__restrict__ bias,
-                     float alpha, int act, float *__restrict__ C, int ldc, long long strideC)
-{
-    const long long total4 = (long long)batch * M * (N / 4);
-    const bool vec = (N % 4 == 0) && (ldc % 4 == 0) && ((((uintptr_t)C) & 15) == 0);
-    if (vec) {
-        for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total4;
-             e += (long long)gridDim.x * blockDim.x) {
-            const int n4 = (int)(e % (N / 4));
-            const long long bm = e / (N / 4);
-            const int m = (int)(bm % M);
-            const long long b = bm / M;
-            const float *src = W + (bm * N + (long long)n4 * 4);
-            float4 s = *(const float4 *)src;
-            for (int i = 1; i < S; ++i) {
-                const float4 t = *(const float4 *)(src + (long long)i * sliceStride);
-                s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
-            }
-            float4 bv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (bias != nullptr) bv = *(const float4 *)(bias + n4 * 4);
-            float4 o;
-            o.x = epilogue_value_rt(s.x, alpha, bv.x, act);
-            o.y = epilogue_value_rt(s.y, alpha, bv.y, act);
-            o.z = epilogue_value_rt(s.z, alpha, bv.z, act);
-            o.w = epilogue_value_rt(s.w, alpha, bv.w, act);
-            *(float4 *)(C + b * strideC + (long long)m * ldc + n4 * 4) = o;
-        }
-    } else {
-        const long long total = (long long)batch * M * N;
-        for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-             e += (long long)gridDim.x * blockDim.x) {
-            const int n = (int)(e % N);
-            const long long bm = e / N;
-            const int m = (int)(bm % M);
-            const long long b = bm / M;
-            float s = W[e];
-            for (int i = 1; i < S; ++i) s += W[e + (long long)i * sliceStride];
-            const float bv = bias != nullptr ? bias[n] : 0.0f;
-            C[b * strideC + (long long)m * ldc + n] = epilogue_value_rt(s, alpha, bv, act);
-        }
-    }
-}
-
 }  // namespace ge

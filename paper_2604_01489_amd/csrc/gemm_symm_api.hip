@@ -84,11 +84,7 @@ ge_status_t run_symm(const ge_fused_args_t &a, const SymmPlan &plan, GemmParams 
     // the terms are the slices of the second pass: added in their order, then the consumer chain
     p.splitK = plan.terms;
     p.sliceStride = (long long)a.batch * a.M * a.N;
-    const long long total = (long long)a.batch * a.M * a.N;
-    long long blocks = (total + 255) / 256;
-    if (blocks > 16 * kNumCU) blocks = 16 * kNumCU;
-    GE_LAUNCH(ge::splitk_reduce_fused_kernel, dim3((unsigned)blocks), dim3(256), 0, hs, p, (const float *)ws);
-    if (ge_host::take_launch_error() != hipSuccess) return GE_ERR_LAUNCH;
+    if (launch_reduce(p, ws, false, hs) != hipSuccess) return GE_ERR_LAUNCH;
     std::snprintf(g_symm_config, sizeof g_symm_config, "bf16_symm_%s_%dx%d_n%d", upper ? "upper" : "lower", plan.st, plan.st, plan.np);
     g_last_config = g_symm_config;
     return GE_OK;
