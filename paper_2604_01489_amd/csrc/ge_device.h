@@ -21,6 +21,19 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2_t;
 struct __attribute__((packed, aligned(2))) u32x2_any_t { u32x2_t v; };
 struct __attribute__((packed, aligned(2))) i32x4_any_t { i32x4_t v; };
 
+// v >> (16 * sh) over the whole 128 bits: element e becomes element e + sh, zeros above; sh >= 8 gives zero.
+__device__ __forceinline__ i32x4_t shift_down_elements(i32x4_t v, int sh)
+{
+    typedef __attribute__((ext_vector_type(2))) unsigned long long u64x2_t;
+    const u64x2_t d = __builtin_bit_cast(u64x2_t, v);
+    const int s = (sh & 3) * 16;
+    const unsigned long long lo = (d[0] >> s) | ((d[1] << 1) << (63 - s)), hi = d[1] >> s;
+    u64x2_t r;
+    r[0] = sh < 4 ? lo : sh < 8 ? hi : 0ull;
+    r[1] = sh < 4 ? hi : 0ull;
+    return __builtin_bit_cast(i32x4_t, r);
+}
+
 enum { ACT_NONE = 0, ACT_RELU = 1, ACT_GELU_TANH = 2 };
 enum { DT_F32 = 0, DT_BF16 = 1 };
 

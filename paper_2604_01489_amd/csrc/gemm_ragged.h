@@ -19,19 +19,6 @@
 
 namespace ge {
 
-// v >> (16 * sh) over the whole 128 bits: element e becomes element e + sh, zeros above; sh >= 8 gives zero.
-__device__ __forceinline__ i32x4_t shift_down_elements(i32x4_t v, int sh)
-{
-    typedef __attribute__((ext_vector_type(2))) unsigned long long u64x2_t;
-    const u64x2_t d = __builtin_bit_cast(u64x2_t, v);
-    const int s = (sh & 3) * 16;
-    const unsigned long long lo = (d[0] >> s) | ((d[1] << 1) << (63 - s)), hi = d[1] >> s;
-    u64x2_t r;
-    r[0] = sh < 4 ? lo : sh < 8 ? hi : 0ull;
-    r[1] = sh < 4 ? hi : 0ull;
-    return __builtin_bit_cast(i32x4_t, r);
-}
-
 // The chunks of one operand that a lane brings in per 64-k step of a tile BX wide (ragged_layout.h).
 template <int BX, bool STRIDED>
 struct RaggedChunks {

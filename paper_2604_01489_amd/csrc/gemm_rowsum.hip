@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/gemm_epilogue.h"
 #include "ge_device.h"
 #include "ge_host.h"
@@ -12,7 +14,14 @@ namespace {
 
 using namespace ge_host;
 
-constexpr int kColChunkRows = 64;       // rows of the matrix one block of the column-sum pass adds up
+// Rows of the matrix one block of the column-sum pass adds up: 64, or fewer where that makes too few blocks for the CUs (a
+// block's rows are a chain of round trips, eight rows each: 911 x 1408, 15 blocks of 64 rows: 19.9 -> 13.7 us for both calls on 1757 rows).
+int col_chunk_rows(int N, int K)
+{
+    int rows = 64;
+    while (rows > 16 && (long long)ceil_div(N, rows) * ceil_div(K, 2048) < kNumCU) rows /= 2;
+    return rows;
+}
 constexpr int kRowWaves = 16;           // waves of a block of the row pass (one staging of v per block)
 constexpr int kBlockRows = 8;           // rows a block of the wide row pass takes, all in flight at once
 constexpr int kBlockCols = kRowWaves * 64 * 8;   // columns its 1024 threads cover in one sweep
@@ -21,6 +30,9 @@ constexpr int kBlockCols = kRowWaves * 64 * 8;   // columns its 1024 threads cov
 // anything in the caches, and on this part a read-only stream measured 7.1 TB/s with it against
 // 6.3 TB/s without (sizes beyond the memory-side cache).
 __device__ inline ge::i32x4_t load_stream16(const void *p) { return __builtin_nontemporal_load((const ge::i32x4_t *)p); }
+
+// The same at any address (a plain load: the hint's builtin wants an aligned one).
+__device__ inline ge::i32x4_t load_any16(const void *p) { return ((const ge::i32x4_any_t *)p)->v; }
 
 __device__ inline float bf16_lo(unsigned w) { return __uint_as_float(w << 16); }
 __device__ inline float bf16_hi(unsigned w) { return __uint_as_float(w & 0xFFFF0000u); }
@@ -91,7 +103,10 @@ rows_dot_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, con
 // long-lived waves that walk their own rows: measured on an 8192 x 8192 matrix beyond the
 // memory-side cache, 23 us against 33-37 us for the kernel above.  Per row: a fixed butterfly inside
 // each wave, then the wave sums of its group added in wave order.
-template <int G>
+// ANY: rows at any address and of any length of at least 8; the chunk at a row's end is pulled back to end there and
+// shifted down, which puts zeros beyond (12096 x 2205 + 2752 x 2205: 50.8 -> 34.3 us for
+// both calls).
+template <int G, bool ANY>
 __global__ void __launch_bounds__(kRowWaves * 64)
 rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, const float *__restrict__ v,
                      float scale, const float *__restrict__ add, float *__restrict__ out)
@@ -107,14 +122,30 @@ rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx
     for (int u = 0; u < kBlockRows; ++u) acc[u] = 0.0f;
     for (int c0 = (wg * 64 + lane) * 8; c0 < C; c0 += SWEEP) {
         ge::i32x4_t x[kBlockRows];
-#pragma unroll
-        for (int u = 0; u < kBlockRows; ++u) {
-            x[u] = ge::i32x4_t{0, 0, 0, 0};
-            if (r0 + u < R) x[u] = load_stream16(X + (r0 + u) * ldx + c0);
-        }
         float vv[8];
+        if constexpr (ANY) {
+            // rows beyond R are the last one again: their sums are not stored
+            const int at = c0 < C - 8 ? c0 : C - 8;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) vv[e] = v != nullptr ? v[c0 + e] : 1.0f;
+            for (int u = 0; u < kBlockRows; ++u) x[u] = load_any16(X + (r0 + u < R ? r0 + u : R - 1) * ldx + at);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const bool inside = c0 + e < C;
+                vv[e] = inside ? (v != nullptr ? v[inside ? c0 + e : 0] : 1.0f) : 0.0f;
+            }
+            if (at != c0) {
+#pragma unroll
+                for (int u = 0; u < kBlockRows; ++u) x[u] = ge::shift_down_elements(x[u], c0 - at);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kBlockRows; ++u) {
+                x[u] = ge::i32x4_t{0, 0, 0, 0};
+                if (r0 + u < R) x[u] = load_stream16(X + (r0 + u) * ldx + c0);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) vv[e] = v != nullptr ? v[c0 + e] : 1.0f;
+        }
 #pragma unroll
         for (int u = 0; u < kBlockRows; ++u) {
 #pragma unroll
@@ -141,44 +172,43 @@ rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx
     }
 }
 
-// partial[chunk][c] = sum over the rows of chunk `chunk` (kColChunkRows rows, in row order) of X[r,c].
-// A thread owns 8 consecutive columns (16 bytes per row) when VEC, one column otherwise.  The loads of
-// 8 rows are issued together, ahead of their additions (left to the compiler's unrolling they went out
-// one by one behind a bounds test: 50 us for 8192 x 8192 against 23 us).
-template <bool VEC>
+// partial[chunk][c] = sum over the rows of chunk `chunk` (chunkRows rows, in row order) of X[r,c].
+// A thread owns 8 consecutive columns (16 bytes per row; ALIGNED: rows of whole aligned pieces, by non-temporal loads; else at any address, the columns
+// at the end of a row are read with those before them and shifted into place), or one column where rows are shorter
+// (WIDE false).  The loads of 8 rows are issued together, ahead of their additions (left to the compiler's unrolling they
+// went out one by one behind a bounds test: 50 us for 8192 x 8192 against 23 us).
+template <bool WIDE, bool ALIGNED>
 __global__ void __launch_bounds__(256)
-cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, float *__restrict__ partial)
+cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, float *__restrict__ partial, int chunkRows)
 {
-    constexpr int W = VEC ? 8 : 1, U = 8;
+    constexpr int W = WIDE ? 8 : 1, U = 8;
     const int c0 = (blockIdx.x * 256 + threadIdx.x) * W;
     if (c0 >= C) return;
-    const int r0 = blockIdx.y * kColChunkRows, r1 = min(R, r0 + kColChunkRows);
+    const int r0 = blockIdx.y * chunkRows, r1 = min(R, r0 + chunkRows);
     float acc[W];
 #pragma unroll
     for (int e = 0; e < W; ++e) acc[e] = 0.0f;
-    if (VEC && c0 + 8 <= C) {
+    if constexpr (WIDE) {
+        const int at = ALIGNED || c0 < C - 8 ? c0 : C - 8;
         for (int r = r0; r < r1; r += U) {
             ge::i32x4_t x[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 x[u] = ge::i32x4_t{0, 0, 0, 0};
-                if (r + u < r1) x[u] = load_stream16(X + (long long)(r + u) * ldx + c0);
+                if (r + u < r1) x[u] = ALIGNED ? load_stream16(X + (long long)(r + u) * ldx + at) : load_any16(X + (long long)(r + u) * ldx + at);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < U; ++u) {
+                if (!ALIGNED && at != c0) x[u] = ge::shift_down_elements(x[u], c0 - at);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     acc[2 * e] += bf16_lo((unsigned)x[u][e]);
                     acc[2 * e + 1] += bf16_hi((unsigned)x[u][e]);
                 }
+            }
         }
     } else {
-        for (int r = r0; r < r1; ++r) {
-            const uint16_t *row = X + (long long)r * ldx;
-#pragma unroll
-            for (int e = 0; e < W; ++e)
-                if (c0 + e < C) acc[e] += bf16_lo((unsigned)row[c0 + e]);
-        }
+        for (int r = r0; r < r1; ++r) acc[0] += bf16_lo((unsigned)X[(long long)r * ldx + c0]);
     }
 #pragma unroll
     for (int e = 0; e < W; ++e)
@@ -216,26 +246,26 @@ cols_finish_kernel(int C, int chunks, const float *__restrict__ partial, float *
     const int g = threadIdx.x / (kFinishCols / 4), cl = (threadIdx.x % (kFinishCols / 4)) * 4;
     const int c = blockIdx.x * kFinishCols + cl;
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    const bool vec = (C % 4 == 0) && c + 4 <= C;          // rows of the partial sums are then 16-byte aligned
+    // four columns by one 16-byte load at any address; those at the end of a row are pulled back and shifted into place
+    const bool wide = C >= 4;
+    const int at = wide && c > C - 4 ? C - 4 : c, sh = c - at;
     for (int q0 = g; q0 < chunks; q0 += 8 * kFinishWays) {
         float v[8][4];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int q = q0 + u * kFinishWays;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[u][e] = 0.0f;
-            if (q < chunks) {
-                const float *src = partial + (long long)q * C + c;
-                if (vec) {
-                    const ge::f32x4_t t = *(const ge::f32x4_t *)src;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[u][e] = t[e];
+            ge::i32x4_t t = {0, 0, 0, 0};
+            if (q < chunks && c < C) {
+                const float *src = partial + (long long)q * C;
+                if (wide) {
+                    t = load_any16(src + at);
                 } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (c + e < C) v[u][e] = src[e];
+                    for (int e = 0; e < C; ++e) t[e] = (int)__float_as_uint(src[e]);
                 }
             }
+            if (sh > 0) t = ge::shift_down_elements(t, 2 * sh);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[u][e] = __uint_as_float((unsigned)t[e]);
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
@@ -264,26 +294,27 @@ vector_sum_kernel(int n, const float *__restrict__ x, float *__restrict__ out)
 
 bool vec_ok(const void *base, long long ld) { return (((uintptr_t)base) & 15u) == 0 && ld % 8 == 0; }
 
-// The wide kernel needs rows in 16-byte pieces and enough columns to give most lanes of a wave one
-// (its narrowest sweep is 512 columns); the grid's block count must fit 31 bits.
-bool rows_wide(int R, int C, const void *X, long long ldx)
-{
-    return vec_ok(X, ldx) && C % 8 == 0 && C >= 384;
-}
+// The wide kernel needs enough columns to give most lanes of a wave a 16-byte piece (its narrowest sweep is 512 columns).
+bool rows_wide(int C) { return C >= 384; }
+bool rows_aligned(int C, const void *X, long long ldx) { return vec_ok(X, ldx) && C % 8 == 0; }
 
 // rows of X times v (or ones), on `st`
 void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float *v, float scale, const float *add,
                      float *out, hipStream_t st)
 {
-    if (rows_wide(R, C, X, ldx)) {
+    if (rows_wide(C)) {
         // the narrowest sweep that covers a row, or the whole block per row
-        const dim3 threads(kRowWaves * 64);
-        auto blocks = [&](int G) { return dim3((unsigned)ceil_div(R, G * kBlockRows)); };
-        if (C <= kBlockCols / 16)     GE_LAUNCH(rows_dot_wide_kernel<16>, blocks(16), threads, 0, st, R, C, X, ldx, v, scale, add, out);
-        else if (C <= kBlockCols / 8) GE_LAUNCH(rows_dot_wide_kernel<8>, blocks(8), threads, 0, st, R, C, X, ldx, v, scale, add, out);
-        else if (C <= kBlockCols / 4) GE_LAUNCH(rows_dot_wide_kernel<4>, blocks(4), threads, 0, st, R, C, X, ldx, v, scale, add, out);
-        else if (C <= kBlockCols / 2) GE_LAUNCH(rows_dot_wide_kernel<2>, blocks(2), threads, 0, st, R, C, X, ldx, v, scale, add, out);
-        else                          GE_LAUNCH(rows_dot_wide_kernel<1>, blocks(1), threads, 0, st, R, C, X, ldx, v, scale, add, out);
+        auto launch = [&](auto groups) {
+            constexpr int G = decltype(groups)::value;
+            const dim3 blocks((unsigned)ceil_div(R, G * kBlockRows)), threads(kRowWaves * 64);
+            if (rows_aligned(C, X, ldx)) GE_LAUNCH((rows_dot_wide_kernel<G, false>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out);
+            else                         GE_LAUNCH((rows_dot_wide_kernel<G, true>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out);
+        };
+        if (C <= kBlockCols / 16)     launch(std::integral_constant<int, 16>{});
+        else if (C <= kBlockCols / 8) launch(std::integral_constant<int, 8>{});
+        else if (C <= kBlockCols / 4) launch(std::integral_constant<int, 4>{});
+        else if (C <= kBlockCols / 2) launch(std::integral_constant<int, 2>{});
+        else                          launch(std::integral_constant<int, 1>{});
         return;
     }
     const int stage = (v != nullptr && (size_t)C * sizeof(float) <= 48 * 1024) ? 1 : 0;
@@ -301,7 +332,7 @@ void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float
 extern "C" size_t gemm_rowsum_params_workspace_bytes(int N, int K, int transB)
 {
     if (N < 1 || K < 1 || !transB) return 0;
-    return (size_t)ceil_div(N, kColChunkRows) * (size_t)K * sizeof(float);
+    return (size_t)ceil_div(N, col_chunk_rows(N, K)) * (size_t)K * sizeof(float);
 }
 
 extern "C" ge_status_t gemm_rowsum_params_bf16(int N, int K, const uint16_t *B, int ldb, int transB,
@@ -317,7 +348,7 @@ extern "C" ge_status_t gemm_rowsum_params_bf16_ex(int N, int K, const uint16_t *
     if (!B || !params) return GE_ERR_NULL;
     if (N < 1 || K < 1) return GE_ERR_SHAPE;
     if (ldb < (transB ? K : N)) return GE_ERR_LD;
-    if (transB && ceil_div(N, kColChunkRows) > 65535) return GE_ERR_SHAPE;      // chunks ride on the grid's y axis
+    if (transB && ceil_div(N, 64) > 65535) return GE_ERR_SHAPE;      // chunks ride on the grid's y axis
     if ((((uintptr_t)B) & 1u) || (((uintptr_t)params) & 3u) || (((uintptr_t)bias) & 3u)) return GE_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
     if (!transB) {
@@ -327,14 +358,15 @@ extern "C" ge_status_t gemm_rowsum_params_bf16_ex(int N, int K, const uint16_t *
         g_last_config = "rowsum_params_rows";
     } else {
         // B is stored N x K: s[k] is the sum of column k, in two passes through the workspace
-        const int chunks = ceil_div(N, kColChunkRows);
+        const int chunkRows = col_chunk_rows(N, K), chunks = ceil_div(N, chunkRows);
         void *ws = nullptr;
         const ge_status_t rc = acquire_workspace((size_t)chunks * (size_t)K * sizeof(float), workspace, workspace_bytes, st, &ws);
         if (rc != GE_OK) return rc;
-        const bool vec = vec_ok(B, ldb);
-        const dim3 grid((unsigned)ceil_div(K, 256 * (vec ? 8 : 1)), (unsigned)chunks);
-        if (vec) GE_LAUNCH(cols_partial_kernel<true>, grid, dim3(256), 0, st, N, K, B, (long long)ldb, (float *)ws);
-        else     GE_LAUNCH(cols_partial_kernel<false>, grid, dim3(256), 0, st, N, K, B, (long long)ldb, (float *)ws);
+        const dim3 grid((unsigned)ceil_div(K, 256 * (K >= 8 ? 8 : 1)), (unsigned)chunks);
+        float *partial = (float *)ws;
+        if (K < 8)                        GE_LAUNCH((cols_partial_kernel<false, false>), grid, dim3(256), 0, st, N, K, B, (long long)ldb, partial, chunkRows);
+        else if (rows_aligned(K, B, ldb)) GE_LAUNCH((cols_partial_kernel<true, true>), grid, dim3(256), 0, st, N, K, B, (long long)ldb, partial, chunkRows);
+        else                              GE_LAUNCH((cols_partial_kernel<true, false>), grid, dim3(256), 0, st, N, K, B, (long long)ldb, partial, chunkRows);
         GE_LAUNCH(cols_finish_kernel, dim3((unsigned)ceil_div(K, kFinishCols) + 1), dim3(256), 0, st, K, chunks, (const float *)ws,
                            params, N, bias);
         g_last_config = "rowsum_params_cols";
@@ -350,6 +382,6 @@ extern "C" ge_status_t gemm_rowsum_bf16(int M, int K, const uint16_t *A, int lda
     if (lda < K) return GE_ERR_LD;
     if ((((uintptr_t)A) & 1u) || (((uintptr_t)params) & 3u) || (((uintptr_t)y) & 3u)) return GE_ERR_ALIGN;
     launch_rows_dot(M, K, A, lda, params, alpha, params + K, y, (hipStream_t)stream);
-    g_last_config = rows_wide(M, K, A, lda) ? "rowsum_rows_wide" : vec_ok(A, lda) ? "rowsum_rows_vec8" : "rowsum_rows_generic";
+    g_last_config = rows_wide(K) && rows_aligned(K, A, lda) ? "rowsum_rows_wide" : vec_ok(A, lda) ? "rowsum_rows_vec8" : "rowsum_rows_generic";
     return ge_host::take_launch_error() == hipSuccess ? GE_OK : GE_ERR_LAUNCH;
 }

@@ -120,3 +120,12 @@ def test_rowsum_equals_the_layer_then_the_sum(oracle):
     long_way = C.double().sum(dim=1).cpu().numpy()
     short_way = y.double().cpu().numpy()
     assert np.linalg.norm(long_way - short_way) <= 1e-5 * np.linalg.norm(long_way)
+
+
+@pytest.mark.parametrize("transB", [False, True])
+def test_rowsum_any_alignment(oracle, transB):
+    """Long rows of any length at any address (pieces pulled back to the end of their row), and column sums over chunks of
+    64, 32 and 16 rows with ragged last chunks and columns that are no multiple of 8 or 4."""
+    for M, N, K, pad, mis in [(130, 385, 511, (0, 0), 0), (77, 1000, 1031, (3, 5), 0), (41, 390, 2050, (0, 0), 1), (9, 65, 8193, (1, 0), 3),
+                              (64, 4100, 391, (0, 0), 0), (5, 17, 9, (0, 0), 1), (1024, 2049, 1024, (0, 0), 0)]:
+        run_rowsum_case(oracle, M, N, K, transB=transB, alpha=0.5, pad=pad, misalign=mis, seed=M + K)
