@@ -160,3 +160,13 @@ def test_symm_argument_errors():
     assert call(K=32, lda=64) == 2          # a symmetric operand is square
     assert call(transA=True) == 8           # its transposed storage is the other triangle: say that instead
     assert call(a_structure=5) == 8
+
+
+@pytest.mark.parametrize("uplo", ["lower", "upper"])
+@pytest.mark.parametrize("transB", [False, True])
+def test_symm_columns_of_any_number(oracle, uplo, transB):
+    """The blocks of B for column counts that are no multiple of 8, from one column to a full image, with padded and odd
+    leading dimensions and a pointer off by one element; M around the super-tiles."""
+    for M, N, kw in [(512, 1, {}), (776, 7, dict(pad=(0, 3, 1))), (1032, 9, {}), (520, 17, dict(pad=(8, 1, 0))), (1024, 31, {}), (768, 33 - 1, dict(pad=(0, 5, 3)))]:
+        _, cfg = run_symm_case(oracle, M, N, uplo=uplo, transB=transB, act="relu", seed=M + N, **kw)
+        assert cfg.startswith(f"bf16_symm_{uplo}"), cfg
