@@ -31,15 +31,25 @@ void launch_conv(const GemmParams &p, bool edge, bool raw, dim3 grid, hipStream_
     constexpr int threads = WM * WN * 64;
     const bool h = p.cType == ge::DT_BF16;
     if (raw) {
-        if (edge) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 1, true, ge::ACT_NONE, false, true, false, false, true>), grid, dim3(threads), 0, st, p);
-        else      GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 0, true, ge::ACT_NONE, false, true, false, false, true>), grid, dim3(threads), 0, st, p);
+        if (edge) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 1, true, ge::ACT_NONE, false, true, false, false, 1>), grid, dim3(threads), 0, st, p);
+        else      GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 0, true, ge::ACT_NONE, false, true, false, false, 1>), grid, dim3(threads), 0, st, p);
     } else if (edge) {
-        if (h) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 1, false, ge::ACT_NONE, false, true, true, true, true>), grid, dim3(threads), 0, st, p);
-        else   GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 1, false, ge::ACT_NONE, false, true, true, false, true>), grid, dim3(threads), 0, st, p);
+        if (h) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 1, false, ge::ACT_NONE, false, true, true, true, 1>), grid, dim3(threads), 0, st, p);
+        else   GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 1, false, ge::ACT_NONE, false, true, true, false, 1>), grid, dim3(threads), 0, st, p);
     } else {
-        if (h) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 0, false, ge::ACT_NONE, false, true, true, true, true>), grid, dim3(threads), 0, st, p);
-        else   GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 0, false, ge::ACT_NONE, false, true, true, false, true>), grid, dim3(threads), 0, st, p);
+        if (h) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 0, false, ge::ACT_NONE, false, true, true, true, 1>), grid, dim3(threads), 0, st, p);
+        else   GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 0, false, ge::ACT_NONE, false, true, true, false, 1>), grid, dim3(threads), 0, st, p);
     }
+}
+
+// channels a multiple of 8 but not of 32: a chunk's tap per lane, the K range may end inside a step
+template <int BM, int BN, int WM, int WN>
+void launch_conv_c8(const GemmParams &p, bool raw, dim3 grid, hipStream_t st)
+{
+    constexpr int threads = WM * WN * 64;
+    if (raw) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 2, true, ge::ACT_NONE, false, true, false, false, 2>), grid, dim3(threads), 0, st, p);
+    else if (p.cType == ge::DT_BF16) GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 2, false, ge::ACT_NONE, false, true, true, true, 2>), grid, dim3(threads), 0, st, p);
+    else GE_LAUNCH((ge::gemm_bf16_kernel<BM, BN, WM, WN, 2, false, ge::ACT_NONE, false, true, true, false, 2>), grid, dim3(threads), 0, st, p);
 }
 
 // Validation and plan of one call: everything that depends on the sizes and on the alignment of the
@@ -49,6 +59,7 @@ struct ConvPlan {
     long long M, K, xElems;
     bool rows;          // the few-channel kernel: a K step is one filter row
     bool rowsPairs;     //   ... whose input rows are 4-byte aligned and even in length
+    bool c8;            // the gathering kernel with channels a multiple of 8 but not of 32
     int halo;           // the halo-staged 3 x 3 kernel: 0 no, else 1 + index into kHaloVariants
     ge_halo::HaloPlan haloPlan;
     Plan pl;
@@ -119,9 +130,10 @@ ge_status_t plan_conv(const ge_conv_args_t &a, ConvPlan *out)
 
     // gathering kernel: a K step is 32 channels of one tap, chunks of 8 channels are 16 aligned
     // bytes, byte offsets into the input fit 31 bits; bf16 output leaves in 16-byte row pieces
-    bool fast = !((((uintptr_t)a.X) | ((uintptr_t)a.Wt)) & 15u) && (a.Cin % 32 == 0) && (a.Cout % 8 == 0) && a.Cout < ge::EDGE_LDC_MAX &&
+    bool gather = !((((uintptr_t)a.X) | ((uintptr_t)a.Wt)) & 15u) && (a.Cin % 8 == 0) && (a.Cout % 8 == 0) && a.Cout < ge::EDGE_LDC_MAX &&
                 xElems * 2 < (1ll << 31) - (1 << 20) && K * 2 * 256 + 1024 < (1ll << 31);
-    if (a.y_type == GE_DTYPE_BF16 && (((uintptr_t)a.Y) & 15u)) fast = false;
+    if (a.y_type == GE_DTYPE_BF16 && (((uintptr_t)a.Y) & 15u)) gather = false;
+    const bool fast = gather && a.Cin % 32 == 0;
     out->OH = OH; out->OW = OW; out->M = M; out->K = K; out->xElems = xElems;
     // few input channels: one filter row per K step (conv_rows.h) where a row of the filter fits the
     // 32 elements of a step, its image of an input row fits 512 dwords, a lane's 8 channels of Y (and
@@ -158,6 +170,15 @@ ge_status_t plan_conv(const ge_conv_args_t &a, ConvPlan *out)
         }
     }
     ge_status_t st = make_plan_bf16((int)M, a.Cout, (int)K, 1, fast, GE_PLAN_AUTO, 0, &out->pl);
+    // Channels a multiple of 8 only: the gathering kernel from a million multiply-adds on (one image of 7 x 7 x 80 -> 32,
+    // 3 x 3, is at that size: 39.1 -> 14.2 us; below, the guarded kernel is the shorter launch), with no more
+    // K slices than the guarded kernel would take (no call needs a workspace, or a larger one, that did not)
+    out->c8 = gather && !fast && !out->rows && opt_force_config() != FORCE_GENERIC && (double)M * a.Cout * K >= 1024.0 * 1024;
+    if (st == GE_OK && out->c8) {
+        const int guarded = out->pl.splitK;
+        st = make_plan_bf16((int)M, a.Cout, (int)K, 1, true, guarded > 1 ? GE_PLAN_AUTO : GE_PLAN_DIRECT, 0, &out->pl);
+        if (st == GE_OK && out->pl.splitK > guarded) st = make_plan_bf16((int)M, a.Cout, (int)K, 1, true, GE_PLAN_SPLITK, guarded, &out->pl);
+    }
     if (st == GE_OK && out->halo) { out->pl.splitK = 1; out->pl.kPerSlice = (int)K; }
     if (st == GE_OK && out->rows) { out->pl.splitK = 1; out->pl.kPerSlice = (int)K; }
     return st;
@@ -261,10 +282,20 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
     hipStream_t hs = (hipStream_t)stream;
     switch (pl.tile) {
     case TILE_256:
+        if (cp.c8) {
+            launch_conv_c8<256, 256, 2, 4>(pg, raw, grid, hs);
+            g_last_config = raw ? "conv_bf16_c8_256x256x32_w8_splitk" : "conv_bf16_c8_256x256x32_w8";
+            break;
+        }
         launch_conv<256, 256, 2, 4>(pg, pl.edge, raw, grid, hs);
         g_last_config = raw ? "conv_bf16_256x256x32_w8_splitk" : "conv_bf16_256x256x32_w8";
         break;
     case TILE_128:
+        if (cp.c8) {
+            launch_conv_c8<128, 128, 2, 2>(pg, raw, grid, hs);
+            g_last_config = raw ? "conv_bf16_c8_128x128x32_w4_splitk" : "conv_bf16_c8_128x128x32_w4";
+            break;
+        }
         launch_conv<128, 128, 2, 2>(pg, pl.edge, raw, grid, hs);
         g_last_config = raw ? "conv_bf16_128x128x32_w4_splitk" : "conv_bf16_128x128x32_w4";
         break;

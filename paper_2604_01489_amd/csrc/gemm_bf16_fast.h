@@ -152,7 +152,10 @@ struct Bf16Tile {
 // channels of one filter tap, so the lane's chunk of a row is 16 contiguous bytes at
 // position base + tap offset, or zeros where the tap falls into the padding (the out-of-range
 // offset of the buffer load).  B is the filter bank stored [Cout][KH*KW*Cin] (TB), C the
-// channels-last output.
+// channels-last output.  CONV 1: channels a multiple of 32, the tap is the step's, kept on the scalar unit.  CONV 2: a
+// multiple of 8, the tap is the 16-byte chunk's: the lane's (one for all of its chunks), advanced by up to 32 / Cin + 1
+// conditional steps per K step (32 images of 56 x 56 x 48 -> 96, 3 x 3: 146.7 us on the guarded
+// kernel, 26.5 here; 4 of 35 x 35 x 80 -> 512: 66.1 / 15.5).
 // K64: the loads move 64 k at a time into a ring of two stages (same LDS as four of 32).  A
 // k-contiguous operand is then staged in rows of 128 bytes, so that eight neighbouring lanes of a
 // load fetch one whole line of the operand instead of half of it now and the other half a step
@@ -163,7 +166,7 @@ struct Bf16Tile {
 // or none 0.75 -> 0.81 ms; the 3x3 convolution over 256 channels 0.139 -> 0.147 ms, so it is used
 // for the first only).  The K range of a block must be a multiple of 64 unless EDGE is 2.
 template <int BM, int BN, int WM, int WN, int EDGE, bool RAW, int ACT, bool TA = false, bool TB = false,
-          bool FUSED = false, bool OUTBF16 = false, bool CONV = false, bool K64 = false>
+          bool FUSED = false, bool OUTBF16 = false, int CONV = 0, bool K64 = false>
 __global__ void __launch_bounds__(WM * WN * 64)
 gemm_bf16_kernel(const GemmParams p)
 {
@@ -189,7 +192,7 @@ gemm_bf16_kernel(const GemmParams p)
     const int m0 = tc.tm * BM, n0 = tc.tn * BN;
     int kBegin = tc.s * p.kPerSlice;
     int kEnd = min(p.K, kBegin + p.kPerSlice);
-    if constexpr (FUSED && !CONV) triangular_k_range(p, m0, BM, kBegin, kEnd);
+    if constexpr (FUSED && CONV == 0) triangular_k_range(p, m0, BM, kBegin, kEnd);
     const int kLen = kEnd - kBegin;
     const int nk = (kLen + BK - 1) / BK;
 
@@ -224,7 +227,7 @@ gemm_bf16_kernel(const GemmParams p)
             // byte offset of (img, ih0, iw0, channel 8c) modulo 2^32: it may be "negative" for a tap
             // in the padding, and adding the tap offset of an inside tap brings it back into
             // [0, 2^31) (the host checks that the input is smaller than that)
-            voffA[j] = ((unsigned)((img * p.convH + ihTap0) * p.convW + iw0[j]) * (unsigned)p.convCin + (unsigned)(c * 8)) * 2u;
+            voffA[j] = ((unsigned)((img * p.convH + ihTap0) * p.convW + iw0[j]) * (unsigned)p.convCin + (unsigned)(CONV == 1 ? c * 8 : 0)) * 2u;
         } else if (!TA) {
             // 1 KB slab = 16 rows of 64 bytes, or 8 rows of 128
             const int row = A64 ? a64_slot_row(j * NW + w, lane) : a_slot_row(j * NW + w, lane);
@@ -267,6 +270,13 @@ gemm_bf16_kernel(const GemmParams p)
         tapH = tap / p.convKW;
         tapW = tap % p.convKW;
     }
+    if (CONV == 2) {                                 // the lane's: of k = kBegin + 8 times its chunk
+        const int k = kBegin + 8 * a_slot_chunk(lane), tap = k / p.convCin;
+        tapC = k - tap * p.convCin;
+        tapH = tap / p.convKW;
+        tapW = tap - tapH * p.convKW;
+    }
+    const int tapSteps = CONV == 2 ? (p.convCin + 24) / p.convCin : 0;
     // issue_prep(kt) sets up tile kt (resource words, K-edge limit, tap offsets); issue_one(l, ...) then
     // issues its load l (A's first, then B's); issue() is both for all loads.
     rsrc_words_t rA, rB;
@@ -290,8 +300,19 @@ gemm_bf16_kernel(const GemmParams p)
             dIw = tapW * p.convDw;
             tapOff = (unsigned)(((dIh * p.convW + dIw) * p.convCin + tapC) * 2);
             tapC += BK;
-            if (tapC >= p.convCin) { tapC = 0; ++tapW; }
-            if (tapW >= p.convKW) { tapW = 0; ++tapH; }
+            if (CONV == 1) {
+                if (tapC >= p.convCin) { tapC = 0; ++tapW; }
+                if (tapW >= p.convKW) { tapW = 0; ++tapH; }
+            } else {
+                for (int q = 0; q < tapSteps; ++q) {
+                    const bool next = tapC >= p.convCin;
+                    tapC -= next ? p.convCin : 0;
+                    tapW += next ? 1 : 0;
+                    const bool row = tapW >= p.convKW;
+                    tapW = row ? 0 : tapW;
+                    tapH += row ? 1 : 0;
+                }
+            }
         }
     };
     auto issue_one = [&](int l, GE_LDS char *dA, GE_LDS char *dB) {
