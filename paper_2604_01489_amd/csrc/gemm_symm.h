@@ -30,7 +30,6 @@ struct SymmParams {
     float *W;                  // [terms][batch][M][N] fp32
     int M, N, lda, ldb, transB, upper, batch;
     int tiles;                 // super-tile rows
-    int bVec;                  // B can be read in aligned 16-byte pieces along n (N % 8 == 0, aligned, not transposed)
     long long bytesA;          // extent of one batch of A: ((M - 1) lda + M) * 2
 };
 
@@ -41,8 +40,9 @@ __device__ __forceinline__ unsigned symm_mask_pair(unsigned w, bool keepLo, bool
 }
 
 // ST: side of a super-tile (a multiple of 128: 256, 512 or 768); NP: columns of the small operand's image (16 or 32);
-// UPPER: the upper triangle is the stored one.
-template <int ST, int NP, bool UPPER>
+// UPPER: the upper triangle is the stored one; BVEC: B can be read in aligned 16-byte pieces along n (N a multiple of 8, aligned,
+// not transposed).
+template <int ST, int NP, bool UPPER, bool BVEC>
 __global__ void __launch_bounds__(256)
 gemm_symm_bf16_kernel(const SymmParams p)
 {
@@ -79,7 +79,7 @@ gemm_symm_bf16_kernel(const SymmParams p)
     // is not of the row is masked off.  (Element by element under a test each, the two blocks of a super-tile were most of
     // the call: 9600 x 17 80.1 -> 45.2 us, 14144 x 18 126 -> 80, 5880 x 5 28.2 -> 20.6.)
     auto stage_small = [&](unsigned dst, int k0) __attribute__((always_inline)) {
-        if (__builtin_expect(p.bVec != 0, 1)) {
+        if constexpr (BVEC) {
             for (int q = threadIdx.x; q < ST * (NP / 8); q += 256) {
                 const int kk = q / (NP / 8), n = (q % (NP / 8)) * 8;
                 i32x4_t v = {0, 0, 0, 0};
