@@ -16,9 +16,10 @@ using namespace ge_host;
 
 // Rows of the matrix one block of the column-sum pass adds up: 64, or fewer where that makes too few blocks for the CUs (a
 // block's rows are a chain of round trips, eight rows each: 911 x 1408, 15 blocks of 64 rows: 19.9 -> 13.7 us for both calls on 1757 rows).
+constexpr int kMaxChunkRows = 64;
 int col_chunk_rows(int N, int K)
 {
-    int rows = 64;
+    int rows = kMaxChunkRows;
     while (rows > 16 && (long long)ceil_div(N, rows) * ceil_div(K, 2048) < kNumCU) rows /= 2;
     return rows;
 }
@@ -95,7 +96,7 @@ rows_dot_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, con
     }
 }
 
-// The same for matrices whose rows can be read in 16-byte pieces (C a multiple of 8) and are at least
+// The same for matrices whose rows can be read in 16-byte pieces (not ANY: C a multiple of 8, aligned) and are at least
 // 512 columns wide: a block of 1024 threads is G groups of 16/G waves, each group takes kBlockRows
 // consecutive rows; a thread owns 8 consecutive columns per sweep of 8192/G columns, holds their v in
 // registers and has one 16-byte load per row in flight, all issued before the first is used.  Many
@@ -358,9 +359,16 @@ extern "C" ge_status_t gemm_rowsum_params_bf16_ex(int N, int K, const uint16_t *
         g_last_config = "rowsum_params_rows";
     } else {
         // B is stored N x K: s[k] is the sum of column k, in two passes through the workspace
-        const int chunkRows = col_chunk_rows(N, K), chunks = ceil_div(N, chunkRows);
+        // of fewer, longer chunks where there is no room for the many: a caller's buffer, or the library's
+        // under capture, that holds the partial sums of 64 rows a chunk is enough
         void *ws = nullptr;
-        const ge_status_t rc = acquire_workspace((size_t)chunks * (size_t)K * sizeof(float), workspace, workspace_bytes, st, &ws);
+        int chunkRows = col_chunk_rows(N, K), chunks = ceil_div(N, chunkRows);
+        ge_status_t rc = acquire_workspace((size_t)chunks * (size_t)K * sizeof(float), workspace, workspace_bytes, st, &ws);
+        while (rc == GE_ERR_WORKSPACE && chunkRows < kMaxChunkRows) {
+            chunkRows *= 2;
+            chunks = ceil_div(N, chunkRows);
+            rc = acquire_workspace((size_t)chunks * (size_t)K * sizeof(float), workspace, workspace_bytes, st, &ws);
+        }
         if (rc != GE_OK) return rc;
         const dim3 grid((unsigned)ceil_div(K, 256 * (K >= 8 ? 8 : 1)), (unsigned)chunks);
         float *partial = (float *)ws;

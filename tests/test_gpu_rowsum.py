@@ -129,3 +129,24 @@ def test_rowsum_any_alignment(oracle, transB):
     for M, N, K, pad, mis in [(130, 385, 511, (0, 0), 0), (77, 1000, 1031, (3, 5), 0), (41, 390, 2050, (0, 0), 1), (9, 65, 8193, (1, 0), 3),
                               (64, 4100, 391, (0, 0), 0), (5, 17, 9, (0, 0), 1), (1024, 2049, 1024, (0, 0), 0)]:
         run_rowsum_case(oracle, M, N, K, transB=transB, alpha=0.5, pad=pad, misalign=mis, seed=M + K)
+
+
+def test_rowsum_small_workspace(oracle):
+    """Column sums of small weights take many short chunks where the workspace holds them and longer ones where it holds only
+    those of 64 rows; one byte less is refused."""
+    import torch
+    from paper_2604_01489_amd import binding, inputs as gen
+    N, K = 911, 1408
+    W = gen.to_bf16_bits(gen.uniform(5, gen.STREAM_B, N * K, -1.0, 1.0).reshape(N, K))
+    dW = to_device(W)
+    small = -(-N // 64) * K * 4
+    assert binding.rowsum_params_workspace_bytes(N, K, True) > small
+    want = np.asarray(gen.bf16_bits_to_f32(W), dtype=np.float64).sum(axis=0)
+    mass = np.abs(np.asarray(gen.bf16_bits_to_f32(W), dtype=np.float64)).sum(axis=0)
+    params = torch.empty(K + 1, dtype=torch.float32, device="cuda:0")
+    binding.gemm_rowsum_params_bf16(N, K, dW, K, True, None, params, workspace=torch.empty(small, dtype=torch.uint8, device="cuda:0"))
+    torch.cuda.synchronize()
+    # each of the at most 64 + 15 additions of a chain rounds once
+    assert np.all(np.abs(params[:K].double().cpu().numpy() - want) <= 80 * 2.0 ** -24 * mass)
+    with pytest.raises(RuntimeError):
+        binding.gemm_rowsum_params_bf16(N, K, dW, K, True, None, params, workspace=torch.empty(small - 1, dtype=torch.uint8, device="cuda:0"))
