@@ -97,9 +97,11 @@ typedef enum {
  *   batch >= 1        number of independent problems (packed strides)
  *   stream            hipStream_t
  * Fast kernels (direct-to-LDS loads) need A and B 16-byte aligned, lda, ldb, N
- * and K multiples of 8; any other legal argument list takes a guarded generic
- * kernel with the same result contract (the coding and debugging guide's rule
- * for vectorised copies: gated by alignment, with a correct fallback).  Large-K
+ * and K multiples of 8; any other legal argument list takes a kernel that loads
+ * 16 bytes at whatever address a row starts (fp32: multiples of 4, any alignment
+ * likewise) or, below about 17 million multiply-adds, a guarded generic one, with
+ * the same result contract (the coding and debugging guide's rule for vectorised
+ * copies: gated by alignment, with a correct fallback).  Large-K
  * small-MN shapes use split-K with the library's workspace of the stream (see
  * "Partial results" above).
  */
@@ -224,8 +226,8 @@ size_t gemm_epilogue_static_scratch_bytes(void);
  * `args` is a HOST pointer, read before the call returns.  The direct-to-LDS
  * kernels need A and B 16-byte aligned, lda and ldb multiples of 8 and the row
  * payloads (K or M for A, N or K for B) multiples of 8, plus for bf16 output an
- * even N and ldc and a 4-byte aligned C; any other legal argument list takes a
- * guarded kernel with the same result contract.
+ * even N and ldc and a 4-byte aligned C; any other legal argument list takes the
+ * kernels for any alignment or the guarded one (as above) with the same result contract.
  * Errors: as gemm_epilogue_bf16, plus GE_ERR_EPILOGUE.
  */
 typedef enum { GE_DTYPE_F32 = 0, GE_DTYPE_BF16 = 1 } ge_dtype_t;
@@ -276,9 +278,9 @@ size_t gemm_epilogue_fused_workspace_bytes(const ge_fused_args_t *args);
  *   Y, y_type         device result [N, OH, OW, Cout] packed; GE_DTYPE_BF16 rounds to nearest-even
  *   the other fields  as in ge_fused_args_t
  * `args` is a HOST pointer, read before the call returns.  The gathering kernel needs X and
- * Wt 16-byte aligned, Cin a multiple of 32, Cout a multiple of 8, an input smaller than
- * 2 GiB and (for bf16 output) Y 16-byte aligned; any other legal argument list takes a guarded
- * kernel with the same result contract.  Shapes with few output tiles and a long K are split
+ * Wt 16-byte aligned, Cin a multiple of 32 (from about a million multiply-adds on: of 8),
+ * Cout a multiple of 8, an input smaller than 2 GiB and (for bf16 output) Y 16-byte
+ * aligned; any other legal argument list takes a guarded kernel with the same result contract.  Shapes with few output tiles and a long K are split
  * over K and summed in slice order (bitwise repeatable); the partial results go to `workspace`
  * (256-byte aligned, at least conv2d_epilogue_workspace_bytes(args) bytes) or, when it is NULL,
  * to the library's buffer of the stream (see "Partial results" above).

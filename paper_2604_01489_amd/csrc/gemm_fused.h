@@ -1,6 +1,6 @@
 // Kernels of the widened operator that are not the main kernel: a guarded GEMM for argument
-// lists the direct-to-LDS kernel does not take (odd sizes, unaligned pointers, odd leading
-// dimensions), with operands stored either way round.  Every global access is predicated (Debugging guide, checklist "Edges").
+// lists neither the direct-to-LDS kernels nor those for any alignment take (small products with odd sizes,
+// unaligned pointers or odd leading dimensions; output rows of 2^24 elements and more), with operands stored either way round.  Every global access is predicated (Debugging guide, checklist "Edges").
 #pragma once
 #include "ge_device.h"
 

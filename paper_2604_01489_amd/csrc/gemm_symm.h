@@ -16,7 +16,7 @@
 // from super-tile (max(X, t), min(X, t)) -- its P1 if it is the super-tile's row block, its P2 if it is
 // its column block.  Every term is written to the workspace W[t][batch][M][N] by exactly one
 // workgroup and the terms are added in the order of t, with the consumer chain, by the second pass of
-// split-K (splitk_reduce_fused_kernel): no atomics, bitwise repeatable.  The partial results cost
+// split-K (splitk_reduce_kernel): no atomics, bitwise repeatable.  The partial results cost
 // 8 N / ST bytes per byte of A (written once, read once): a quarter at N = 16 with ST = 512.
 #pragma once
 #include "gemm_bf16_fast.h"
