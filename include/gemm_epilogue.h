@@ -367,8 +367,10 @@ ge_status_t gemm_epilogue_diag_bf16(int M, int N, const float *d,
  */
 ge_status_t gemm_rowsum_params_bf16(int N, int K, const uint16_t *B, int ldb, int transB,
                                     const float *bias, float *params, void *stream);
-/* The same with a caller's workspace (256-byte aligned, at least gemm_rowsum_params_workspace_bytes(N, K,
- * transB) bytes, which is 0 for transB == 0): never allocates.  workspace == NULL selects the library's. */
+/* The same with a caller's workspace (256-byte aligned, gemm_rowsum_params_workspace_bytes(N, K, transB)
+ * bytes, which is 0 for transB == 0): never allocates.  workspace == NULL selects the library's.  A smaller
+ * one is accepted from ceil(N / 64) * K * 4 bytes on (the library's under capture likewise): the same sums
+ * bit for bit, up to twice as slow where that is less than asked for. */
 ge_status_t gemm_rowsum_params_bf16_ex(int N, int K, const uint16_t *B, int ldb, int transB,
                                        const float *bias, float *params,
                                        void *workspace, size_t workspace_bytes, void *stream);

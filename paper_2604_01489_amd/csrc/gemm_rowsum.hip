@@ -46,6 +46,14 @@ __device__ inline float wave_sum(float v)
     return v;
 }
 
+// n terms (a power of two) added in pairs, then pairs of pairs: the halves of the range are sums of the same kind
+template <int n>
+__device__ inline float pair_sum(const float *t)
+{
+    if constexpr (n == 1) return t[0];
+    else return pair_sum<n / 2>(t) + pair_sum<n / 2>(t + n / 2);
+}
+
 // out[r] = scale * sum_c X[r,c] * v[c] + add[0]   (v == nullptr: ones; add == nullptr: 0)
 // One wave per row at a time, a lane takes 8 consecutive columns per step (16 bytes of X) when
 // VEC, single columns otherwise; v is staged in LDS once per block when it fits (`stage`), and a
@@ -173,47 +181,57 @@ rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx
     }
 }
 
-// partial[chunk][c] = sum over the rows of chunk `chunk` (chunkRows rows, in row order) of X[r,c].
+// partial[chunk][c] = sum over the rows of chunk `chunk` (chunkRows rows) of X[r,c]: SUBS runs of chunkRows / SUBS rows, each added in row
+// order, then in pairs.  The runs are what the sizes ask for (col_chunk_rows) and SUBS is 1, unless the workspace holds only longer chunks: then a block
+// adds up here, in the same pairs, the runs that cols_finish_kernel adds up otherwise, and the sums are the same bit for bit.
 // A thread owns 8 consecutive columns (16 bytes per row; ALIGNED: rows of whole aligned pieces, by non-temporal loads; else at any address, the columns
 // at the end of a row are read with those before them and shifted into place), or one column where rows are shorter
 // (WIDE false).  The loads of 8 rows are issued together, ahead of their additions (left to the compiler's unrolling they
 // went out one by one behind a bounds test: 50 us for 8192 x 8192 against 23 us).
-template <bool WIDE, bool ALIGNED>
+template <bool WIDE, bool ALIGNED, int SUBS>
 __global__ void __launch_bounds__(256)
 cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, float *__restrict__ partial, int chunkRows)
 {
     constexpr int W = WIDE ? 8 : 1, U = 8;
     const int c0 = (blockIdx.x * 256 + threadIdx.x) * W;
     if (c0 >= C) return;
-    const int r0 = blockIdx.y * chunkRows, r1 = min(R, r0 + chunkRows);
-    float acc[W];
+    const int runRows = chunkRows / SUBS, chunkEnd = min(R, (int)(blockIdx.y + 1) * chunkRows);
+    float acc[SUBS][W];
 #pragma unroll
-    for (int e = 0; e < W; ++e) acc[e] = 0.0f;
-    if constexpr (WIDE) {
-        const int at = ALIGNED || c0 < C - 8 ? c0 : C - 8;
-        for (int r = r0; r < r1; r += U) {
-            ge::i32x4_t x[U];
+    for (int q = 0; q < SUBS; ++q) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                x[u] = ge::i32x4_t{0, 0, 0, 0};
-                if (r + u < r1) x[u] = ALIGNED ? load_stream16(X + (long long)(r + u) * ldx + at) : load_any16(X + (long long)(r + u) * ldx + at);
-            }
+        for (int e = 0; e < W; ++e) acc[q][e] = 0.0f;
+        const int r0 = blockIdx.y * chunkRows + q * runRows, r1 = min(chunkEnd, r0 + runRows);
+        if constexpr (WIDE) {
+            const int at = ALIGNED || c0 < C - 8 ? c0 : C - 8;
+            for (int r = r0; r < r1; r += U) {
+                ge::i32x4_t x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (!ALIGNED && at != c0) x[u] = ge::shift_down_elements(x[u], c0 - at);
+                for (int u = 0; u < U; ++u) {
+                    x[u] = ge::i32x4_t{0, 0, 0, 0};
+                    if (r + u < r1) x[u] = ALIGNED ? load_stream16(X + (long long)(r + u) * ldx + at) : load_any16(X + (long long)(r + u) * ldx + at);
+                }
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[2 * e] += bf16_lo((unsigned)x[u][e]);
-                    acc[2 * e + 1] += bf16_hi((unsigned)x[u][e]);
+                for (int u = 0; u < U; ++u) {
+                    if (!ALIGNED && at != c0) x[u] = ge::shift_down_elements(x[u], c0 - at);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        acc[q][2 * e] += bf16_lo((unsigned)x[u][e]);
+                        acc[q][2 * e + 1] += bf16_hi((unsigned)x[u][e]);
+                    }
                 }
             }
+        } else {
+            for (int r = r0; r < r1; ++r) acc[q][0] += bf16_lo((unsigned)X[(long long)r * ldx + c0]);
         }
-    } else {
-        for (int r = r0; r < r1; ++r) acc[0] += bf16_lo((unsigned)X[(long long)r * ldx + c0]);
     }
 #pragma unroll
-    for (int e = 0; e < W; ++e)
-        if (c0 + e < C) partial[(long long)blockIdx.y * C + c0 + e] = acc[e];
+    for (int e = 0; e < W; ++e) {
+        float t[SUBS];
+#pragma unroll
+        for (int q = 0; q < SUBS; ++q) t[q] = acc[q][e];
+        if (c0 + e < C) partial[(long long)blockIdx.y * C + c0 + e] = pair_sum<SUBS>(t);
+    }
 }
 
 // sum of x[0..n) by one block: a thread adds every 256th element, then a fixed tree (x may be null: 0)
@@ -231,12 +249,13 @@ __device__ inline void block_vector_sum(int n, const float *__restrict__ x, floa
 
 // s[c] = sum of the chunks' partial sums; the block past the last column block adds up the bias into
 // s[C].  A block covers 64 columns: 16 groups of 16 threads, a thread 4 consecutive columns (16 bytes per
-// load).  Group g adds chunks g, g + 16, ... in ascending order, eight loads in flight at a time, then
-// the 16 sums are added in the order of g (32 groups of 8 threads: the same 5 us, a launch and a round trip).  (One thread per column over all chunks left the pass at
+// load).  Group g adds up 64-row chunks g, g + 16, ... in ascending order, eight loads in flight at a time, a chunk
+// whose partial sums are of 64 / SUBS rows in pairs; then the 16 sums are added in the order of g (32 groups of 8 threads: the same 5 us, a launch and a round trip).  (One thread per column over all chunks left the pass at
 // the latency of a chain of dependent loads: 10 us for 2 MB; 8 groups of single columns: 6.9 us.)
 constexpr int kFinishCols = 64, kFinishWays = 16;
+template <int SUBS>
 __global__ void __launch_bounds__(256)
-cols_finish_kernel(int C, int chunks, const float *__restrict__ partial, float *__restrict__ s, int nBias,
+cols_finish_kernel(int C, int partials, const float *__restrict__ partial, float *__restrict__ s, int nBias,
                    const float *__restrict__ bias)
 {
     if (blockIdx.x == gridDim.x - 1) {
@@ -250,28 +269,31 @@ cols_finish_kernel(int C, int chunks, const float *__restrict__ partial, float *
     // four columns by one 16-byte load at any address; those at the end of a row are pulled back and shifted into place
     const bool wide = C >= 4;
     const int at = wide && c > C - 4 ? C - 4 : c, sh = c - at;
-    for (int q0 = g; q0 < chunks; q0 += 8 * kFinishWays) {
-        float v[8][4];
+    constexpr int U = 8 / SUBS;                           // chunks whose loads are on their way together
+    for (int q0 = g; q0 * SUBS < partials; q0 += U * kFinishWays) {
+        float v[U][4][SUBS];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int q = q0 + u * kFinishWays;
-            ge::i32x4_t t = {0, 0, 0, 0};
-            if (q < chunks && c < C) {
-                const float *src = partial + (long long)q * C;
-                if (wide) {
-                    t = load_any16(src + at);
-                } else {
-                    for (int e = 0; e < C; ++e) t[e] = (int)__float_as_uint(src[e]);
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < SUBS; ++i) {
+                const int q = (q0 + u * kFinishWays) * SUBS + i;
+                ge::i32x4_t t = {0, 0, 0, 0};
+                if (q < partials && c < C) {
+                    const float *src = partial + (long long)q * C;
+                    if (wide) {
+                        t = load_any16(src + at);
+                    } else {
+                        for (int e = 0; e < C; ++e) t[e] = (int)__float_as_uint(src[e]);
+                    }
                 }
+                if (sh > 0) t = ge::shift_down_elements(t, 2 * sh);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[u][e][i] = __uint_as_float((unsigned)t[e]);
             }
-            if (sh > 0) t = ge::shift_down_elements(t, 2 * sh);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[u][e] = __uint_as_float((unsigned)t[e]);
-        }
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += v[u][e];
+            for (int e = 0; e < 4; ++e) acc[e] += pair_sum<SUBS>(v[u][e]);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) part[g][cl + e] = acc[e];
@@ -358,25 +380,36 @@ extern "C" ge_status_t gemm_rowsum_params_bf16_ex(int N, int K, const uint16_t *
         GE_LAUNCH(vector_sum_kernel, dim3(1), dim3(256), 0, st, N, bias, params + K);
         g_last_config = "rowsum_params_rows";
     } else {
-        // B is stored N x K: s[k] is the sum of column k, in two passes through the workspace
-        // of fewer, longer chunks where there is no room for the many: a caller's buffer, or the library's
-        // under capture, that holds the partial sums of 64 rows a chunk is enough
+        // B is stored N x K: s[k] is the sum of column k, in two passes through the workspace.  A caller's buffer (or the
+        // library's, under capture) that holds the partial sums of 64 rows a chunk is enough: where it has no room for
+        // those of the shorter runs the sizes ask for, a block adds up several runs, in the order of the second pass.
+        const int runRows = col_chunk_rows(N, K);
+        int subs = 1, partials = ceil_div(N, runRows);
         void *ws = nullptr;
-        int chunkRows = col_chunk_rows(N, K), chunks = ceil_div(N, chunkRows);
-        ge_status_t rc = acquire_workspace((size_t)chunks * (size_t)K * sizeof(float), workspace, workspace_bytes, st, &ws);
-        while (rc == GE_ERR_WORKSPACE && chunkRows < kMaxChunkRows) {
-            chunkRows *= 2;
-            chunks = ceil_div(N, chunkRows);
-            rc = acquire_workspace((size_t)chunks * (size_t)K * sizeof(float), workspace, workspace_bytes, st, &ws);
+        ge_status_t rc = acquire_workspace((size_t)partials * (size_t)K * sizeof(float), workspace, workspace_bytes, st, &ws);
+        while (rc == GE_ERR_WORKSPACE && runRows * subs < kMaxChunkRows) {
+            subs *= 2;
+            partials = ceil_div(N, runRows * subs);
+            rc = acquire_workspace((size_t)partials * (size_t)K * sizeof(float), workspace, workspace_bytes, st, &ws);
         }
         if (rc != GE_OK) return rc;
-        const dim3 grid((unsigned)ceil_div(K, 256 * (K >= 8 ? 8 : 1)), (unsigned)chunks);
         float *partial = (float *)ws;
-        if (K < 8)                        GE_LAUNCH((cols_partial_kernel<false, false>), grid, dim3(256), 0, st, N, K, B, (long long)ldb, partial, chunkRows);
-        else if (rows_aligned(K, B, ldb)) GE_LAUNCH((cols_partial_kernel<true, true>), grid, dim3(256), 0, st, N, K, B, (long long)ldb, partial, chunkRows);
-        else                              GE_LAUNCH((cols_partial_kernel<true, false>), grid, dim3(256), 0, st, N, K, B, (long long)ldb, partial, chunkRows);
-        GE_LAUNCH(cols_finish_kernel, dim3((unsigned)ceil_div(K, kFinishCols) + 1), dim3(256), 0, st, K, chunks, (const float *)ws,
-                           params, N, bias);
+        const dim3 grid((unsigned)ceil_div(K, 256 * (K >= 8 ? 8 : 1)), (unsigned)partials);
+        auto sums = [&](auto subsC) {
+            constexpr int S = decltype(subsC)::value;
+            const int chunkRows = runRows * S;
+            if (K < 8)                        GE_LAUNCH((cols_partial_kernel<false, false, S>), grid, dim3(256), 0, st, N, K, B, (long long)ldb, partial, chunkRows);
+            else if (rows_aligned(K, B, ldb)) GE_LAUNCH((cols_partial_kernel<true, true, S>), grid, dim3(256), 0, st, N, K, B, (long long)ldb, partial, chunkRows);
+            else                              GE_LAUNCH((cols_partial_kernel<true, false, S>), grid, dim3(256), 0, st, N, K, B, (long long)ldb, partial, chunkRows);
+        };
+        if (subs == 1)      sums(std::integral_constant<int, 1>{});
+        else if (subs == 2) sums(std::integral_constant<int, 2>{});
+        else                sums(std::integral_constant<int, 4>{});
+        const dim3 finish((unsigned)ceil_div(K, kFinishCols) + 1);
+        const int left = kMaxChunkRows / (runRows * subs);         // partial sums of a 64-row chunk
+        if (left == 1)      GE_LAUNCH(cols_finish_kernel<1>, finish, dim3(256), 0, st, K, partials, (const float *)ws, params, N, bias);
+        else if (left == 2) GE_LAUNCH(cols_finish_kernel<2>, finish, dim3(256), 0, st, K, partials, (const float *)ws, params, N, bias);
+        else                GE_LAUNCH(cols_finish_kernel<4>, finish, dim3(256), 0, st, K, partials, (const float *)ws, params, N, bias);
         g_last_config = "rowsum_params_cols";
     }
     return ge_host::take_launch_error() == hipSuccess ? GE_OK : GE_ERR_LAUNCH;

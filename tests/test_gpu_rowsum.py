@@ -150,3 +150,25 @@ def test_rowsum_small_workspace(oracle):
     assert np.all(np.abs(params[:K].double().cpu().numpy() - want) <= 80 * 2.0 ** -24 * mass)
     with pytest.raises(RuntimeError):
         binding.gemm_rowsum_params_bf16(N, K, dW, K, True, None, params, workspace=torch.empty(small - 1, dtype=torch.uint8, device="cuda:0"))
+
+
+@pytest.mark.parametrize("N,K,misalign", [(911, 1408, 0), (2049, 1029, 1), (77, 8, 0), (130, 3, 0), (9001, 100, 1), (9024, 2048, 0)])
+def test_rowsum_params_do_not_depend_on_the_workspace(N, K, misalign):
+    """The same sums bit for bit from every workspace that is accepted: one for the partial sums of the runs the sizes ask for
+    (16 rows, 32 for the two longest) and the smaller ones that hold those of 32 and 64 rows."""
+    import torch
+    from paper_2604_01489_amd import binding, inputs as gen
+    W = gen.to_bf16_bits(gen.uniform(9, gen.STREAM_B, N * K + misalign, -1.0, 1.0))
+    dW = to_device(W)[misalign:]
+    outs, default = [], binding.rowsum_params_workspace_bytes(N, K, True)
+    for rows in (16, 32, 64):
+        need = -(-N // rows) * K * 4
+        if need > default:
+            continue
+        params = torch.full((K + 1,), -7.0e30, dtype=torch.float32, device="cuda:0")
+        ws = torch.full((need,), 0x7F, dtype=torch.uint8, device="cuda:0")
+        binding.gemm_rowsum_params_bf16(N, K, dW, K, True, None, params, workspace=ws)
+        torch.cuda.synchronize()
+        outs.append(params.cpu().numpy().tobytes())
+    assert len(outs) == (3 if default == -(-N // 16) * K * 4 else 2)
+    assert all(o == outs[0] for o in outs)
