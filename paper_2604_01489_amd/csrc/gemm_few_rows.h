@@ -6,7 +6,11 @@
 // of eight (seven on their way; four where the workgroups are more than the CUs, so that two or three share one), both operands by direct-to-LDS loads in 256-byte row pieces, the weights with the
 // non-temporal hint; each workgroup starts its walk at another stage.  Four waves: two blocks of 16 weight rows x two halves
 // of a stage's k; the halves are added through LDS in a fixed order, then the chain, 32 consecutive columns of a row of C
-// at a time.  (Weights straight from memory into the fragments' registers, 16 rows of 64 bytes per load instruction and
+// at a time.  A wave adds in runs of four stages (256 of its k, eight matrix instructions) and the runs' sums in turn: one
+// chain over all of its k was less exact than the tiles' K slices, which are chains of 512 k or more (error
+// against 64 bits, slices / one chain / runs: 1.30e-7 / 1.86e-7 / 9.8e-8 at 16 x 8192 x 2048, 2.73e-7 / 3.97e-7 / 1.18e-7 at
+// 16 x 8192 x 8192, 3.52e-7 / 5.73e-7 / 1.40e-7 at 5 x 6144 x 16384), and costs nothing
+// at 16 x 8192 x 8192; 12 x 2808 x 2880, 88 workgroups, 8.7 -> 9.2 us).  (Weights straight from memory into the fragments' registers, 16 rows of 64 bytes per load instruction and
 // no LDS, were slower: 35.9 us at 16 x 8192 x 8192, the 128 x 128 tile with K slices 38.4, this
 // 23.0: 5.9 TB/s, launch included.  32 rows 38.4 -> 25.2.  An image of 64 rows, six stages deep, was built and taken out:
 // 64 x 8192 x 8192 39.8 -> 33.3 us, but 63 x 10432 x 6024, 326 workgroups, 47.2 -> 58.4.)
@@ -24,6 +28,7 @@ gemm_few_rows_kernel(const GemmParams p)
     using namespace ge_skinny;
     constexpr int NJ = MP / 16, S_BYTES = MP * A_ROW_BYTES, S_SLABS = S_BYTES / 1024, STAGE = A_BYTES + S_BYTES;
     constexpr int LOADS = A_SLABS / 4 + S_SLABS / 4;       // loads per wave and stage
+    constexpr int RUN = 4;                                 // stages whose products are one chain of additions
     static_assert((STAGES - 2) * LOADS <= 63 && S_SLABS % 4 == 0, "range of the load counter; the loads divide over the waves");
     __shared__ __attribute__((aligned(1024))) char smem[STAGES * STAGE];
     const unsigned ldsBase = (unsigned)(size_t)(GE_LDS char *)smem;
@@ -80,22 +85,34 @@ gemm_few_rows_kernel(const GemmParams p)
 #pragma unroll
     for (int t = 0; t < STAGES - 1; ++t) issue(t, t);
     int slot = 0;                                        // of stage t: t % STAGES
-    for (int t = 0; t < steps; ++t) {
-        // stage t has landed, and every wave is past the multiply of t - 1, whose ring slot is refilled now
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 2) * LOADS) : "memory");
-        issue(t + STAGES - 1, slot == 0 ? STAGES - 1 : slot - 1);
-        const unsigned img = ldsBase + (unsigned)(slot * STAGE);
-        slot = slot == STAGES - 1 ? 0 : slot + 1;
+    for (int t0 = 0; t0 < steps; t0 += RUN) {
+        f32x4_t run[NJ];
 #pragma unroll
-        for (int ks = 0; ks < KS / 64; ++ks) {           // this wave's half of the stage, 32 k at a time
-            const int kk = kh * (KS / 2) + 32 * ks;
-            const bf16x8_t fw = *(const GE_LDS bf16x8_t *)(size_t)(img + (unsigned)ge_skinny::a_frag_offset(16 * rg, kk, lane));
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const bf16x8_t fs = *(const GE_LDS bf16x8_t *)(size_t)(img + (unsigned)(A_BYTES + ge_skinny::a_frag_offset(16 * j, kk, lane)));
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw, fs, acc[j], 0, 0, 0);
+            for (int r = 0; r < 4; ++r) run[j][r] = 0.0f;
+        const int end = min(steps, t0 + RUN);
+        for (int t = t0; t < end; ++t) {
+            // stage t has landed, and every wave is past the multiply of t - 1, whose ring slot is refilled now
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 2) * LOADS) : "memory");
+            issue(t + STAGES - 1, slot == 0 ? STAGES - 1 : slot - 1);
+            const unsigned img = ldsBase + (unsigned)(slot * STAGE);
+            slot = slot == STAGES - 1 ? 0 : slot + 1;
+#pragma unroll
+            for (int ks = 0; ks < KS / 64; ++ks) {       // this wave's half of the stage, 32 k at a time
+                const int kk = kh * (KS / 2) + 32 * ks;
+                const bf16x8_t fw = *(const GE_LDS bf16x8_t *)(size_t)(img + (unsigned)ge_skinny::a_frag_offset(16 * rg, kk, lane));
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    const bf16x8_t fs = *(const GE_LDS bf16x8_t *)(size_t)(img + (unsigned)(A_BYTES + ge_skinny::a_frag_offset(16 * j, kk, lane)));
+                    run[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw, fs, run[j], 0, 0, 0);
+                }
             }
         }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[j][r] += run[j][r];
     }
     // the empty loads of the stages past the end have retired; every wave is done with the ring
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");

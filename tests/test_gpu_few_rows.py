@@ -41,3 +41,23 @@ def test_few_rows_is_repeatable_and_ignores_the_padding(oracle):
     ref = A[:, :K].double() @ W[:, :K].double().t()
     # fp32 sums of K exact products of N(0, 1) values: sqrt(K) 2^-24 of their size, sqrt(K)
     assert np.abs(outs[0] - ref.cpu().numpy()).max() < 8 * K * 2.0 ** -24
+
+
+@pytest.mark.parametrize("M,N,K,slices", [(16, 8192, 2048, 4), (12, 2808, 2880, 5), (32, 1024, 3072, 6), (16, 8192, 8192, 4), (5, 6144, 16384, 8),
+                                          (32, 8192, 16384, 16)])
+def test_few_rows_are_as_exact_as_k_slices(M, N, K, slices):
+    """fp32 output: no further from the 64-bit result than the tiles with as many K slices as their plan takes or more.
+    The errors are those of 32768 to 262144 outputs: their norm is steady to a percent."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.randn(M, K, device="cuda", generator=g).bfloat16()
+    W = torch.randn(N, K, device="cuda", generator=g).bfloat16()
+    ref = A.double() @ W.double().t().contiguous()
+    err = {}
+    for plan, kw in [("auto", {}), ("splitk", dict(split_k=slices))]:
+        C = torch.empty(M, N, device="cuda")
+        binding.gemm_epilogue_bf16_fused(M, N, K, A, K, W, K, C, N, transB=True, plan=plan, **kw)
+        torch.cuda.synchronize()
+        assert ("few_rows" in binding.last_config()) == (plan == "auto"), binding.last_config()
+        err[plan] = float((C.double() - ref).norm() / ref.norm())
+    assert err["auto"] <= 1.01 * err["splitk"], err
