@@ -264,3 +264,18 @@ def test_planner_properties_over_random_shapes(lib):
     # many output tiles are never sliced, one tile with a long K always is
     assert binding.auto_split_k(8192, 8192, 65536) == 1
     assert binding.auto_split_k(128, 128, 65536) > 8
+
+
+def test_any_alignment_takes_the_guarded_kernels_slices(lib):
+    """Operands the direct-to-LDS kernels do not take: the kernel for any alignment and the guarded one slice K alike, so that
+    the sums are as exact on either (shapes whose slice of K is no multiple of 64 among them)."""
+    def bytes_of(M, N, K, kw, option):
+        binding.set_option("force_config", option)
+        try:
+            return binding.fused_workspace_bytes(binding.fused_args(M, N, K, P + 2, K, P, K, P, N, transB=True, row_scale_ptr=P, **kw))
+        finally:
+            binding.set_option("force_config", None)
+    shapes = [(257, 259, 4097, {}), (131, 1027, 16383, {}), (300, 301, 1025, {}), (131, 67, 2051, {}), (1999, 1537, 2051, {}),
+              (769, 771, 33, dict(plan="splitk", split_k=2)), (131, 1027, 1000, dict(plan="splitk", split_k=7)), (99, 101, 8191, dict(batch=3))]
+    for M, N, K, kw in shapes:
+        assert bytes_of(M, N, K, kw, None) == bytes_of(M, N, K, kw, "generic"), (M, N, K, kw)
