@@ -101,7 +101,8 @@ typedef enum {
  * 16 bytes at whatever address a row starts (fp32: multiples of 4, any alignment
  * likewise) or, below about 17 million multiply-adds, a guarded generic one, with
  * the same result contract (the coding and debugging guide's rule for vectorised
- * copies: gated by alignment, with a correct fallback).  Large-K
+ * copies: gated by alignment, with a correct fallback).  fp32 results whose rows are
+ * 2^24 elements or more apart take the guarded kernel unless whole tiles cover them.  Large-K
  * small-MN shapes use split-K with the library's workspace of the stream (see
  * "Partial results" above).
  */

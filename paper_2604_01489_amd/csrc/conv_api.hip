@@ -130,7 +130,7 @@ ge_status_t plan_conv(const ge_conv_args_t &a, ConvPlan *out)
 
     // gathering kernel: a K step is 32 channels of one tap, chunks of 8 channels are 16 aligned
     // bytes, byte offsets into the input fit 31 bits; bf16 output leaves in 16-byte row pieces
-    bool gather = !((((uintptr_t)a.X) | ((uintptr_t)a.Wt)) & 15u) && (a.Cin % 8 == 0) && (a.Cout % 8 == 0) && a.Cout < ge::EDGE_LDC_MAX &&
+    bool gather = !((((uintptr_t)a.X) | ((uintptr_t)a.Wt)) & 15u) && (a.Cin % 8 == 0) && (a.Cout % 8 == 0) &&
                 xElems * 2 < (1ll << 31) - (1 << 20) && K * 2 * 256 + 1024 < (1ll << 31);
     if (a.y_type == GE_DTYPE_BF16 && (((uintptr_t)a.Y) & 15u)) gather = false;
     const bool fast = gather && a.Cin % 32 == 0;
@@ -169,7 +169,8 @@ ge_status_t plan_conv(const ge_conv_args_t &a, ConvPlan *out)
             if (!out->halo || hp.cost < out->haloPlan.cost) { out->halo = 1 + v; out->haloPlan = hp; }
         }
     }
-    ge_status_t st = make_plan_bf16((int)M, a.Cout, (int)K, 1, fast, GE_PLAN_AUTO, 0, &out->pl);
+    const bool f32Out = a.y_type == GE_DTYPE_F32;
+    ge_status_t st = make_plan_bf16_for((int)M, a.Cout, (int)K, 1, fast, GE_PLAN_AUTO, 0, a.Cout, f32Out, &out->pl);
     // Channels a multiple of 8 only: the gathering kernel from a million multiply-adds on (one image of 7 x 7 x 80 -> 32,
     // 3 x 3, is at that size: 39.1 -> 14.2 us; below, the guarded kernel is the shorter launch), with as many K slices as the
     // guarded kernel takes: no call needs a workspace, or a larger one, that did not, and the sums are as exact (9 x 9 x 200 ->
@@ -177,7 +178,7 @@ ge_status_t plan_conv(const ge_conv_args_t &a, ConvPlan *out)
     out->c8 = gather && !fast && !out->rows && opt_force_config() != FORCE_GENERIC && (double)M * a.Cout * K >= 1024.0 * 1024;
     if (st == GE_OK && out->c8) {
         const int slices = out->pl.splitK;
-        st = make_plan_bf16((int)M, a.Cout, (int)K, 1, true, slices > 1 ? GE_PLAN_SPLITK : GE_PLAN_DIRECT, slices, &out->pl);
+        st = make_plan_bf16_for((int)M, a.Cout, (int)K, 1, true, slices > 1 ? GE_PLAN_SPLITK : GE_PLAN_DIRECT, slices, a.Cout, f32Out, &out->pl);
     }
     if (st == GE_OK && out->halo) { out->pl.splitK = 1; out->pl.kPerSlice = (int)K; }
     if (st == GE_OK && out->rows) { out->pl.splitK = 1; out->pl.kPerSlice = (int)K; }

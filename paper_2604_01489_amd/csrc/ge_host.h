@@ -86,6 +86,13 @@ bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bo
 // likewise the kernel for operands of any alignment, where `fast` is not given
 ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t plan, int split_k, Plan *out,
                            bool skinny = false, bool ragged = false);
+// The same for a result whose rows are ldc elements apart.  Tiles on the edge of C leave fp32 (the result, or the partial sums
+// of a K slice, rows of N) through 31-bit offsets (edge_rows): rows of EDGE_LDC_MAX elements and more take the guarded kernel
+// there (250 x 4096 x 1024 with rows 2^24 apart 57 us, 21 with a branch per masked store, which costs the others 5 to 8).
+// Full tiles, bf16 output and the tall-skinny kernel are stored through 64-bit addresses and stay where they are (256 rows of
+// the same: 12 us).
+ge_status_t make_plan_bf16_for(int M, int N, int K, int batch, bool fast, ge_plan_t plan, int split_k, int ldc, bool f32Out, Plan *out,
+                               bool skinny = false, bool ragged = false);
 size_t partial_bytes(int M, int N, int batch, int splitK);
 int choose_group_m(int tilesM, int tilesN);
 // The four-wave kernel (gemm_bf16_w4.h) takes launches of 256 x 256 tiles whose blocks walk a K range

@@ -63,7 +63,6 @@ bool fast_ok(const ge_fused_args_t &a)
 {
     if ((((uintptr_t)a.A) | ((uintptr_t)a.B)) & 15u) return false;
     if ((a.lda | a.ldb) & 7) return false;
-    if (a.ldc >= ge::EDGE_LDC_MAX) return false;
     if ((a.transA ? a.M : a.K) & 7) return false;
     if ((a.K | a.N) & 7) return false;            // B's row payload; N also for the 16-byte pieces of a bf16 C
     // bf16 output leaves the kernel in 16-byte row pieces
@@ -103,6 +102,16 @@ bool few_rows_ok(const ge_fused_args_t &a)
     return (long long)ceil_div(a.N, 32) * a.batch >= kNumCU * 3 / 4 || a.K <= 3072;
 }
 
+// a triangular A: every tile walks its own K range, in one pass (K slices would cut across them);
+// a symmetric A given by one triangle: the guarded kernel (it mirrors indices element by element),
+// unless the kernel for few output columns takes the call
+ge_status_t plan_of(const ge_fused_args_t &a, Plan *out)
+{
+    const bool triangular = a.a_structure == GE_A_LOWER || a.a_structure == GE_A_UPPER;
+    return make_plan_bf16_for(a.M, a.N, a.K, a.batch, fast_ok(a) && !is_symmetric(a), triangular ? GE_PLAN_DIRECT : a.plan, a.split_k, a.ldc,
+                              a.c_type == GE_DTYPE_F32, out, false, ragged(a));
+}
+
 template <int BM>
 bool launch_tile(const GemmParams &p, const Plan &pl, bool raw, dim3 grid, hipStream_t st)
 {
@@ -135,9 +144,7 @@ extern "C" size_t gemm_epilogue_fused_workspace_bytes(const ge_fused_args_t *arg
     }
     if (few_rows_ok(a)) return 0;
     Plan pl;
-    const bool triangular = a.a_structure == GE_A_LOWER || a.a_structure == GE_A_UPPER;
-    const bool fast = fast_ok(a) && !is_symmetric(a);
-    if (make_plan_bf16(a.M, a.N, a.K, a.batch, fast, triangular ? GE_PLAN_DIRECT : a.plan, a.split_k, &pl, false, ragged(a)) != GE_OK) return 0;
+    if (plan_of(a, &pl) != GE_OK) return 0;
     return partial_bytes(a.M, a.N, a.batch, pl.splitK);
 }
 
@@ -154,12 +161,7 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
         return run_bf16(a.M, a.N, a.K, a.A, a.lda, a.B, a.ldb, a.bias, a.alpha, a.act, (float *)a.C, a.ldc, a.batch, a.plan,
                         a.split_k, a.workspace, a.workspace_bytes, stream);
     Plan pl;
-    // a triangular A: every tile walks its own K range, in one pass (K slices would cut across them);
-    // a symmetric A given by one triangle: the guarded kernel (it mirrors indices element by element),
-    // unless the kernel for few output columns takes the call (below)
-    const bool triangular = a.a_structure == GE_A_LOWER || a.a_structure == GE_A_UPPER;
-    const ge_plan_t plan = triangular ? GE_PLAN_DIRECT : a.plan;
-    st = make_plan_bf16(a.M, a.N, a.K, a.batch, fast_ok(a) && !is_symmetric(a), plan, a.split_k, &pl, false, ragged(a));
+    st = plan_of(a, &pl);
     if (st != GE_OK) return st;
     const bool fewRows = few_rows_ok(a);
     if (fewRows) pl.splitK = 1;

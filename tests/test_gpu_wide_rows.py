@@ -1,0 +1,90 @@
+"""Rows of C that are 2^24 elements and more apart, and just less: full tiles and bf16 output are stored through 64-bit addresses and
+keep their kernels, fp32 tiles on the edge of C go through 31-bit offsets up to that distance and to the guarded kernels beyond."""
+import pytest
+
+from paper_2604_01489_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+LIMIT = 1 << 24
+CANARY = -7.0e30
+
+
+def _buffer(rows, ld, cols, dtype):
+    import torch
+    if torch.cuda.mem_get_info()[0] < 24 << 30:
+        pytest.skip("needs 24 GB")
+    return torch.full(((rows - 1) * ld + cols + 8,), CANARY, device="cuda", dtype=dtype)
+
+
+def _check(buf, rows, ld, cols, ref, tol):
+    """The rows are right and nothing else was written."""
+    import torch
+    got = buf.as_strided((rows, cols), (ld, 1))
+    assert torch.isfinite(got).all()
+    assert float((got.double() - ref).norm() / ref.norm()) <= tol
+    written = sum(int((piece != CANARY).sum()) for piece in buf.split(1 << 28)) if buf.dtype == torch.float32 else None
+    assert written is None or written == rows * cols
+
+
+def _operands(M, N, K, dtype):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn(M, K, device="cuda", generator=g).to(dtype)
+    B = torch.randn(K, N, device="cuda", generator=g).to(dtype)
+    return A, B, A.double() @ B.double()
+
+
+# kernels whose tiles are all full, or whose output is bf16: the same kernel at any distance of the rows
+@pytest.mark.parametrize("M,N,K,out", [(128, 256, 64, "f32"), (136, 264, 96, "bf16"), (32, 264, 200, "bf16")])
+def test_bf16_kernels_at_any_distance(M, N, K, out):
+    import torch
+    A, B, ref = _operands(M, N, K, torch.bfloat16)
+    dtype = torch.float32 if out == "f32" else torch.bfloat16
+    names = []
+    for ldc in (N, LIMIT, LIMIT + 8):
+        C = _buffer(M, ldc, N, dtype)
+        binding.gemm_epilogue_bf16_fused(M, N, K, A, K, B, N, C, ldc)
+        names.append(binding.last_config())
+        torch.cuda.synchronize()
+        # fp32 sums of K products of N(0, 1) values; half a bf16 step
+        _check(C, M, ldc, N, ref, 2e-6 if out == "f32" else 2.0 ** -9)
+        del C
+    assert len(set(names)) == 1 and "128x128" in names[0], names
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 128, 48), (64, 64, 256)])
+def test_f32_kernels_at_any_distance(M, N, K):
+    import torch
+    A, B, ref = _operands(M, N, K, torch.float32)
+    names = []
+    for ldc in (N, LIMIT, LIMIT + 1):
+        C = _buffer(M, ldc, N, torch.float32)
+        binding.gemm_epilogue_f32(M, N, K, A, K, B, N, None, 1.0, "none", C, ldc)
+        names.append(binding.last_config())
+        torch.cuda.synchronize()
+        _check(C, M, ldc, N, ref, 2e-6)
+        del C
+    assert len(set(names)) == 1 and "generic" not in names[0], names
+
+
+# tiles on the edge, fp32: the offsets at their largest, and the guarded kernels from there on
+@pytest.mark.parametrize("ldc,past", [(LIMIT - 1, False), (LIMIT, True)])
+@pytest.mark.parametrize("M,N,K,dtype,aligned", [(96, 136, 64, "bf16", True), (96, 200, 900, "bf16", False), (96, 68, 48, "f32", True), (96, 67, 33, "f32", False)])
+def test_edge_tiles_near_the_limit(M, N, K, dtype, aligned, ldc, past):
+    import torch
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    A, B, ref = _operands(M, N, K, td)
+    C = _buffer(M, ldc, N, torch.float32)
+    shift = 0 if aligned else 1                       # B one element off: no kernel of aligned operands takes it
+    Bs = torch.zeros(K * N + shift, device="cuda", dtype=td)
+    Bs[shift:] = B.reshape(-1)
+    call = binding.gemm_epilogue_bf16 if dtype == "bf16" else binding.gemm_epilogue_f32
+    call(M, N, K, A, K, Bs[shift:], N, None, 1.0, "none", C, ldc)
+    name = binding.last_config()
+    torch.cuda.synchronize()
+    _check(C, M, ldc, N, ref, 2e-6)
+    if aligned:
+        assert (("generic" in name) if dtype == "bf16" else ("w4" not in name)) == past, name
+
+
