@@ -15,6 +15,10 @@
 
 namespace ge {
 
+// Whether rows (columns, k) first .. first + n - 1 of a tile lie inside 0 .. end - 1: first <= the largest int, so nothing is
+// added to it (a tile at the end of 2^31 - 1 rows would seem to lie inside, and store a row beyond C).
+GE_HD constexpr bool tile_inside(int first, int n, int end) { return end - first >= n; }
+
 // LDS byte offset of 16-byte chunk c (8 bf16 along k, c < 4) of row r in an A stage.  Address
 // bits 4-5: chunk ^ r[2:1]; bit 6: r[0]; bit 7: r[3]; 256-byte line: (r/16)*4 + r[2:1].  Any 8
 // or 16 consecutive rows reading the same chunk fall in distinct banks.

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bf16_layout.h"
+
 namespace ge {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
@@ -85,7 +87,7 @@ enum { TRI_NONE = 0, TRI_LOWER = 1, TRI_UPPER = 2, TRI_SYM_LOWER = 3, TRI_SYM_UP
 // of every kernel's K step, so the range stays aligned to it.
 __device__ inline void triangular_k_range(const GemmParams &p, int m0, int BM, int &kBegin, int &kEnd)
 {
-    if (p.triA == TRI_LOWER) kEnd = min(kEnd, m0 + BM);
+    if (p.triA == TRI_LOWER && tile_inside(m0, BM, kEnd)) kEnd = m0 + BM;
     if (p.triA == TRI_UPPER) kBegin = max(kBegin, m0);
     if (kEnd < kBegin) kEnd = kBegin;
 }

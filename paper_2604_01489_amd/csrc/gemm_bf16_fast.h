@@ -694,7 +694,7 @@ gemm_bf16_kernel(const GemmParams p)
                 (waveE % WN) * T::WTN + 4 * (laneE >> 4), waveE, laneE, resInLds);
         } else {
             // only the tiles that hang over M or N pay for masked stores (a uniform branch)
-            if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) fused_epilogue_f32_direct<TM, TN, false>(p, tc.b, acc, rowLane, colLane);
+            if (!EDGE || (tile_inside(m0, BM, p.M) && tile_inside(n0, BN, p.N))) fused_epilogue_f32_direct<TM, TN, false>(p, tc.b, acc, rowLane, colLane);
             else fused_epilogue_f32_direct<TM, TN, EDGE != 0>(p, tc.b, acc, rowLane, colLane);
         }
     } else {
@@ -708,7 +708,7 @@ gemm_bf16_kernel(const GemmParams p)
             cBase = p.C + (long long)tc.b * p.strideC;
         }
         // only the tiles that hang over M or N pay for masked stores (a uniform branch)
-        if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) store_plain_tile<RAW, ACT, false>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
+        if (!EDGE || (tile_inside(m0, BM, p.M) && tile_inside(n0, BN, p.N))) store_plain_tile<RAW, ACT, false>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
         else store_plain_tile<RAW, ACT, EDGE != 0>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
     }
 }

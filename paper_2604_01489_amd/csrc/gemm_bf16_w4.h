@@ -317,7 +317,7 @@ gemm_bf16_w4_kernel(const GemmParams p)
         } else {
             // only the tiles that hang over M or N pay for masked stores (a uniform branch; masked, the
             // stores of an 8192^3-sized launch cost 10 % of its run)
-            if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) fused_epilogue_f32_direct<TM, TN, false>(p, tc.b, acc, rowLane, colLane);
+            if (!EDGE || (tile_inside(m0, BM, p.M) && tile_inside(n0, BN, p.N))) fused_epilogue_f32_direct<TM, TN, false>(p, tc.b, acc, rowLane, colLane);
             else fused_epilogue_f32_direct<TM, TN, EDGE>(p, tc.b, acc, rowLane, colLane);
         }
     } else {
@@ -331,7 +331,7 @@ gemm_bf16_w4_kernel(const GemmParams p)
             cBase = p.C + (long long)tc.b * p.strideC;
         }
         // only the tiles that hang over M or N pay for masked stores (a uniform branch)
-        if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) store_plain_tile<RAW, ACT, false>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
+        if (!EDGE || (tile_inside(m0, BM, p.M) && tile_inside(n0, BN, p.N))) store_plain_tile<RAW, ACT, false>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
         else store_plain_tile<RAW, ACT, EDGE != 0>(p.bias, p.alpha, cBase, ldc, p.M, p.N, acc, rowLane, colLane);
     }
 }

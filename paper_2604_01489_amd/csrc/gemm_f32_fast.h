@@ -212,7 +212,7 @@ gemm_f32_fast_kernel(const GemmParams p)
     };
     // the case of the activation, then the mask of a tile on the edge: uniform branches around the whole tile
     auto store_by_mask = [&](auto actC) {
-        if (!EDGE || (m0 + BM <= p.M && n0 + BN <= p.N)) store_tile(std::false_type{}, actC);
+        if (!EDGE || (tile_inside(m0, BM, p.M) && tile_inside(n0, BN, p.N))) store_tile(std::false_type{}, actC);
         else store_tile(std::bool_constant<EDGE>{}, actC);
     };
     if (RAW || p.act == ACT_NONE) store_by_mask(std::integral_constant<int, ACT_NONE>{});

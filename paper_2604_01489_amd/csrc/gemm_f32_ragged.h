@@ -257,7 +257,7 @@ gemm_f32_ragged_kernel(const GemmParams p)
     };
     // the case of the activation, then the mask of a tile on the edge: uniform branches around the whole tile
     auto store_by_mask = [&](auto actC) {
-        if (m0 + BT <= p.M && n0 + BT <= p.N) store_tile(std::false_type{}, actC);
+        if (tile_inside(m0, BT, p.M) && tile_inside(n0, BT, p.N)) store_tile(std::false_type{}, actC);
         else store_tile(std::true_type{}, actC);
     };
     if (RAW || p.act == ACT_NONE) store_by_mask(std::integral_constant<int, ACT_NONE>{});

@@ -220,11 +220,11 @@ gemm_bf16_ragged_kernel(const GemmParams p)
     } else {
         const int rowLane = m0 + wm * WT + 4 * (lane >> 4), colLane = n0 + wn * WT + (lane & 15);
         if constexpr (MODE == 1) {
-            if (m0 + BT <= p.M && n0 + BT <= p.N) fused_epilogue_f32_direct<T, T, false>(p, tc.b, acc, rowLane, colLane);
+            if (tile_inside(m0, BT, p.M) && tile_inside(n0, BT, p.N)) fused_epilogue_f32_direct<T, T, false>(p, tc.b, acc, rowLane, colLane);
             else fused_epilogue_f32_direct<T, T, true>(p, tc.b, acc, rowLane, colLane);
         } else {
             float *cBase = p.C + (long long)tc.s * p.sliceStride + (long long)tc.b * p.M * p.N;
-            if (m0 + BT <= p.M && n0 + BT <= p.N) store_plain_tile<true, ACT_NONE, false>(nullptr, 1.0f, cBase, p.N, p.M, p.N, acc, rowLane, colLane);
+            if (tile_inside(m0, BT, p.M) && tile_inside(n0, BT, p.N)) store_plain_tile<true, ACT_NONE, false>(nullptr, 1.0f, cBase, p.N, p.M, p.N, acc, rowLane, colLane);
             else store_plain_tile<true, ACT_NONE, true>(nullptr, 1.0f, cBase, p.N, p.M, p.N, acc, rowLane, colLane);
         }
     }

@@ -91,6 +91,15 @@ int main()
             run<64, false>(few, n, n + 1, 0, n);
             run<64, true>(n, 9, n + 1, 0, 9);
         }
+    // tiles at the largest sizes: what hangs over the end does, at no sum beyond the largest int
+    for (int n : {32, 64, 128, 256})
+        for (long long end : {1ll, 63ll, 64ll, 255ll, 256ll, 257ll, (1ll << 31) - 257, (1ll << 31) - 256, (1ll << 31) - 129, (1ll << 31) - 64, (1ll << 31) - 1}) {
+            volatile int first = (int)((end - 1) / n * n), size = (int)end;
+            if (tile_inside(first, n, size) != (first + (long long)n <= end)) {
+                std::printf("tile of %d at %d of %lld\n", n, first, end);
+                return 1;
+            }
+        }
     std::printf("ragged layout ok: %lld elements\n", checked);
     return 0;
 }
