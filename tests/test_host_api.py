@@ -279,3 +279,16 @@ def test_any_alignment_takes_the_guarded_kernels_slices(lib):
               (769, 771, 33, dict(plan="splitk", split_k=2)), (131, 1027, 1000, dict(plan="splitk", split_k=7)), (99, 101, 8191, dict(batch=3))]
     for M, N, K, kw in shapes:
         assert bytes_of(M, N, K, kw, None) == bytes_of(M, N, K, kw, "generic"), (M, N, K, kw)
+
+
+def test_any_alignment_refuses_what_the_guarded_kernel_refuses(lib):
+    """The limit on output tiles is that of the guarded kernel's 64 x 64 ones, whichever tile a call gets (host only: a plan)."""
+    def slices_bytes(M, option):
+        binding.set_option("force_config", option)
+        try:
+            return binding.fused_workspace_bytes(binding.fused_args(M, 8, 64, P + 2, 64, P, 64, P, 8, transB=True, plan="splitk", split_k=2))
+        finally:
+            binding.set_option("force_config", None)
+    for M in (1 << 20, (1 << 31) - 64, (1 << 31) - 63, (1 << 31) - 1):
+        assert slices_bytes(M, None) == slices_bytes(M, "generic"), M
+    assert slices_bytes((1 << 31) - 1, None) == 0
