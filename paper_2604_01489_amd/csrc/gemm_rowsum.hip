@@ -129,7 +129,9 @@ rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx
     float acc[kBlockRows];
 #pragma unroll
     for (int u = 0; u < kBlockRows; ++u) acc[u] = 0.0f;
-    for (int c0 = (wg * 64 + lane) * 8; c0 < C; c0 += SWEEP) {
+    // (unsigned: a sweep beyond the last of nearly 2^31 columns is past the largest int)
+    for (unsigned first = (wg * 64 + lane) * 8; first < (unsigned)C; first += SWEEP) {
+        const int c0 = (int)first;
         ge::i32x4_t x[kBlockRows];
         float vv[8];
         if constexpr (ANY) {
@@ -240,7 +242,7 @@ __device__ inline void block_vector_sum(int n, const float *__restrict__ x, floa
     __shared__ float part[4];
     float acc = 0.0f;
     if (x != nullptr)
-        for (int i = threadIdx.x; i < n; i += 256) acc += x[i];
+        for (unsigned i = threadIdx.x; i < (unsigned)n; i += 256) acc += x[i];
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
     __syncthreads();

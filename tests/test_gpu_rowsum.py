@@ -172,3 +172,19 @@ def test_rowsum_params_do_not_depend_on_the_workspace(N, K, misalign):
         outs.append(params.cpu().numpy().tobytes())
     assert len(outs) == (3 if default == -(-N // 16) * K * 4 else 2)
     assert all(o == outs[0] for o in outs)
+
+
+@pytest.mark.parametrize("K", [2 ** 31 - 1, 2 ** 31 - 8])
+def test_rowsum_of_the_longest_rows(K):
+    """Rows of nearly 2^31 columns, odd and aligned: the sweep over them ends at the last one (every other product is zero)."""
+    import torch
+    from paper_2604_01489_amd import binding
+    if torch.cuda.mem_get_info()[0] < 24 << 30:
+        pytest.skip("needs 24 GB")
+    A = torch.zeros(K, device="cuda", dtype=torch.bfloat16)
+    params = torch.zeros(K + 1, device="cuda")
+    A[0], A[K - 1], params[0], params[K - 1], params[K] = 2.0, -4.0, 3.0, 5.0, 0.5
+    y = torch.empty(1, device="cuda")
+    binding.gemm_rowsum_bf16(1, K, A, K, params, 0.25, y)
+    torch.cuda.synchronize()
+    assert float(y) == 0.25 * (2.0 * 3.0 - 4.0 * 5.0) + 0.5
