@@ -205,7 +205,8 @@ size_t gemm_epilogue_static_scratch_bytes(void);
  *                     GE_A_GENERAL nothing; GE_A_LOWER: opA(A)[m,k] == 0 for k > m;
  *                     GE_A_UPPER: opA(A)[m,k] == 0 for k < m.  A promise about the VALUES, in
  *                     every batch: the operand is still a full M x K array holding those zeros,
- *                     the result is that of the general call bit for bit, and the library skips
+ *                     the result is that of the general call bit for bit (of one that adds K in one
+ *                     pass: GE_PLAN_DIRECT, and GE_PLAN_AUTO where it takes no K slices), and the library skips
  *                     the K ranges in which a whole tile row of A is zero (about half the
  *                     multiply-adds of a square product).  With a false promise the skipped
  *                     terms are missing from the result.  Not with GE_PLAN_SPLITK.

@@ -37,7 +37,8 @@ gemm_few_rows_kernel(const GemmParams p)
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rg = w & 1, kh = w >> 1;                   // block of 16 weight rows, half of the stage's k
     const int n0 = (int)blockIdx.x * BM, b = (int)blockIdx.y;
-    const int steps = (p.K + KS - 1) / KS;
+    // a lower triangular A is zero from column M on: the stages beyond add nothing
+    const int steps = ((p.triA == TRI_LOWER ? min(p.K, p.M) : p.K) + KS - 1) / KS;
 
     const long long offW = 2 * ((long long)b * p.strideB + (long long)n0 * p.ldb);
     const long long offS = 2 * ((long long)b * p.strideA);

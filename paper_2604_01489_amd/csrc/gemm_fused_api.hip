@@ -94,7 +94,8 @@ bool stage_k64(bool transA, bool transB)
 // draw: 16 x 2048 x 8192 18.1 us, on the tiles with K slices 13.5; 12 x 2808 x 2880 10.5 / 13.5.)
 bool few_rows_ok(const ge_fused_args_t &a)
 {
-    if (a.transA || !a.transB || a.M > 32 || a.a_structure != GE_A_GENERAL || a.plan != GE_PLAN_AUTO || opt_force_config() != FORCE_NONE) return false;
+    // (a triangular A adds in the same order as the same A without the promise, so it goes the same way)
+    if (a.transA || !a.transB || a.M > 32 || is_symmetric(a) || a.plan != GE_PLAN_AUTO || opt_force_config() != FORCE_NONE) return false;
     // 16-byte pieces along k; a panel of 32 rows, or the rows of A, within 31-bit byte offsets
     if ((((uintptr_t)a.A | (uintptr_t)a.B) & 15u) || ((a.lda | a.ldb | a.K) & 7) || a.batch > 65535) return false;
     if ((long long)a.lda * 64 + 1024 >= (1ll << 31) || (long long)a.ldb * 64 + 1024 >= (1ll << 31)) return false;

@@ -61,3 +61,14 @@ def test_few_rows_are_as_exact_as_k_slices(M, N, K, slices):
         assert ("few_rows" in binding.last_config()) == (plan == "auto"), binding.last_config()
         err[plan] = float((C.double() - ref).norm() / ref.norm())
     assert err["auto"] <= 1.01 * err["splitk"], err
+
+
+@pytest.mark.parametrize("structure", ["lower", "upper"])
+@pytest.mark.parametrize("M,N,K,out", [(16, 1024, 512, "f32"), (32, 8200, 1160, "f32"), (5, 520, 2056, "bf16"), (17, 6152, 200, "f32")])
+def test_few_rows_of_a_triangular_a(oracle, M, N, K, out, structure):
+    """With the promise, the bits of the same call without it: the same kernel, which leaves out stages of zeros."""
+    kw = dict(transB=True, alpha=0.5, act="relu", with_row_scale=True, out=out, seed=M + K, a_structure=structure)
+    got, _, _, cfg = run_fused_case(oracle, M, N, K, **kw)
+    plain, _, _, cfg2 = run_fused_case(oracle, M, N, K, hint=False, **kw)
+    assert cfg == cfg2 and "few_rows" in cfg
+    assert np.array_equal(got, plain)

@@ -74,8 +74,11 @@ def test_ragged_triangular(oracle, structure):
     """Blocks whose K range ends at, or starts inside, their own tile; some of them empty."""
     for M, N, K in [(331, 197, 331), (131, 401, 517), (517, 401, 131)]:
         for transA in (False, True):
-            _, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=True, alpha=0.5, act="relu", seed=M, a_structure=structure, plan="direct")
+            kw = dict(transA=transA, transB=True, alpha=0.5, act="relu", seed=M, a_structure=structure, plan="direct")
+            got, _, _, cfg = run_fused_case(oracle, M, N, K, **kw)
             assert "ragged" in cfg
+            plain, _, _, cfg = run_fused_case(oracle, M, N, K, hint=False, **kw)       # the bits of the call without the promise
+            assert "ragged" in cfg and (got == plain).all()
 
 
 @pytest.mark.gpu
@@ -109,3 +112,10 @@ def test_small_tiles_of_aligned_operands(oracle, M, N, K, out):
         outs.append(got)
         assert ("ragged_64x64x64" in cfg) == (option is None), cfg
     assert (outs[0] == outs[1]).all()
+    # a promised triangular A stays on the larger tiles, with the bits of the call without the promise on these
+    kw = dict(transB=True, with_row_scale=True, out=out, seed=N)
+    binding.set_option("force_config", None)
+    for structure in ("lower", "upper"):
+        got, _, _, cfg = run_fused_case(oracle, M, N, K, a_structure=structure, **kw)
+        plain, _, _, cfg2 = run_fused_case(oracle, M, N, K, a_structure=structure, hint=False, **kw)
+        assert "ragged" not in cfg and "ragged_64x64x64" in cfg2 and (got == plain).all(), (cfg, cfg2)
