@@ -417,7 +417,8 @@ ge_status_t ge_set_option(const char *name, const char *value);
 const char *ge_status_string(ge_status_t status);
 
 /* Name of the kernel configuration the last successful call on this thread
- * launched ("bf16_256x256x64_w4", "bf16_256x256x32_w8", "f32_128x128x16", ...); for reports. */
+ * launched ("bf16_256x256x64_w4", "bf16_256x256x32_w8", "f32_128x128x16_w4", "f32_ragged_64x64x32",
+ * ...); for reports.  The names may change from one build to the next. */
 const char *ge_last_config(void);
 
 #ifdef __cplusplus

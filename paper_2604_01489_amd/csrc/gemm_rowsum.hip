@@ -425,6 +425,7 @@ extern "C" ge_status_t gemm_rowsum_bf16(int M, int K, const uint16_t *A, int lda
     if (lda < K) return GE_ERR_LD;
     if ((((uintptr_t)A) & 1u) || (((uintptr_t)params) & 3u) || (((uintptr_t)y) & 3u)) return GE_ERR_ALIGN;
     launch_rows_dot(M, K, A, lda, params, alpha, params + K, y, (hipStream_t)stream);
-    g_last_config = rows_wide(K) && rows_aligned(K, A, lda) ? "rowsum_rows_wide" : vec_ok(A, lda) ? "rowsum_rows_vec8" : "rowsum_rows_generic";
+    g_last_config = rows_wide(K) ? (rows_aligned(K, A, lda) ? "rowsum_rows_wide" : "rowsum_rows_wide_any")
+                                 : vec_ok(A, lda) ? "rowsum_rows_vec8" : "rowsum_rows_generic";
     return ge_host::take_launch_error() == hipSuccess ? GE_OK : GE_ERR_LAUNCH;
 }

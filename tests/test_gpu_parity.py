@@ -86,12 +86,12 @@ def test_f32_fast_kernels(oracle):
     _, _, _, cfg = run_case(oracle, "f32", 72, 200, 20, batch=5, act="relu", seed=34)
     assert cfg == "f32_64x64x16_w4"
     _, _, _, cfg = run_case(oracle, "f32", 129, 130, 31, act="none", seed=35)
-    assert cfg == "f32_generic_128x128x16"
+    assert cfg == "f32_ragged_128x128x32"
 
 
 def test_f32_k_slices(oracle):
     """Few tiles and a long K: the fp32 kernels slice K (direct-to-LDS kernel on both tiles, full and ragged slices;
-    the guarded kernel), partial sums added in slice order by the second pass: matches the oracle, repeats bit for bit."""
+    the kernel for any alignment), partial sums added in slice order by the second pass: matches the oracle, repeats bit for bit."""
     _, _, _, cfg = run_case(oracle, "f32", 256, 256, 4096, alpha=0.5, act="gelu_tanh", seed=40)
     assert cfg == "f32_64x64x16_w4_splitk"
     _, _, _, cfg = run_case(oracle, "f32", 200, 136, 2076, alpha=0.25, act="relu", seed=41, lda=2080, ldb=140, ldc=137)
@@ -99,7 +99,7 @@ def test_f32_k_slices(oracle):
     _, _, _, cfg = run_case(oracle, "f32", 2048, 1024, 2048, act="none", with_bias=False, seed=42)
     assert cfg == "f32_128x128x16_w4_splitk"                    # 128 tiles of 128 x 128: two slices
     _, _, _, cfg = run_case(oracle, "f32", 130, 257, 2075, alpha=0.5, act="relu", seed=43)
-    assert cfg == "f32_generic_128x128x16_splitk"
+    assert cfg == "f32_ragged_128x128x32_splitk"
     _, _, _, cfg = run_case(oracle, "f32", 128, 64, 1536, batch=3, act="none", seed=44)
     assert cfg == "f32_64x64x16_w4_splitk"
     outs = [run_case(oracle, "f32", 256, 256, 4096, alpha=0.5, act="gelu_tanh", seed=40)[0].tobytes() for _ in range(2)]

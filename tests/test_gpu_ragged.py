@@ -83,16 +83,16 @@ def test_ragged_triangular(oracle, structure):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K,cfg", [
-    (257, 513, 33, "f32_generic_64x64x16"),            # one over the tiles and a 32-k step
-    (323, 517, 31, "f32_generic_64x64x16"),            # one step, not full
-    (321, 518, 95, "f32_generic_64x64x16"),            # three steps
-    (1000, 130, 5, "f32_generic_64x64x16"),            # barely more than a chunk of k
-    (2047, 1922, 33, "f32_generic_128x128x16"),
-    (1921, 2046, 66, "f32_generic_128x128x16"),
-    (300, 3, 50, "f32_generic_64x64x16"),              # rows of B shorter than a chunk
-    (130, 515, 3, "f32_generic_64x64x16"),             # rows of A shorter than a chunk
-    (70, 3, 1100, "f32_generic_64x64x16_splitk"),
-    (257, 515, 1061, "f32_generic_64x64x16_splitk"),   # slices that end inside a step
+    (257, 513, 33, "f32_ragged_64x64x32"),            # one over the tiles and a 32-k step
+    (323, 517, 31, "f32_ragged_64x64x32"),            # one step, not full
+    (321, 518, 95, "f32_ragged_64x64x32"),            # three steps
+    (1000, 130, 5, "f32_ragged_64x64x32"),            # barely more than a chunk of k
+    (2047, 1922, 33, "f32_ragged_128x128x32"),
+    (1921, 2046, 66, "f32_ragged_128x128x32"),
+    (300, 3, 50, "f32_elements_64x64x32"),              # rows of B shorter than a chunk
+    (130, 515, 3, "f32_elements_64x64x32"),             # rows of A shorter than a chunk
+    (70, 3, 1100, "f32_elements_64x64x32_splitk"),
+    (257, 515, 1061, "f32_ragged_64x64x32_splitk"),   # slices that end inside a step
 ])
 def test_f32_any_alignment(oracle, M, N, K, cfg):
     """fp32 operands of any alignment (csrc/gemm_f32_ragged.h): odd sizes, odd leading dimensions, pointers off by 4 bytes."""

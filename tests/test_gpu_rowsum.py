@@ -128,7 +128,8 @@ def test_rowsum_any_alignment(oracle, transB):
     64, 32 and 16 rows with ragged last chunks and columns that are no multiple of 8 or 4."""
     for M, N, K, pad, mis in [(130, 385, 511, (0, 0), 0), (77, 1000, 1031, (3, 5), 0), (41, 390, 2050, (0, 0), 1), (9, 65, 8193, (1, 0), 3),
                               (64, 4100, 391, (0, 0), 0), (5, 17, 9, (0, 0), 1), (1024, 2049, 1024, (0, 0), 0)]:
-        run_rowsum_case(oracle, M, N, K, transB=transB, alpha=0.5, pad=pad, misalign=mis, seed=M + K)
+        _, _, cfg_y = run_rowsum_case(oracle, M, N, K, transB=transB, alpha=0.5, pad=pad, misalign=mis, seed=M + K)
+        assert cfg_y == ("rowsum_rows_generic" if K < 384 else "rowsum_rows_wide" if K == 1024 else "rowsum_rows_wide_any")
 
 
 def test_rowsum_small_workspace(oracle):

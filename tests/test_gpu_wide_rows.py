@@ -65,7 +65,7 @@ def test_f32_kernels_at_any_distance(M, N, K):
         torch.cuda.synchronize()
         _check(C, M, ldc, N, ref, 2e-6)
         del C
-    assert len(set(names)) == 1 and "generic" not in names[0], names
+    assert len(set(names)) == 1 and names[0] in ("f32_64x64x16_w4", "f32_small_32x32_k4"), names
 
 
 # tiles on the edge, fp32: the offsets at their largest, and the guarded kernels from there on
@@ -84,7 +84,9 @@ def test_edge_tiles_near_the_limit(M, N, K, dtype, aligned, ldc, past):
     name = binding.last_config()
     torch.cuda.synchronize()
     _check(C, M, ldc, N, ref, 2e-6)
-    if aligned:
-        assert (("generic" in name) if dtype == "bf16" else ("w4" not in name)) == past, name
+    if dtype == "bf16":
+        assert name == ("bf16_generic_64x64x32" if past else "bf16_128x128x32_w4" if aligned else "bf16_ragged_64x64x64"), name
+    else:
+        assert name == ("f32_elements_64x64x32" if past else "f32_64x64x16_w4" if aligned else "f32_ragged_128x128x32"), name
 
 
