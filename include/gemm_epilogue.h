@@ -227,8 +227,8 @@ size_t gemm_epilogue_static_scratch_bytes(void);
  *
  * `args` is a HOST pointer, read before the call returns.  The direct-to-LDS
  * kernels need A and B 16-byte aligned, lda and ldb multiples of 8 and the row
- * payloads (K or M for A, N or K for B) multiples of 8, plus for bf16 output an
- * even N and ldc and a 4-byte aligned C; any other legal argument list takes the
+ * payloads (K or M for A, N or K for B) and N multiples of 8, plus for bf16 output ldc
+ * a multiple of 8 and a 16-byte aligned C; any other legal argument list takes the
  * kernels for any alignment or the guarded one (as above) with the same result contract.
  * Errors: as gemm_epilogue_bf16, plus GE_ERR_EPILOGUE.
  */
@@ -361,8 +361,8 @@ ge_status_t gemm_epilogue_diag_bf16(int M, int N, const float *d,
  *   A, lda            device, bf16 bits, A[m,k] = A[m*lda + k], lda >= K
  *   params            device, fp32[K + 1] as written by gemm_rowsum_params_bf16
  *   y                 device, fp32[M], written
- * 16-byte row pieces are used when the pointer and leading dimension allow it, single elements
- * otherwise.  gemm_rowsum_params_bf16 with transB != 0 parks partial column sums in the library's
+ * Rows are read in 16-byte pieces: at any alignment by the column sums (K >= 8) and for rows of 384 columns and
+ * more, in shorter rows where the pointer and the leading dimension allow it; else by single elements.  gemm_rowsum_params_bf16 with transB != 0 parks partial column sums in the library's
  * workspace of the stream (see "Partial results" at the top).
  * Errors: GE_ERR_NULL, GE_ERR_SHAPE, GE_ERR_LD, GE_ERR_ALIGN (a pointer not aligned to its
  * element), GE_ERR_WORKSPACE, GE_ERR_LAUNCH.
@@ -399,7 +399,7 @@ ge_status_t ge_release_workspace(void);
 /*
  * Switches for timing runs and tests; none changes a result contract.
  *   "force_config"  "256x256" | "128x128" | "generic": block tile of the bf16 kernels
- *                   ("generic" also for fp32), whatever the planner would pick
+ *                   ("generic" also for fp32: its kernels for any alignment), whatever the planner would pick
  *   "waves"         "8": full 256 x 256 tiles stay on the eight-wave kernel ("4": default)
  *   "stage_k"       "32": no 64-k load phases in the eight-wave kernel ("64": default)
  *   "conv_halo"     "off": 3 x 3 convolutions stay on the gathering kernel; "on": the

@@ -172,8 +172,9 @@ ge_status_t plan_conv(const ge_conv_args_t &a, ConvPlan *out)
     const bool f32Out = a.y_type == GE_DTYPE_F32;
     ge_status_t st = make_plan_bf16_for((int)M, a.Cout, (int)K, 1, fast, GE_PLAN_AUTO, 0, a.Cout, f32Out, &out->pl);
     // Channels a multiple of 8 only: the gathering kernel from a million multiply-adds on (one image of 7 x 7 x 80 -> 32,
-    // 3 x 3, is at that size: 39.1 -> 14.2 us; below, the guarded kernel is the shorter launch), with as many K slices as the
-    // guarded kernel takes: no call needs a workspace, or a larger one, that did not, and the sums are as exact (9 x 9 x 200 ->
+    // 3 x 3, is at that size: 39.1 -> 14.1 us).  The guarded kernel keeps the smaller calls, which have been tested on it, though it is the
+    // slower one there too (7 x 7 x 40 -> 32, 3 x 3, 0.56 M: 23.0 / 9.3; 14 x 14 x 8 -> 16, 0.23 M: 10.4 / 5.7; 4 x 4 x 72 -> 32, 1 x 1,
+    // 0.04 M: 7.4 / 5.5).  As many K slices as the guarded kernel takes: no call needs a workspace, or a larger one, that did not, and the sums are as exact (9 x 9 x 200 ->
     // 104, 3 x 3, error against 64 bits: three slices 1.39e-7, one chain over K 2.39e-7; 14.9 against 28.6 us)
     out->c8 = gather && !fast && !out->rows && opt_force_config() != FORCE_GENERIC && (double)M * a.Cout * K >= 1024.0 * 1024;
     if (st == GE_OK && out->c8) {

@@ -3,16 +3,18 @@
 // its tall operand and the rows of A, which run along k like theirs, as its skinny one.
 //
 // A workgroup owns 32 rows of the weights (32 columns of C) and every row of A, and walks K in stages of 128 through a ring
-// of eight (seven on their way; four where the workgroups are more than the CUs, so that two or three share one), both operands by direct-to-LDS loads in 256-byte row pieces, the weights with the
-// non-temporal hint; each workgroup starts its walk at another stage.  Four waves: two blocks of 16 weight rows x two halves
+// of eight (seven on their way; four where the workgroups are more than the CUs, so that two or three share one), both
+// operands by direct-to-LDS loads in 256-byte row pieces, the weights with the non-temporal hint; each workgroup starts its walk at another stage.  Four waves: two blocks of 16 weight rows x two halves
 // of a stage's k; the halves are added through LDS in a fixed order, then the chain, 32 consecutive columns of a row of C
 // at a time.  A wave adds in runs of four stages (256 of its k, eight matrix instructions) and the runs' sums in turn: one
 // chain over all of its k was less exact than the tiles' K slices, which are chains of 512 k or more (error
 // against 64 bits, slices / one chain / runs: 1.30e-7 / 1.86e-7 / 9.8e-8 at 16 x 8192 x 2048, 2.73e-7 / 3.97e-7 / 1.18e-7 at
-// 16 x 8192 x 8192, 3.52e-7 / 5.73e-7 / 1.40e-7 at 5 x 6144 x 16384), and costs nothing
-// at 16 x 8192 x 8192; 12 x 2808 x 2880, 88 workgroups, 8.7 -> 9.2 us).  (Weights straight from memory into the fragments' registers, 16 rows of 64 bytes per load instruction and
-// no LDS, were slower: 35.9 us at 16 x 8192 x 8192, the 128 x 128 tile with K slices 38.4, this
-// 23.0: 5.9 TB/s, launch included.  32 rows 38.4 -> 25.2.  An image of 64 rows, six stages deep, was built and taken out:
+// 16 x 8192 x 8192, 3.52e-7 / 5.73e-7 / 1.40e-7 at 5 x 6144 x 16384).  The runs take no time at 16 x 8192 x 8192 (22.7 -> 22.5
+// us) and 8.7 -> 9.2 us at 12 x 2808 x 2880, 88 workgroups; their end must not be a branch inside the loop over the stages, which
+// copies the accumulators in every stage (23.5 and 10.1 us).
+// (Weights straight from memory into the fragments' registers, 16 rows of 64 bytes per load instruction and no LDS, were slower:
+// 35.9 us at 16 x 8192 x 8192, the 128 x 128 tile with K slices 38.4, this 22.5: 6.0 TB/s, launch included.  32 rows 38.4 -> 25.2.
+// An image of 64 rows, six stages deep, was built and taken out:
 // 64 x 8192 x 8192 39.8 -> 33.3 us, but 63 x 10432 x 6024, 326 workgroups, 47.2 -> 58.4.)
 #pragma once
 #include "gemm_fused.h"

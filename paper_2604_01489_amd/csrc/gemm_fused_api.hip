@@ -91,7 +91,7 @@ bool stage_k64(bool transA, bool transB)
 
 // A few rows through weights stored N x K: the kernel that streams the weights (gemm_few_rows.h), where their 32-row pieces
 // cover three of four CUs, or the walk over K is short.  (Fewer pieces and a long K are a stream that few CUs cannot
-// draw: 16 x 2048 x 8192 18.1 us, on the tiles with K slices 13.5; 12 x 2808 x 2880 10.5 / 13.5.)
+// draw: 16 x 2048 x 8192 18.1 us, on the tiles with K slices 13.5; 12 x 2808 x 2880 10.5 / 13.5, a caller's clock.)
 bool few_rows_ok(const ge_fused_args_t &a)
 {
     // (a triangular A adds in the same order as the same A without the promise, so it goes the same way)

@@ -1,5 +1,6 @@
 // Guarded GEMM kernels for argument lists the fast kernels do not take (odd
-// sizes, unaligned pointers, odd leading dimensions) and that are small.
+// sizes, unaligned pointers, odd leading dimensions) and that are small, or
+// whose fp32 rows of C are 2^24 elements and more apart under ragged tiles.
 // Every global access is predicated on the M/N/K remainders and stores are
 // masked (Debugging guide, checklist "Edges").  Same matrix instructions and
 // the same in-register epilogue as the fast path.

@@ -56,20 +56,20 @@ __device__ inline float pair_sum(const float *t)
 
 // out[r] = scale * sum_c X[r,c] * v[c] + add[0]   (v == nullptr: ones; add == nullptr: 0)
 // One wave per row at a time, a lane takes 8 consecutive columns per step (16 bytes of X) when
-// VEC, single columns otherwise; v is staged in LDS once per block when it fits (`stage`), and a
+// VEC, single columns otherwise; v, shorter than the wide kernel's 384 columns, is staged in LDS once per block, and a
 // block of 16 waves walks rows with the stride of the grid so that the staging is paid once per many rows.
 template <bool VEC>
 __global__ void __launch_bounds__(kRowWaves * 64)
 rows_dot_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, const float *__restrict__ v,
-                float scale, const float *__restrict__ add, float *__restrict__ out, int stage)
+                float scale, const float *__restrict__ add, float *__restrict__ out)
 {
     extern __shared__ float vs[];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (stage) {
+    if (v != nullptr) {
         for (int c = threadIdx.x; c < C; c += kRowWaves * 64) vs[c] = v[c];
         __syncthreads();
     }
-    const float *vv = stage ? vs : v;
+    const float *vv = v != nullptr ? vs : nullptr;
     const float addv = add != nullptr ? add[0] : 0.0f;
     for (long long r = (long long)blockIdx.x * kRowWaves + w; r < R; r += (long long)gridDim.x * kRowWaves) {
         const uint16_t *row = X + r * ldx;
@@ -183,12 +183,13 @@ rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx
     }
 }
 
-// partial[chunk][c] = sum over the rows of chunk `chunk` (chunkRows rows) of X[r,c]: SUBS runs of chunkRows / SUBS rows, each added in row
-// order, then in pairs.  The runs are what the sizes ask for (col_chunk_rows) and SUBS is 1, unless the workspace holds only longer chunks: then a block
-// adds up here, in the same pairs, the runs that cols_finish_kernel adds up otherwise, and the sums are the same bit for bit.
-// A thread owns 8 consecutive columns (16 bytes per row; ALIGNED: rows of whole aligned pieces, by non-temporal loads; else at any address, the columns
-// at the end of a row are read with those before them and shifted into place), or one column where rows are shorter
-// (WIDE false).  The loads of 8 rows are issued together, ahead of their additions (left to the compiler's unrolling they
+// partial[chunk][c] = sum over the rows of chunk `chunk` (chunkRows rows) of X[r,c]: SUBS runs of chunkRows / SUBS rows, each
+// added in row order, then in pairs.  The runs are what the sizes ask for (col_chunk_rows) and SUBS is 1, unless the workspace
+// holds only longer chunks: then a block adds up here, in the same pairs, the runs that cols_finish_kernel adds up
+// otherwise, and the sums are the same bit for bit.
+// A thread owns 8 consecutive columns (16 bytes per row; ALIGNED: rows of whole aligned pieces, by non-temporal loads; else at
+// any address, the columns at the end of a row are read with those before them and shifted into place), or one column
+// where rows are shorter (WIDE false).  The loads of 8 rows are issued together, ahead of their additions (left to the compiler's unrolling they
 // went out one by one behind a bounds test: 50 us for 8192 x 8192 against 23 us).
 template <bool WIDE, bool ALIGNED, int SUBS>
 __global__ void __launch_bounds__(256)
@@ -342,14 +343,13 @@ void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float
         else                          launch(std::integral_constant<int, 1>{});
         return;
     }
-    const int stage = (v != nullptr && (size_t)C * sizeof(float) <= 48 * 1024) ? 1 : 0;
-    const size_t lds = stage ? (size_t)C * sizeof(float) : 0;
+    const size_t lds = v != nullptr ? (size_t)C * sizeof(float) : 0;
     long long blocks = ((long long)R + kRowWaves - 1) / kRowWaves;
     const long long cap = 2ll * kNumCU;             // two blocks of 16 waves per CU; many rows per staging of v
     if (blocks > cap) blocks = cap;
     const dim3 threads(kRowWaves * 64);
-    if (vec_ok(X, ldx)) GE_LAUNCH(rows_dot_kernel<true>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out, stage);
-    else                GE_LAUNCH(rows_dot_kernel<false>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out, stage);
+    if (vec_ok(X, ldx)) GE_LAUNCH(rows_dot_kernel<true>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out);
+    else                GE_LAUNCH(rows_dot_kernel<false>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out);
 }
 
 }  // namespace
