@@ -276,23 +276,33 @@ cols_finish_kernel(int C, int partials, const float *__restrict__ partial, float
     for (int q0 = g; q0 * SUBS < partials; q0 += U * kFinishWays) {
         float v[U][4][SUBS];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+            const int first = (q0 + u * kFinishWays) * SUBS;
+            ge::i32x4_t t[SUBS];
 #pragma unroll
-            for (int i = 0; i < SUBS; ++i) {
-                const int q = (q0 + u * kFinishWays) * SUBS + i;
-                ge::i32x4_t t = {0, 0, 0, 0};
-                if (q < partials && c < C) {
-                    const float *src = partial + (long long)q * C;
-                    if (wide) {
-                        t = load_any16(src + at);
-                    } else {
-                        for (int e = 0; e < C; ++e) t[e] = (int)__float_as_uint(src[e]);
+            for (int i = 0; i < SUBS; ++i) t[i] = ge::i32x4_t{0, 0, 0, 0};
+            const float *src = partial + (long long)first * C + (wide ? at : 0);
+            if (wide && first + SUBS <= partials && c < C) {
+#pragma unroll
+                for (int i = 0; i < SUBS; ++i) t[i] = load_any16(src + (long long)i * C);
+            } else if (c < C) {                           // the last chunk, of fewer runs
+#pragma unroll
+                for (int i = 0; i < SUBS; ++i)
+                    if (first + i < partials) {
+                        if (wide) t[i] = load_any16(src + (long long)i * C);
+                        else
+                            for (int e = 0; e < C; ++e) t[i][e] = (int)__float_as_uint(src[(long long)i * C + e]);
                     }
-                }
-                if (sh > 0) t = ge::shift_down_elements(t, 2 * sh);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[u][e][i] = __uint_as_float((unsigned)t[e]);
             }
+            if (sh > 0) {
+#pragma unroll
+                for (int i = 0; i < SUBS; ++i) t[i] = ge::shift_down_elements(t[i], 2 * sh);
+            }
+#pragma unroll
+            for (int i = 0; i < SUBS; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[u][e][i] = __uint_as_float((unsigned)t[i][e]);
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
