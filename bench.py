@@ -69,21 +69,21 @@ _F32 = ("bf16_layout.h", "ge_device.h", "gemm_f32_fast.h")
 # workload -> (kernel configuration, FETCH_SIZE KiB, WRITE_SIZE KiB, source files, their hash)
 # TRAFFIC-BEGIN (rows written from the counter runs; see profiles/)
 TRAFFIC = {
-    "c1_f32_256": ("f32_small_32x32_k4", 1243, 256, ('ge_device.h', 'gemm_f32_small.h'), "3280712d45bb1cbd"),
-    "c2_bf16_4096": ("bf16_256x256x64_w4", 98445, 65536, _MAIN_W4, "1b4721d4e11ba1a4"),
-    "c3_bf16_8192_bias_gelu": ("bf16_256x256x64_w4", 799255, 262146, _MAIN_W4, "1b4721d4e11ba1a4"),
-    "c4_bf16_batched_512x512x64": ("bf16_256x256x32_w8", 16477, 262146, _MAIN_W8, "23ee57442d63625a"),
-    "c5_bf16_splitk_1024x1024x65536": ("bf16_256x256x64_w4_splitk", 131261, 65536, _MAIN_W4, "1b4721d4e11ba1a4"),
-    "c6_fused_nt_8192_bias_gelu_bf16out": ("bf16_fused_256x256x64_w4_nt", 795344, 131146, _MAIN_W4, "1b4721d4e11ba1a4"),
-    "c7_fused_tn_8192_chain": ("bf16_fused_256x256x32_w8_tn", 854946, 131072, _MAIN_W8, "23ee57442d63625a"),
-    "c8_fused_batched_512x512x64_bf16out": ("bf16_fused_256x256x32_w8_nn", 16542, 131072, _MAIN_W8, "23ee57442d63625a"),
-    "c9_diag_bf16_8192": ("diag_rows_vec4", 65970, 262692, ('gemm_diag.hip',), "95489dc912964713"),
-    "c10_conv3x3_256_bf16out": ("conv_bf16_halo_3x3_w4_14_11", 60943, 50176, ('bf16_layout.h', 'conv_halo.h', 'conv_halo_launch.h', 'conv_halo_layout.h', 'ge_device.h', 'gemm_bf16_fast.h'), "c7e5dc1182c45be1"),
-    "c11_fused_lower_8192_bias_relu": ("bf16_fused_256x256x64_w4_nn", 654403, 262144, _MAIN_W4, "1b4721d4e11ba1a4"),
-    "c12_rowsum_linear_8192": ("rowsum_rows_wide", 133356, 4337, ('ge_device.h', 'gemm_rowsum.hip'), "87383341e318c3ab"),
-    "c13_f32_8192x8192x2048": ("f32_128x128x16_w4", 783926, 262144, _F32, "0cd6a6f94fc96f4f"),
-    "c15_conv7x7_first_layer_bf16out": ("conv_bf16_rows_k32", 16594, 50176, ('conv_rows.h', 'conv_rows_layout.h', 'ge_device.h'), "70cd2b61e0685e94"),
-    "c14_symm_lower_16384_n16": ("bf16_symm_lower_768x768_n16", 146144, 23552, ('ge_device.h', 'gemm_symm.h', 'splitk_reduce.h', 'symm_layout.h'), "5041ec6927ebc1c8"),
+    "c1_f32_256": ("f32_small_32x32_k4", 1243, 256, ('bf16_layout.h', 'ge_device.h', 'gemm_f32_small.h'), "498771dccb580fbe"),
+    "c2_bf16_4096": ("bf16_256x256x64_w4", 98447, 65536, _MAIN_W4, "22b85d300136d772"),
+    "c3_bf16_8192_bias_gelu": ("bf16_256x256x64_w4", 792297, 262146, _MAIN_W4, "22b85d300136d772"),
+    "c4_bf16_batched_512x512x64": ("bf16_256x256x32_w8", 16469, 262147, _MAIN_W8, "106d9e23471a6331"),
+    "c5_bf16_splitk_1024x1024x65536": ("bf16_256x256x64_w4_splitk", 131219, 65536, _MAIN_W4, "22b85d300136d772"),
+    "c6_fused_nt_8192_bias_gelu_bf16out": ("bf16_fused_256x256x64_w4_nt", 790443, 131174, _MAIN_W4, "22b85d300136d772"),
+    "c7_fused_tn_8192_chain": ("bf16_fused_256x256x32_w8_tn", 852364, 131072, _MAIN_W8, "106d9e23471a6331"),
+    "c8_fused_batched_512x512x64_bf16out": ("bf16_fused_256x256x32_w8_nn", 16536, 131072, _MAIN_W8, "106d9e23471a6331"),
+    "c9_diag_bf16_8192": ("diag_rows_vec4", 65964, 262666, ('gemm_diag.hip',), "95489dc912964713"),
+    "c10_conv3x3_256_bf16out": ("conv_bf16_halo_3x3_w4_14_11", 60945, 50176, ('bf16_layout.h', 'conv_halo.h', 'conv_halo_launch.h', 'conv_halo_layout.h', 'ge_device.h', 'gemm_bf16_fast.h'), "307f1241d7ffba76"),
+    "c11_fused_lower_8192_bias_relu": ("bf16_fused_256x256x64_w4_nn", 654644, 262144, _MAIN_W4, "22b85d300136d772"),
+    "c12_rowsum_linear_8192": ("rowsum_rows_wide", 133360, 4390, ('bf16_layout.h', 'ge_device.h', 'gemm_rowsum.hip'), "2877d351e8d78ea1"),
+    "c13_f32_8192x8192x2048": ("f32_128x128x16_w4", 783944, 262144, _F32, "2b99fdce10bb8826"),
+    "c15_conv7x7_first_layer_bf16out": ("conv_bf16_rows_k32", 16594, 50176, ('bf16_layout.h', 'conv_rows.h', 'conv_rows_layout.h', 'ge_device.h'), "6c4db93c683436ae"),
+    "c14_symm_lower_16384_n16": ("bf16_symm_lower_768x768_n16", 146154, 23552, ('bf16_layout.h', 'ge_device.h', 'gemm_symm.h', 'splitk_reduce.h', 'symm_layout.h'), "febcd6d6e73df301"),
 }
 # TRAFFIC-END
 
