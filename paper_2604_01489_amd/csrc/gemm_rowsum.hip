@@ -188,8 +188,7 @@ rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx
 // holds only longer chunks: then a block adds up here, in the same pairs, the runs that cols_finish_kernel adds up
 // otherwise, and the sums are the same bit for bit.
 // A thread owns 8 consecutive columns (16 bytes per row; ALIGNED: rows of whole aligned pieces, by non-temporal loads; else at
-// any address, the columns at the end of a row are read with those before them and shifted into place), or one column
-// where rows are shorter (WIDE false).  The loads of 8 rows are issued together, ahead of their additions (left to the compiler's unrolling they
+// any address), or one column where rows are shorter (WIDE false).  The loads of 8 rows are issued together, ahead of their additions (left to the compiler's unrolling they
 // went out one by one behind a bounds test: 50 us for 8192 x 8192 against 23 us).
 template <bool WIDE, bool ALIGNED, int SUBS>
 __global__ void __launch_bounds__(256)
@@ -198,6 +197,8 @@ cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx,
     constexpr int W = WIDE ? 8 : 1, U = 8;
     const int c0 = (blockIdx.x * 256 + threadIdx.x) * W;
     if (c0 >= C) return;
+    // the columns at the end of a row are read with those before them; only they are stored
+    const int at = WIDE && !ALIGNED && c0 > C - 8 ? C - 8 : c0;
     const int runRows = chunkRows / SUBS, chunkEnd = min(R, (int)(blockIdx.y + 1) * chunkRows);
     float acc[SUBS][W];
 #pragma unroll
@@ -206,24 +207,27 @@ cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx,
         for (int e = 0; e < W; ++e) acc[q][e] = 0.0f;
         const int r0 = blockIdx.y * chunkRows + q * runRows, r1 = min(chunkEnd, r0 + runRows);
         if constexpr (WIDE) {
-            const int at = ALIGNED || c0 < C - 8 ? c0 : C - 8;
-            for (int r = r0; r < r1; r += U) {
+            auto trip = [&](int r, auto whole) {          // U rows; not whole: those beyond r1 are the last one again, and not added
+                constexpr bool WHOLE = decltype(whole)::value;
                 ge::i32x4_t x[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    x[u] = ge::i32x4_t{0, 0, 0, 0};
-                    if (r + u < r1) x[u] = ALIGNED ? load_stream16(X + (long long)(r + u) * ldx + at) : load_any16(X + (long long)(r + u) * ldx + at);
+                    const uint16_t *src = X + (long long)(WHOLE || r + u < r1 ? r + u : r1 - 1) * ldx + at;
+                    x[u] = ALIGNED ? load_stream16(src) : load_any16(src);
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (!ALIGNED && at != c0) x[u] = ge::shift_down_elements(x[u], c0 - at);
+                    const bool inside = WHOLE || r + u < r1;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        acc[q][2 * e] += bf16_lo((unsigned)x[u][e]);
-                        acc[q][2 * e + 1] += bf16_hi((unsigned)x[u][e]);
+                        acc[q][2 * e] += inside ? bf16_lo((unsigned)x[u][e]) : 0.0f;
+                        acc[q][2 * e + 1] += inside ? bf16_hi((unsigned)x[u][e]) : 0.0f;
                     }
                 }
-            }
+            };
+            int r = r0;
+            for (; r + U <= r1; r += U) trip(r, std::true_type{});
+            if (r < r1) trip(r, std::false_type{});
         } else {
             for (int r = r0; r < r1; ++r) acc[q][0] += bf16_lo((unsigned)X[(long long)r * ldx + c0]);
         }
@@ -233,7 +237,8 @@ cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx,
         float t[SUBS];
 #pragma unroll
         for (int q = 0; q < SUBS; ++q) t[q] = acc[q][e];
-        if (c0 + e < C) partial[(long long)blockIdx.y * C + c0 + e] = pair_sum<SUBS>(t);
+        const int c = at + e;
+        if (c >= c0 && c < C) partial[(long long)blockIdx.y * C + c] = pair_sum<SUBS>(t);
     }
 }
 
@@ -269,47 +274,45 @@ cols_finish_kernel(int C, int partials, const float *__restrict__ partial, float
     const int g = threadIdx.x / (kFinishCols / 4), cl = (threadIdx.x % (kFinishCols / 4)) * 4;
     const int c = blockIdx.x * kFinishCols + cl;
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    // four columns by one 16-byte load at any address; those at the end of a row are pulled back and shifted into place
+    // four columns by one 16-byte load at any address; those at the end of a row are read with the ones before them, and only
+    // they are kept
     const bool wide = C >= 4;
-    const int at = wide && c > C - 4 ? C - 4 : c, sh = c - at;
+    const int at = wide && c > C - 4 ? C - 4 : c;
     constexpr int U = 8 / SUBS;                           // chunks whose loads are on their way together
     for (int q0 = g; q0 * SUBS < partials; q0 += U * kFinishWays) {
-        float v[U][4][SUBS];
+        ge::i32x4_t t[U][SUBS];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int first = (q0 + u * kFinishWays) * SUBS;
-            ge::i32x4_t t[SUBS];
 #pragma unroll
-            for (int i = 0; i < SUBS; ++i) t[i] = ge::i32x4_t{0, 0, 0, 0};
+            for (int i = 0; i < SUBS; ++i) t[u][i] = ge::i32x4_t{0, 0, 0, 0};
             const float *src = partial + (long long)first * C + (wide ? at : 0);
             if (wide && first + SUBS <= partials && c < C) {
 #pragma unroll
-                for (int i = 0; i < SUBS; ++i) t[i] = load_any16(src + (long long)i * C);
+                for (int i = 0; i < SUBS; ++i) t[u][i] = load_any16(src + (long long)i * C);
             } else if (c < C) {                           // the last chunk, of fewer runs
 #pragma unroll
                 for (int i = 0; i < SUBS; ++i)
                     if (first + i < partials) {
-                        if (wide) t[i] = load_any16(src + (long long)i * C);
+                        if (wide) t[u][i] = load_any16(src + (long long)i * C);
                         else
-                            for (int e = 0; e < C; ++e) t[i][e] = (int)__float_as_uint(src[(long long)i * C + e]);
+                            for (int e = 0; e < C; ++e) t[u][i][e] = (int)__float_as_uint(src[(long long)i * C + e]);
                     }
             }
-            if (sh > 0) {
-#pragma unroll
-                for (int i = 0; i < SUBS; ++i) t[i] = ge::shift_down_elements(t[i], 2 * sh);
-            }
-#pragma unroll
-            for (int i = 0; i < SUBS; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[u][e][i] = __uint_as_float((unsigned)t[i][e]);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += pair_sum<SUBS>(v[u][e]);
+            for (int e = 0; e < 4; ++e) {
+                float v[SUBS];
+#pragma unroll
+                for (int i = 0; i < SUBS; ++i) v[i] = __uint_as_float((unsigned)t[u][i][e]);
+                acc[e] += pair_sum<SUBS>(v);
+            }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) part[g][cl + e] = acc[e];
+    for (int e = 0; e < 4; ++e)
+        if (at + e >= c) part[g][cl + (at - c) + e] = acc[e];
     __syncthreads();
     if (threadIdx.x < kFinishCols) {
         const int cc = blockIdx.x * kFinishCols + threadIdx.x;
