@@ -56,20 +56,20 @@ __device__ inline float pair_sum(const float *t)
 
 // out[r] = scale * sum_c X[r,c] * v[c] + add[0]   (v == nullptr: ones; add == nullptr: 0)
 // One wave per row at a time, a lane takes 8 consecutive columns per step (16 bytes of X) when
-// VEC, single columns otherwise; v, shorter than the wide kernel's 384 columns, is staged in LDS once per block, and a
+// VEC, single columns otherwise; v is staged in LDS once per block when it fits (`stage`), and a
 // block of 16 waves walks rows with the stride of the grid so that the staging is paid once per many rows.
 template <bool VEC>
 __global__ void __launch_bounds__(kRowWaves * 64)
 rows_dot_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, const float *__restrict__ v,
-                float scale, const float *__restrict__ add, float *__restrict__ out)
+                float scale, const float *__restrict__ add, float *__restrict__ out, int stage)
 {
     extern __shared__ float vs[];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (v != nullptr) {
+    if (stage) {
         for (int c = threadIdx.x; c < C; c += kRowWaves * 64) vs[c] = v[c];
         __syncthreads();
     }
-    const float *vv = v != nullptr ? vs : nullptr;
+    const float *vv = stage ? vs : v;
     const float addv = add != nullptr ? add[0] : 0.0f;
     for (long long r = (long long)blockIdx.x * kRowWaves + w; r < R; r += (long long)gridDim.x * kRowWaves) {
         const uint16_t *row = X + r * ldx;
@@ -333,15 +333,28 @@ vector_sum_kernel(int n, const float *__restrict__ x, float *__restrict__ out)
 
 bool vec_ok(const void *base, long long ld) { return (((uintptr_t)base) & 15u) == 0 && ld % 8 == 0; }
 
-// The wide kernel needs enough columns to give most lanes of a wave a 16-byte piece (its narrowest sweep is 512 columns).
-bool rows_wide(int C) { return C >= 384; }
 bool rows_aligned(int C, const void *X, long long ldx) { return vec_ok(X, ldx) && C % 8 == 0; }
+
+// The wide kernel needs enough columns to give most lanes of a wave a 16-byte piece (its narrowest sweep is 512 columns).
+// Rows that are no whole aligned pieces take it only where it is the shorter call (us, one wave a row / wide):
+// - at any address, from 2048 columns on (2049 x 4096 rows 14.4 / 7.0, 8191 x 8192 rows 51.9 / 36.9) or 2^23 elements (911 columns:
+//   8192 rows 5.4 / 9.1, 12288 10.5 / 9.2; 505: 16384 5.8 / 9.7, 24576 11.6 / 9.8; 1351: 4096 6.2 / 7.7, 8192 10.6 / 7.9);
+// - at 16-byte addresses and of a length that is no multiple of 8, which the other kernel reads in aligned pieces but for the last
+//   columns, for few long rows (5685 x 1160 8.5 / 7.1, x 4096 11.8 / 15.3; 16385 x 1160 20.3 / 13.2; 4097 x 512 5.9 / 6.0; 2049 x
+//   16384 13.1 / 24.5).
+bool rows_wide(int R, int C, const void *X, long long ldx)
+{
+    if (C < 384) return false;
+    if (rows_aligned(C, X, ldx)) return true;
+    if (vec_ok(X, ldx)) return C > 4608 && R >= 32 && R <= 2048;
+    return C >= 2048 || (double)R * C >= 8.0 * 1024 * 1024;
+}
 
 // rows of X times v (or ones), on `st`
 void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float *v, float scale, const float *add,
                      float *out, hipStream_t st)
 {
-    if (rows_wide(C)) {
+    if (rows_wide(R, C, X, ldx)) {
         // the narrowest sweep that covers a row, or the whole block per row
         auto launch = [&](auto groups) {
             constexpr int G = decltype(groups)::value;
@@ -356,13 +369,14 @@ void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float
         else                          launch(std::integral_constant<int, 1>{});
         return;
     }
-    const size_t lds = v != nullptr ? (size_t)C * sizeof(float) : 0;
+    const int stage = (v != nullptr && (size_t)C * sizeof(float) <= 48 * 1024) ? 1 : 0;
+    const size_t lds = stage ? (size_t)C * sizeof(float) : 0;
     long long blocks = ((long long)R + kRowWaves - 1) / kRowWaves;
     const long long cap = 2ll * kNumCU;             // two blocks of 16 waves per CU; many rows per staging of v
     if (blocks > cap) blocks = cap;
     const dim3 threads(kRowWaves * 64);
-    if (vec_ok(X, ldx)) GE_LAUNCH(rows_dot_kernel<true>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out);
-    else                GE_LAUNCH(rows_dot_kernel<false>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out);
+    if (vec_ok(X, ldx)) GE_LAUNCH(rows_dot_kernel<true>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out, stage);
+    else                GE_LAUNCH(rows_dot_kernel<false>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out, stage);
 }
 
 }  // namespace
@@ -438,7 +452,7 @@ extern "C" ge_status_t gemm_rowsum_bf16(int M, int K, const uint16_t *A, int lda
     if (lda < K) return GE_ERR_LD;
     if ((((uintptr_t)A) & 1u) || (((uintptr_t)params) & 3u) || (((uintptr_t)y) & 3u)) return GE_ERR_ALIGN;
     launch_rows_dot(M, K, A, lda, params, alpha, params + K, y, (hipStream_t)stream);
-    g_last_config = rows_wide(K) ? (rows_aligned(K, A, lda) ? "rowsum_rows_wide" : "rowsum_rows_wide_any")
+    g_last_config = rows_wide(M, K, A, lda) ? (rows_aligned(K, A, lda) ? "rowsum_rows_wide" : "rowsum_rows_wide_any")
                                  : vec_ok(A, lda) ? "rowsum_rows_vec8" : "rowsum_rows_generic";
     return ge_host::take_launch_error() == hipSuccess ? GE_OK : GE_ERR_LAUNCH;
 }

@@ -58,7 +58,7 @@ def test_f32_any_alignment(M, N, K, kernel):
     _same(run, kernel)
 
 
-@pytest.mark.parametrize("M,N,K,pad", [(130, 385, 511, 3), (77, 1000, 1031, 1), (9, 65, 8193, 5), (5, 17, 9, 2)])
+@pytest.mark.parametrize("M,N,K,pad", [(130, 385, 511, 3), (77, 1000, 1031, 1), (9, 65, 8193, 5), (5, 17, 9, 2), (9001, 9, 1001, 3), (40, 9, 5001, 7)])
 @pytest.mark.parametrize("transB", [False, True])
 def test_rowsum(M, N, K, pad, transB):
     import torch

@@ -126,10 +126,19 @@ def test_rowsum_equals_the_layer_then_the_sum(oracle):
 def test_rowsum_any_alignment(oracle, transB):
     """Long rows of any length at any address (pieces pulled back to the end of their row), and column sums over chunks of
     64, 32 and 16 rows with ragged last chunks and columns that are no multiple of 8 or 4."""
-    for M, N, K, pad, mis in [(130, 385, 511, (0, 0), 0), (77, 1000, 1031, (3, 5), 0), (41, 390, 2050, (0, 0), 1), (9, 65, 8193, (1, 0), 3),
-                              (64, 4100, 391, (0, 0), 0), (5, 17, 9, (0, 0), 1), (1024, 2049, 1024, (0, 0), 0)]:
+    for M, N, K, pad, mis, cfg in [(130, 385, 511, (0, 0), 0, "rowsum_rows_generic"), (77, 1000, 1031, (3, 5), 0, "rowsum_rows_generic"),
+                                   (41, 390, 2050, (0, 0), 1, "rowsum_rows_wide_any"), (9, 65, 8193, (1, 0), 3, "rowsum_rows_wide_any"),
+                                   (64, 4100, 391, (0, 0), 0, "rowsum_rows_generic"), (5, 17, 9, (0, 0), 1, "rowsum_rows_generic"),
+                                   (1024, 2049, 1024, (0, 0), 0, "rowsum_rows_wide"),
+                                   # short rows, many of them: every width of the wide kernel's groups
+                                   (19701, 9, 431, (0, 0), 0, "rowsum_rows_wide_any"), (9001, 9, 1001, (0, 3), 1, "rowsum_rows_wide_any"),
+                                   (7003, 9, 1201, (2, 0), 0, "rowsum_rows_wide_any"),
+                                   # rows at 16-byte addresses whose length is no multiple of 8
+                                   (40, 9, 5001, (7, 0), 0, "rowsum_rows_wide_any"), (3, 9, 5001, (7, 0), 0, "rowsum_rows_vec8"),
+                                   (2500, 9, 1203, (5, 5), 0, "rowsum_rows_vec8"), (33, 9, 13001, (7, 0), 0, "rowsum_rows_wide_any"),
+                                   (9, 20, 13001, (7, 4), 0, "rowsum_rows_vec8")]:
         _, _, cfg_y = run_rowsum_case(oracle, M, N, K, transB=transB, alpha=0.5, pad=pad, misalign=mis, seed=M + K)
-        assert cfg_y == ("rowsum_rows_generic" if K < 384 else "rowsum_rows_wide" if K == 1024 else "rowsum_rows_wide_any")
+        assert cfg_y == cfg, (M, K, cfg_y)
 
 
 def test_rowsum_small_workspace(oracle):
