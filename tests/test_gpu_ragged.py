@@ -40,6 +40,15 @@ def test_ragged_plain(oracle, M, N, K, tile):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,batch,tile", [(9, 4099, 41, 16, "64x64"), (48, 2316, 33, 16, "64x64"), (2316, 48, 33, 16, "64x64"),
+                                              (129, 129, 33, 60, "64x64"), (67, 131, 41, 200, "128x128")])
+def test_ragged_tile_of_slivers(oracle, M, N, K, batch, tile):
+    """Many tiles of which most is padding: the small ones, where a large one takes the place of fewer than two and a half."""
+    _, _, _, cfg = run_case(oracle, "bf16", M, N, K, batch=batch, alpha=0.5, act="relu", seed=M + N, misalign=1)
+    assert cfg == f"bf16_ragged_{tile}x64"
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("transA,transB", LAYOUTS)
 def test_ragged_layouts(oracle, transA, transB):
     for M, N, K, kw in [(300, 301, 259, dict(pad=(1, 3, 2, 5), residual="f32", beta=0.5, clamp=(-0.1, 2.0), act="gelu_tanh")),
