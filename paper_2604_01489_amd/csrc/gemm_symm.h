@@ -20,6 +20,7 @@
 // 8 N / ST bytes per byte of A (written once, read once): a quarter at N = 16 with ST = 512.
 #pragma once
 #include "gemm_bf16_fast.h"
+#include "gemm_skinny.h"
 #include "symm_layout.h"
 
 namespace ge {
@@ -33,28 +34,46 @@ struct SymmParams {
     long long bytesA;          // extent of one batch of A: ((M - 1) lda + M) * 2
 };
 
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
+
 // keep element e of a fragment register pair iff keepLo / keepHi
 __device__ __forceinline__ unsigned symm_mask_pair(unsigned w, bool keepLo, bool keepHi)
 {
     return w & ((keepLo ? 0x0000FFFFu : 0u) | (keepHi ? 0xFFFF0000u : 0u));
 }
 
+// Sub-tiles on their way: four, 128 KB, where a workgroup has its CU to itself; two for super-tiles of 256, which live for
+// four sub-tiles, two workgroups to a CU: one's beginning and end run under the other's loads (four stages and a CU
+// each: 12288 x 4 52.0 us, this 38.6).
+constexpr int symm_stages(int st) { return st == 256 ? 2 : 4; }
+// whether both blocks of B have a place of their own beside the stages
+constexpr bool symm_own_j(int st, int np) { return symm_stages(st) * ge_symm::STAGE_BYTES + 2 * st * np * 2 <= (st == 256 ? 80 : 160) * 1024; }
+
 // ST: side of a super-tile (a multiple of 128: 256, 512 or 768); NP: columns of the small operand's image (16 or 32);
 // UPPER: the upper triangle is the stored one; BVEC: B can be read in aligned 16-byte pieces along n (N a multiple of 8, aligned,
 // not transposed).
+//
+// Bound by HBM.  Room for the ring of sub-tiles: the fragments of B's rows of J, which every sub-tile row wants again, stay in
+// registers.  The walk is a loop over the rows of sub-tiles (unrolled over all of them a workgroup ran through 95 KB of code
+// once).  16384 x 16: 68.4 -> 59 us, launch and second pass included.
 template <int ST, int NP, bool UPPER, bool BVEC>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, ST == 256 ? 2 : 1)
 gemm_symm_bf16_kernel(const SymmParams p)
 {
     using namespace ge_symm;
     constexpr int NS = ST / SUB;            // sub-tiles per side of a super-tile
     constexpr int NJ = NP / 16;             // 16-column blocks of the result
+    constexpr int KS = SUB / 32;            // 32-k steps of a sub-tile
     constexpr int SMALL_BYTES = ST * NP * 2;
-    // two sub-tiles on their way while one is multiplied, where the LDS has room for three stages (one otherwise)
-    constexpr int STAGES = 3 * STAGE_BYTES + 2 * SMALL_BYTES <= 152 * 1024 ? 3 : 2, AHEAD = STAGES - 1;
-    __shared__ __attribute__((aligned(1024))) char smem[STAGES * STAGE_BYTES + 2 * SMALL_BYTES];
+    constexpr int STAGES = symm_stages(ST), LOADS = SLABS / 4;
+    // stages, then B's rows of I and, where the LDS has room, its rows of J.  Else the latter pass, until their fragments are in
+    // registers, through the last stage (BVEC) or the place of the former.
+    constexpr bool OWN_J = symm_own_j(ST, NP);
+    static_assert(!BVEC || OWN_J || STAGES == 4, "a stage to spare");
+    __shared__ __attribute__((aligned(1024))) char smem[STAGES * STAGE_BYTES + (OWN_J ? 2 : 1) * SMALL_BYTES];
     const unsigned ldsBase = (unsigned)(size_t)(GE_LDS char *)smem;
-    const unsigned smallJ = ldsBase + STAGES * STAGE_BYTES;
+    const unsigned smallI = ldsBase + STAGES * STAGE_BYTES;
+    const unsigned smallJ = OWN_J ? smallI + SMALL_BYTES : BVEC ? ldsBase + (STAGES - 1) * STAGE_BYTES : smallI;
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -68,81 +87,78 @@ gemm_symm_bf16_kernel(const SymmParams p)
     const int I = __builtin_amdgcn_readfirstlane(UPPER ? (int)c : (int)a);     // super-tile row
     const int J = __builtin_amdgcn_readfirstlane(UPPER ? (int)a : (int)c);     // super-tile column
     const bool diag = I == J;
-    const unsigned smallI = diag ? smallJ : smallJ + SMALL_BYTES;
+    // sub-tiles of the super-tile that lie inside the matrix
+    const int nI = min(NS, (p.M - I * ST + SUB - 1) / SUB), nJ = min(NS, (p.M - J * ST + SUB - 1) / SUB);
 
     const char *gA = (const char *)p.A + (long long)b * p.M * p.lda * 2;
     const uint16_t *gB = (const uint16_t *)p.B + (long long)b * (p.transB ? (long long)p.N * p.ldb : (long long)p.M * p.ldb);
 
     // ---- the blocks of the small operand: its rows (k) k0 .. k0 + ST - 1, zero beyond M and beyond N --------
-    // Where the columns are no multiple of 8: every load of a thread is on its way before the first is used, and none sits
-    // behind a test; a chunk of 8 columns is 16 bytes at whatever address, pulled back to end inside the operand, and what
+    // BVEC: straight into LDS, no register and no wait of its own.
+    auto stage_vec = [&](unsigned dst, int k0) __attribute__((always_inline)) {
+        const rsrc_words_t res = make_rsrc(gB + (long long)k0 * p.ldb, RSRC_RECORDS);
+#pragma unroll
+        for (int q = 0; q < SMALL_BYTES / 4096; ++q) {
+            const int slab = q * 4 + w, chunk = slab * 64 + lane, kk = chunk / (NP / 8), n = chunk % (NP / 8) * 8;
+            const unsigned v = k0 + kk < p.M && n < p.N ? (unsigned)kk * (unsigned)p.ldb * 2u + (unsigned)n * 2u : OOB_OFFSET;
+            lds_dma16(res, dst + (unsigned)(slab * 1024), v);
+        }
+    };
+    // Else through registers: every load of a thread is on its way before the first is used, and none sits behind a
+    // test; a chunk of 8 columns is 16 bytes at whatever address, pulled back to end inside the operand, and what
     // is not of the row is masked off.  (Element by element under a test each, the two blocks of a super-tile were most of
     // the call: 9600 x 17 80.1 -> 45.2 us, 14144 x 18 126 -> 80, 5880 x 5 28.2 -> 20.6.)
-    auto stage_small = [&](unsigned dst, int k0) __attribute__((always_inline)) {
-        if constexpr (BVEC) {
-            for (int q = threadIdx.x; q < ST * (NP / 8); q += 256) {
-                const int kk = q / (NP / 8), n = (q % (NP / 8)) * 8;
-                i32x4_t v = {0, 0, 0, 0};
-                if (k0 + kk < p.M && n < p.N) v = *(const i32x4_t *)(gB + (long long)(k0 + kk) * p.ldb + n);
-                *(GE_LDS i32x4_t *)(size_t)(dst + (unsigned)small_offset(NP, kk, n)) = v;
-            }
-        } else if (!p.transB) {
-            constexpr int CPR = NP / 8, PER = ST * CPR / 256;
-            const long long lastChunk = (long long)(p.M - 1) * p.ldb + p.N - 8;
-            i32x4_t v[PER];
-            int count[PER];
+    constexpr int CPR = NP / 8, PER = ST * CPR / 256;
+    const long long lastChunk = (long long)(p.M - 1) * p.ldb + p.N - 8;
+    auto load_small = [&](int k0, i32x4_t (&v)[PER]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < PER; ++q) {
-                const int kk = (q * 256 + (int)threadIdx.x) / CPR, n = (int)threadIdx.x % CPR * 8;
-                const long long want = (long long)(k0 + kk) * p.ldb + n, at = want < lastChunk ? want : lastChunk;
-                count[q] = k0 + kk < p.M ? p.N - n : 0;
-                v[q] = ((const i32x4_any_t *)(gB + at))->v;
-                if (count[q] > 0) v[q] = shift_down_elements(v[q], (int)(want - at));
-            }
+        for (int q = 0; q < PER; ++q) {
+            const int kk = (q * 256 + (int)threadIdx.x) / CPR, n = (int)threadIdx.x % CPR * 8;
+            const long long want = (long long)(k0 + kk) * p.ldb + n;
+            v[q] = ((const i32x4_any_t *)(gB + (want < lastChunk ? want : lastChunk)))->v;
+        }
+    };
+    auto store_small = [&](unsigned dst, int k0, const i32x4_t (&loaded)[PER]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < PER; ++q) {
-                const int kk = (q * 256 + (int)threadIdx.x) / CPR, n = (int)threadIdx.x % CPR * 8;
+        for (int q = 0; q < PER; ++q) {
+            const int kk = (q * 256 + (int)threadIdx.x) / CPR, n = (int)threadIdx.x % CPR * 8;
+            const long long want = (long long)(k0 + kk) * p.ldb + n;
+            const int count = k0 + kk < p.M ? p.N - n : 0;
+            i32x4_t v = loaded[q];
+            if (count > 0 && want > lastChunk) v = shift_down_elements(v, (int)(want - lastChunk));
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[q][e] = (int)symm_mask_pair((unsigned)v[q][e], 2 * e < count[q], 2 * e + 1 < count[q]);
-                *(GE_LDS i32x4_t *)(size_t)(dst + (unsigned)small_offset(NP, kk, n)) = v[q];
-            }
-        } else {
+            for (int e = 0; e < 4; ++e) v[e] = (int)symm_mask_pair((unsigned)v[e], 2 * e < count, 2 * e + 1 < count);
+            *(GE_LDS i32x4_t *)(size_t)(dst + (unsigned)small_offset(NP, kk, n)) = v;
+        }
+    };
+    auto stage_transposed = [&](unsigned dst, int k0) __attribute__((always_inline)) {
 #pragma unroll 8
-            for (int q = threadIdx.x; q < ST * NP; q += 256) {
-                const int kk = q % ST, n = q / ST;             // neighbouring threads on neighbouring k
-                const bool inside = k0 + kk < p.M && n < p.N;
-                const unsigned short v = gB[inside ? (long long)n * p.ldb + (k0 + kk) : 0ll];
-                *(GE_LDS unsigned short *)(size_t)(dst + (unsigned)small_offset(NP, kk, n)) = inside ? v : (unsigned short)0;
-            }
+        for (int q = threadIdx.x; q < ST * NP; q += 256) {
+            const int kk = q % ST, n = q / ST;             // neighbouring threads on neighbouring k
+            const bool inside = k0 + kk < p.M && n < p.N;
+            const unsigned short v = gB[inside ? (long long)n * p.ldb + (k0 + kk) : 0ll];
+            *(GE_LDS unsigned short *)(size_t)(dst + (unsigned)small_offset(NP, kk, n)) = inside ? v : (unsigned short)0;
         }
     };
 
-    // ---- loads of sub-tile (rs, cs) of the super-tile into stage st: 8 per wave ---------------------------
-    auto issue_sub = [&](int rs, int cs, int st) __attribute__((always_inline)) {
+    // ---- loads of sub-tile (rs, cs) of the super-tile into ring slot st: 8 per wave ------------------------
+    // (the swizzle of a slab's rows repeats every 16 rows: one lane offset, a step of 16 rows per load).  Wide super-tiles are
+    // for triangles the 256 MB memory-side cache does not hold, which go past it (16384 x 16, 268 MB: 63.6 us through, 58.3 past
+    // it; 8192 x 17, 67 MB: 34.8 / 38.1).
+    const int row0 = slab_row(w, lane), ch0 = slab_chunk(w, lane);
+    const unsigned voff0 = (unsigned)row0 * (unsigned)p.lda * 2u + (unsigned)ch0 * 16u, rows16 = 32u * (unsigned)p.lda;
+    auto issue_sub = [&](bool live, int rs, int cs, int st) __attribute__((always_inline)) {
         const int r0 = I * ST + rs * SUB, c0 = J * ST + cs * SUB;
-        const long long origin = ((long long)r0 * p.lda + c0) * 2;
-        // a sub-tile wholly outside the matrix (a ragged last super-tile) goes through an empty resource
-        const bool live = r0 < p.M && c0 < p.M;
-        const rsrc_words_t res = make_rsrc(gA + (live ? origin : 0), live ? records_left(p.bytesA, origin) : 0u);
+        const long long origin = live ? ((long long)r0 * p.lda + c0) * 2 : 0;
+        // past the end of the walk through an empty resource; rows beyond the matrix are beyond the resource's end
+        const rsrc_words_t res = make_rsrc(gA + origin, live ? records_left(p.bytesA, origin) : 0u);
+        const unsigned v = c0 + ch0 * 8 >= p.M ? OOB_OFFSET : voff0, dst = ldsBase + (unsigned)(st * STAGE_BYTES + w * 1024);
 #pragma unroll
-        for (int q = 0; q < SLABS / 4; ++q) {
-            const int slab = q * 4 + w;
-            const int row = slab_row(slab, lane), ch = slab_chunk(slab, lane);
-            unsigned v = (unsigned)row * (unsigned)p.lda * 2u + (unsigned)ch * 16u;
-            if (r0 + row >= p.M || c0 + ch * 8 >= p.M) v = OOB_OFFSET;
-            lds_dma16(res, ldsBase + (unsigned)(st * STAGE_BYTES + slab * 1024), v);
+        for (int q = 0; q < LOADS; ++q) {
+            if constexpr (ST > 256) lds_dma16_nt(res, dst + (unsigned)(q * 4096), v + (unsigned)q * rows16);
+            else                    lds_dma16(res, dst + (unsigned)(q * 4096), v + (unsigned)q * rows16);
         }
     };
-
-    f32x4_t acc1[NS][2][NJ], acc2[NS][2][NJ];
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) { acc1[s][i][j][r] = 0.0f; acc2[s][i][j][r] = 0.0f; }
 
     // fragment of a small-operand image: the 32 k from kBase, column block j
     auto small_frag = [&](unsigned img, int kBase, int j) __attribute__((always_inline)) {
@@ -153,111 +169,160 @@ gemm_symm_bf16_kernel(const SymmParams p)
         return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
 
-    // (Every lambda below is forced inline: called from dozens of unrolled places the large ones would
-    // otherwise stay functions, and the accumulator arrays they index would live in scratch memory.)
-    // Sub-tile (rs, cs) from stage st: P1 into acc1[rs], P2 into acc2[cs].  onDiag: the sub-tile lies on the
-    // diagonal of the matrix and the fragments are cleared of the other triangle.  (Called from fully
-    // unrolled loops: rs, cs and onDiag are constants by then.)
-    auto multiply = [&](int rs, int cs, bool onDiag, int st) __attribute__((always_inline)) {
-        const unsigned img = ldsBase + (unsigned)(st * STAGE_BYTES);
+    auto lds_barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    // A sub-tile on the diagonal: the other triangle, which may hold anything, is cleared in the image, before the multiply of P1;
+    // and the diagonal itself, which belongs to P1, before that of P2.
+    auto clear_triangle = [&](unsigned img) __attribute__((always_inline)) {
+        constexpr int AT_ONCE = 4;
+        static_assert(SUB * SUB / 8 % (256 * AT_ONCE) == 0, "the chunks divide over the threads");
+#pragma unroll 1
+        for (int q0 = 0; q0 < SUB * SUB / 8; q0 += 256 * AT_ONCE) {
+            i32x4_t v[AT_ONCE];
 #pragma unroll
-        for (int ks = 0; ks < SUB / 32; ++ks) {
+            for (int q = 0; q < AT_ONCE; ++q) {
+                const int id = q0 + q * 256 + (int)threadIdx.x;
+                v[q] = *(const GE_LDS i32x4_t *)(size_t)(img + (unsigned)image_offset(id >> 4, id & 15));
+            }
+#pragma unroll
+            for (int q = 0; q < AT_ONCE; ++q) {
+                const int id = q0 + q * 256 + (int)threadIdx.x, r = id >> 4;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int c0 = 8 * (id & 15) + 2 * e, c1 = c0 + 1;
+                    v[q][e] = (int)symm_mask_pair((unsigned)v[q][e], UPPER ? c0 >= r : c0 <= r, UPPER ? c1 >= r : c1 <= r);
+                }
+                *(GE_LDS i32x4_t *)(size_t)(img + (unsigned)image_offset(r, id & 15)) = v[q];
+            }
+        }
+        lds_barrier();
+    };
+    auto clear_diagonal = [&](unsigned img) __attribute__((always_inline)) {
+        lds_barrier();
+        const int r = (int)threadIdx.x;
+        if (r < SUB) *(GE_LDS short *)(size_t)(img + (unsigned)(image_offset(r, r >> 3) + (r & 7) * 2)) = 0;
+        lds_barrier();
+    };
+
+    // ---- the walk: the sub-tiles row by row, a ring of them on their way ------------------------------------
+    // On the diagonal of the matrix only the stored triangle's: columns 0 .. u of sub-tile row u, or (upper) u .. nJ - 1.
+    auto first_of = [&](int u) { return UPPER && diag ? u : 0; };
+    auto last_of = [&](int u) { return !UPPER && diag ? u : nJ - 1; };
+    int pu = 0, pv = 0;                                  // the next sub-tile to load
+    auto issue_next = [&](int st) __attribute__((always_inline)) {
+        issue_sub(pu < nI, pu, pv, st);
+        if (pv == last_of(pu)) { ++pu; pv = first_of(pu); }
+        else ++pv;
+    };
+    bf16x8_t fbJ[NS * KS][NJ];
+    auto read_fragments_of_J = [&] __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < NS * KS; ++k)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) fbJ[k][j] = small_frag(smallJ, 32 * k, j);
+    };
+    if constexpr (BVEC) {
+        constexpr int FIRST = OWN_J ? STAGES : STAGES - 1;
+        stage_vec(smallJ, J * ST);
+        stage_vec(smallI, I * ST);
+#pragma unroll
+        for (int t = 0; t < FIRST; ++t) issue_next(t);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FIRST * LOADS) : "memory");
+        read_fragments_of_J();
+        if constexpr (!OWN_J) {
+            lds_barrier();
+            issue_next(STAGES - 1);
+        }
+    } else if (!p.transB) {
+        i32x4_t vJ[PER], vI[PER];
+        // (the wait for the registers is one for whatever else is on its way by then: the other stages' loads follow it)
+        issue_next(0);
+        load_small(J * ST, vJ);
+        load_small(I * ST, vI);
+        store_small(smallJ, J * ST, vJ);
+        if constexpr (!OWN_J) {
+            lds_barrier();
+            read_fragments_of_J();
+            lds_barrier();
+        }
+        store_small(smallI, I * ST, vI);
+#pragma unroll
+        for (int t = 1; t < STAGES; ++t) issue_next(t);
+        lds_barrier();
+        if constexpr (OWN_J) read_fragments_of_J();
+    } else {
+#pragma unroll
+        for (int t = 0; t < STAGES; ++t) issue_next(t);
+        stage_transposed(smallJ, J * ST);
+        lds_barrier();
+        read_fragments_of_J();
+        if constexpr (!OWN_J) lds_barrier();
+        stage_transposed(smallI, I * ST);
+        lds_barrier();
+    }
+
+    f32x4_t acc1[NS][2][NJ], acc2[NS][2][NJ];    // P1 of sub-tile row s, P2 of sub-tile column s
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { acc1[s][i][j][r] = 0.0f; acc2[s][i][j][r] = 0.0f; }
+
+    int slot = 0;
+#pragma unroll 1
+    for (int u = 0; u < nI; ++u) {
+        bf16x8_t fbI[KS][NJ];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) fbI[ks][j] = small_frag(smallI, u * SUB + 32 * ks, j);
+        f32x4_t run[2][NJ];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) run[i][j][r] = 0.0f;
+        const int first = first_of(u), last = last_of(u);
+#pragma unroll
+        for (int v = 0; v < NS; ++v) {
+            if (v < first || v > last) continue;
+            // the sub-tile has landed (the loads complete in order), every wave's part of it
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * LOADS) : "memory");
+            const unsigned img = ldsBase + (unsigned)(slot * STAGE_BYTES);
+            const bool onDiag = diag && u == v;
+            if (onDiag) clear_triangle(img);
             // ---- P1: rows 32 w + 16 i + l%16 of the sub-tile, k = its columns 32 ks + 8 (l/16) + e
-            bf16x8_t fbJ[NJ];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) fbJ[j] = small_frag(smallJ, cs * SUB + 32 * ks, j);
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int rowBase = 32 * w + 16 * i;
-                i32x4_t raw = *(const GE_LDS i32x4_t *)(size_t)(img + (unsigned)row_frag_offset(rowBase, ks, lane));
-                if (onDiag) {
-                    const int r = rowBase + (lane & 15), col = 32 * ks + 8 * (lane >> 4);
+                for (int i = 0; i < 2; ++i) {
+                    const bf16x8_t fa = *(const GE_LDS bf16x8_t *)(size_t)(img + (unsigned)row_frag_offset(32 * w + 16 * i, ks, lane));
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int c0 = col + 2 * q, c1 = c0 + 1;
-                        raw[q] = (int)symm_mask_pair((unsigned)raw[q], UPPER ? c0 >= r : c0 <= r, UPPER ? c1 >= r : c1 <= r);
-                    }
+                    for (int j = 0; j < NJ; ++j)
+                        run[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fbJ[v * KS + ks][j], fa, run[i][j], 0, 0, 0);
                 }
-                const bf16x8_t fa = __builtin_bit_cast(bf16x8_t, raw);
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc1[rs][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fbJ[j], acc1[rs][i][j], 0, 0, 0);
-            }
+            if (onDiag) clear_diagonal(img);
             // ---- P2: output rows = columns 32 w + 16 i + l%16 of the sub-tile, k = its rows 32 ks + 8 (l/16) + e
-            bf16x8_t fbI[NJ];
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) fbI[j] = small_frag(smallI, rs * SUB + 32 * ks, j);
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int colBase = 32 * w + 16 * i;
-                const GE_LDS char *p0 = (const GE_LDS char *)(size_t)(img + (unsigned)col_frag_offset(colBase, ks, lane, 0));
-                const GE_LDS char *p1 = (const GE_LDS char *)(size_t)(img + (unsigned)col_frag_offset(colBase, ks, lane, 1));
-                short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GE_LDS short4_t *)p0);
-                short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GE_LDS short4_t *)p1);
-                i32x4_t raw = __builtin_bit_cast(i32x4_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                if (onDiag) {
-                    // the mirrored part only: the diagonal itself belongs to P1
-                    const int cc = colBase + (lane & 15), row = 32 * ks + 8 * (lane >> 4);
+                for (int i = 0; i < 2; ++i) {
+                    const GE_LDS char *p0 = (const GE_LDS char *)(size_t)(img + (unsigned)col_frag_offset(32 * w + 16 * i, ks, lane, 0));
+                    const GE_LDS char *p1 = (const GE_LDS char *)(size_t)(img + (unsigned)col_frag_offset(32 * w + 16 * i, ks, lane, 1));
+                    const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GE_LDS short4_t *)p0);
+                    const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((GE_LDS short4_t *)p1);
+                    const bf16x8_t fa = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int r0 = row + 2 * q, r1 = r0 + 1;
-                        raw[q] = (int)symm_mask_pair((unsigned)raw[q], UPPER ? cc > r0 : cc < r0, UPPER ? cc > r1 : cc < r1);
-                    }
+                    for (int j = 0; j < NJ; ++j)
+                        acc2[v][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fbI[ks][j], fa, acc2[v][i][j], 0, 0, 0);
                 }
-                const bf16x8_t fa = __builtin_bit_cast(bf16x8_t, raw);
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc2[cs][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fbI[j], acc2[cs][i][j], 0, 0, 0);
-            }
+            lds_barrier();                               // every wave is done with the slot
+            issue_next(slot);
+            slot = slot == STAGES - 1 ? 0 : slot + 1;
         }
-    };
-
-    // ---- the walk over the sub-tiles, two loading while one is multiplied --------------------------------
-    // Off the diagonal every sub-tile of the super-tile, (u, v) = (row, column).  On it only those of the
-    // stored triangle: v <= u with (row, column) = (u, v) for the lower, (v, u) for the upper triangle.
-    // Both loops are fully unrolled, so the accumulators are indexed by constants.  Per sub-tile t: its data
-    // have landed (the loads complete in order: all but those of t + 1) and every wave is past the multiply
-    // of t - 1 -- one barrier for both -- then the loads of t + AHEAD go into the stage t - 1 occupied.
-    auto walk = [&](auto diagC) __attribute__((always_inline)) {
-        constexpr bool DIAG = decltype(diagC)::value;
-        auto row_of = [](int u, int v) { return (DIAG && UPPER) ? v : u; };
-        auto col_of = [](int u, int v) { return (DIAG && UPPER) ? u : v; };
-        // (u, v) one step on; u == NS: past the end
-        auto step_u = [](int u, int v) { return (DIAG ? v == u : v == NS - 1) ? u + 1 : u; };
-        auto step_v = [](int u, int v) { return (DIAG ? v == u : v == NS - 1) ? 0 : v + 1; };
-        issue_sub(0, 0, 0);
-        if (AHEAD == 2 && step_u(0, 0) < NS) issue_sub(row_of(step_u(0, 0), step_v(0, 0)), col_of(step_u(0, 0), step_v(0, 0)), 1);
-        stage_small(smallJ, J * ST);
-        if (!DIAG) stage_small(smallI, I * ST);
-        int t = 0;
-#pragma unroll
-        for (int u = 0; u < NS; ++u) {
-#pragma unroll
-            for (int v = 0; v < NS; ++v) {
-                if (DIAG && v > u) continue;
-                const int u1 = step_u(u, v), v1 = step_v(u, v);
-                const int u2 = u1 < NS ? step_u(u1, v1) : NS, v2 = u1 < NS ? step_v(u1, v1) : 0;
-                if (AHEAD == 2 && u1 < NS) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(SLABS / 4) : "memory");
-                else                       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                if (AHEAD == 2) {
-                    if (u2 < NS) issue_sub(row_of(u2, v2), col_of(u2, v2), (t + 2) % STAGES);
-                } else if (u1 < NS) {
-                    issue_sub(row_of(u1, v1), col_of(u1, v1), (t + 1) % STAGES);
-                }
-                multiply(row_of(u, v), col_of(u, v), DIAG && u == v, t % STAGES);
-                ++t;
-            }
-        }
-    };
-
-    if (diag) walk(std::true_type{});
-    else walk(std::false_type{});
-
-    // ---- the terms: P1 is term J of row block I, P2 term I of row block J; on the diagonal their sum is
-    // term I of row block I.  Register r of lane l: row 4 (l/16) + r, column l%16 of its 16 x 16 block.
-    const long long slice = (long long)p.batch * p.M * p.N;
-    auto store_term = [&](f32x4_t (&acc)[NS][2][NJ], int rowBlock, int term) __attribute__((always_inline)) {
-        float *dst = p.W + (long long)term * slice + (long long)b * p.M * p.N;
 #pragma unroll
         for (int s = 0; s < NS; ++s)
 #pragma unroll
@@ -265,11 +330,8 @@ gemm_symm_bf16_kernel(const SymmParams p)
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int m = rowBlock * ST + s * SUB + 32 * w + 16 * i + 4 * (lane >> 4) + r, n = 16 * j + (lane & 15);
-                        if (m < p.M && n < p.N) dst[(long long)m * p.N + n] = acc[s][i][j][r];
-                    }
-    };
+                    for (int r = 0; r < 4; ++r) acc1[s][i][j][r] = s == u ? run[i][j][r] : acc1[s][i][j][r];
+    }
     if (diag) {
 #pragma unroll
         for (int s = 0; s < NS; ++s)
@@ -279,11 +341,78 @@ gemm_symm_bf16_kernel(const SymmParams p)
                 for (int j = 0; j < NJ; ++j)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) acc1[s][i][j][r] += acc2[s][i][j][r];
-        store_term(acc1, I, I);
-    } else {
-        store_term(acc1, I, J);
-        store_term(acc2, J, I);
     }
+
+    // ---- the terms: P1 is term J of row block I, P2 term I of row block J; on the diagonal their sum is term I of row
+    // block I.  The rows of a term's block are one run of memory.  Register r of lane l is row l%16, column 4 (l/16) + r of a
+    // 16 x 16 block (the small operand's fragments are the first operand of the matrix instruction): column counts that are
+    // multiples of 4 and those below 3 are few store instructions, straight from the registers; with others, up to 128 a wave with
+    // most of their lanes idle, the run leaves through an image of it in LDS, 1 KB a wave instruction (straight / image: 8192 x
+    // 17 38.1 / 31.2 us, 16384 x 16 58.8 / 60.1, x 32 98.5 / 104.5, 12288 x 4 38.5 / 39.0).  (P1 row by row inside the walk, for half the
+    // stores to be over by its end: 16384 x 16 58.3 -> 61.8 us, the waits for the loads then wait for the stores.)
+    const unsigned pitch = (unsigned)p.N * 4u;
+    const int col = 4 * (lane >> 4);
+    auto term_rows = [&](int rowBlock, int term) { return (char *)(p.W + ((long long)term * p.batch + b) * p.M * p.N + (long long)rowBlock * ST * p.N); };
+    auto bytes_of = [&](int rowBlock) { return min(ST, p.M - rowBlock * ST) * p.N * 4; };      // a multiple of 32: M is one of 8
+    // the empty loads past the end of the walk have landed, too
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const bool quads = (p.N & 3) == 0;
+    if (quads || p.N < 3) {
+        auto store = [&](const f32x4_t (&acc)[NS][2][NJ], int rowBlock, int term) __attribute__((always_inline)) {
+            // rows beyond the matrix are beyond the resource's end, columns beyond N out of any range
+            const buffer_t rows = __builtin_amdgcn_make_buffer_rsrc(term_rows(rowBlock, term), 0, bytes_of(rowBlock), 0x00020000);
+            const unsigned at = (unsigned)(32 * w + (lane & 15)) * pitch + 4u * (unsigned)col;
+            auto offset = [&](int s, int i, int c) { return (int)(col + c < p.N ? at + (unsigned)(s * SUB + 16 * i) * pitch + 4u * c : OOB_OFFSET); };
+            if (quads) {
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < NJ; ++j) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[s][i][j]), rows, offset(s, i, 16 * j), 0, 0);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    if (r >= p.N) break;
+#pragma unroll
+                    for (int s = 0; s < NS; ++s)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[s][i][0][r]), rows, offset(s, i, r), 0, 0);
+                }
+            }
+        };
+        store(acc1, I, J);
+        if (!diag) store(acc2, J, I);
+        return;
+    }
+    lds_barrier();                                       // every wave is done with the stages
+    constexpr int IMAGE = ST * NP * 4;
+    static_assert(2 * IMAGE <= STAGES * STAGE_BYTES + SMALL_BYTES, "both terms' images fit");
+    auto put = [&](unsigned image, const f32x4_t (&acc)[NS][2][NJ]) __attribute__((always_inline)) {
+        const unsigned at = image + (unsigned)(32 * w + (lane & 15)) * pitch + 4u * (unsigned)col;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (16 * j + col + r < p.N) {
+#pragma unroll
+                    for (int s = 0; s < NS; ++s)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            *(GE_LDS float *)(size_t)(at + (unsigned)(s * SUB + 16 * i) * pitch + 64u * j + 4u * r) = acc[s][i][j][r];
+                }
+    };
+    put(ldsBase, acc1);
+    if (!diag) put(ldsBase + IMAGE, acc2);
+    lds_barrier();
+    auto send = [&](unsigned image, int rowBlock, int term) {
+        char *dst = term_rows(rowBlock, term);
+        const int bytes = bytes_of(rowBlock);
+#pragma unroll 4
+        for (int at = (int)threadIdx.x * 16; at < bytes; at += 4096) *(i32x4_t *)(dst + at) = *(const GE_LDS i32x4_t *)(size_t)(image + (unsigned)at);
+    };
+    send(ldsBase, I, J);
+    if (!diag) send(ldsBase + IMAGE, J, I);
 }
 
 }  // namespace ge

@@ -48,13 +48,22 @@ namespace {
 template <int ST, int NP>
 void launch_symm(const ge::SymmParams &sp, bool upper, bool bVec, dim3 grid, hipStream_t st)
 {
-    if (bVec) {
-        if (upper) GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, true, true>), grid, dim3(256), 0, st, sp);
-        else       GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, false, true>), grid, dim3(256), 0, st, sp);
-    } else {
-        if (upper) GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, true, false>), grid, dim3(256), 0, st, sp);
-        else       GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, false, false>), grid, dim3(256), 0, st, sp);
+    auto launch = [&](auto vecC) {
+        constexpr bool BVEC = decltype(vecC)::value;
+        if (upper) GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, true, BVEC>), grid, dim3(256), 0, st, sp);
+        else       GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, false, BVEC>), grid, dim3(256), 0, st, sp);
+    };
+    if constexpr (ge::symm_stages(ST) == 4 || ge::symm_own_j(ST, NP)) {
+        if (bVec) return launch(std::true_type{});
     }
+    launch(std::false_type{});
+}
+
+template <int ST>
+void launch_symm(const ge::SymmParams &sp, int np, bool upper, bool bVec, dim3 grid, hipStream_t st)
+{
+    if (np == 16) launch_symm<ST, 16>(sp, upper, bVec, grid, st);
+    else          launch_symm<ST, 32>(sp, upper, bVec, grid, st);
 }
 
 }  // namespace
@@ -72,19 +81,14 @@ ge_status_t run_symm(const ge_fused_args_t &a, const SymmPlan &plan, GemmParams 
     sp.upper = a.a_structure == GE_A_SYM_UPPER ? 1 : 0;
     sp.batch = a.batch;
     sp.tiles = plan.terms;
-    const bool bVec = !a.transB && (a.N % 8) == 0 && (a.ldb % 8) == 0 && !(((uintptr_t)a.B) & 15u);
+    // (the offsets of a super-tile's rows of B are 32-bit)
+    const bool bVec = !a.transB && a.ldb < (1 << 20) && (a.N % 8) == 0 && (a.ldb % 8) == 0 && !(((uintptr_t)a.B) & 15u);
     sp.bytesA = 2 * (((long long)a.M - 1) * a.lda + a.M);
     const dim3 grid((unsigned)((long long)plan.terms * (plan.terms + 1) / 2), (unsigned)a.batch);
     const bool upper = sp.upper != 0;
-    if (plan.st == 768) {
-        launch_symm<768, 16>(sp, upper, bVec, grid, hs);
-    } else if (plan.st == 512) {
-        if (plan.np == 16) launch_symm<512, 16>(sp, upper, bVec, grid, hs);
-        else               launch_symm<512, 32>(sp, upper, bVec, grid, hs);
-    } else {
-        if (plan.np == 16) launch_symm<256, 16>(sp, upper, bVec, grid, hs);
-        else               launch_symm<256, 32>(sp, upper, bVec, grid, hs);
-    }
+    if (plan.st == 768)      launch_symm<768, 16>(sp, upper, bVec, grid, hs);
+    else if (plan.st == 512) launch_symm<512>(sp, plan.np, upper, bVec, grid, hs);
+    else                     launch_symm<256>(sp, plan.np, upper, bVec, grid, hs);
     if (ge_host::take_launch_error() != hipSuccess) return GE_ERR_LAUNCH;
     // the terms are the slices of the second pass: added in their order, then the consumer chain
     p.splitK = plan.terms;

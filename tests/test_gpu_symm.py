@@ -170,3 +170,12 @@ def test_symm_columns_of_any_number(oracle, uplo, transB):
     for M, N, kw in [(512, 1, {}), (776, 7, dict(pad=(0, 3, 1))), (1032, 9, {}), (520, 17, dict(pad=(8, 1, 0))), (1024, 31, {}), (768, 33 - 1, dict(pad=(0, 5, 3)))]:
         _, cfg = run_symm_case(oracle, M, N, uplo=uplo, transB=transB, act="relu", seed=M + N, **kw)
         assert cfg.startswith(f"bf16_symm_{uplo}"), cfg
+
+
+@pytest.mark.parametrize("M,N", [(520, 2), (776, 3), (1032, 4), (1288, 5), (640, 20), (904, 28)])
+def test_symm_terms_by_every_store(oracle, M, N):
+    """The ways a super-tile's terms leave it: straight from the registers in 16-byte pieces (columns a multiple of 4) or single ones
+    (one or two columns), else through their image in LDS; the last super-tile hangs over the matrix by whole and by partial sub-tiles."""
+    for uplo in ("lower", "upper"):
+        _, cfg = run_symm_case(oracle, M, N, uplo=uplo, seed=M + N)
+        assert cfg.startswith(f"bf16_symm_{uplo}_"), cfg
