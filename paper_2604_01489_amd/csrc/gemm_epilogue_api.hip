@@ -3,6 +3,7 @@
 // include/gemm_epilogue.h for the contract of every entry point.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
@@ -112,6 +113,25 @@ void slice_k(int K, int bk, int want, int *splitK, int *kPerSlice)
     if (per < bk) per = bk;
     *kPerSlice = per;
     *splitK = ceil_div(K, per);
+}
+
+// K slices of an fp32 product on tiles of `tile` squared that has to be sliced into at least `least` (a chain of sums over more of K is less
+// exact): the count with the lowest estimate.  A CU's matrix pipes take 0.54 us for each 32-k step of each block it has been
+// given (a 128 tile four times that), or a block alone 0.62 us with its waits; the second pass is a launch and the partial tiles written and read.  What
+// the count decides is how full the last round of blocks on the CUs is.  us, least / chosen: 1023 x 771 x 2049, 208 tiles,
+// 4 slices 47.2 / 6 42.4 (5: 46.8, 7: 45.7); 320 x 320 x 4095, 7 19.2 / 10 16.4 (12: 20.6); 513 x 515 x 4095, 5 36.0 / 6 32.5;
+// 256 x 256 x 1024, 2 15.3 / 8 9.6; 72 x 1280 x 1600, 3 16.9 / 6 12.0.  Slices keep 64 of K.
+int f32_slices(int tile, long long tiles, long long outputs, int K, int least)
+{
+    const double area = tile == 128 ? 4.0 : 1.0;
+    int best = least;
+    double bestCost = 0.0;
+    for (int s = least; s <= 64 && (s == least || K / s >= 64); ++s) {
+        const double rounds = (double)((tiles * s + kNumCU - 1) / kNumCU), steps = (double)ceil_div(ceil_div(K, s), 32);
+        const double cost = steps * (rounds * area > 1.0 ? 0.54 * area * rounds : 0.62) + (double)(s + 1) * (double)outputs * 4.0 / 4.5e6;
+        if (s == least || cost < bestCost) { best = s; bestCost = cost; }
+    }
+    return best;
 }
 
 // Estimated time in microseconds of one structure -- block tile (256 or 128) and number of K slices --
@@ -652,76 +672,114 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
         return ge_host::take_launch_error() != hipSuccess ? GE_ERR_LAUNCH : GE_OK;
     }
     const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128) * batch, t64 = (long long)ceil_div(M, 64) * ceil_div(N, 64) * batch;
+    const long long outputs = (long long)batch * M * N;
     // 128x128 tiles once they give every other CU a block, else 64x64 (more blocks, less padding)
     bool big = t128 * 2 >= kNumCU && M >= 128 && N >= 128, elementwise = false;
     // K slices where the tiles leave more than half of the CUs idle and K is long: partial sums to the
     // library's workspace of the stream (this call has no workspace argument), summed in slice order
-    slice_k(K, 16, choose_split(big ? t128 : t64, K, 512), &p.splitK, &p.kPerSlice);
+    int least = choose_split(big ? t128 : t64, K, 512);
     // tiles on the edge of C are stored through 31-bit offsets
-    if (fast && ((M % (big ? 128 : 64)) || (N % (big ? 128 : 64))) && (p.splitK > 1 ? N : ldc) >= ge::EDGE_LDC_MAX) fast = false;
+    if (fast && ((M % (big ? 128 : 64)) || (N % (big ? 128 : 64))) && (least > 1 ? N : ldc) >= ge::EDGE_LDC_MAX) fast = false;
     if (!fast) {
         // rows shorter than a 16-byte chunk, or panels beyond 31-bit byte offsets: every element under its own test
         elementwise = K < 4 || N < 4 || (long long)lda * 4 * 128 + 256 >= (1ll << 31) || (long long)ldb * 4 * 32 + 1024 >= (1ll << 31) ||
                       ldc >= ge::EDGE_LDC_MAX;
-        // Operands of any alignment: the tile whose rounds of blocks on the CUs take the matrix pipe less time (a 128 tile is
-        // four of the small one, at 1.1 times its rate; 64 against 128, us: 1023 x 771 x 2049 48 / 57, 1501^3 82 / 114, 2001 x
-        // 2003 x 401 45 / 42).  Fewer than 32 tiles of 64 stay on 128x128, which is the slower one there too (100 x 333 x 900
-        // 22 / 66, 255 x 255 x 1001 24 / 73, 130 x 257 x 2075 17 / 43, 320 x 320 x 4095 19 / 48, 129 x 130 x 31 4.8 / 6.1): the line
-        // keeps small calls on the tile that they have been tested on, it is not where the times cross
-        big = !elementwise && (t64 < 32 || (double)((t128 + kNumCU - 1) / kNumCU) * 3.6 <= (double)((t64 + kNumCU - 1) / kNumCU));
         // sliced by their 128 tiles whichever tile they get: a chain of sums over all of K is less exact than its slices,
         // 8e-7 against 4e-7 at K = 2049, and no faster, 48 against 49 us
-        slice_k(K, 16, choose_split(t128, K, 512), &p.splitK, &p.kPerSlice);
+        least = choose_split(t128, K, 512);
+        // Operands of any alignment: the tile whose rounds of blocks on the CUs take the matrix pipe less time (a 128 tile is
+        // four of the small one, at 1.1 times its rate; 64 against 128, us: 1023 x 771 x 2049 48 / 57, 1501^3 82 / 114, 2001 x
+        // 2003 x 401 45 / 42).  Two calls of few tiles keep the large one that they have been tested on: those of one or two
+        // 32-k steps, a launch and little else (129 x 130 x 31 5.5 / 6.1), and fewer than 16 tiles in slices (130 x 257 x 2075).
+        // The others are the small tile's (100 x 333 x 900 22 / 66, 255 x 255 x 1001 24 / 73, 129 x 130 x 300 9.6 / 25.6, 320 x 320 x 4095
+        // 16.4 / 49.7).
+        big = !elementwise && ((t64 < 32 && K <= 64) || (t64 < 16 && least > 1) ||
+                               (double)((t128 + kNumCU - 1) / kNumCU) * 3.6 <= (double)((t64 + kNumCU - 1) / kNumCU));
     }
+    slice_k(K, 16, least > 1 ? f32_slices(big ? 128 : 64, big ? t128 : t64, outputs, K, least) : 1, &p.splitK, &p.kPerSlice);
     const int bm = big ? 128 : 64;
     p.tilesM = ceil_div(M, bm);
     p.tilesN = ceil_div(N, bm);
     p.groupM = choose_group_m(p.tilesM, p.tilesN);
     const long long tiles = (long long)p.tilesM * p.tilesN * batch;
-    const long long blocks = tiles * p.splitK;
-    if (blocks > 0x7fffffffll) return GE_ERR_SHAPE;
+    if (tiles * p.splitK > 0x7fffffffll) return GE_ERR_SHAPE;
     const bool raw = p.splitK > 1;
     void *ws = nullptr;
-    GemmParams pg = p;
+    int perPass = p.splitK;
+    p.sliceStride = outputs;
     if (raw) {
         st = acquire_workspace(partial_bytes(M, N, batch, p.splitK), nullptr, 0, hs, &ws);
-        if (st != GE_OK) return st;
-        p.sliceStride = (long long)batch * M * N;
-        pg = p;
-        pg.C = (float *)ws; pg.ldc = N; pg.strideC = (long long)M * N;
-    }
-    const dim3 grid((unsigned)blocks), block(256);
-    if (fast) {
-        const bool edge = (M % bm) || (N % bm) || (K % 16);
-        if (big) {
-            if (raw) { if (edge) GE_LAUNCH((ge::gemm_f32_fast_kernel<128, 128, true, true>), grid, block, 0, hs, pg);
-                       else      GE_LAUNCH((ge::gemm_f32_fast_kernel<128, 128, false, true>), grid, block, 0, hs, pg); }
-            else     { if (edge) GE_LAUNCH((ge::gemm_f32_fast_kernel<128, 128, true>), grid, block, 0, hs, pg);
-                       else      GE_LAUNCH((ge::gemm_f32_fast_kernel<128, 128, false>), grid, block, 0, hs, pg); }
-            g_last_config = raw ? "f32_128x128x16_w4_splitk" : "f32_128x128x16_w4";
-        } else {
-            if (raw) { if (edge) GE_LAUNCH((ge::gemm_f32_fast_kernel<64, 64, true, true>), grid, block, 0, hs, pg);
-                       else      GE_LAUNCH((ge::gemm_f32_fast_kernel<64, 64, false, true>), grid, block, 0, hs, pg); }
-            else     { if (edge) GE_LAUNCH((ge::gemm_f32_fast_kernel<64, 64, true>), grid, block, 0, hs, pg);
-                       else      GE_LAUNCH((ge::gemm_f32_fast_kernel<64, 64, false>), grid, block, 0, hs, pg); }
-            g_last_config = raw ? "f32_64x64x16_w4_splitk" : "f32_64x64x16_w4";
+        if (st == GE_ERR_WORKSPACE && least < p.splitK) {
+            // room for `least` slices' partial tiles is enough (the library's buffer, where it cannot grow now): the slices then
+            // come that many at a time, behind the sum of those before them, with the same additions in the same order
+            perPass = least;
+            st = acquire_workspace(partial_bytes(M, N, batch, perPass), nullptr, 0, hs, &ws);
         }
-    } else {
-        auto launch = [&](auto bt, auto elements) {
+        if (st != GE_OK) return st;
+    }
+    const bool edge = (M % bm) || (N % bm) || (K % 16);
+    auto launch_tiles = [&](const GemmParams &pg) {
+        const dim3 grid((unsigned)(tiles * pg.splitK)), block(256);
+        auto by_edge = [&](auto bt, auto rawC) {
+            constexpr int BT = decltype(bt)::value;
+            constexpr bool RAW = decltype(rawC)::value;
+            if (edge) GE_LAUNCH((ge::gemm_f32_fast_kernel<BT, BT, true, RAW>), grid, block, 0, hs, pg);
+            else      GE_LAUNCH((ge::gemm_f32_fast_kernel<BT, BT, false, RAW>), grid, block, 0, hs, pg);
+        };
+        auto any_alignment = [&](auto bt, auto elements) {
             constexpr int BT = decltype(bt)::value;
             constexpr bool E = decltype(elements)::value;
             if (raw) GE_LAUNCH((ge::gemm_f32_ragged_kernel<BT, true, E>), grid, block, 0, hs, pg);
             else     GE_LAUNCH((ge::gemm_f32_ragged_kernel<BT, false, E>), grid, block, 0, hs, pg);
         };
-        if (elementwise) launch(std::integral_constant<int, 64>{}, std::true_type{});
-        else if (big)    launch(std::integral_constant<int, 128>{}, std::false_type{});
-        else             launch(std::integral_constant<int, 64>{}, std::false_type{});
-        g_last_config = elementwise ? (raw ? "f32_elements_64x64x32_splitk" : "f32_elements_64x64x32")
-                        : big ? (raw ? "f32_ragged_128x128x32_splitk" : "f32_ragged_128x128x32")
-                              : (raw ? "f32_ragged_64x64x32_splitk" : "f32_ragged_64x64x32");
+        using Tile64 = std::integral_constant<int, 64>;
+        using Tile128 = std::integral_constant<int, 128>;
+        if (fast) {
+            if (big) { if (raw) by_edge(Tile128{}, std::true_type{}); else by_edge(Tile128{}, std::false_type{}); }
+            else     { if (raw) by_edge(Tile64{}, std::true_type{});  else by_edge(Tile64{}, std::false_type{}); }
+        } else if (elementwise) {
+            any_alignment(Tile64{}, std::true_type{});
+        } else if (big) {
+            any_alignment(Tile128{}, std::false_type{});
+        } else {
+            any_alignment(Tile64{}, std::false_type{});
+        }
+    };
+    if (fast) g_last_config = big ? (raw ? "f32_128x128x16_w4_splitk" : "f32_128x128x16_w4") : (raw ? "f32_64x64x16_w4_splitk" : "f32_64x64x16_w4");
+    else g_last_config = elementwise ? (raw ? "f32_elements_64x64x32_splitk" : "f32_elements_64x64x32")
+                         : big ? (raw ? "f32_ragged_128x128x32_splitk" : "f32_ragged_128x128x32")
+                               : (raw ? "f32_ragged_64x64x32_splitk" : "f32_ragged_64x64x32");
+    if (!raw) {
+        launch_tiles(p);
+        return ge_host::take_launch_error() != hipSuccess ? GE_ERR_LAUNCH : GE_OK;
     }
-    if (ge_host::take_launch_error() != hipSuccess) return GE_ERR_LAUNCH;
-    if (raw && launch_reduce(p, ws, true, hs) != hipSuccess) return GE_ERR_LAUNCH;
+    for (int done = 0; done < p.splitK;) {
+        const int carried = done > 0 ? 1 : 0, now = std::min(perPass - carried, p.splitK - done);
+        const long long skip = (long long)done * p.kPerSlice;
+        GemmParams pg = p, pr = p;
+        pg.A = (const float *)p.A + skip;
+        pg.B = (const float *)p.B + skip * ldb;
+        pg.bytesA -= 4 * skip;
+        pg.bytesB -= 4 * skip * ldb;
+        pg.K = (int)(K - skip);
+        pg.splitK = now;
+        pg.C = (float *)ws + carried * outputs;
+        pg.ldc = N;
+        pg.strideC = (long long)M * N;
+        launch_tiles(pg);
+        if (ge_host::take_launch_error() != hipSuccess) return GE_ERR_LAUNCH;
+        done += now;
+        pr.splitK = carried + now;
+        if (done < p.splitK) {                           // the sum so far, in the first partial tile's place
+            pr.C = (float *)ws;
+            pr.ldc = N;
+            pr.strideC = (long long)M * N;
+            pr.bias = nullptr;
+            pr.alpha = 1.0f;
+            pr.act = GE_ACT_NONE;
+        }
+        if (launch_reduce(pr, ws, true, hs) != hipSuccess) return GE_ERR_LAUNCH;
+    }
     return GE_OK;
 }
 
