@@ -163,12 +163,11 @@ double plan_cost_us(int M, int N, int K, int batch, int tile, int slices)
     return t;
 }
 
-// Multiply-adds below which the guarded kernel keeps a product that the direct-to-LDS kernels do not take.  Not where the two
-// cross: the any-alignment kernel is the shorter one on both sides (us, guarded / any alignment: 130 x 70 x 1500, 13.7 M,
-// 47.3 / 9.3; 513 x 515 x 33, 8.7 M, 7.5 / 5.2; 33 x 33 x 4096, 4.5 M, 27.4 / 8.1; 221 x 155 x 44, 1.5 M, 7.6 / 5.1; 67 x 45 x 33,
-// 0.1 M, 7.0 / 5.1; above, 65 x 129 x 2000, 16.8 M, 42.5 / 9.1).  The line keeps small calls on the kernel that they have been
-// tested on.
-constexpr double kRaggedMinWork = 16.0 * 1024 * 1024;
+// Multiply-adds from which the kernel for operands of any alignment takes what the direct-to-LDS kernels do not (us, guarded / any
+// alignment: 130 x 70 x 1500, 13.7 M, 47.3 / 9.3; 513 x 515 x 33, 8.7 M, 7.5 / 5.2; 33 x 33 x 4096, 4.5 M, 27.4 / 8.1; 221 x 155 x
+// 44, 1.5 M, 7.6 / 5.1).  Below, where it is still the shorter call (67 x 45 x 33, 0.1 M, 7.0 / 5.1), and for K slices that the
+// caller asks for up to kRaggedMinSliced, the guarded kernel keeps the calls that it is tested on.
+constexpr double kRaggedMinWork = 1024.0 * 1024, kRaggedMinSliced = 16.0 * 1024 * 1024;
 
 // The slice count of lowest estimated cost for a tile (1 = none); slices keep at least minSlice of K.
 int best_slices(int M, int N, int K, int batch, int tile, int minSlice, double *cost)
@@ -214,7 +213,7 @@ bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bo
     if (K < 8 || (transA && M < 8) || (!transB && N < 8)) return false;
     // byte offsets of a lane inside a tile panel: 128 rows along k, or 64 rows along M or N
     if ((long long)lda * (transA ? 128 : 256) + 1024 >= (1ll << 31) || (long long)ldb * (transB ? 256 : 128) + 1024 >= (1ll << 31)) return false;
-    return (double)M * N * K * batch >= kRaggedMinWork;
+    return (double)M * N * K * batch > kRaggedMinWork;
 }
 
 ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t plan, int split_k, Plan *out, bool skinny, bool ragged)
@@ -244,7 +243,7 @@ ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t 
         if (plan == GE_PLAN_SPLITK) want = split_k > 0 ? split_k : choose_split(tiles, K, 512);
         else if (plan == GE_PLAN_AUTO) want = choose_split(tiles, K, 512);
         if (plan == GE_PLAN_SPLITK && want < 2) want = 2;
-        if (ragged && force != FORCE_GENERIC) {
+        if (ragged && force != FORCE_GENERIC && (plan != GE_PLAN_SPLITK || (double)M * N * K * batch >= kRaggedMinSliced)) {
             // the same slices on the larger tiles of gemm_ragged.h: 128 x 128 where they make three blocks for every
             // four CUs, else 64 x 64 (64 against 128, us: 1999 x 1537 x 2051, 208 blocks of 128, 45 / 34; 3001 x 3001 x
             // 901, 576 blocks, 47 / 42; 1031 x 2051 x 1024, 153 blocks, 17.1 / 17.3; 1001^3, 64 blocks, 9.4 / 19.5), and where
