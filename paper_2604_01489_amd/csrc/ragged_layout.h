@@ -27,6 +27,32 @@ GE_HD constexpr void ragged_place(int j, int w, int lane, int &r, int &c, int &s
     }
 }
 
+// The place in its slab, 16 bytes each, that a lane fills so that neighbouring lanes hold neighbouring chunks of a row (ragged_place
+// of that place gives the lane's row and chunk); the same for every j.
+template <int BX, bool STRIDED>
+GE_HD constexpr int ragged_slot(int w, int lane)
+{
+    if constexpr (STRIDED) {
+        constexpr int PER_ROW = BX / 8;
+        return (lane & ~(PER_ROW - 1)) | (lds_b_offset<BX>(b_slot_k<BX>(w, lane) & 31, lane & (PER_ROW - 1)) % (BX * 2) / 16);
+    } else {
+        return (lane & ~7) | (a64_slot_chunk(w, lane) & 7);
+    }
+}
+
+// Rows that start at an odd element are read from the element after, at 4-byte addresses, and put together from
+// two neighbouring chunks; what then is missing is the first element of each row.  Row i of those that chunk j of a wave's lanes
+// covers, and where its first element lies in the stage.
+template <int BX, bool STRIDED>
+GE_HD constexpr int ragged_rows() { return STRIDED ? 512 / BX : 8; }
+template <int BX, bool STRIDED>
+GE_HD constexpr void ragged_first(int j, int i, int w, int &r, int &at)
+{
+    int c = 0, slab = 0;
+    ragged_place<BX, STRIDED>(j, w, i * (64 / ragged_rows<BX, STRIDED>()), r, c, slab);
+    at = STRIDED ? (r / 32) * (BX * 64) + lds_b_offset<BX>(r % 32, 0) : lds_a64_offset(r, 0);
+}
+
 // fp32: a 32-k step of a tile BX wide, BX / 32 chunks per lane, is two images of 16 k: 64-byte rows of A (along k), B in
 // rows of BX floats.
 template <int BX, bool STRIDED>
@@ -42,7 +68,8 @@ GE_HD constexpr void ragged_place_f32(int j, int w, int lane, int &r, int &c, in
 // A step that is not the block's last: `left` is the number of the operand's rows (columns if STRIDED) from the tile's
 // first.  Rows beyond are the last one again, chunks beyond the end of a row along M or N the tile's first; a chunk that
 // hangs over such an end reads on into the row after it, which exists: the step is not the last, and the rows (hence the
-// leading dimension) are at least E elements long.
+// leading dimension) are at least E elements long.  One that is read an element further on, as rows at odd elements are,
+// ends inside the next step or the row after it as well.
 template <bool STRIDED, int E>
 GE_HD constexpr unsigned ragged_offset(int r, int c, int ld, int left)
 {
