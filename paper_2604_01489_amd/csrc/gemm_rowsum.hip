@@ -25,7 +25,6 @@ int col_chunk_rows(int N, int K)
 }
 constexpr int kRowWaves = 16;           // waves of a block of the row pass (one staging of v per block)
 constexpr int kBlockRows = 8;           // rows a block of the wide row pass takes, all in flight at once
-constexpr int kBlockCols = kRowWaves * 64 * 8;   // columns its 1024 threads cover in one sweep
 
 // A streamed operand is read once and never again: the non-temporal hint keeps it from displacing
 // anything in the caches, and on this part a read-only stream measured 7.1 TB/s with it against
@@ -105,22 +104,24 @@ rows_dot_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, con
 }
 
 // The same for matrices whose rows can be read in 16-byte pieces (not ANY: C a multiple of 8, aligned) and are at least
-// 512 columns wide: a block of 1024 threads is G groups of 16/G waves, each group takes kBlockRows
-// consecutive rows; a thread owns 8 consecutive columns per sweep of 8192/G columns, holds their v in
+// 384 columns wide: a block of WAVES waves is G groups, each group takes kBlockRows
+// consecutive rows; a thread owns 8 consecutive columns per sweep of 512 WAVES / G columns, holds their v in
 // registers and has one 16-byte load per row in flight, all issued before the first is used.  Many
 // short-lived blocks that each ask for everything up front keep more of the memory system busy than few
 // long-lived waves that walk their own rows: measured on an 8192 x 8192 matrix beyond the
-// memory-side cache, 23 us against 33-37 us for the kernel above.  Per row: a fixed butterfly inside
-// each wave, then the wave sums of its group added in wave order.
+// memory-side cache, 23 us against 33-37 us for the kernel above.  Small blocks, because a CU that holds several is
+// still reading for some while others add up, and because a small call waits for the start of its largest block: with four or eight
+// waves instead of 16 both calls on 16384 x 4096 + 8192 x 4096 take 47.0 us for 56.1, on 2048 x 2048 twice 12.8 for 17.7, 8192 x
+// 8192 twice 57.4 for 58.5.  Starting each block's sweeps at another column changed nothing.  Per row: a sweep's eight products, the
+// sweeps, a fixed butterfly inside each wave, then the wave sums of its group added in wave order.
 // ANY: rows at any address and of any length of at least 8; the chunk at a row's end is pulled back to end there and
-// shifted down, which puts zeros beyond (12096 x 2205 + 2752 x 2205: 50.8 -> 34.3 us for
-// both calls).
-template <int G, bool ANY>
-__global__ void __launch_bounds__(kRowWaves * 64)
+// shifted down, which puts zeros beyond (12096 x 2205 + 2752 x 2205: 26.1 us for both calls, 50.8 by the kernel above).
+template <int WAVES, int G, bool ANY>
+__global__ void __launch_bounds__(WAVES * 64)
 rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, const float *__restrict__ v,
                      float scale, const float *__restrict__ add, float *__restrict__ out)
 {
-    constexpr int WG = kRowWaves / G;               // waves of a group
+    constexpr int WG = WAVES / G;                   // waves of a group
     constexpr int SWEEP = WG * 64 * 8;              // columns a group covers in one sweep
     __shared__ float part[G * kBlockRows][WG];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -159,11 +160,13 @@ rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx
         }
 #pragma unroll
         for (int u = 0; u < kBlockRows; ++u) {
+            float t = 0.0f;                             // a sweep's eight products, then the sweeps
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                acc[u] = __builtin_fmaf(bf16_lo((unsigned)x[u][e]), vv[2 * e], acc[u]);
-                acc[u] = __builtin_fmaf(bf16_hi((unsigned)x[u][e]), vv[2 * e + 1], acc[u]);
+                t = __builtin_fmaf(bf16_lo((unsigned)x[u][e]), vv[2 * e], t);
+                t = __builtin_fmaf(bf16_hi((unsigned)x[u][e]), vv[2 * e + 1], t);
             }
+            acc[u] += t;
         }
     }
 #pragma unroll
@@ -188,8 +191,10 @@ rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx
 // holds only longer chunks: then a block adds up here, in the same pairs, the runs that cols_finish_kernel adds up
 // otherwise, and the sums are the same bit for bit.
 // A thread owns 8 consecutive columns (16 bytes per row; ALIGNED: rows of whole aligned pieces, by non-temporal loads; else at
-// any address), or one column where rows are shorter (WIDE false).  The loads of 8 rows are issued together, ahead of their additions (left to the compiler's unrolling they
-// went out one by one behind a bounds test: 50 us for 8192 x 8192 against 23 us).
+// any address), or one column where rows are shorter (WIDE false).  The loads of 8 rows are issued together, ahead of the additions of the 8
+// before (left to the compiler's unrolling they went out one by one behind a bounds test: 50 us for 8192 x 8192 against 23 us).  What bounds it
+// is the reads in flight: two blocks of four waves on a CU.  With nothing asked for while a wave added, 5312 x 5685 + 8191 x 5685
+// took 56.6 us for both calls, 47.1 now; aligned rows, 2048 x 1024 twice, 16.3 / 14.9.
 template <bool WIDE, bool ALIGNED, int SUBS>
 __global__ void __launch_bounds__(256)
 cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, float *__restrict__ partial, int chunkRows)
@@ -207,17 +212,18 @@ cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx,
         for (int e = 0; e < W; ++e) acc[q][e] = 0.0f;
         const int r0 = blockIdx.y * chunkRows + q * runRows, r1 = min(chunkEnd, r0 + runRows);
         if constexpr (WIDE) {
-            auto trip = [&](int r, auto whole) {          // U rows; not whole: those beyond r1 are the last one again, and not added
-                constexpr bool WHOLE = decltype(whole)::value;
-                ge::i32x4_t x[U];
+            // U rows; not whole: those beyond r1 are the last one again, and not added
+            auto fetch = [&](int r, ge::i32x4_t (&x)[U], auto whole) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const uint16_t *src = X + (long long)(WHOLE || r + u < r1 ? r + u : r1 - 1) * ldx + at;
+                    const uint16_t *src = X + (long long)(decltype(whole)::value || r + u < r1 ? r + u : r1 - 1) * ldx + at;
                     x[u] = ALIGNED ? load_stream16(src) : load_any16(src);
                 }
+            };
+            auto add = [&](int r, const ge::i32x4_t (&x)[U], auto whole) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const bool inside = WHOLE || r + u < r1;
+                    const bool inside = decltype(whole)::value || r + u < r1;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         acc[q][2 * e] += inside ? bf16_lo((unsigned)x[u][e]) : 0.0f;
@@ -225,9 +231,27 @@ cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx,
                     }
                 }
             };
+            constexpr std::true_type whole{};
+            constexpr std::false_type part{};
+            ge::i32x4_t x[2][U];
             int r = r0;
-            for (; r + U <= r1; r += U) trip(r, std::true_type{});
-            if (r < r1) trip(r, std::false_type{});
+            if (r + 2 * U <= r1) {
+                fetch(r, x[0], whole);
+                for (; r + 4 * U <= r1; r += 2 * U) {
+                    fetch(r + U, x[1], whole);
+                    add(r, x[0], whole);
+                    fetch(r + 2 * U, x[0], whole);
+                    add(r + U, x[1], whole);
+                }
+                fetch(r + U, x[1], whole);
+                add(r, x[0], whole);
+                add(r + U, x[1], whole);
+                r += 2 * U;
+            }
+            for (; r < r1; r += U) {
+                fetch(r, x[0], part);
+                add(r, x[0], part);
+            }
         } else {
             for (int r = r0; r < r1; ++r) acc[q][0] += bf16_lo((unsigned)X[(long long)r * ldx + c0]);
         }
@@ -355,18 +379,21 @@ void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float
                      float *out, hipStream_t st)
 {
     if (rows_wide(R, C, X, ldx)) {
-        // the narrowest sweep that covers a row, or the whole block per row
-        auto launch = [&](auto groups) {
-            constexpr int G = decltype(groups)::value;
-            const dim3 blocks((unsigned)ceil_div(R, G * kBlockRows)), threads(kRowWaves * 64);
-            if (rows_aligned(C, X, ldx)) GE_LAUNCH((rows_dot_wide_kernel<G, false>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out);
-            else                         GE_LAUNCH((rows_dot_wide_kernel<G, true>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out);
+        auto launch = [&](auto waves, auto groups) {
+            constexpr int W = decltype(waves)::value, G = decltype(groups)::value;
+            const dim3 blocks((unsigned)ceil_div(R, G * kBlockRows)), threads(W * 64);
+            if (rows_aligned(C, X, ldx)) GE_LAUNCH((rows_dot_wide_kernel<W, G, false>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out);
+            else                         GE_LAUNCH((rows_dot_wide_kernel<W, G, true>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out);
         };
-        if (C <= kBlockCols / 16)     launch(std::integral_constant<int, 16>{});
-        else if (C <= kBlockCols / 8) launch(std::integral_constant<int, 8>{});
-        else if (C <= kBlockCols / 4) launch(std::integral_constant<int, 4>{});
-        else if (C <= kBlockCols / 2) launch(std::integral_constant<int, 2>{});
-        else                          launch(std::integral_constant<int, 1>{});
+        using std::integral_constant;
+        constexpr integral_constant<int, 4> four{};
+        // Eight waves for long rows of which there are too few for two blocks to a CU (both calls, us, four / eight waves: 2048 x 4096
+        // 17.1 / 16.1, 1024 x 8192 18.6 / 17.9, 2048 x 32768 39.4 / 32.8; 4096 x 8192 31.9 / 33.1, 8192 x 16384 57.6 / 71.6, 2048 x
+        // 2048 13.6 / 14.5); else four, the narrowest sweep that covers a row or the whole block per row.
+        if (C > 2048 && R < kBlockRows * 2 * kNumCU) launch(integral_constant<int, 8>{}, integral_constant<int, 1>{});
+        else if (C <= 512)                           launch(four, integral_constant<int, 4>{});
+        else if (C <= 1024)                          launch(four, integral_constant<int, 2>{});
+        else                                         launch(four, integral_constant<int, 1>{});
         return;
     }
     const int stage = (v != nullptr && (size_t)C * sizeof(float) <= 48 * 1024) ? 1 : 0;
