@@ -1,6 +1,6 @@
 """The bf16 kernel for operands of any alignment (csrc/gemm_ragged.h) against the CPU oracles, on sizes around its tiles
 (64 and 128) and its 64-k steps, with rows that start at any 2-byte address, in every operand storage, output type and
-slicing of K.  Small products stay on the guarded kernel, so every case here has at least 2^24 multiply-adds.  The padding
+slicing of K.  Products of up to 2^20 multiply-adds stay on the guarded kernel.  The padding
 of the operands holds huge finite values and the last row ends where the allocation's payload ends (gpu_util)."""
 import os
 import subprocess
