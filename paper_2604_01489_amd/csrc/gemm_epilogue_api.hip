@@ -249,9 +249,14 @@ ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t 
             // 901, 576 blocks, 47 / 42; 1031 x 2051 x 1024, 153 blocks, 17.1 / 17.3; 1001^3, 64 blocks, 9.4 / 19.5), and where
             // such a tile takes the place of two and a half small ones or more, else much of it is padding (two: batches of 16, K = 48,
             // 9 x 4099 8.7 / 12.2, 48 x 2316 8.2 / 10.6; 48 x 30001 x 2049 25.7 / 28.5; 2.25: 300 of 129 x 129 x 33 16.2 / 20.8, x 1025
-            // 63 / 76; 2.5: 40 of 129 x 300 x 65 7.7 / 7.8, x 2049 43 / 37; 3.3: 200 of 67 x 300 x 48 16.7 / 15.5)
+            // 63 / 76; 2.5: 40 of 129 x 300 x 65 7.7 / 7.8, x 2049 43 / 37; 3.3: 200 of 67 x 300 x 48 16.7 / 15.5).  Fewer of the large
+            // ones, but more than two small ones to a CU, and K long enough for what the second round of these costs: the
+            // large ones too (1601^3 31.6 / 27.2, 1501 x 1501 x 2051 35.8 / 30.0, 1405 x 1501 x 1501, 528 small ones, 29.1 / 25.2, 40 of 200 x
+            // 200 x 1001 19.2 / 16.5; two or fewer: 1401^3, 484, 19.1 / 22.7, 901 x 2049 x 1024, 495, 14.2 / 17.2, 25 of 129 x 300 x
+            // 2049, 375, 23.9 / 27.5; short K: 1405 x 1501 x 301 10.2 / 10.3, 1700 x 1700 x 129 8.6 / 9.1, 1601 x 1601 x 33 7.3 / 8.2)
             const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128) * batch;
-            const bool big = t128 * want * 4 >= kNumCU * 3 && 2 * tiles >= 5 * t128;
+            const bool fills = t128 * want * 4 >= kNumCU * 3 || (tiles * want > 2 * kNumCU && K / want > 256);
+            const bool big = fills && 2 * tiles >= 5 * t128;
             pl.tile = big ? TILE_RAGGED_128 : TILE_RAGGED_64;
             pl.bm = pl.bn = big ? 128 : 64;
             pl.bk = 64;

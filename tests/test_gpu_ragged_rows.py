@@ -47,3 +47,10 @@ def test_small_products(oracle, M, N, K):
     for dtype_kw in [dict(), dict(misalign=1)]:
         _, _, _, cfg = run_case(oracle, "bf16", M, N, K, alpha=0.5, act="gelu_tanh", seed=M + N + K, **dtype_kw)
         assert cfg.replace("_splitk", "") == "bf16_ragged_64x64x64", cfg
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,tile", [(1405, 1501, 257, "128x128"), (1405, 1501, 256, "64x64"), (1401, 1401, 300, "64x64"), (1409, 1409, 300, "128x128")])
+def test_large_tiles_for_more_than_two_rounds_of_small_ones(oracle, M, N, K, tile):
+    _, _, _, cfg = run_case(oracle, "bf16", M, N, K, alpha=0.5, act="relu", seed=M + K)
+    assert cfg == f"bf16_ragged_{tile}x64", cfg
