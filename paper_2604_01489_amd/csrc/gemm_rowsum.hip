@@ -360,7 +360,8 @@ bool vec_ok(const void *base, long long ld) { return (((uintptr_t)base) & 15u) =
 bool rows_aligned(int C, const void *X, long long ldx) { return vec_ok(X, ldx) && C % 8 == 0; }
 
 // The wide kernel needs enough columns to give most lanes of a wave a 16-byte piece (its narrowest sweep is 512 columns).
-// Rows that are no whole aligned pieces take it only where it is the shorter call (us, one wave a row / wide):
+// Rows that are no whole aligned pieces take it only where it is the shorter call (us, one wave a row / wide, the latter with blocks of 16
+// waves, before they had four or eight):
 // - at any address, from 2048 columns on (2049 x 4096 rows 14.4 / 7.0, 8191 x 8192 rows 51.9 / 36.9) or 2^23 elements (911 columns:
 //   8192 rows 5.4 / 9.1, 12288 10.5 / 9.2; 505: 16384 5.8 / 9.7, 24576 11.6 / 9.8; 1351: 4096 6.2 / 7.7, 8192 10.6 / 7.9);
 // - at 16-byte addresses and of a length that is no multiple of 8, which the other kernel reads in aligned pieces but for the last
