@@ -85,7 +85,7 @@ def run_symm_case(oracle, M, N, *, uplo="lower", batch=1, transB=False, alpha=0.
 
 @pytest.mark.parametrize("uplo", ["lower", "upper"])
 def test_symm_few_columns_every_element_once(oracle, uplo):
-    """The kernel for few output columns: one super-tile and several, 256 and 512 wide, ragged last
+    """The kernel for few output columns: one super-tile and several, 256 wide (the wider ones: test_gpu_symm_wide.py), ragged last
     super-tile, N of one column to 32, both column widths of the small operand's image."""
     for M, N, kw in [(512, 16, {}), (1024, 8, dict(pad=(8, 0, 3))), (1288, 32, dict(act="gelu_tanh")),
                      (2048, 1, dict(with_bias=False)), (1536, 24, dict(act="relu", clamp=(0.0, 0.4)))]:
