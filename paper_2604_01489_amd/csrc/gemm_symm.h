@@ -31,6 +31,7 @@ struct SymmParams {
     float *W;                  // [terms][batch][M][N] fp32
     int M, N, lda, ldb, transB, upper, batch;
     int tiles;                 // super-tile rows
+    int past;                  // super-tiles wider than 256: their loads go past the memory-side cache
     long long bytesA;          // extent of one batch of A: ((M - 1) lda + M) * 2
 };
 
@@ -142,9 +143,7 @@ gemm_symm_bf16_kernel(const SymmParams p)
     };
 
     // ---- loads of sub-tile (rs, cs) of the super-tile into ring slot st: 8 per wave ------------------------
-    // (the swizzle of a slab's rows repeats every 16 rows: one lane offset, a step of 16 rows per load).  Wide super-tiles are
-    // for triangles the 256 MB memory-side cache does not hold, which go past it (16384 x 16, 268 MB: 63.6 us through, 58.3 past
-    // it; 8192 x 17, 67 MB: 34.8 / 38.1).
+    // (the swizzle of a slab's rows repeats every 16 rows: one lane offset, a step of 16 rows per load)
     const int row0 = slab_row(w, lane), ch0 = slab_chunk(w, lane);
     const unsigned voff0 = (unsigned)row0 * (unsigned)p.lda * 2u + (unsigned)ch0 * 16u, rows16 = 32u * (unsigned)p.lda;
     auto issue_sub = [&](bool live, int rs, int cs, int st) __attribute__((always_inline)) {
@@ -155,8 +154,8 @@ gemm_symm_bf16_kernel(const SymmParams p)
         const unsigned v = c0 + ch0 * 8 >= p.M ? OOB_OFFSET : voff0, dst = ldsBase + (unsigned)(st * STAGE_BYTES + w * 1024);
 #pragma unroll
         for (int q = 0; q < LOADS; ++q) {
-            if constexpr (ST > 256) lds_dma16_nt(res, dst + (unsigned)(q * 4096), v + (unsigned)q * rows16);
-            else                    lds_dma16(res, dst + (unsigned)(q * 4096), v + (unsigned)q * rows16);
+            if (ST > 256 && p.past) lds_dma16_nt(res, dst + (unsigned)(q * 4096), v + (unsigned)q * rows16);
+            else                   lds_dma16(res, dst + (unsigned)(q * 4096), v + (unsigned)q * rows16);
         }
     };
 

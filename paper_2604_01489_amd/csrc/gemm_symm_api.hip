@@ -84,6 +84,12 @@ ge_status_t run_symm(const ge_fused_args_t &a, const SymmPlan &plan, GemmParams 
     // (the offsets of a super-tile's rows of B are 32-bit)
     const bool bVec = !a.transB && a.ldb < (1 << 20) && (a.N % 8) == 0 && (a.ldb % 8) == 0 && !(((uintptr_t)a.B) & 15u);
     sp.bytesA = 2 * (((long long)a.M - 1) * a.lda + a.M);
+    // Wide super-tiles: past the 256 MB memory-side cache what it does not hold.  us, through / past, one triangle again and again and two
+    // in turn: 16384 x 16, 268 MB, 57.3 / 61.3 and 69.2 / 61.6; 18432 x 16, 340 MB, 90.6 / 86.4 and 93.0 / 87.0; 15360 x 16, 236 MB,
+    // 56.7 / 60.3 and 64.7 / 60.5; 11264 x 16, 127 MB, 31.7 / 35.1 and 33.1 / 36.2; 8192 x 32, 67 MB, 35.4 / 38.4.  Rows that are no whole
+    // lines go through it at any size: two sub-tiles share the line between them (16848 x 16, 284 MB, 63.3 / 71.4 and 68.6 / 71.4).
+    const bool lines = a.lda % 64 == 0 && !(((uintptr_t)a.A) & 127u);
+    sp.past = lines && (double)a.batch * a.M * (a.M + 1.0) > 256.0 * 1024 * 1024 ? 1 : 0;
     const dim3 grid((unsigned)((long long)plan.terms * (plan.terms + 1) / 2), (unsigned)a.batch);
     const bool upper = sp.upper != 0;
     if (plan.st == 768)      launch_symm<768, 16>(sp, upper, bVec, grid, hs);
