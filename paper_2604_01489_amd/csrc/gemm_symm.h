@@ -146,11 +146,11 @@ gemm_symm_bf16_kernel(const SymmParams p)
     // (the swizzle of a slab's rows repeats every 16 rows: one lane offset, a step of 16 rows per load)
     const int row0 = slab_row(w, lane), ch0 = slab_chunk(w, lane);
     const unsigned voff0 = (unsigned)row0 * (unsigned)p.lda * 2u + (unsigned)ch0 * 16u, rows16 = 32u * (unsigned)p.lda;
-    auto issue_sub = [&](bool live, int rs, int cs, int st) __attribute__((always_inline)) {
+    auto issue_sub = [&](int rs, int cs, int st) __attribute__((always_inline)) {
         const int r0 = I * ST + rs * SUB, c0 = J * ST + cs * SUB;
-        const long long origin = live ? ((long long)r0 * p.lda + c0) * 2 : 0;
-        // past the end of the walk through an empty resource; rows beyond the matrix are beyond the resource's end
-        const rsrc_words_t res = make_rsrc(gA + origin, live ? records_left(p.bytesA, origin) : 0u);
+        const long long origin = ((long long)r0 * p.lda + c0) * 2;
+        // rows beyond the matrix are beyond the resource's end
+        const rsrc_words_t res = make_rsrc(gA + origin, records_left(p.bytesA, origin));
         const unsigned v = c0 + ch0 * 8 >= p.M ? OOB_OFFSET : voff0, dst = ldsBase + (unsigned)(st * STAGE_BYTES + w * 1024);
 #pragma unroll
         for (int q = 0; q < LOADS; ++q) {
@@ -172,26 +172,21 @@ gemm_symm_bf16_kernel(const SymmParams p)
     // A sub-tile on the diagonal: the other triangle, which may hold anything, is cleared in the image, before the multiply of P1;
     // and the diagonal itself, which belongs to P1, before that of P2.
     auto clear_triangle = [&](unsigned img) __attribute__((always_inline)) {
-        constexpr int AT_ONCE = 4;
-        static_assert(SUB * SUB / 8 % (256 * AT_ONCE) == 0, "the chunks divide over the threads");
-#pragma unroll 1
-        for (int q0 = 0; q0 < SUB * SUB / 8; q0 += 256 * AT_ONCE) {
-            i32x4_t v[AT_ONCE];
 #pragma unroll
-            for (int q = 0; q < AT_ONCE; ++q) {
-                const int id = q0 + q * 256 + (int)threadIdx.x;
-                v[q] = *(const GE_LDS i32x4_t *)(size_t)(img + (unsigned)image_offset(id >> 4, id & 15));
+        for (int q = 0; q < SUB * SUB / 8 / 256; ++q) {
+            const int id = q * 256 + (int)threadIdx.x, r = id >> 4, c = id & 15;
+            if (UPPER ? c < r >> 3 : c > r >> 3) *(GE_LDS i32x4_t *)(size_t)(img + (unsigned)image_offset(r, c)) = i32x4_t{0, 0, 0, 0};
+        }
+        const int r = (int)threadIdx.x;                  // the chunk of its row that the diagonal crosses
+        if (r < SUB) {
+            GE_LDS i32x4_t *const at = (GE_LDS i32x4_t *)(size_t)(img + (unsigned)image_offset(r, r >> 3));
+            i32x4_t v = *at;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int c0 = (r & ~7) + 2 * e, c1 = c0 + 1;
+                v[e] = (int)symm_mask_pair((unsigned)v[e], UPPER ? c0 >= r : c0 <= r, UPPER ? c1 >= r : c1 <= r);
             }
-#pragma unroll
-            for (int q = 0; q < AT_ONCE; ++q) {
-                const int id = q0 + q * 256 + (int)threadIdx.x, r = id >> 4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int c0 = 8 * (id & 15) + 2 * e, c1 = c0 + 1;
-                    v[q][e] = (int)symm_mask_pair((unsigned)v[q][e], UPPER ? c0 >= r : c0 <= r, UPPER ? c1 >= r : c1 <= r);
-                }
-                *(GE_LDS i32x4_t *)(size_t)(img + (unsigned)image_offset(r, id & 15)) = v[q];
-            }
+            *at = v;
         }
         lds_barrier();
     };
@@ -206,12 +201,27 @@ gemm_symm_bf16_kernel(const SymmParams p)
     // On the diagonal of the matrix only the stored triangle's: columns 0 .. u of sub-tile row u, or (upper) u .. nJ - 1.
     auto first_of = [&](int u) { return UPPER && diag ? u : 0; };
     auto last_of = [&](int u) { return !UPPER && diag ? u : nJ - 1; };
+    // Past its end nothing is loaded: a super-tile of 256 is four sub-tiles, and the two empty ones behind them cost as much of the vector
+    // cache's time as these did.  With them, a barrier behind every sub-tile and all of a diagonal sub-tile read and written again for its
+    // other triangle 512 x 16 took 10.3 us, 1464 x 4 10.7, 3472 x 1 12.2; now 9.3, 9.5 and 11.0.
     int pu = 0, pv = 0;                                  // the next sub-tile to load
+    int ahead = 0;                                       // sub-tiles on their way
     auto issue_next = [&](int st) __attribute__((always_inline)) {
-        issue_sub(pu < nI, pu, pv, st);
+        if (pu >= nI) return;
+        issue_sub(pu, pv, st);
+        ++ahead;
         if (pv == last_of(pu)) { ++pu; pv = first_of(pu); }
         else ++pv;
     };
+    // the first sub-tile on its way has landed (the loads complete in order), every wave's part of it
+    auto wait_first = [&] __attribute__((always_inline)) {
+        if (ahead >= STAGES)               asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * LOADS) : "memory");
+        else if (STAGES > 2 && ahead == 3) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * LOADS) : "memory");
+        else if (STAGES > 2 && ahead == 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LOADS) : "memory");
+        else                               asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        --ahead;
+    };
+    static_assert(STAGES == 2 || STAGES == 4, "a wait for each number of sub-tiles on their way");
     bf16x8_t fbJ[NS * KS][NJ];
     auto read_fragments_of_J = [&] __attribute__((always_inline)) {
 #pragma unroll
@@ -225,7 +235,9 @@ gemm_symm_bf16_kernel(const SymmParams p)
         stage_vec(smallI, I * ST);
 #pragma unroll
         for (int t = 0; t < FIRST; ++t) issue_next(t);
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FIRST * LOADS) : "memory");
+        // both blocks of B have landed
+        if (ahead == FIRST) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(FIRST * LOADS) : "memory");
+        else                asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         read_fragments_of_J();
         if constexpr (!OWN_J) {
             lds_barrier();
@@ -233,8 +245,9 @@ gemm_symm_bf16_kernel(const SymmParams p)
         }
     } else if (!p.transB) {
         i32x4_t vJ[PER], vI[PER];
-        // (the wait for the registers is one for whatever else is on its way by then: the other stages' loads follow it)
-        issue_next(0);
+        // (the wait for the registers is one for whatever else is on its way by then: half of the stages' loads follow it)
+#pragma unroll
+        for (int t = 0; t < STAGES / 2; ++t) issue_next(t);
         load_small(J * ST, vJ);
         load_small(I * ST, vI);
         store_small(smallJ, J * ST, vJ);
@@ -245,7 +258,7 @@ gemm_symm_bf16_kernel(const SymmParams p)
         }
         store_small(smallI, I * ST, vI);
 #pragma unroll
-        for (int t = 1; t < STAGES; ++t) issue_next(t);
+        for (int t = STAGES / 2; t < STAGES; ++t) issue_next(t);
         lds_barrier();
         if constexpr (OWN_J) read_fragments_of_J();
     } else {
@@ -288,8 +301,7 @@ gemm_symm_bf16_kernel(const SymmParams p)
 #pragma unroll
         for (int v = 0; v < NS; ++v) {
             if (v < first || v > last) continue;
-            // the sub-tile has landed (the loads complete in order), every wave's part of it
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * LOADS) : "memory");
+            wait_first();
             const unsigned img = ldsBase + (unsigned)(slot * STAGE_BYTES);
             const bool onDiag = diag && u == v;
             if (onDiag) clear_triangle(img);
@@ -318,8 +330,10 @@ gemm_symm_bf16_kernel(const SymmParams p)
                     for (int j = 0; j < NJ; ++j)
                         acc2[v][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fbI[ks][j], fa, acc2[v][i][j], 0, 0, 0);
                 }
-            lds_barrier();                               // every wave is done with the slot
-            issue_next(slot);
+            if (pu < nI) {
+                lds_barrier();                           // every wave is done with the slot
+                issue_next(slot);
+            }
             slot = slot == STAGES - 1 ? 0 : slot + 1;
         }
 #pragma unroll
@@ -353,8 +367,6 @@ gemm_symm_bf16_kernel(const SymmParams p)
     const int col = 4 * (lane >> 4);
     auto term_rows = [&](int rowBlock, int term) { return (char *)(p.W + ((long long)term * p.batch + b) * p.M * p.N + (long long)rowBlock * ST * p.N); };
     auto bytes_of = [&](int rowBlock) { return min(ST, p.M - rowBlock * ST) * p.N * 4; };      // a multiple of 32: M is one of 8
-    // the empty loads past the end of the walk have landed, too
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const bool quads = (p.N & 3) == 0;
     if (quads || p.N < 3) {
         auto store = [&](const f32x4_t (&acc)[NS][2][NJ], int rowBlock, int term) __attribute__((always_inline)) {
