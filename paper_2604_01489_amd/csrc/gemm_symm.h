@@ -68,13 +68,12 @@ gemm_symm_bf16_kernel(const SymmParams p)
     constexpr int SMALL_BYTES = ST * NP * 2;
     constexpr int STAGES = symm_stages(ST), LOADS = SLABS / 4;
     // stages, then B's rows of I and, where the LDS has room, its rows of J.  Else the latter pass, until their fragments are in
-    // registers, through the last stage (BVEC) or the place of the former.
+    // registers, through the last of four stages (BVEC) or the place of the former.
     constexpr bool OWN_J = symm_own_j(ST, NP);
-    static_assert(!BVEC || OWN_J || STAGES == 4, "a stage to spare");
     __shared__ __attribute__((aligned(1024))) char smem[STAGES * STAGE_BYTES + (OWN_J ? 2 : 1) * SMALL_BYTES];
     const unsigned ldsBase = (unsigned)(size_t)(GE_LDS char *)smem;
     const unsigned smallI = ldsBase + STAGES * STAGE_BYTES;
-    const unsigned smallJ = OWN_J ? smallI + SMALL_BYTES : BVEC ? ldsBase + (STAGES - 1) * STAGE_BYTES : smallI;
+    const unsigned smallJ = OWN_J ? smallI + SMALL_BYTES : BVEC && STAGES == 4 ? ldsBase + (STAGES - 1) * STAGE_BYTES : smallI;
 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -229,7 +228,18 @@ gemm_symm_bf16_kernel(const SymmParams p)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) fbJ[k][j] = small_frag(smallJ, 32 * k, j);
     };
-    if constexpr (BVEC) {
+    if constexpr (BVEC && !OWN_J && STAGES == 2) {
+        // (through registers at any address, as it was without this: 520 x 24 11.5 us, 6656 x 24 21.3, 12288 x 32 62.8; so 10.4, 19.7 and 60.5)
+        stage_vec(smallJ, J * ST);
+        issue_next(0);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LOADS) : "memory");
+        read_fragments_of_J();
+        lds_barrier();
+        stage_vec(smallI, I * ST);
+        issue_next(1);
+        if (ahead == 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LOADS) : "memory");
+        else            asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    } else if constexpr (BVEC) {
         constexpr int FIRST = OWN_J ? STAGES : STAGES - 1;
         stage_vec(smallJ, J * ST);
         stage_vec(smallI, I * ST);

@@ -53,10 +53,8 @@ void launch_symm(const ge::SymmParams &sp, bool upper, bool bVec, dim3 grid, hip
         if (upper) GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, true, BVEC>), grid, dim3(256), 0, st, sp);
         else       GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, false, BVEC>), grid, dim3(256), 0, st, sp);
     };
-    if constexpr (ge::symm_stages(ST) == 4 || ge::symm_own_j(ST, NP)) {
-        if (bVec) return launch(std::true_type{});
-    }
-    launch(std::false_type{});
+    if (bVec) launch(std::true_type{});
+    else      launch(std::false_type{});
 }
 
 template <int ST>
