@@ -131,13 +131,26 @@ gemm_symm_bf16_kernel(const SymmParams p)
             *(GE_LDS i32x4_t *)(size_t)(dst + (unsigned)small_offset(NP, kk, n)) = v;
         }
     };
+    // Stored N x K: 8 k of one column by a 16-byte load at whatever address (M is a multiple of 8, so none hangs over the end), all of a
+    // thread's on their way before the first is used; neighbouring lanes on neighbouring columns, which is one row of the image.
+    // (Element by element, 16 columns' bank conflicts a store and a round trip for every eight: 520 x 32 15.9 us, 8192 x 16 35.3, 16384 x 32
+    // 130; so 12.5, 26.1 and 106.)
     auto stage_transposed = [&](unsigned dst, int k0) __attribute__((always_inline)) {
-#pragma unroll 8
-        for (int q = threadIdx.x; q < ST * NP; q += 256) {
-            const int kk = q % ST, n = q / ST;             // neighbouring threads on neighbouring k
-            const bool inside = k0 + kk < p.M && n < p.N;
-            const unsigned short v = gB[inside ? (long long)n * p.ldb + (k0 + kk) : 0ll];
-            *(GE_LDS unsigned short *)(size_t)(dst + (unsigned)small_offset(NP, kk, n)) = inside ? v : (unsigned short)0;
+        i32x4_t v[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int id = q * 256 + (int)threadIdx.x, n = id % NP, k = k0 + id / NP * 8;
+            v[q] = ((const i32x4_any_t *)(gB + (long long)min(n, p.N - 1) * p.ldb + min(k, p.M - 8)))->v;
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int id = q * 256 + (int)threadIdx.x, n = id % NP, kk = id / NP * 8;
+            const bool inside = n < p.N && k0 + kk < p.M;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const unsigned w = inside ? (unsigned)v[q][e / 2] : 0u;
+                *(GE_LDS unsigned short *)(size_t)(dst + (unsigned)small_offset(NP, kk + e, n)) = (unsigned short)(e & 1 ? w >> 16 : w);
+            }
         }
     };
 
@@ -273,13 +286,18 @@ gemm_symm_bf16_kernel(const SymmParams p)
         if constexpr (OWN_J) read_fragments_of_J();
     } else {
 #pragma unroll
-        for (int t = 0; t < STAGES; ++t) issue_next(t);
+        for (int t = 0; t < STAGES / 2; ++t) issue_next(t);
         stage_transposed(smallJ, J * ST);
-        lds_barrier();
-        read_fragments_of_J();
-        if constexpr (!OWN_J) lds_barrier();
+        if constexpr (!OWN_J) {
+            lds_barrier();
+            read_fragments_of_J();
+            lds_barrier();
+        }
         stage_transposed(smallI, I * ST);
+#pragma unroll
+        for (int t = STAGES / 2; t < STAGES; ++t) issue_next(t);
         lds_barrier();
+        if constexpr (OWN_J) read_fragments_of_J();
     }
 
     f32x4_t acc1[NS][2][NJ], acc2[NS][2][NJ];    // P1 of sub-tile row s, P2 of sub-tile column s
