@@ -50,14 +50,17 @@ constexpr int symm_stages(int st) { return st == 256 ? 2 : 4; }
 // whether both blocks of B have a place of their own beside the stages
 constexpr bool symm_own_j(int st, int np) { return symm_stages(st) * ge_symm::STAGE_BYTES + 2 * st * np * 2 <= (st == 256 ? 80 : 160) * 1024; }
 
+// Whether a super-tile's terms leave through their image in LDS (see there), by its side and the columns.
+constexpr bool symm_image(int st, int n) { return n % 4 != 0 && n > (st == 512 ? 8 : 2); }
+
 // ST: side of a super-tile (a multiple of 128: 256, 512 or 768); NP: columns of the small operand's image (16 or 32);
 // UPPER: the upper triangle is the stored one; BVEC: B can be read in aligned 16-byte pieces along n (N a multiple of 8, aligned,
-// not transposed).
+// not transposed); IMAGE: symm_image of the call.
 //
 // Bound by HBM.  Room for the ring of sub-tiles: the fragments of B's rows of J, which every sub-tile row wants again, stay in
 // registers.  The walk is a loop over the rows of sub-tiles (unrolled over all of them a workgroup ran through 95 KB of code
 // once).  16384 x 16: 68.4 -> 59 us, launch and second pass included.
-template <int ST, int NP, bool UPPER, bool BVEC>
+template <int ST, int NP, bool UPPER, bool BVEC, bool IMAGE>
 __global__ void __launch_bounds__(256, ST == 256 ? 2 : 1)
 gemm_symm_bf16_kernel(const SymmParams p)
 {
@@ -389,14 +392,16 @@ gemm_symm_bf16_kernel(const SymmParams p)
     // 16 x 16 block (the small operand's fragments are the first operand of the matrix instruction): column counts that are
     // multiples of 4 and those below 3 are few store instructions, straight from the registers; with others, up to 128 a wave with
     // most of their lanes idle, the run leaves through an image of it in LDS, 1 KB a wave instruction (straight / image: 8192 x
-    // 17 38.1 / 31.2 us, 16384 x 16 58.8 / 60.1, x 32 98.5 / 104.5, 12288 x 4 38.5 / 39.0).  (P1 row by row inside the walk, for half the
+    // 17 34.3 / 30.4 us, 16384 x 16 58.8 / 60.1, x 32 98.3 / 113, 12288 x 4 38.5 / 39.0).  Super-tiles of 512, one a CU: straight up to 8 columns
+    // (9736 x 5 28.2 / 29.2, x 7 28.7 / 29.3; x 9 30.2 / 30.1, 10800 x 13 33.5 / 32.5), and a kernel of its own for either way: with the image's code
+    // in it the straight stores took longer, too (9736 x 1 26.9 / 27.7).  (P1 row by row inside the walk, for half the
     // stores to be over by its end: 16384 x 16 58.3 -> 61.8 us, the waits for the loads then wait for the stores.)
     const unsigned pitch = (unsigned)p.N * 4u;
     const int col = 4 * (lane >> 4);
     auto term_rows = [&](int rowBlock, int term) { return (char *)(p.W + ((long long)term * p.batch + b) * p.M * p.N + (long long)rowBlock * ST * p.N); };
     auto bytes_of = [&](int rowBlock) { return min(ST, p.M - rowBlock * ST) * p.N * 4; };      // a multiple of 32: M is one of 8
     const bool quads = (p.N & 3) == 0;
-    if (quads || p.N < 3) {
+    if constexpr (!IMAGE) {
         auto store = [&](const f32x4_t (&acc)[NS][2][NJ], int rowBlock, int term) __attribute__((always_inline)) {
             // rows beyond the matrix are beyond the resource's end, columns beyond N out of any range
             const buffer_t rows = __builtin_amdgcn_make_buffer_rsrc(term_rows(rowBlock, term), 0, bytes_of(rowBlock), 0x00020000);
@@ -411,7 +416,7 @@ gemm_symm_bf16_kernel(const SymmParams p)
                         for (int j = 0; j < NJ; ++j) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[s][i][j]), rows, offset(s, i, 16 * j), 0, 0);
             } else {
 #pragma unroll
-                for (int r = 0; r < 2; ++r) {
+                for (int r = 0; r < 4; ++r) {
                     if (r >= p.N) break;
 #pragma unroll
                     for (int s = 0; s < NS; ++s)
@@ -425,8 +430,8 @@ gemm_symm_bf16_kernel(const SymmParams p)
         return;
     }
     lds_barrier();                                       // every wave is done with the stages
-    constexpr int IMAGE = ST * NP * 4;
-    static_assert(2 * IMAGE <= STAGES * STAGE_BYTES + SMALL_BYTES, "both terms' images fit");
+    constexpr int IMAGE_BYTES = ST * NP * 4;
+    static_assert(2 * IMAGE_BYTES <= STAGES * STAGE_BYTES + SMALL_BYTES, "both terms' images fit");
     auto put = [&](unsigned image, const f32x4_t (&acc)[NS][2][NJ]) __attribute__((always_inline)) {
         const unsigned at = image + (unsigned)(32 * w + (lane & 15)) * pitch + 4u * (unsigned)col;
 #pragma unroll
@@ -442,7 +447,7 @@ gemm_symm_bf16_kernel(const SymmParams p)
                 }
     };
     put(ldsBase, acc1);
-    if (!diag) put(ldsBase + IMAGE, acc2);
+    if (!diag) put(ldsBase + IMAGE_BYTES, acc2);
     lds_barrier();
     auto send = [&](unsigned image, int rowBlock, int term) {
         char *dst = term_rows(rowBlock, term);
@@ -451,7 +456,7 @@ gemm_symm_bf16_kernel(const SymmParams p)
         for (int at = (int)threadIdx.x * 16; at < bytes; at += 4096) *(i32x4_t *)(dst + at) = *(const GE_LDS i32x4_t *)(size_t)(image + (unsigned)at);
     };
     send(ldsBase, I, J);
-    if (!diag) send(ldsBase + IMAGE, J, I);
+    if (!diag) send(ldsBase + IMAGE_BYTES, J, I);
 }
 
 }  // namespace ge

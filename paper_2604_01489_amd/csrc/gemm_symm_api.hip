@@ -48,13 +48,14 @@ namespace {
 template <int ST, int NP>
 void launch_symm(const ge::SymmParams &sp, bool upper, bool bVec, dim3 grid, hipStream_t st)
 {
-    auto launch = [&](auto vecC) {
-        constexpr bool BVEC = decltype(vecC)::value;
-        if (upper) GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, true, BVEC>), grid, dim3(256), 0, st, sp);
-        else       GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, false, BVEC>), grid, dim3(256), 0, st, sp);
+    auto launch = [&](auto vecC, auto imageC) {
+        constexpr bool BVEC = decltype(vecC)::value, IMAGE = decltype(imageC)::value;
+        if (upper) GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, true, BVEC, IMAGE>), grid, dim3(256), 0, st, sp);
+        else       GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, false, BVEC, IMAGE>), grid, dim3(256), 0, st, sp);
     };
-    if (bVec) launch(std::true_type{});
-    else      launch(std::false_type{});
+    if (bVec)                          launch(std::true_type{}, std::false_type{});
+    else if (ge::symm_image(ST, sp.N)) launch(std::false_type{}, std::true_type{});
+    else                              launch(std::false_type{}, std::false_type{});
 }
 
 template <int ST>
