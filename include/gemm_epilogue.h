@@ -116,7 +116,10 @@ ge_status_t gemm_epilogue_bf16(int M, int N, int K,
  * would leave more than half of the CUs idle and whose K is long is sliced over K and summed in slice
  * order (bitwise repeatable); this call has no workspace argument, so its partial sums always go to
  * the library's buffer of the stream (see "Partial results" above: inside a stream capture such a
- * call needs one earlier call of the same size on that stream, else GE_ERR_WORKSPACE). */
+ * call needs one earlier call of the same size on that stream, else GE_ERR_WORKSPACE.  A buffer that
+ * an earlier call of another size left, with room for the fewest slices that the product is to have, is
+ * taken as well: the slices are then recorded a few at a time, two launches each time, which gives the
+ * same bits and takes longer). */
 ge_status_t gemm_epilogue_f32(int M, int N, int K,
                               const float *A, int lda,
                               const float *B, int ldb,

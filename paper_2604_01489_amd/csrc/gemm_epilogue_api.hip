@@ -121,7 +121,7 @@ void slice_k(int K, int bk, int want, int *splitK, int *kPerSlice)
 // 1.2 us (element by element, where a step takes several times as long, this does not count: 705 x 3 x 6400 22.6 with it, 20.9 without); the
 // second pass is a launch and the partial tiles written and read.  What the count decides is how full the last round of blocks on the CUs
 // is.  us, least / chosen: 1023 x 771 x 2049, 208 tiles, 4 slices 47.2 / 6 42.4 (5: 46.8, 7: 45.7); 320 x 320 x 4095, 7 19.2 / 10 16.4 (12:
-// 20.6); 513 x 515 x 4095, 5 36.0 / 6 32.5; 256 x 256 x 1024, 2 15.3 / 8 9.6; 72 x 1280 x 1600, 3 16.9 / 6 12.0.  Where the least count already
+// 20.6); 513 x 515 x 4095, 5 36.0 / 6 32.5; 256 x 256 x 1024, 2 15.3 / 16 9.1 (8: 9.6); 72 x 1280 x 1600, 3 16.9 / 6 12.0.  Where the least count already
 // is one round of the CUs, twice as many are no shorter: 80 x 966 x 4120, 8 19.4 (15: 20.5); 496 x 66 x 8368, 16 19.5 (30: 20.6); 2 of 460 x
 // 40 x 8600, 16 18.9 (30: 19.9).  Slices keep 64 of K.
 int f32_slices(int tile, long long tiles, long long outputs, int K, int least, bool elementwise)
@@ -717,12 +717,13 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
     p.sliceStride = outputs;
     if (raw) {
         st = acquire_workspace(partial_bytes(M, N, batch, p.splitK), nullptr, 0, hs, &ws);
-        if (st == GE_ERR_WORKSPACE && least < p.splitK) {
-            // room for `least` slices' partial tiles is enough (the library's buffer, where it cannot grow now): the slices then
-            // come that many at a time, behind the sum of those before them, with the same additions in the same order
-            perPass = least;
-            st = acquire_workspace(partial_bytes(M, N, batch, perPass), nullptr, 0, hs, &ws);
-        }
+        // Room for fewer slices' partial tiles is enough, down to the least count (the library's buffer, where it cannot grow now: in a
+        // capture): the slices then come as many at a time as it holds, behind the sum of those before them, with the same additions in the
+        // same order, two launches a pass (us a replay: 256 x 256 x 1024, 16 slices, 9.1 at once, room for 15 14.5, 8 19.9, 4 32, the least, 2, 87;
+        // 1023 x 771 x 2049, 6 slices, 46.6, 5 63.6, 4 65.8).
+        int atLeast, perLeast;
+        slice_k(K, 16, least, &atLeast, &perLeast);
+        while (st == GE_ERR_WORKSPACE && perPass > atLeast) st = acquire_workspace(partial_bytes(M, N, batch, --perPass), nullptr, 0, hs, &ws);
         if (st != GE_OK) return st;
     }
     const bool edge = (M % bm) || (N % bm) || (K % 16);
@@ -753,10 +754,13 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
             any_alignment(Tile64{}, std::false_type{});
         }
     };
-    if (fast) g_last_config = big ? (raw ? "f32_128x128x16_w4_splitk" : "f32_128x128x16_w4") : (raw ? "f32_64x64x16_w4_splitk" : "f32_64x64x16_w4");
-    else g_last_config = elementwise ? (raw ? "f32_elements_64x64x32_splitk" : "f32_elements_64x64x32")
-                         : big ? (raw ? "f32_ragged_128x128x32_splitk" : "f32_ragged_128x128x32")
-                               : (raw ? "f32_ragged_64x64x32_splitk" : "f32_ragged_64x64x32");
+    // one pass over all of K, its slices in one pass, or in several
+    static const char *const names[5][3] = {{"f32_64x64x16_w4", "f32_64x64x16_w4_splitk", "f32_64x64x16_w4_splitk_passes"},
+                                            {"f32_128x128x16_w4", "f32_128x128x16_w4_splitk", "f32_128x128x16_w4_splitk_passes"},
+                                            {"f32_ragged_64x64x32", "f32_ragged_64x64x32_splitk", "f32_ragged_64x64x32_splitk_passes"},
+                                            {"f32_ragged_128x128x32", "f32_ragged_128x128x32_splitk", "f32_ragged_128x128x32_splitk_passes"},
+                                            {"f32_elements_64x64x32", "f32_elements_64x64x32_splitk", "f32_elements_64x64x32_splitk_passes"}};
+    g_last_config = names[elementwise ? 4 : (fast ? 0 : 2) + (big ? 1 : 0)][!raw ? 0 : perPass == p.splitK ? 1 : 2];
     if (!raw) {
         launch_tiles(p);
         return ge_host::take_launch_error() != hipSuccess ? GE_ERR_LAUNCH : GE_OK;

@@ -66,3 +66,42 @@ def test_same_bits_from_a_buffer_with_room_for_fewer_slices(M, N, K, aligned):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, eager)
+
+
+@pytest.mark.parametrize("M,N,K,room", [
+    (256, 256, 1024, 2),            # two slices, then one at a time behind the carried sum
+    (256, 256, 1024, 5),            # five, then four at a time, then what is left
+    (256, 256, 1024, 15),           # all but one
+    (255, 255, 20000, 38),         # 39 slices asked for at least, 38 after rounding
+    (67, 45, 2051, 4),
+])
+def test_slices_a_few_at_a_time(M, N, K, room):
+    """A capture on a stream whose buffer has room for `room` partial tiles and no more: taken down to the least count, in as many passes
+    as that makes, with the bits of the eager call."""
+    import torch
+    binding.release_workspace()           # (pooled streams come with buffers of earlier tests)
+    A, B, bias, (dA, dB, dbias) = _operands(M, N, K, 1, 5)
+    eager, out = torch.empty(M, N, device="cuda:0"), torch.empty(M, N, device="cuda:0")
+    binding.gemm_epilogue_f32(M, N, K, dA, K, dB, N, dbias, 0.5, "gelu_tanh", eager, N)
+    torch.cuda.synchronize()
+    whole = binding.last_config()
+    side = torch.cuda.Stream()
+    H = torch.zeros(256, 64 * room, dtype=torch.bfloat16, device="cuda:0")
+    W = torch.zeros(64 * room, 256, dtype=torch.bfloat16, device="cuda:0")
+    C2 = torch.empty(M, N, device="cuda:0")
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        binding.gemm_epilogue_bf16_ex(M, N, 64 * room, H, 64 * room, W, 256, None, 1.0, "none", C2, N, plan="splitk", split_k=room, stream=side)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            binding.gemm_epilogue_f32(M, N, K, dA, K, dB, N, dbias, 0.5, "gelu_tanh", out, N, stream=side)
+            captured = binding.last_config()
+    assert whole.endswith("_splitk") and captured == whole + "_passes", (whole, captured)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        out.fill_(-1.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
