@@ -80,8 +80,9 @@ int opt_conv_halo();
 int choose_split(long long tiles, int K, int minSlice);
 void slice_k(int K, int bk, int want, int *splitK, int *kPerSlice);
 // Whether the kernel for operands of any alignment (gemm_ragged.h) takes a product the direct-to-LDS kernels do not:
-// rows of 8 elements or more, panels (and row blocks of C) within 31-bit byte offsets, and enough work.
-bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bool transB, int ldc);
+// rows of 8 elements or more, panels (and row blocks of C) within 31-bit byte offsets, and enough work.  plain: the plain
+// operator, whose guarded kernel is the shorter one on slivers.
+bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bool transB, int ldc, bool plain = false);
 // skinny: the caller can launch the tall-skinny kernel (the plain operator only), so the plan may name it; ragged:
 // likewise the kernel for operands of any alignment, where `fast` is not given
 ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t plan, int split_k, Plan *out,

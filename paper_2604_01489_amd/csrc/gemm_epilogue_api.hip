@@ -209,7 +209,7 @@ bool small_tile_pays(int M, int N, int K, int batch, double otherCost)
 // 5.1 / 4.8; above the line 1024 x 1024 x 1024 11.1 / 8.9).
 constexpr int kSmallTileMinK = 384;
 
-bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bool transB, int ldc)
+bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bool transB, int ldc, bool plain)
 {
     if (ldc >= ge::EDGE_LDC_MAX) return false;
     if (opt_force_config() == FORCE_GENERIC) return false;
@@ -217,6 +217,12 @@ bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bo
     if (K < 8 || (transA && M < 8) || (!transB && N < 8)) return false;
     // byte offsets of a lane inside a tile panel: 128 rows along k, or 64 rows along M or N
     if ((long long)lda * (transA ? 128 : 256) + 1024 >= (1ll << 31) || (long long)ldb * (transB ? 256 : 128) + 1024 >= (1ll << 31)) return false;
+    // Slivers of the plain operator, of whose 64 x 64 tiles there are four or more to a CU with one output in twelve or fewer inside, and one 32-k
+    // step: the guarded kernel reads no more than is there.  us, guarded / any alignment: 2 x 185 x 9, 3794 of them, 28.2 / 34.0; 6 x 10 x
+    // 9, 3568, 10.7 / 12.4; 1 x 567 x 16, 227, 7.5 / 8.2; the other side: 18 x 37 x 12, 1273, 7.3 / 6.9; 2 x 55 x 14, 741, 4.9 / 4.8; with
+    // the widened operator's chain 1 x 237 x 19, 1562, 31.4 / 19.9.
+    const double tiles = (double)ceil_div(M, 64) * ceil_div(N, 64) * batch;
+    if (plain && K <= 32 && tiles >= 4.0 * kNumCU && 12.0 * M * N * batch <= 4096.0 * tiles) return false;
     return (double)M * N * K * batch > kRaggedMinWork;
 }
 
@@ -491,7 +497,7 @@ ge_status_t run_bf16(int M, int N, int K, const uint16_t *A, int lda, const uint
     if (st != GE_OK) return st;
     Plan pl;
     st = make_plan_bf16_for(M, N, K, batch, fast_path_ok(N, K, A, lda, B, ldb), plan, split_k, ldc, true, &pl, skinny_ld_ok(ldb),
-                            ragged_ok(M, N, K, batch, lda, false, ldb, false, ldc));
+                            ragged_ok(M, N, K, batch, lda, false, ldb, false, ldc, true));
     if (st != GE_OK) return st;
 
     GemmParams p = base_params(M, N, K, A, lda, B, ldb, bias, alpha, (int)act, C, ldc, batch);
@@ -637,7 +643,7 @@ ge_status_t gemm_epilogue_bf16_static(int M, int N, int K, const uint16_t *A, in
     if (st != GE_OK) return st;
     Plan pl;
     st = make_plan_bf16_for(M, N, K, batch, fast_path_ok(N, K, A, lda, B, ldb), plan, split_k, ldc, true, &pl, skinny_ld_ok(ldb),
-                            ragged_ok(M, N, K, batch, lda, false, ldb, false, ldc));
+                            ragged_ok(M, N, K, batch, lda, false, ldb, false, ldc, true));
     if (st != GE_OK) return st;
     void *ws = nullptr;
     if (pl.splitK > 1) {

@@ -229,10 +229,16 @@ gemm_bf16_ragged_kernel(const GemmParams p)
     // memory in every step: 1999 x 1537 x 2051 on 208 tiles of 128 x 128 took 39 us.)
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, 1>;
-    if (nk > 0) {
+    if (nk == 1) {                            // nothing to ask for ahead: a short K would read its one step three times over
+        load(0, S0{});
+        store(S0{}, true);
+        barrier();
+        multiply(0);
+        barrier();
+    } else if (nk > 1) {
         load(0, S0{});
         load(1, S1{});
-        store(S0{}, nk == 1);
+        store(S0{}, false);
         load(2, S0{});
         barrier();
         int t = 0;

@@ -54,3 +54,27 @@ def test_small_products(oracle, M, N, K):
 def test_large_tiles_for_more_than_two_rounds_of_small_ones(oracle, M, N, K, tile):
     _, _, _, cfg = run_case(oracle, "bf16", M, N, K, alpha=0.5, act="relu", seed=M + K)
     assert cfg == f"bf16_ragged_{tile}x64", cfg
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("transA,transB", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("K", [8, 9, 31, 33, 63, 64])
+def test_one_step(oracle, transA, transB, K):
+    """K of one step: read once, pulled back at its end, on both tiles and from odd elements."""
+    for M, N, tile, kw in [(257, 1031, "64x64", dict(batch=3)), (259, 1024, "64x64", dict(misalign=1, batch=3)), (2056, 2189, "128x128", dict(misalign=1)),
+                           (2056, 2184, "128x128", dict(pad=(1, 2, 0, 0)))]:
+        for out in ("f32", "bf16"):
+            _, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=transB, act="relu", out=out, plan="direct", seed=M + K, **kw)
+            assert f"ragged_{tile}x64" in cfg, cfg
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,batch,kernel", [
+    (5, 67, 31, 512, "bf16_generic_64x64x32"),               # 1024 tiles, hardly any of them inside
+    (5, 67, 33, 512, "bf16_ragged_64x64x64"),                # more than one of the guarded kernel's steps
+    (5, 67, 31, 511, "bf16_ragged_64x64x64"),                # fewer tiles
+    (11, 63, 31, 1024, "bf16_ragged_64x64x64"),              # more than one output in twelve inside
+])
+def test_slivers(oracle, M, N, K, batch, kernel):
+    _, _, _, cfg = run_case(oracle, "bf16", M, N, K, batch=batch, alpha=0.5, act="relu", seed=M + K)
+    assert cfg == kernel, cfg
