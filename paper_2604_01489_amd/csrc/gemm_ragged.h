@@ -103,8 +103,9 @@ typedef unsigned short __attribute__((may_alias)) u16_alias_t;
 
 // A stored M x K or (TA) K x M, B stored K x N or (TB) N x K.  MODE: 0 fp32 partial sums of one K slice, 1 the run-time
 // consumer chain with fp32 output, 2 with bf16 output.  Four waves (NW) in a 2 x 2 or eight in
-// a 2 x 4 arrangement on a BT x BT tile.
-template <int BT, int NW, bool TA, bool TB, int MODE>
+// a 2 x 4 arrangement on a BT x BT tile.  ONE: a block's K is one step at most (a kernel of its own: as a branch of the other
+// it took registers from that, and eight waves spilled).
+template <int BT, int NW, bool TA, bool TB, int MODE, bool ONE>
 __global__ void __launch_bounds__(NW * 64, NW / 2)
 gemm_bf16_ragged_kernel(const GemmParams p)
 {
@@ -229,16 +230,18 @@ gemm_bf16_ragged_kernel(const GemmParams p)
     // memory in every step: 1999 x 1537 x 2051 on 208 tiles of 128 x 128 took 39 us.)
     using S0 = std::integral_constant<int, 0>;
     using S1 = std::integral_constant<int, 1>;
-    if (nk == 1) {                            // nothing to ask for ahead: a short K would read its one step three times over
-        load(0, S0{});
-        store(S0{}, true);
-        barrier();
-        multiply(0);
-        barrier();
-    } else if (nk > 1) {
+    if constexpr (ONE) {                      // nothing to ask for ahead: below, a short K reads its one step three times over
+        if (nk > 0) {
+            load(0, S0{});
+            store(S0{}, true);
+            barrier();
+            multiply(0);
+            barrier();
+        }
+    } else if (nk > 0) {
         load(0, S0{});
         load(1, S1{});
-        store(S0{}, false);
+        store(S0{}, nk == 1);
         load(2, S0{});
         barrier();
         int t = 0;

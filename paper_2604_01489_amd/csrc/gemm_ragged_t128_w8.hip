@@ -3,6 +3,6 @@
 
 namespace ge_host {
 
-void launch_ragged_128_w8(const ge::GemmParams &p, bool raw, dim3 grid, hipStream_t st) { launch_ragged_tile<128, 8>(p, raw, grid, st); }
+void launch_ragged_128_w8(const ge::GemmParams &p, bool raw, dim3 grid, hipStream_t st) { launch_ragged_tile<128, 8, false>(p, raw, grid, st); }
 
 }  // namespace ge_host

@@ -3,6 +3,10 @@
 
 namespace ge_host {
 
-void launch_ragged_64(const ge::GemmParams &p, bool raw, dim3 grid, hipStream_t st) { launch_ragged_tile<64, 4>(p, raw, grid, st); }
+void launch_ragged_64(const ge::GemmParams &p, bool raw, dim3 grid, hipStream_t st)
+{
+    if (p.kPerSlice <= 64) launch_ragged_tile<64, 4, true>(p, raw, grid, st);
+    else                   launch_ragged_tile<64, 4, false>(p, raw, grid, st);
+}
 
 }  // namespace ge_host
