@@ -88,12 +88,13 @@ rows_dot_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, con
                     for (int e = 0; e < 8; ++e) acc += f[e];
                 }
             }
-            for (int c = c8 * 8 + lane; c < C; c += 64) {
+            // (unsigned: 64 columns on from the last of nearly 2^31 is past the largest int)
+            for (unsigned c = c8 * 8 + lane; c < (unsigned)C; c += 64) {
                 const float f = bf16_lo((unsigned)row[c]);
                 acc = vv != nullptr ? __builtin_fmaf(f, vv[c], acc) : acc + f;
             }
         } else {
-            for (int c = lane; c < C; c += 64) {
+            for (unsigned c = lane; c < (unsigned)C; c += 64) {
                 const float f = bf16_lo((unsigned)row[c]);
                 acc = vv != nullptr ? __builtin_fmaf(f, vv[c], acc) : acc + f;
             }

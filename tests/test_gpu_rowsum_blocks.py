@@ -56,3 +56,21 @@ def test_long_chunks():
     """Chunks of 64, 32 and 16 rows, the last one of any length."""
     for N, K in [(8192 + 5, 8192), (4096 + 33, 4099), (2048 + 11, 2048), (777, 1024)]:
         _run(64, N, K, True)
+
+
+def test_row_of_nearly_2_31_columns():
+    """The kernel of one wave a row at the end of its longest aligned row: the columns behind the last whole piece, and none in front of
+    the row."""
+    import torch
+    N, ld = 2 ** 31 - 9, 2 ** 31 - 8
+    B = torch.zeros(ld + 128, dtype=torch.bfloat16, device="cuda:0")
+    B[:128] = float("nan")                                # in front of the row
+    row = B[128:]
+    row[N - 80:N] = 1.0
+    row[N:] = float("nan")
+    row[0] = 2.0
+    params = torch.full((2,), float("nan"), device="cuda:0")
+    binding.gemm_rowsum_params_bf16(N, 1, row, ld, False, None, params)
+    torch.cuda.synchronize()
+    assert binding.last_config() == "rowsum_params_rows"
+    assert params.tolist() == [82.0, 0.0]
