@@ -15,7 +15,7 @@
 // -> 7.1e6, and two waves on each SIMD that cover each other's waits: 33.8 -> 31.5 us (aligned rows, 1999 x 1540 x 2052, where
 // only the waves tell: 27.9 -> 27.5); 1999 x 1537 x 4099 58.6 -> 53.0.  Four waves that move rows into place gain nothing (34.0 -> 36),
 // nor does the 64 x 64 tile (1001^3 9.8 -> 11.1): a wave alone on its SIMD pays for the moves what the look-ups give.
-// The matrix pipes are busy for 0.25 of the cycles now, the LDS for 0.34.  The line between the two numbers of waves: gemm_ragged_t128.hip.
+// The matrix pipes are busy for 0.25 of the cycles now, the LDS for 0.34.  The line between the two numbers of waves: ragged_layout.h.
 #pragma once
 #include <type_traits>
 

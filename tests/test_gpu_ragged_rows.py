@@ -1,5 +1,6 @@
 """bf16 operands whose rows start at odd elements: each row is put together from 4-byte addresses (csrc/gemm_ragged.h).  Rows all
-odd, every other one odd, one operand only; and the small products from 2^20 multiply-adds on, which take the same kernel."""
+odd, every other one odd, one operand only; and the small products of more than 2^20 multiply-adds, which take the same kernel.  The names do not
+tell four waves from eight: which calls take which is asserted by the host model (ragged_rows_check.cpp)."""
 import os
 import subprocess
 
@@ -33,7 +34,8 @@ def test_rows_at_odd_elements(oracle, transA, transB):
             (2049, 1543, 129, True, dict(misalign=1)),                         # large tiles, eight waves
             (2049, 1543, 65, True, dict(misalign=1)),
             (2056, 1537, 200, True, dict()),
-            (2056, 2184, 193, True, dict(pad=(1, 3, 0, 0))),                   # more tiles than CUs: eight waves where both have odd rows
+            (2056, 2184, 193, True, dict(pad=(1, 3, 0, 0))),                   # more tiles than CUs: eight waves where both have odd rows (A stored K x M)
+            (2056, 2184, 192, True, dict(pad=(1, 3, 0, 0))),                   # in every storage
             (2056, 2184, 192, True, dict(pad=(1, 4, 0, 0))),                   # four where one alone has
             (2056, 2184, 128, True, dict(misalign=1))]:
         for out in ("f32", "bf16"):
