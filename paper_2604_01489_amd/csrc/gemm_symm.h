@@ -50,8 +50,8 @@ constexpr int symm_stages(int st) { return st == 256 ? 2 : 4; }
 // whether both blocks of B have a place of their own beside the stages
 constexpr bool symm_own_j(int st, int np) { return symm_stages(st) * ge_symm::STAGE_BYTES + 2 * st * np * 2 <= (st == 256 ? 80 : 160) * 1024; }
 
-// Whether a super-tile's terms leave through their image in LDS (see there), by its side and the columns.
-constexpr bool symm_image(int st, int n) { return n % 4 != 0 && n > (st == 512 ? 8 : 2); }
+// Whether a super-tile's terms leave through their image in LDS (see there), by the columns.
+constexpr bool symm_image(int n) { return n > 16 && n % 4 != 0; }
 
 // ST: side of a super-tile (a multiple of 128: 256, 512 or 768); NP: columns of the small operand's image (16 or 32);
 // UPPER: the upper triangle is the stored one; BVEC: B can be read in aligned 16-byte pieces along n (N a multiple of 8, aligned,
@@ -389,40 +389,44 @@ gemm_symm_bf16_kernel(const SymmParams p)
 
     // ---- the terms: P1 is term J of row block I, P2 term I of row block J; on the diagonal their sum is term I of row
     // block I.  The rows of a term's block are one run of memory.  Register r of lane l is row l%16, column 4 (l/16) + r of a
-    // 16 x 16 block (the small operand's fragments are the first operand of the matrix instruction): column counts that are
-    // multiples of 4 and those below 3 are few store instructions, straight from the registers; with others, up to 128 a wave with
-    // most of their lanes idle, the run leaves through an image of it in LDS, 1 KB a wave instruction (straight / image: 8192 x
-    // 17 34.3 / 30.4 us, 16384 x 16 58.8 / 60.1, x 32 98.3 / 113, 12288 x 4 38.5 / 39.0).  Super-tiles of 512, one a CU: straight up to 8 columns
-    // (9736 x 5 28.2 / 29.2, x 7 28.7 / 29.3; x 9 30.2 / 30.1, 10800 x 13 33.5 / 32.5), and a kernel of its own for either way: with the image's code
+    // 16 x 16 block (the small operand's fragments are the first operand of the matrix instruction): up to 16 columns, or a multiple of 4, leave
+    // straight from the registers, 16 bytes a lane at whatever 4-byte address and what is behind the last whole four by one store more; with others, and
+    // most of the lanes' pieces across two lines, the run leaves through an image of it in LDS, 1 KB a wave instruction (straight / image: 8192 x
+    // 27 34.4 / 32.6 us, 12288 x 31 60.9 / 58.5, 8192 x 17 31.1 / 30.8, 520 x 21 11.7 / 12.4; 9736 x 9 29.4 / 30.8, 14336 x 13 54.0 / 56.6, 8192 x 9 25.3 / 25.9,
+    // 520 x 9 9.4 / 10.0, 16384 x 9 62.6 / 62.1; before, in 4-byte stores, 9736 x 9 30.2, x 5 28.2, now 27.8).  A kernel of its own for either way: with the image's code
     // in it the straight stores took longer, too (9736 x 1 26.9 / 27.7).  (P1 row by row inside the walk, for half the
     // stores to be over by its end: 16384 x 16 58.3 -> 61.8 us, the waits for the loads then wait for the stores.)
     const unsigned pitch = (unsigned)p.N * 4u;
     const int col = 4 * (lane >> 4);
     auto term_rows = [&](int rowBlock, int term) { return (char *)(p.W + ((long long)term * p.batch + b) * p.M * p.N + (long long)rowBlock * ST * p.N); };
     auto bytes_of = [&](int rowBlock) { return min(ST, p.M - rowBlock * ST) * p.N * 4; };      // a multiple of 32: M is one of 8
-    const bool quads = (p.N & 3) == 0;
     if constexpr (!IMAGE) {
         auto store = [&](const f32x4_t (&acc)[NS][2][NJ], int rowBlock, int term) __attribute__((always_inline)) {
-            // rows beyond the matrix are beyond the resource's end, columns beyond N out of any range
+            // rows beyond the matrix are beyond the resource's end, quads not whole out of any range; the columns behind the last whole one by
+            // a store of their own
             const buffer_t rows = __builtin_amdgcn_make_buffer_rsrc(term_rows(rowBlock, term), 0, bytes_of(rowBlock), 0x00020000);
             const unsigned at = (unsigned)(32 * w + (lane & 15)) * pitch + 4u * (unsigned)col;
-            auto offset = [&](int s, int i, int c) { return (int)(col + c < p.N ? at + (unsigned)(s * SUB + 16 * i) * pitch + 4u * c : OOB_OFFSET); };
-            if (quads) {
+            auto offset = [&](int s, int i, int c) { return (int)(col + c + 3 < p.N ? at + (unsigned)(s * SUB + 16 * i) * pitch + 4u * c : OOB_OFFSET); };
+            if (p.N > 3) {
 #pragma unroll
                 for (int s = 0; s < NS; ++s)
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
 #pragma unroll
                         for (int j = 0; j < NJ; ++j) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[s][i][j]), rows, offset(s, i, 16 * j), 0, 0);
-            } else {
+            }
+            if (const int left = p.N & 3; NP == 16 && left) {
+                const bool mine = col == (p.N & 12);
+                auto tail = [&](int s, int i) { return (int)(mine ? at + (unsigned)(s * SUB + 16 * i) * pitch : OOB_OFFSET); };
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    if (r >= p.N) break;
+                for (int s = 0; s < NS; ++s)
 #pragma unroll
-                    for (int s = 0; s < NS; ++s)
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[s][i][0][r]), rows, offset(s, i, r), 0, 0);
-                }
+                    for (int i = 0; i < 2; ++i) {
+                        const u32x4_t v = __builtin_bit_cast(u32x4_t, acc[s][i][0]);
+                        if (left == 1)      __builtin_amdgcn_raw_buffer_store_b32(v[0], rows, tail(s, i), 0, 0);
+                        else if (left == 2) __builtin_amdgcn_raw_buffer_store_b64(__builtin_shufflevector(v, v, 0, 1), rows, tail(s, i), 0, 0);
+                        else                __builtin_amdgcn_raw_buffer_store_b96(__builtin_shufflevector(v, v, 0, 1, 2), rows, tail(s, i), 0, 0);
+                    }
             }
         };
         store(acc1, I, J);

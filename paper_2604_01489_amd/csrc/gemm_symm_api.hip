@@ -53,9 +53,11 @@ void launch_symm(const ge::SymmParams &sp, bool upper, bool bVec, dim3 grid, hip
         if (upper) GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, true, BVEC, IMAGE>), grid, dim3(256), 0, st, sp);
         else       GE_LAUNCH((ge::gemm_symm_bf16_kernel<ST, NP, false, BVEC, IMAGE>), grid, dim3(256), 0, st, sp);
     };
-    if (bVec)                          launch(std::true_type{}, std::false_type{});
-    else if (ge::symm_image(ST, sp.N)) launch(std::false_type{}, std::true_type{});
-    else                              launch(std::false_type{}, std::false_type{});
+    if (bVec) return launch(std::true_type{}, std::false_type{});
+    if constexpr (NP == 32) {
+        if (ge::symm_image(sp.N)) return launch(std::false_type{}, std::true_type{});
+    }
+    launch(std::false_type{}, std::false_type{});
 }
 
 template <int ST>

@@ -172,10 +172,10 @@ def test_symm_columns_of_any_number(oracle, uplo, transB):
         assert cfg.startswith(f"bf16_symm_{uplo}"), cfg
 
 
-@pytest.mark.parametrize("M,N", [(520, 2), (776, 3), (1032, 4), (1288, 5), (640, 20), (904, 28)])
+@pytest.mark.parametrize("M,N", [(520, 2), (776, 3), (1032, 4), (1288, 5), (640, 20), (904, 28), (648, 6), (904, 11), (776, 27)])
 def test_symm_terms_by_every_store(oracle, M, N):
-    """The ways a super-tile's terms leave it: straight from the registers in 16-byte pieces (columns a multiple of 4) or single ones
-    (one or two columns), else through their image in LDS; the last super-tile hangs over the matrix by whole and by partial sub-tiles."""
+    """The ways a super-tile's terms leave it: straight from the registers in 16-byte pieces (up to 16 columns, with the one to
+    three columns behind the last piece in a store of their own, or a multiple of 4), else through their image in LDS; the last super-tile hangs over the matrix by whole and by partial sub-tiles."""
     for uplo in ("lower", "upper"):
         _, cfg = run_symm_case(oracle, M, N, uplo=uplo, seed=M + N)
         assert cfg.startswith(f"bf16_symm_{uplo}_"), cfg

@@ -1,6 +1,6 @@
 """Wide super-tiles of the symmetric kernel (512 and 768) on batches of matrices that are no multiple of them: every way the blocks of B
-are brought in (16-byte pieces straight into LDS, any address through registers, stored N x K) and the terms leave (16 bytes, one or
-two columns, through their image in LDS), both triangles, the other one filled with NaN.  Reference: the mirrored matrices in fp64."""
+are brought in (16-byte pieces straight into LDS, any address through registers, stored N x K) and the terms leave (whole fours of
+columns, the one to three behind them, through their image in LDS), both triangles, the other one filled with NaN.  Reference: the mirrored matrices in fp64."""
 import pytest
 
 from paper_2604_01489_amd import binding
@@ -32,7 +32,7 @@ def stored():
 
 
 @pytest.mark.parametrize("uplo", ["lower", "upper"])
-@pytest.mark.parametrize("width,columns", [(512, (1, 5, 16, 24, 31, 32)), (768, (1, 5, 8, 12))])
+@pytest.mark.parametrize("width,columns", [(512, (1, 3, 5, 10, 15, 16, 24, 31, 32)), (768, (1, 2, 5, 7, 8, 12, 14))])
 def test_wide_super_tiles(stored, width, columns, uplo):
     import torch
     batch, M = SIZES[width]
