@@ -54,22 +54,30 @@ GE_HD constexpr void ragged_first(int j, int i, int w, int &r, int &at)
 }
 
 // Waves of a workgroup of the bf16 kernel's 128 x 128 tile, for `blocks` of them, and whether their K is read as one step (`one`: kPerSlice is
-// 64 or less).  oddA, oddB: that operand has rows at odd elements; ldsOdd: both leading dimensions are odd.
+// 64 or less).  oddA, oddB: that operand has rows at odd elements; ldsOdd: both leading dimensions are odd, so that every other row is in
+// place as it is; bytes: operands and result.
 // Eight waves where a block has its CU to itself, or where both operands have rows at odd elements: more blocks cover each other's
 // waits, and then only the look-ups saved count.  us, four / eight waves: 208 blocks, 1999 x 1537 x 2051 33.8 / 31.5, aligned rows
 // 27.9 / 27.5, A stored K x M 1999 x 1537 x 515 14.8 / 12.7; more blocks, both odd, 2047 x 2049 x 2051 53.8 / 49.0, 3001 x 3001 x 901
 // 41.9 / 40.5, 4095 x 4093 x 2047 108.4 / 104.3; one odd, 4001 x 3003 x 700 33.8 / 34.5, 3000 x 3001 x 1024 40.7 / 41.4; none, 2500 x
-// 3001 x 704 with B stored N x K 19.3 / 19.7.  Not with both odd where odd leading dimensions make every other row so, B is stored N x K and
-// there are four blocks to a CU: half of what is moved was in place (201 x 3520 x 1433, 20 of them, 102.6 / 115.8; 1724 x 1680 x 77, 20,
-// 70.8 / 81.2; fewer blocks 2047 x 2049 x 2051, 52.0 / 47.5).  One step of K is never moved: four waves, in the kernel that asks for no more, but for
+// 3001 x 704 with B stored N x K 19.3 / 19.7.  Where every other row is in place only half of what is moved gains, and four waves stay:
+// - past the 256 MB memory-side cache, where memory and not the look-ups is the bound (112 x 4927 x 4757, 7 of them, B N x K, 164.6 / 196.4;
+//   120 x 1770 x 3836, 20, 123.0 / 145.1; 124 x 1300 x 1120, 100, 114.2 / 128.9);
+// - B stored N x K with four blocks to a CU (201 x 3520 x 1433, 20, 102.6 / 115.8; 1724 x 1680 x 77, 20, 70.8 / 81.2) or, A M x K, with more than
+//   1536 k to a block (1123 x 4209 x 1711 46.8 / 51.1, 1408 x 184 x 1812, 20, 51.0 / 56.2; fewer of both 2047 x 2049 x 515 19.6 / 18.1);
+// - three steps of K with A stored K x M and B K x N (1658 x 2678 x 177 11.5 / 12.8, 5373 x 1299 x 191 13.4 / 14.4; two steps 1.00, four 0.97 of it).
+// One step of K is never moved: four waves, in the kernel that asks for no more, but for
 // few blocks (4001 x 3003 x 60 with A stored K x M, 768 blocks, 12.3 / 16.2; 1341 x 104 x 48, 20 of them, 220 blocks, 7.5 / 6.9).
 constexpr int RAGGED_CUS = 256;
 struct RaggedWaves { int waves; bool one; };
-constexpr RaggedWaves ragged_128_waves(unsigned blocks, int kPerSlice, bool oddA, bool oddB, bool ldsOdd, bool transB)
+constexpr RaggedWaves ragged_128_waves(unsigned blocks, int kPerSlice, bool oddA, bool oddB, bool ldsOdd, bool transA, bool transB, double bytes)
 {
     if (blocks <= (unsigned)RAGGED_CUS) return {8, false};
     if (kPerSlice <= 64) return {4, true};
-    return {oddA && oddB && !(ldsOdd && transB && blocks >= 4u * RAGGED_CUS) ? 8 : 4, false};
+    if (!oddA || !oddB) return {4, false};
+    const bool four = bytes > 256.0 * 1024 * 1024 || (transB && (blocks >= 4u * RAGGED_CUS || (!transA && kPerSlice > 1536))) ||
+                      (transA && !transB && kPerSlice == 192);
+    return {ldsOdd && four ? 4 : 8, false};
 }
 
 // fp32: a 32-k step of a tile BX wide, BX / 32 chunks per lane, is two images of 16 k: 64-byte rows of A (along k), B in

@@ -70,7 +70,8 @@ int variant(int M, int N, int K, int padA, int padB, int start, bool transA, boo
 {
     const int lda = (transA ? M : K) + padA, ldb = (transB ? K : N) + padB;
     const bool oddA = (lda | start) & 1, oddB = (ldb | start) & 1;
-    const RaggedWaves v = ragged_128_waves((unsigned)((M + 127) / 128 * ((N + 127) / 128)), (K + 63) / 64 * 64, oddA, oddB, (lda & ldb) & 1, transB);
+    const RaggedWaves v = ragged_128_waves((unsigned)((M + 127) / 128 * ((N + 127) / 128)), (K + 63) / 64 * 64, oddA, oddB, (lda & ldb) & 1, transA, transB,
+                                           2.0 * (M + N) * K + 4.0 * M * N);
     return 2 * v.waves + (v.one ? 1 : 0);
 }
 
@@ -82,9 +83,13 @@ void check_variants()
         {2049, 1543, 129, 0, 0, 1, {EIGHT, EIGHT, EIGHT, EIGHT}}, {2049, 1543, 65, 0, 0, 1, {EIGHT, EIGHT, EIGHT, EIGHT}},
         {2056, 1537, 200, 0, 0, 0, {EIGHT, EIGHT, EIGHT, EIGHT}},
         {2056, 2184, 193, 1, 3, 0, {FOUR, FOUR, EIGHT, FOUR}}, {2056, 2184, 192, 1, 4, 0, {FOUR, FOUR, FOUR, FOUR}},
-        {2056, 2184, 192, 1, 3, 0, {EIGHT, EIGHT, EIGHT, EIGHT}}, {2056, 2184, 128, 0, 0, 1, {EIGHT, EIGHT, EIGHT, EIGHT}},
+        {2056, 2184, 200, 1, 3, 0, {EIGHT, EIGHT, EIGHT, EIGHT}}, {2056, 2184, 128, 0, 0, 1, {EIGHT, EIGHT, EIGHT, EIGHT}},
         {2056, 2189, 64, 0, 0, 1, {FOUR_ONE, FOUR_ONE, FOUR_ONE, FOUR_ONE}}, {2056, 2184, 33, 1, 2, 0, {FOUR_ONE, FOUR_ONE, FOUR_ONE, FOUR_ONE}},
-        {4097, 4097, 129, 0, 0, 0, {EIGHT, FOUR, EIGHT, FOUR}}};          // four blocks to a CU, every other row odd
+        // every other row odd: four blocks to a CU; three steps, and two and four; 1537 k to a block, and 1536; more than 256 MB, and less
+        {4097, 4097, 129, 0, 0, 0, {EIGHT, FOUR, FOUR, FOUR}}, {2049, 2047, 191, 0, 0, 0, {EIGHT, EIGHT, FOUR, EIGHT}},
+        {2049, 2047, 127, 0, 0, 0, {EIGHT, EIGHT, EIGHT, EIGHT}}, {2049, 2047, 193, 0, 0, 0, {EIGHT, EIGHT, EIGHT, EIGHT}},
+        {2049, 2047, 1537, 0, 0, 0, {EIGHT, FOUR, EIGHT, EIGHT}}, {2049, 2047, 1535, 0, 0, 0, {EIGHT, EIGHT, EIGHT, EIGHT}},
+        {125, 42001, 3185, 0, 0, 0, {FOUR, FOUR, FOUR, FOUR}}, {125, 36001, 1535, 0, 0, 0, {EIGHT, EIGHT, EIGHT, EIGHT}}};
     for (const auto &c : calls)
         for (int s = 0; s < 4; ++s) {
             const int got = variant(c.M, c.N, c.K, c.padA, c.padB, c.start, s >= 2, s & 1);

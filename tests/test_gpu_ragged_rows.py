@@ -35,7 +35,7 @@ def test_rows_at_odd_elements(oracle, transA, transB):
             (2049, 1543, 65, True, dict(misalign=1)),
             (2056, 1537, 200, True, dict()),
             (2056, 2184, 193, True, dict(pad=(1, 3, 0, 0))),                   # more tiles than CUs: eight waves where both have odd rows (A stored K x M)
-            (2056, 2184, 192, True, dict(pad=(1, 3, 0, 0))),                   # in every storage
+            (2056, 2184, 200, True, dict(pad=(1, 3, 0, 0))),                   # in every storage
             (2056, 2184, 192, True, dict(pad=(1, 4, 0, 0))),                   # four where one alone has
             (2056, 2184, 128, True, dict(misalign=1))]:
         for out in ("f32", "bf16"):
