@@ -119,7 +119,8 @@ void slice_k(int K, int bk, int want, int *splitK, int *kPerSlice)
 // exact): the count with the lowest estimate.  A CU's matrix pipes take 0.54 us for each 32-k step of each block it has been
 // given (a 128 tile four times that), or a block alone 0.62 us with its waits; each round of blocks beyond the first begins and ends for
 // 1.2 us (element by element, where a step takes several times as long, this does not count: 705 x 3 x 6400 22.6 with it, 20.9 without); the
-// second pass is a launch and the partial tiles written and read.  What the count decides is how full the last round of blocks on the CUs
+// second pass is a launch, the partial tiles written and read and, for each slice, 0.057 us of round trips, eight slices each (without it 2 of 5 x 204 x 17484
+// took 61 slices instead of 32: 20.4 us, 18.9 on these; 453 x 4 x 15976 63 instead of 31, 18.9 / 17.9).  What the count decides is how full the last round of blocks on the CUs
 // is.  us, least / chosen: 1023 x 771 x 2049, 208 tiles, 4 slices 47.2 / 6 42.4 (5: 46.8, 7: 45.7); 320 x 320 x 4095, 7 19.2 / 10 16.4 (12:
 // 20.6); 513 x 515 x 4095, 5 36.0 / 6 32.5; 256 x 256 x 1024, 2 15.3 / 16 9.1 (8: 9.6); 72 x 1280 x 1600, 3 16.9 / 6 12.0.  Where the least count already
 // is one round of the CUs, twice as many are no shorter: 80 x 966 x 4120, 8 19.4 (15: 20.5); 496 x 66 x 8368, 16 19.5 (30: 20.6); 2 of 460 x
@@ -132,7 +133,7 @@ int f32_slices(int tile, long long tiles, long long outputs, int K, int least, b
     for (int s = least; s <= 64 && (s == least || K / s >= 64); ++s) {
         const double rounds = (double)((tiles * s + kNumCU - 1) / kNumCU), steps = (double)ceil_div(ceil_div(K, s), 32);
         const double cost = steps * (rounds * area > 1.0 ? 0.54 * area * rounds : 0.62) + (elementwise ? 0.0 : 1.2 * (rounds - 1.0)) +
-                            (double)(s + 1) * (double)outputs * 4.0 / 4.5e6;
+                            0.057 * s + (double)(s + 1) * (double)outputs * 4.0 / 4.5e6;
         if (s == least || cost < bestCost) { best = s; bestCost = cost; }
     }
     return best;
