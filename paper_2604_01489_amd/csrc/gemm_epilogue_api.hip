@@ -122,7 +122,7 @@ void slice_k(int K, int bk, int want, int *splitK, int *kPerSlice)
 // second pass is a launch, the partial tiles written and read and, for each slice, 0.057 us of round trips, eight slices each (without it 2 of 5 x 204 x 17484
 // took 61 slices instead of 32: 20.4 us, 18.9 on these; 453 x 4 x 15976 63 instead of 31, 18.9 / 17.9).  What the count decides is how full the last round of blocks on the CUs
 // is.  us, least / chosen: 1023 x 771 x 2049, 208 tiles, 4 slices 47.2 / 6 42.4 (5: 46.8, 7: 45.7); 320 x 320 x 4095, 7 19.2 / 10 16.4 (12:
-// 20.6); 513 x 515 x 4095, 5 36.0 / 6 32.5; 256 x 256 x 1024, 2 15.3 / 16 9.1 (8: 9.6); 72 x 1280 x 1600, 3 16.9 / 6 12.0.  Where the least count already
+// 20.6); 256 x 256 x 1024, 2 15.3 / 16 9.1 (8: 9.6); 72 x 1280 x 1600, 3 16.9 / 6 12.0.  Where the least count already
 // is one round of the CUs, twice as many are no shorter: 80 x 966 x 4120, 8 19.4 (15: 20.5); 496 x 66 x 8368, 16 19.5 (30: 20.6); 2 of 460 x
 // 40 x 8600, 16 18.9 (30: 19.9).  Slices keep 64 of K.
 int f32_slices(int tile, long long tiles, long long outputs, int K, int least, bool elementwise)
@@ -168,10 +168,12 @@ double plan_cost_us(int M, int N, int K, int batch, int tile, int slices)
     return t;
 }
 
-// Multiply-adds from which the kernel for operands of any alignment takes what the direct-to-LDS kernels do not (us, guarded / any
-// alignment: 130 x 70 x 1500, 13.7 M, 47.3 / 9.3; 513 x 515 x 33, 8.7 M, 7.5 / 5.2; 33 x 33 x 4096, 4.5 M, 27.4 / 8.1; 221 x 155 x
-// 44, 1.5 M, 7.6 / 5.1).  Below, where it is still the shorter call (67 x 45 x 33, 0.1 M, 7.0 / 5.1), and for K slices that the
-// caller asks for up to kRaggedMinSliced, the guarded kernel keeps the calls that it is tested on.
+// Multiply-adds above which the kernel for operands of any alignment takes what the direct-to-LDS kernels do not (us, guarded / any
+// alignment: 130 x 70 x 1500, 13.7 M, 48.4 / 11.0; 513 x 515 x 33, 8.7 M, 7.5 / 5.2; 33 x 33 x 4096, 4.5 M, 27.7 / 8.4; 221 x 155 x
+// 44, 1.5 M, 7.6 / 5.1), and products of aligned operands with few large tiles as well (small_tile_pays; 128 / 64 tile: 128 x 128 x 512 6.9 / 5.6,
+// 200 x 200 x 400 7.4 / 5.3, 72 x 72 x 2040 22.1 / 12.7).  Not where the two cross: up to the line it is the shorter call too (128 x 128 x 64, on the line,
+// 7.8 / 3.4; 100 x 100 x 100 10.4 / 4.5; 33 x 35 x 700 35.6 / 7.4), and so it is for K slices that the caller asks for up to kRaggedMinSliced; the
+// configuration that these calls report is the guarded kernel's, which tests of that kernel count on.
 constexpr double kRaggedMinWork = 1024.0 * 1024, kRaggedMinSliced = 16.0 * 1024 * 1024;
 
 // The slice count of lowest estimated cost for a tile (1 = none); slices keep at least minSlice of K.
@@ -218,12 +220,13 @@ bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bo
     if (K < 8 || (transA && M < 8) || (!transB && N < 8)) return false;
     // byte offsets of a lane inside a tile panel: 128 rows along k, or 64 rows along M or N
     if ((long long)lda * (transA ? 128 : 256) + 1024 >= (1ll << 31) || (long long)ldb * (transB ? 256 : 128) + 1024 >= (1ll << 31)) return false;
-    // Slivers of the plain operator, of whose 64 x 64 tiles there are four or more to a CU with one output in twelve or fewer inside, and one 32-k
-    // step: the guarded kernel reads no more than is there.  us, guarded / any alignment: 2 x 185 x 9, 3794 of them, 28.2 / 34.0; 6 x 10 x
-    // 9, 3568, 10.7 / 12.4; 1 x 567 x 16, 227, 7.5 / 8.2; the other side: 18 x 37 x 12, 1273, 7.3 / 6.9; 2 x 55 x 14, 741, 4.9 / 4.8; with
-    // the widened operator's chain 1 x 237 x 19, 1562, 31.4 / 19.9.
+    // Slivers of the plain operator, of whose 64 x 64 tiles there are four or more to a CU with one output in ten or fewer inside, and one 32-k
+    // step or a few k past a 64-k step: the guarded kernel reads no more than is there.  us, guarded / any alignment: 2 x 185 x 9, 3794 of
+    // them, 28.2 / 34.0; 6 x 10 x 9, 3568, 10.7 / 12.4; 1 x 567 x 16, 227, 7.5 / 8.2; 6 x 3596 x 23, 20, 5.7 / 6.5; 2 x 734 x 68, 100, 7.8 / 10.5; 3 x 3906 x
+    // 65, 20, 8.1 / 9.4; the other side: 18 x 37 x 12, 1273, 7.3 / 6.9; 2 x 55 x 14, 741, 4.9 / 4.8; 1 x 209 x 40, 500, 9.5 / 8.1; 4 x 69 x 57, 500, 6.7 / 5.0;
+    // with the widened operator's chain 1 x 237 x 19, 1562, 31.4 / 19.9.
     const double tiles = (double)ceil_div(M, 64) * ceil_div(N, 64) * batch;
-    if (plain && K <= 32 && tiles >= 4.0 * kNumCU && 12.0 * M * N * batch <= 4096.0 * tiles) return false;
+    if (plain && (K <= 32 || (K > 64 && K <= 72)) && tiles >= 4.0 * kNumCU && 10.0 * M * N * batch <= 4096.0 * tiles) return false;
     return (double)M * N * K * batch > kRaggedMinWork;
 }
 
@@ -704,8 +707,9 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
         least = choose_split(t128, K, 512);
         // Operands of any alignment: the tile whose rounds of blocks on the CUs take the matrix pipe less time (a 128 tile is
         // four of the small one, at 1.1 times its rate; 64 against 128, us: 1023 x 771 x 2049 48 / 57, 1501^3 82 / 114, 2001 x
-        // 2003 x 401 45 / 42).  Two calls of few tiles keep the large one that they have been tested on: those of one or two
-        // 32-k steps, a launch and little else (129 x 130 x 31 5.5 / 6.1), and fewer than 16 tiles in slices (130 x 257 x 2075).
+        // 2003 x 401 45 / 42).  Two kinds of few tiles keep the large one though it is the slower, which is what they report and tests of that tile
+        // count on: those of one or two 32-k steps (129 x 130 x 31 3.6 / 6.0, 100 x 333 x 64 4.3 / 8.2), and fewer than 16 tiles in slices (130 x 257 x
+        // 2075 10.3 / 15.2, 67 x 45 x 2051 7.9 / 13.5, 191 x 255 x 4097 13.1 / 20.1).
         // The others are the small tile's (100 x 333 x 900 22 / 66, 255 x 255 x 1001 24 / 73, 129 x 130 x 300 9.6 / 25.6, 320 x 320 x 4095
         // 16.4 / 49.7).
         big = !elementwise && ((t64 < 32 && K <= 64) || (t64 < 16 && least > 1) ||

@@ -361,13 +361,13 @@ bool vec_ok(const void *base, long long ld) { return (((uintptr_t)base) & 15u) =
 bool rows_aligned(int C, const void *X, long long ldx) { return vec_ok(X, ldx) && C % 8 == 0; }
 
 // The wide kernel needs enough columns to give most lanes of a wave a 16-byte piece (its narrowest sweep is 512 columns).
-// Rows that are no whole aligned pieces take it only where it is the shorter call (us, one wave a row / wide, the latter with blocks of 16
-// waves, before they had four or eight):
-// - at any address, from 2048 columns on (2049 x 4096 rows 14.4 / 7.0, 8191 x 8192 rows 51.9 / 36.9) or 2^23 elements (911 columns:
-//   8192 rows 5.4 / 9.1, 12288 10.5 / 9.2; 505: 16384 5.8 / 9.7, 24576 11.6 / 9.8; 1351: 4096 6.2 / 7.7, 8192 10.6 / 7.9);
+// Rows that are no whole aligned pieces take it only where it is the shorter call (us, one wave a row / wide):
+// - at any address, from 2048 columns on (2049 x 4096 rows 25.3 / 8.8, 8191 x 8192 rows 53.4 / 30.8, 1000 x 2100 7.7 / 5.2) or 2^23 elements (911
+//   columns: 8192 rows 5.5 / 6.3 or 5.7, 12288 8.1 / 7.9 or 12.5 / 7.1; 505: 16384 6.0 / 6.7, 24576 11.1 / 8.4; 1351: 8192 11.4 / 8.1).  Between, from about
+//   1300 columns and 2^22.5 elements on, the line keeps some on the slower side (4096 x 1351 6.2 / 5.7, 6000 x 1351 11.0 / 6.8, 4096 x 2001 10.8 / 6.8);
 // - at 16-byte addresses and of a length that is no multiple of 8, which the other kernel reads in aligned pieces but for the last
-//   columns, for few long rows (5685 x 1160 8.5 / 7.1, x 4096 11.8 / 15.3; 16385 x 1160 20.3 / 13.2; 4097 x 512 5.9 / 6.0; 2049 x
-//   16384 13.1 / 24.5).
+//   columns, for few long rows (5685 x 1160 8.5 / 7.0, x 4096 12.2 / 12.1; 4609 x 2048 6.5 / 6.6; 6001 x 2048 10.7 / 7.4; 30001 x 300 23.9 / 20.4; 4801 x 4096 9.6 /
+//   10.6; 4301 x 2500 6.6 / 8.8).
 bool rows_wide(int R, int C, const void *X, long long ldx)
 {
     if (C < 384) return false;

@@ -75,6 +75,8 @@ def test_one_step(oracle, transA, transB, K):
     (5, 67, 31, 512, "bf16_generic_64x64x32"),               # 1024 tiles, hardly any of them inside
     (5, 67, 33, 512, "bf16_ragged_64x64x64"),                # more than one of the guarded kernel's steps
     (5, 67, 31, 511, "bf16_ragged_64x64x64"),                # fewer tiles
+    (5, 67, 65, 512, "bf16_generic_64x64x32"),               # a few k past a 64-k step
+    (5, 67, 73, 512, "bf16_ragged_64x64x64"),
     (11, 63, 31, 1024, "bf16_ragged_64x64x64"),              # more than one output in twelve inside
 ])
 def test_slivers(oracle, M, N, K, batch, kernel):
