@@ -221,13 +221,14 @@ bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bo
     // byte offsets of a lane inside a tile panel: 128 rows along k, or 64 rows along M or N
     if ((long long)lda * (transA ? 128 : 256) + 1024 >= (1ll << 31) || (long long)ldb * (transB ? 256 : 128) + 1024 >= (1ll << 31)) return false;
     // Slivers of the plain operator, of whose 64 x 64 tiles there are four or more to a CU with one output in ten or fewer inside, and one 32-k
-    // step or a few k past a 64-k step: the guarded kernel reads no more than is there.  us, guarded / any alignment: 2 x 185 x 9, 3794 of
+    // step or, in few multiply-adds, a few k past a 64-k step: the guarded kernel reads no more than is there.  us, guarded / any alignment: 2 x 185 x 9, 3794 of
     // them, 28.2 / 34.0; 6 x 10 x 9, 3568, 10.7 / 12.4; 1 x 567 x 16, 227, 7.5 / 8.2; 6 x 3596 x 23, 20, 5.7 / 6.5; 2 x 734 x 68, 100, 7.8 / 10.5; 3 x 3906 x
-    // 65, 20, 8.1 / 9.4; the other side: 18 x 37 x 12, 1273, 7.3 / 6.9; 2 x 55 x 14, 741, 4.9 / 4.8; 1 x 209 x 40, 500, 9.5 / 8.1; 4 x 69 x 57, 500, 6.7 / 5.0;
+    // 65, 20, 8.1 / 9.4; 5 x 350 x 28, 500, 11.0 / 20.9; the other side: 4 x 4426 x 66, 100, 55.0 / 28.6; 1 x 4932 x 65, 100, 56.4 / 40.3; 18 x 37 x 12, 1273, 7.3 / 6.9; 2 x 55 x 14, 741, 4.9 / 4.8; 1 x 209 x 40, 500, 9.5 / 8.1; 4 x 69 x 57, 500, 6.7 / 5.0;
     // with the widened operator's chain 1 x 237 x 19, 1562, 31.4 / 19.9.
     const double tiles = (double)ceil_div(M, 64) * ceil_div(N, 64) * batch;
-    if (plain && (K <= 32 || (K > 64 && K <= 72)) && tiles >= 4.0 * kNumCU && 10.0 * M * N * batch <= 4096.0 * tiles) return false;
-    return (double)M * N * K * batch > kRaggedMinWork;
+    const double work = (double)M * N * K * batch;
+    if (plain && (K <= 32 || (K > 64 && K <= 72 && work < 16.0 * 1024 * 1024)) && tiles >= 4.0 * kNumCU && 10.0 * M * N * batch <= 4096.0 * tiles) return false;
+    return work > kRaggedMinWork;
 }
 
 ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t plan, int split_k, Plan *out, bool skinny, bool ragged)

@@ -393,10 +393,10 @@ void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float
         // 17.1 / 16.1, 1024 x 8192 18.6 / 17.9, 2048 x 32768 39.4 / 32.8; 4096 x 8192 31.9 / 33.1, 8192 x 16384 57.6 / 71.6, 2048 x
         // 2048 13.6 / 14.5); else four, the narrowest sweep that covers a row or the whole block per row.
         // Aligned rows of a length and number that make nearly one block of 16 waves a CU, two or four rows of waves: those (the row pass, us, four or
-        // eight / 16 waves: 3204 x 3072 8.1 / 8.0, 4000 x 4000 10.4 / 9.9, 3601 x 2816 8.0 / 7.9; 128 blocks 2100 x 3800 9.2 / 9.2, 2300 x 2304 6.8 / 7.0;
+        // eight / 16 waves: 3204 x 3072 8.1 / 8.0, 4000 x 4000 10.4 / 9.9, 3601 x 2816 8.0 / 7.9, 2077 x 3384 8.3 / 7.7, 2303 x 3752 9.0 / 8.3; 144 blocks 2300 x 2304 6.8 / 7.0;
         // 6475 x 1712 9.1 / 8.8, 8000 x 2000 10.4 / 10.0; 160 blocks 5000 x 1536 7.0 / 7.8).
         const long long of16 = C > 2048 ? ceil_div(R, 16) : ceil_div(R, 32);
-        const bool one16 = rows_aligned(C, X, ldx) && C > 1024 && C <= 4096 && of16 <= kNumCU && of16 * 16 > kNumCU * (C > 2048 ? 9 : 12);
+        const bool one16 = rows_aligned(C, X, ldx) && C > 1024 && C <= 4096 && of16 <= kNumCU && of16 * 16 > kNumCU * (C > 2560 ? 8 : C > 2048 ? 9 : 12);
         if (one16 && C > 2048) GE_LAUNCH((rows_dot_wide_kernel<16, 2, false>), dim3((unsigned)of16), dim3(1024), 0, st, R, C, X, ldx, v, scale, add, out);
         else if (one16)        GE_LAUNCH((rows_dot_wide_kernel<16, 4, false>), dim3((unsigned)of16), dim3(1024), 0, st, R, C, X, ldx, v, scale, add, out);
         else if (C > 2048 && R < kBlockRows * 2 * kNumCU) launch(integral_constant<int, 8>{}, integral_constant<int, 1>{});

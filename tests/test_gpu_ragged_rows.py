@@ -77,6 +77,7 @@ def test_one_step(oracle, transA, transB, K):
     (5, 67, 31, 511, "bf16_ragged_64x64x64"),                # fewer tiles
     (5, 67, 65, 512, "bf16_generic_64x64x32"),               # a few k past a 64-k step
     (5, 67, 73, 512, "bf16_ragged_64x64x64"),
+    (5, 67, 65, 1024, "bf16_ragged_64x64x64"),               # more than 2^24 multiply-adds
     (11, 63, 31, 1024, "bf16_ragged_64x64x64"),              # more than one output in twelve inside
 ])
 def test_slivers(oracle, M, N, K, batch, kernel):

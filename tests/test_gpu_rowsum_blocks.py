@@ -38,7 +38,7 @@ def _run(M, N, K, transB, lda=None, ldb=None):
 @pytest.mark.parametrize("M,K", [(1, 384), (33, 512), (31, 520), (17, 1024), (15, 1032), (9, 2048), (7, 2056), (4095, 2056), (4096, 2056), (4097, 2048),
                                  (8, 4096), (1, 8200), (4103, 4104),
                                  # nearly one block of 16 waves to a CU, and one row beyond or short of that
-                                 (2304, 4096), (2305, 4096), (4096, 2064), (6144, 1032), (6145, 1032), (8192, 2048), (8193, 2048)])
+                                 (2048, 2568), (2049, 2568), (2304, 2560), (2305, 2560), (4096, 2064), (6144, 1032), (6145, 1032), (8192, 2048), (8193, 2048)])
 def test_rows_around_a_sweep(M, K):
     assert _run(M, 40, K, True) == "rowsum_rows_wide"
     if K >= 2048 and M < 1000:
