@@ -38,7 +38,10 @@
  * stream that is being captured is refused such a first allocation
  * (GE_ERR_WORKSPACE): run the call once on that stream before capturing, or
  * pass a workspace.  Calls on different streams use different buffers; calls
- * on one stream are ordered by it.
+ * on one stream are ordered by it.  (Where the library itself would slice K, up
+ * to 2560, for at most 256 tiles of 32 x 32, each workgroup adds up its tile's
+ * slices and nothing is parked; the workspace query is the plan's all the same,
+ * and a workspace that is given must still be as large.)
  *
  * Errors.  Every call validates its arguments first and returns a status; on
  * any status other than GE_OK nothing was enqueued and C is untouched.
@@ -421,7 +424,8 @@ const char *ge_status_string(ge_status_t status);
 
 /* Name of the kernel configuration the last successful call on this thread
  * launched ("bf16_256x256x64_w4", "bf16_256x256x32_w8", "f32_128x128x16_w4", "f32_ragged_64x64x32",
- * ...); for reports.  The names may change from one build to the next. */
+ * ...); for reports.  The names may change from one build to the next.  The tile is the plan's:
+ * bf16 products of few tiles go to workgroups in 32 x 32 pieces of it under the same name. */
 const char *ge_last_config(void);
 
 #ifdef __cplusplus

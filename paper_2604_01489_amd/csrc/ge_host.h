@@ -94,6 +94,11 @@ ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t 
 // the same: 12 us).
 ge_status_t make_plan_bf16_for(int M, int N, int K, int batch, bool fast, ge_plan_t plan, int split_k, int ldc, bool f32Out, Plan *out,
                                bool skinny = false, bool ragged = false);
+// Whether the call goes to workgroups in the 32 x 32 tiles of gemm_small.h, with the sums of the plan: few of them (small_layout.h), the library's own choice of
+// slices, panels within 31-bit byte offsets.  The plan, and with it the configuration's name, stays as it is.
+bool small_ok(const Plan &pl, const GemmParams &p, ge_plan_t plan);
+// Such a call needs no workspace; one that is given is held to the plan's size, as before there were such calls.
+ge_status_t check_unused_workspace(size_t need, const void *user, size_t user_bytes);
 size_t partial_bytes(int M, int N, int batch, int splitK);
 int choose_group_m(int tilesM, int tilesN);
 // The four-wave kernel (gemm_bf16_w4.h) takes launches of 256 x 256 tiles whose blocks walk a K range

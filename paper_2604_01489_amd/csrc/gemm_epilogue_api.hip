@@ -20,8 +20,10 @@
 #include "gemm_generic.h"
 #include "gemm_ragged_launch.h"
 #include "gemm_skinny.h"
+#include "gemm_small_launch.h"
 #include "ge_host.h"
 #include "plan_rates.h"
+#include "small_layout.h"
 #include "splitk_reduce.h"
 
 namespace ge_host {
@@ -330,6 +332,19 @@ ge_status_t make_plan_bf16_for(int M, int N, int K, int batch, bool fast, ge_pla
     return rowLength < ge::EDGE_LDC_MAX ? st : make_plan_bf16(M, N, K, batch, false, plan, split_k, out);
 }
 
+bool small_ok(const Plan &pl, const GemmParams &p, ge_plan_t plan)
+{
+    if ((pl.tile != TILE_128 && pl.tile != TILE_RAGGED_64) || p.triA != ge::TRI_NONE || plan == GE_PLAN_SPLITK || opt_force_config() != FORCE_NONE) return false;
+    // 256 rows along k, or 32 along M or N
+    if ((long long)p.lda * (p.transA ? 512 : 64) + 1024 >= (1ll << 31) || (long long)p.ldb * (p.transB ? 64 : 512) + 1024 >= (1ll << 31)) return false;
+    return ge::small_tile_takes((long long)ceil_div(p.M, 32) * ceil_div(p.N, 32) * p.batch, pl.splitK, p.K, pl.tile == TILE_RAGGED_64);
+}
+
+ge_status_t check_unused_workspace(size_t need, const void *user, size_t user_bytes)
+{
+    return user && need && (user_bytes < need || ((uintptr_t)user & 255u)) ? GE_ERR_WORKSPACE : GE_OK;
+}
+
 size_t partial_bytes(int M, int N, int batch, int splitK)
 {
     return splitK <= 1 ? 0 : (size_t)splitK * (size_t)batch * (size_t)M * (size_t)N * sizeof(float);
@@ -516,8 +531,12 @@ ge_status_t run_bf16(int M, int N, int K, const uint16_t *A, int lda, const uint
     p.bytesA = 2 * (((long long)batch * M - 1) * lda + K);
     p.bytesB = 2 * (((long long)batch * K - 1) * ldb + N);
 
-    const bool raw = pl.splitK > 1;
+    const bool sliced = pl.splitK > 1, small = small_ok(pl, p, plan), raw = sliced && !small;
     void *ws = nullptr;
+    if (small) {
+        st = check_unused_workspace(partial_bytes(M, N, batch, pl.splitK), workspace, workspace_bytes);
+        if (st != GE_OK) return st;
+    }
     if (raw) {
         st = acquire_workspace(partial_bytes(M, N, batch, pl.splitK), workspace, workspace_bytes, (hipStream_t)stream, &ws);
         if (st != GE_OK) return st;
@@ -560,18 +579,26 @@ ge_status_t run_bf16(int M, int N, int K, const uint16_t *A, int lda, const uint
         g_last_config = raw ? "bf16_256x256x32_w8_splitk" : "bf16_256x256x32_w8";
         break;
     case TILE_128:
-        err = launch_fast<128, 128, 2, 2>(p, tile_edge(pl, K, 32), raw, (int)act, grid, hs);
-        g_last_config = raw ? "bf16_128x128x32_w4_splitk" : "bf16_128x128x32_w4";
+        if (small) {
+            p.clampLo = -INFINITY;   // as below
+            p.clampHi = INFINITY;
+            launch_small(p, hs);
+            err = ge_host::take_launch_error();
+        } else {
+            err = launch_fast<128, 128, 2, 2>(p, tile_edge(pl, K, 32), raw, (int)act, grid, hs);
+        }
+        g_last_config = sliced ? "bf16_128x128x32_w4_splitk" : "bf16_128x128x32_w4";
         break;
     case TILE_RAGGED_128:
     case TILE_RAGGED_64:
         p.clampLo = -INFINITY;       // the run-time consumer chain, with nothing beyond the plain operator's
         p.clampHi = INFINITY;
-        if (pl.tile == TILE_RAGGED_128) launch_ragged_128(p, raw, grid, hs);
-        else                            launch_ragged_64(p, raw, grid, hs);
+        if (small)                           launch_small(p, hs);
+        else if (pl.tile == TILE_RAGGED_128) launch_ragged_128(p, raw, grid, hs);
+        else                                 launch_ragged_64(p, raw, grid, hs);
         err = ge_host::take_launch_error();
         g_last_config = pl.tile == TILE_RAGGED_128 ? (raw ? "bf16_ragged_128x128x64_splitk" : "bf16_ragged_128x128x64")
-                                                   : (raw ? "bf16_ragged_64x64x64_splitk" : "bf16_ragged_64x64x64");
+                                                   : (sliced ? "bf16_ragged_64x64x64_splitk" : "bf16_ragged_64x64x64");
         break;
     default:
         if (raw) GE_LAUNCH(ge::gemm_bf16_generic_kernel<true>, grid, dim3(256), 0, hs, p);

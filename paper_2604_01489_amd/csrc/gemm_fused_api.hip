@@ -12,6 +12,7 @@
 #include "gemm_fused.h"
 #include "gemm_fused_launch.h"
 #include "gemm_ragged_launch.h"
+#include "gemm_small_launch.h"
 #include "ge_host.h"
 
 namespace {
@@ -113,13 +114,18 @@ ge_status_t plan_of(const ge_fused_args_t &a, Plan *out)
                               a.c_type == GE_DTYPE_F32, out, false, ragged(a));
 }
 
-template <int BM>
-bool launch_tile(const GemmParams &p, const Plan &pl, bool raw, dim3 grid, hipStream_t st)
+bool tile_k64(const GemmParams &p, int tile, dim3 grid)
 {
     // 128 x 128 blocks: only where more than one block shares a CU (measured with both operands along
     // k, bf16 out: 4096x2048x2048, 512 blocks, 33 us with 64 k per load phase against 44 us with 32;
     // 2048^3, 256 blocks, 27 against 22 us; 2048x2048x8192 81 against 66 us)
-    const bool k64 = stage_k64(p.transA != 0, p.transB != 0) && (BM == 256 || grid.x > (unsigned)kNumCU);
+    return stage_k64(p.transA != 0, p.transB != 0) && (tile == 256 || grid.x > (unsigned)kNumCU);
+}
+
+template <int BM>
+bool launch_tile(const GemmParams &p, const Plan &pl, bool raw, dim3 grid, hipStream_t st)
+{
+    const bool k64 = tile_k64(p, BM, grid);
     const int edge = tile_edge(pl, p.K, k64 ? 64 : 32);
     if (BM == 256) {
         if (edge == 2) fused_tile_256_kedge(p, k64, raw, grid, st);
@@ -208,9 +214,13 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
         if (sp.fast) return run_symm(a, sp, p, (hipStream_t)stream);
     }
 
-    const bool raw = pl.splitK > 1;
+    const bool sliced = pl.splitK > 1, small = !fewRows && small_ok(pl, p, a.plan), raw = sliced && !small;
     void *ws = nullptr;
     GemmParams pg = p;                      // the GEMM pass: partial tiles go to the workspace
+    if (small) {
+        st = check_unused_workspace(partial_bytes(a.M, a.N, a.batch, pl.splitK), a.workspace, a.workspace_bytes);
+        if (st != GE_OK) return st;
+    }
     if (raw) {
         st = acquire_workspace(partial_bytes(a.M, a.N, a.batch, pl.splitK), a.workspace, a.workspace_bytes, (hipStream_t)stream, &ws);
         if (st != GE_OK) return st;
@@ -245,7 +255,10 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
         else set_config("256x256x32_w8", a.transA, a.transB, raw);
         break;
     case TILE_128:
-        if (launch_tile<128>(pg, pl, raw, grid, hs)) set_config("128x128x64_w4", a.transA, a.transB, raw);
+        if (small) {
+            launch_small(p, hs);
+            set_config(tile_k64(p, 128, grid) ? "128x128x64_w4" : "128x128x32_w4", a.transA, a.transB, sliced);
+        } else if (launch_tile<128>(pg, pl, raw, grid, hs)) set_config("128x128x64_w4", a.transA, a.transB, raw);
         else set_config("128x128x32_w4", a.transA, a.transB, raw);
         break;
     case TILE_RAGGED_128:
@@ -253,8 +266,9 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
         set_config("ragged_128x128x64", a.transA, a.transB, raw);
         break;
     case TILE_RAGGED_64:
-        launch_ragged_64(pg, raw, grid, hs);
-        set_config("ragged_64x64x64", a.transA, a.transB, raw);
+        if (small) launch_small(p, hs);
+        else       launch_ragged_64(pg, raw, grid, hs);
+        set_config("ragged_64x64x64", a.transA, a.transB, sliced);
         break;
     default:
         if (raw) GE_LAUNCH(ge::gemm_bf16_fused_generic_kernel<true>, grid, dim3(256), 0, hs, pg);

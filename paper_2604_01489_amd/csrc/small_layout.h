@@ -1,0 +1,55 @@
+// Which 16-byte chunk of an operand each lane brings in, and where it lies in LDS, for the kernel of few output tiles (gemm_small.h), as
+// plain index functions that are compiled into the kernel and into the host-side model test.  The images are bf16_layout.h's, four of 64 k to a step.
+#pragma once
+#include "bf16_layout.h"
+#include "ragged_layout.h"
+
+namespace ge {
+
+constexpr int SMALL_STEP = 256;             // k of a step
+
+// Chunks that a lane of NW waves brings in per step of an operand BX wide
+template <int BX, int NW>
+GE_HD constexpr int small_chunks() { return BX / 2 / NW; }
+
+// Chunk j of a lane of wave w: its row (k row of the step if STRIDED) and chunk along it (of the step if not), and its place in the operand's
+// stage; neighbouring lanes, neighbouring chunks of a row, a wave's chunks within one image of 64 k.
+template <int BX, int NW, bool STRIDED>
+GE_HD constexpr void small_place(int j, int w, int lane, int &r, int &c, int &at)
+{
+    constexpr int PER_IMAGE = BX / 8;                        // wave-wide loads
+    const int idx = w * small_chunks<BX, NW>() + j, image = idx / PER_IMAGE, q = (idx % PER_IMAGE) * 64 + lane;
+    if constexpr (STRIDED) {
+        const int k = q / (BX / 8);
+        c = q % (BX / 8);
+        r = image * 64 + k;
+        at = image * (BX * 128) + (k / 32) * (BX * 64) + lds_b_offset<BX>(k % 32, c);
+    } else {
+        r = q / 8;
+        c = image * 8 + q % 8;
+        at = image * (BX * 128) + lds_a64_offset(r, q % 8);
+    }
+}
+
+// Whether a product whose plan names the 128 x 128 tile or (ragged) the 64 x 64 one of gemm_ragged.h goes to workgroups in 32 x 32 tiles: tiles of those,
+// K slices of the plan, K.  Up to one tile to a CU it does: us, plan's tile / small, 192 x 312 x 640 6.5 / 5.0, 264 x 232 x 1920 12.5 / 8.6 (B N x K,
+// bf16 out, 11.9 / 7.7), 72 x 1096 x 1160 9.0 / 6.2, 200^3 5.8 / 3.7, 512^3 5.8 / 4.9; over 21000 drawn calls 0.72 of the time on average and 1 % of
+// them slower by more than 3 %, all of one 64-k step, for which the other has a kernel of its own (533 x 416 x 47 3.6 / 4.0).
+// Beyond that only what is over in one step of 256, which has no walk to wait in: more than 128 k, up to two tiles a CU beside the 64 x 64 tile
+// (0.83 to 0.97 of its time) or three beside the 128 x 128 one (0.7 to 0.98; four 1.1); more than 64 k, two beside the latter (0.8 to 0.94; K <= 64 1.02; 640^3, 400 tiles, 6.5 / 6.9).
+// In place of K slices, which cost a second launch and its round trip, where one walk over K is the shorter way: 512 x 512 x 2048, five slices, 10.9 / 8.9, 44 x 690 x
+// 1109 8.8 / 6.3; aligned operands, whose slices are the longer kernel's, up to 2560 (144 x 448 x 2688 9.8 / 9.8), the others up to 1792 (40 x 1678 x 2119 9.1 / 10.9).
+constexpr int SMALL_CUS = 256;
+GE_HD constexpr bool small_tile_takes(long long tiles, int slices, int K, bool ragged)
+{
+    if (slices > 1) return tiles <= SMALL_CUS && K <= (ragged ? 1792 : 2560);
+    if (ragged && K <= 64) return false;
+    if (tiles <= SMALL_CUS) return true;
+    if (K > SMALL_STEP || K <= 64) return false;
+    return K > 128 ? tiles <= (ragged ? 2 : 3) * SMALL_CUS : !ragged && tiles <= 2 * SMALL_CUS;
+}
+
+// Steps whose sums form one chain before they are added to the others: a plan's K slice, so that the sums are as exact as in slices.
+GE_HD constexpr int small_run(int slices, int kPerSlice) { return slices > 1 ? (kPerSlice >= SMALL_STEP ? kPerSlice / SMALL_STEP : 1) : 0x7fffffff; }
+
+}  // namespace ge
