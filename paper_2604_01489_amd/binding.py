@@ -5,15 +5,22 @@ of ``libgemm_epilogue.so``.  Tensors are torch device tensors used purely as
 device memory; the stream is torch's current HIP stream unless one is given.
 There is no CPU fallback: if the library is missing or no GPU is present the
 calls raise.
+
+The calls that launch kernels go through native marshalling (``_marshal``, csrc/py_marshal.cpp) where every
+argument is what it takes; it returns None, before it has called anything, where one is not, and the code
+below, which says what a call does with its arguments, takes it from the start.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libgemm_epilogue.so")
 PROBES_LIB_PATH = os.path.join(_HERE, "libge_probes.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 ACT = {"none": 0, "relu": 1, "gelu_tanh": 2}
 PLAN = {"auto": 0, "direct": 1, "splitk": 2}
@@ -65,6 +72,9 @@ class ConvArgs(ctypes.Structure):
 
 _lib = None
 _probes = None
+_native = None        # the native marshalling, with the entry points' addresses and torch's stream queries for it
+_entry = {}
+_raw = None
 
 
 class GemmEpilogueError(RuntimeError):
@@ -75,7 +85,7 @@ class GemmEpilogueError(RuntimeError):
 
 def load():
     """Load the shared library (built by ``paper_2604_01489_amd.build``)."""
-    global _lib
+    global _lib, _native, _raw
     if _lib is not None:
         return _lib
     # PyTorch ships a HIP runtime of its own.  It has to be in the process before this library is, or the
@@ -83,9 +93,10 @@ def load():
     # hands over (every launch then fails with "no device").
     import torch  # noqa: F401
     path = os.environ.get("GE_LIBRARY", LIB_PATH)     # another build of the same library, for A/B timing
-    if not os.path.exists(path):
-        raise FileNotFoundError(
-            f"{path} is missing: run `python -m paper_2604_01489_amd.build` first")
+    for needed in (path, MARSHAL_PATH):
+        if not os.path.exists(needed):
+            raise FileNotFoundError(
+                f"{needed} is missing: run `python -m paper_2604_01489_amd.build` first")
     lib = ctypes.CDLL(path)
     c_int, c_void, c_float, c_size = ctypes.c_int, ctypes.c_void_p, ctypes.c_float, ctypes.c_size_t
     common = [c_int, c_int, c_int, c_void, c_int, c_void, c_int, c_void, c_float, c_int,
@@ -131,6 +142,15 @@ def load():
     lib.conv2d_epilogue_workspace_bytes.argtypes = [ctypes.POINTER(ConvArgs)]
     lib.ge_set_option.restype = c_int
     lib.ge_set_option.argtypes = [ctypes.c_char_p, ctypes.c_char_p]
+    spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    for name in ("gemm_epilogue_bf16", "gemm_epilogue_f32", "gemm_epilogue_bf16_fused", "conv2d_epilogue_bf16",
+                 "gemm_rowsum_params_bf16_ex", "gemm_rowsum_bf16"):
+        _entry[name] = ctypes.cast(getattr(lib, name), c_void).value
+    if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+        _raw = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    _native = native
     _lib = lib
     return lib
 
@@ -217,6 +237,10 @@ def _require_extent(t, rows, cols, ld, batch=1, what="operand"):
 def gemm_epilogue_bf16(M, N, K, A, lda, B, ldb, bias, alpha, act, C, ldc, batch=1, stream=None):
     """C = act(alpha*A@B + bias); A, B: device tensors of bf16 bit patterns
     (torch.bfloat16, int16 or uint16), bias/C: float32 device tensors."""
+    if _native is not None:
+        status = _native.plain(_entry["gemm_epilogue_bf16"], _raw, M, N, K, A, lda, B, ldb, bias, alpha, act, C, ldc, batch, stream)
+        if status is not None:
+            return _check(status)
     _require_device(A, B, C, bias)
     _require_operands(M, N, K, A, lda, B, ldb, bias, C, ldc, batch)
     _check(load().gemm_epilogue_bf16(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(bias), alpha,
@@ -225,6 +249,10 @@ def gemm_epilogue_bf16(M, N, K, A, lda, B, ldb, bias, alpha, act, C, ldc, batch=
 
 def gemm_epilogue_f32(M, N, K, A, lda, B, ldb, bias, alpha, act, C, ldc, batch=1, stream=None):
     """fp32 operands, fp32 matrix instructions."""
+    if _native is not None:
+        status = _native.plain(_entry["gemm_epilogue_f32"], _raw, M, N, K, A, lda, B, ldb, bias, alpha, act, C, ldc, batch, stream)
+        if status is not None:
+            return _check(status)
     _require_device(A, B, C, bias)
     _require_operands(M, N, K, A, lda, B, ldb, bias, C, ldc, batch)
     _check(load().gemm_epilogue_f32(M, N, K, _ptr(A), lda, _ptr(B), ldb, _ptr(bias), alpha,
@@ -308,6 +336,11 @@ def gemm_epilogue_bf16_fused(M, N, K, A, lda, B, ldb, C, ldc, *, batch=1, transA
     tensors.  A and B hold bf16 bits (int16/uint16/bfloat16 tensors); the output type follows
     ``C.dtype`` (float32 or bfloat16/int16), the residual's its tensor's.  ``a_structure``:
     "general", or the caller's promise that opA(A) is "lower" / "upper" triangular."""
+    if _native is not None:
+        status = _native.fused(_entry["gemm_epilogue_bf16_fused"], _raw, M, N, K, A, lda, B, ldb, C, ldc, batch, transA, transB, alpha,
+                               row_scale, bias, residual, ldr, beta, act, clamp, plan, split_k, workspace, stream, a_structure)
+        if status is not None:
+            return _check(status)
     import torch
     _require_device(A, B, C, row_scale, bias, residual, workspace)
     _require_operands(M, N, K, A, lda, B, ldb, bias, C, ldc, batch, transA, transB, residual, ldr)
@@ -349,6 +382,11 @@ def conv2d_epilogue_bf16(X, Wt, Y, *, stride=(1, 1), pad=(0, 0), dil=(1, 1), alp
                          beta=1.0, act="none", clamp=None, workspace=None, stream=None):
     """Channels-last convolution with the fused consumer chain on device tensors: ``X`` [N,H,W,Cin] and
     ``Wt`` [Cout,KH,KW,Cin] hold bf16 (bits), ``Y`` [N,OH,OW,Cout] is float32 or bfloat16."""
+    if _native is not None:
+        status = _native.conv(_entry["conv2d_epilogue_bf16"], _raw, X, Wt, Y, stride, pad, dil, alpha, bias, residual, beta, act, clamp,
+                              workspace, stream)
+        if status is not None:
+            return _check(status)
     import torch
     _require_device(X, Wt, Y, bias, residual, workspace)
 
@@ -380,6 +418,10 @@ def raw_diag(M, N, d_ptr, B_ptr, ldb, bias_ptr, alpha, act, C_ptr, ldc, batch) -
 def gemm_rowsum_params_bf16(N, K, B, ldb, transB, bias, params, workspace=None, stream=None):
     """``params[k] = sum_n opB(B)[k, n]`` for k < K, ``params[K] = sum(bias)``: the parameter-only part of
     the row sum of a linear layer, on device tensors."""
+    if _native is not None:
+        status = _native.rowsum_params(_entry["gemm_rowsum_params_bf16_ex"], _raw, N, K, B, ldb, transB, bias, params, workspace, stream)
+        if status is not None:
+            return _check(status)
     _require_device(B, bias, params, workspace)
     _require_extent(B, N if transB else K, K if transB else N, ldb, 1, "B")
     _require_extent(params, 1, K + 1, K + 1, 1, "params")
@@ -394,6 +436,10 @@ def rowsum_params_workspace_bytes(N, K, transB) -> int:
 
 def gemm_rowsum_bf16(M, K, A, lda, params, alpha, y, stream=None):
     """``y[m] = alpha * sum_k A[m, k] * params[k] + params[K]``: the row sum of the layer's output."""
+    if _native is not None:
+        status = _native.rowsum(_entry["gemm_rowsum_bf16"], _raw, M, K, A, lda, params, alpha, y, stream)
+        if status is not None:
+            return _check(status)
     _require_device(A, params, y)
     _check(load().gemm_rowsum_bf16(M, K, _ptr(A), lda, _ptr(params), alpha, _ptr(y), _stream_handle(stream)))
 

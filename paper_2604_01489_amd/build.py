@@ -1,5 +1,6 @@
 """Build step: compile the HIP sources into ``libgemm_epilogue.so`` (the operator) and
-``libge_probes.so`` (the measurement probes) for gfx950.
+``libge_probes.so`` (the measurement probes) for gfx950, and the binding's argument marshalling into
+an extension module of this interpreter.
 
 ``python -m paper_2604_01489_amd.build`` or ``build_library()``.  hipcc cross
 compiles without a GPU.  The library is kept in-tree, next to this file.
@@ -9,11 +10,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgemm_epilogue.so")
 PROBES_LIB = os.path.join(HERE, "libge_probes.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+MARSHAL_SOURCE = os.path.join(CSRC, "py_marshal.cpp")
 # the longest compiles first (the pool takes the sources in this order)
 LIB_SOURCES = ["conv_halo_14_11.hip", "conv_halo_12_12.hip", "conv_api.hip", "gemm_fused_t256.hip", "gemm_fused_t256_edge.hip", "gemm_fused_t256_kedge.hip", "gemm_fused_t128.hip",
                "gemm_fused_t128_edge.hip", "gemm_fused_t128_kedge.hip",
@@ -35,6 +39,23 @@ def _includes(path, seen):
     for inc in re.findall(r'^\s*#include\s+"([^"]+)"', open(path).read(), flags=re.M):
         _includes(os.path.normpath(os.path.join(os.path.dirname(path), inc)), seen)
     return seen
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """The extension module: host code only, against torch's headers and the libraries that ``import torch`` loads."""
+    import torch
+    top = os.path.dirname(torch.__file__)
+    lib = os.path.join(top, "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(top, "include"), "-o", MARSHAL, MARSHAL_SOURCE,
+           "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + lib]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("g++ failed on py_marshal.cpp")
+    return MARSHAL
 
 
 def build_library(verbose: bool = False, extra_flags=(), incremental: bool = False) -> str:
@@ -61,8 +82,15 @@ def build_library(verbose: bool = False, extra_flags=(), incremental: bool = Fal
             raise RuntimeError(f"hipcc failed on {src}")
         return obj
 
+    def marshal():
+        deps = _includes(MARSHAL_SOURCE, set())
+        if not incremental or not os.path.exists(MARSHAL) or any(os.path.getmtime(d) > os.path.getmtime(MARSHAL) for d in deps):
+            build_marshal(verbose)
+
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
+        marshalled = pool.submit(marshal)
         objs = list(pool.map(compile_one, SOURCES))
+        marshalled.result()
     n = len(LIB_SOURCES)
     for out, group in ((LIB, objs[:n]), (PROBES_LIB, objs[n:])):
         cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out, *group]
@@ -76,9 +104,9 @@ def build_library(verbose: bool = False, extra_flags=(), incremental: bool = Fal
 
 
 def library_is_current() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(PROBES_LIB):
+    if not all(os.path.exists(f) for f in (LIB, PROBES_LIB, MARSHAL)):
         return False
-    t = min(os.path.getmtime(LIB), os.path.getmtime(PROBES_LIB))
+    t = min(os.path.getmtime(f) for f in (LIB, PROBES_LIB, MARSHAL))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)]
     inc = os.path.join(os.path.dirname(HERE), "include")
     deps += [os.path.join(inc, f) for f in os.listdir(inc)]
