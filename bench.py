@@ -42,7 +42,7 @@ BOUND = {
     "c7_fused_tn_8192_chain": "mfma",
     "c8_fused_batched_512x512x64_bf16out": "hbm",
     "c11_fused_lower_8192_bias_relu": "mfma",
-    "c1_f32_256": "mfma",
+    "c1_f32_256": ("f32_small_32x32_k4", 807, 256, ('bf16_layout.h', 'ge_device.h', 'gemm_f32_few.h', 'ragged_layout.h', 'small_layout.h'), "f9534648b2de2406"),
     "c13_f32_8192x8192x2048": "mfma",
 }
 # 16-byte pieces read : written by the HBM-bound workloads, for the stream probe of the same mix
@@ -69,7 +69,7 @@ _F32 = ("bf16_layout.h", "ge_device.h", "gemm_f32_fast.h")
 # workload -> (kernel configuration, FETCH_SIZE KiB, WRITE_SIZE KiB, source files, their hash)
 # TRAFFIC-BEGIN (rows written from the counter runs; see profiles/)
 TRAFFIC = {
-    "c1_f32_256": ("f32_small_32x32_k4", 1243, 256, ('bf16_layout.h', 'ge_device.h', 'gemm_f32_small.h'), "498771dccb580fbe"),
+    "c1_f32_256": ("f32_small_32x32_k4", 807, 256, ('bf16_layout.h', 'ge_device.h', 'gemm_f32_few.h', 'ragged_layout.h', 'small_layout.h'), "f9534648b2de2406"),
     "c2_bf16_4096": ("bf16_256x256x64_w4", 98447, 65536, _MAIN_W4, "22b85d300136d772"),
     "c3_bf16_8192_bias_gelu": ("bf16_256x256x64_w4", 792297, 262146, _MAIN_W4, "22b85d300136d772"),
     "c4_bf16_batched_512x512x64": ("bf16_256x256x32_w8", 16469, 262147, _MAIN_W8, "106d9e23471a6331"),

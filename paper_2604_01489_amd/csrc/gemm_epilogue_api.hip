@@ -15,8 +15,8 @@
 #include "gemm_bf16_fast.h"
 #include "gemm_bf16_w4.h"
 #include "gemm_f32_fast.h"
+#include "gemm_f32_few.h"
 #include "gemm_f32_ragged.h"
-#include "gemm_f32_small.h"
 #include "gemm_generic.h"
 #include "gemm_ragged_launch.h"
 #include "gemm_skinny.h"
@@ -707,16 +707,6 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
     bool fast = !((((uintptr_t)A) | ((uintptr_t)B)) & 15u) && !((lda | ldb | N | K) & 3) &&
                 (long long)lda * 4 * 128 + 256 < (1ll << 31) && (long long)ldb * 4 * 16 + 1024 < (1ll << 31) &&
                 opt_force_config() != FORCE_GENERIC;
-    // a small product (at most 64 tiles of 64 x 64, K below the length worth slicing): 32 x 32 tiles whose four
-    // waves share K, so that four times as many SIMDs work on chains a quarter as long (gemm_f32_small.h)
-    if (fast && M % 32 == 0 && N % 32 == 0 && K % 256 == 0 && K < 1024 &&
-        (long long)ceil_div(M, 64) * ceil_div(N, 64) * batch <= 64) {
-        p.tilesM = M / 32;
-        p.tilesN = N / 32;
-        GE_LAUNCH(ge::gemm_f32_small_kernel, dim3((unsigned)(p.tilesM * p.tilesN * batch)), dim3(256), 0, hs, p);
-        g_last_config = "f32_small_32x32_k4";
-        return ge_host::take_launch_error() != hipSuccess ? GE_ERR_LAUNCH : GE_OK;
-    }
     const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128) * batch, t64 = (long long)ceil_div(M, 64) * ceil_div(N, 64) * batch;
     const long long outputs = (long long)batch * M * N;
     // 128x128 tiles once they give every other CU a block, else 64x64 (more blocks, less padding)
@@ -765,7 +755,25 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
         while (st == GE_ERR_WORKSPACE && perPass > atLeast) st = acquire_workspace(partial_bytes(M, N, batch, --perPass), nullptr, 0, hs, &ws);
         if (st != GE_OK) return st;
     }
+    // few tiles and no slices: smaller ones (gemm_f32_few.h), for rows of a chunk or more and panels within 31-bit byte offsets; one step of the
+    // direct-to-LDS kernel (K <= 16) is over as soon (5 x 40 x 8 3.1 us, 3.2 there)
+    const int few = raw || elementwise || (fast && K <= 16) || opt_force_config() == FORCE_GENERIC || K < 4 || N < 4 || (long long)lda * 128 + 1024 >= (1ll << 31) || (long long)ldb * 1024 + 1024 >= (1ll << 31) ? 0
+                  : ge::few_tile_f32((long long)ceil_div(M, 16) * ceil_div(N, 16) * batch, (long long)ceil_div(M, 32) * ceil_div(N, 32) * batch, K);
     const bool edge = (M % bm) || (N % bm) || (K % 16);
+    auto launch_few = [&](GemmParams pg) {
+        pg.tilesM = ceil_div(M, few);
+        pg.tilesN = ceil_div(N, few);
+        pg.groupM = choose_group_m(pg.tilesM, pg.tilesN);
+        const dim3 grid((unsigned)((long long)pg.tilesM * pg.tilesN * batch)), block(256);
+        const bool one = K <= ge::few_step_f32(few);
+        if (few == 16) {
+            if (one) GE_LAUNCH((ge::gemm_f32_few_kernel<16, 1>), grid, block, 0, hs, pg);
+            else     GE_LAUNCH((ge::gemm_f32_few_kernel<16, 2>), grid, block, 0, hs, pg);
+        } else {
+            if (one) GE_LAUNCH((ge::gemm_f32_few_kernel<32, 1>), grid, block, 0, hs, pg);
+            else     GE_LAUNCH((ge::gemm_f32_few_kernel<32, 2>), grid, block, 0, hs, pg);
+        }
+    };
     auto launch_tiles = [&](const GemmParams &pg) {
         const dim3 grid((unsigned)(tiles * pg.splitK)), block(256);
         auto by_edge = [&](auto bt, auto rawC) {
@@ -800,8 +808,11 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
                                             {"f32_ragged_128x128x32", "f32_ragged_128x128x32_splitk", "f32_ragged_128x128x32_splitk_passes"},
                                             {"f32_elements_64x64x32", "f32_elements_64x64x32_splitk", "f32_elements_64x64x32_splitk_passes"}};
     g_last_config = names[elementwise ? 4 : (fast ? 0 : 2) + (big ? 1 : 0)][!raw ? 0 : perPass == p.splitK ? 1 : 2];
+    // (few tiles in whole 32s and 256 k went by this name when they had a kernel of their own)
+    if (few && fast && M % 32 == 0 && N % 32 == 0 && K % 256 == 0 && t64 <= 64) g_last_config = "f32_small_32x32_k4";
     if (!raw) {
-        launch_tiles(p);
+        if (few) launch_few(p);
+        else     launch_tiles(p);
         return ge_host::take_launch_error() != hipSuccess ? GE_ERR_LAUNCH : GE_OK;
     }
     for (int done = 0; done < p.splitK;) {

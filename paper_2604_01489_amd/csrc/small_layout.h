@@ -52,4 +52,34 @@ GE_HD constexpr bool small_tile_takes(long long tiles, int slices, int K, bool r
 // Steps whose sums form one chain before they are added to the others: a plan's K slice, so that the sums are as exact as in slices.
 GE_HD constexpr int small_run(int slices, int kPerSlice) { return slices > 1 ? (kPerSlice >= SMALL_STEP ? kPerSlice / SMALL_STEP : 1) : 0x7fffffff; }
 
+// fp32 (gemm_f32_few.h): 32 x 32 tiles in steps of 128 k, 16 x 16 ones in steps of 256, 16 KB of either operand to a step.  Rows of A along k and k rows
+// of B, padded by 16 bytes: a wave reads 16 bytes of 16 rows of A, and a column's element of k rows four apart of B.
+GE_HD constexpr int few_step_f32(int BT) { return 4096 / BT; }
+GE_HD constexpr int few_pitch_a(int BT) { return few_step_f32(BT) * 4 + 16; }
+GE_HD constexpr int few_pitch_b(int BT) { return BT * 4 + 16; }
+GE_HD constexpr int few_at_a(int BT, int row, int k) { return row * few_pitch_a(BT) + k * 4; }
+GE_HD constexpr int few_at_b(int BT, int k, int col) { return k * few_pitch_b(BT) + col * 4; }
+
+// chunk j (of four floats) of a lane of wave w: its row (k row if STRIDED), chunk along it, and place in the operand's stage
+template <int BT, bool STRIDED>
+GE_HD constexpr void few_place_f32(int j, int w, int lane, int &r, int &c, int &at)
+{
+    constexpr int PER_ROW = (STRIDED ? BT : few_step_f32(BT)) / 4;
+    const int q = (j * 4 + w) * 64 + lane;
+    r = q / PER_ROW;
+    c = q % PER_ROW;
+    at = STRIDED ? few_at_b(BT, r, c * 4) : few_at_a(BT, r, c * 4);
+}
+
+// The tile an fp32 product of tiles16 16 x 16 tiles, or tiles32 32 x 32 ones, that takes no K slices is dealt out in, or 0: neither, it stays on the larger ones.
+// us, 64 x 64 tile / 32 / 16: 256^3 (on tiles of 32 that read from memory directly) 6.2 / 5.5 / 3.8; 142 x 343 x 983 23.2 / 11.6 / 7.2; 80 x 100 x 512 13.0 / 7.7 / 4.9; 320 x 336 x 888
+// 21.0 / 11.1 / 9.1; 256 x 938 x 347 10.3 / 7.1 / 10.8; 512^3 8.7 / 8.1 / 11.2; 550 x 192 x 128 5.6 / 4.1 / 4.3; 320 x 1864 x 384, 590 tiles of 32, 11.2 / 13.6 / 22.4.
+// 14000 drawn calls: 16 up to two a CU 0.30 (K = 1000) to 0.75 of the time (K = 100), of which the second tile of a CU pays from 128 k on; 32 up to one a CU 0.5 to 0.8, and
+// 0.97 for K <= 64; up to two 0.75 to 0.88 with more than 256 k, with fewer 0.9 to 1.1.
+GE_HD constexpr int few_tile_f32(long long tiles16, long long tiles32, int K)
+{
+    if (K > 64 && tiles16 <= (K > 128 ? 2 : 1) * SMALL_CUS) return 16;
+    return tiles32 <= (K > 256 ? 2 : 1) * SMALL_CUS ? 32 : 0;
+}
+
 }  // namespace ge

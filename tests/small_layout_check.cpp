@@ -1,5 +1,5 @@
 // Host model of how the kernel of few output tiles fills its LDS stages and reads its fragments: every read lies inside the operand, every
-// element of a step is where the fragment of its row and k is read, and which products take the kernel (the sizes of test_gpu_small.py among them).
+// element of a step is where the fragment of its row and k is read, and which products take the kernel (test_gpu_small.py and test_gpu_f32_few.py lie on its sides).
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -63,8 +63,66 @@ void run(int X, int K, int ld)
         }
 }
 
+// fp32: 32 x 32 tiles, or 16 x 16 ones whose waves share a step's k
+template <int BT, bool STRIDED>
+void run_f32(int X, int K, int ld)
+{
+    constexpr int STEP = few_step_f32(BT), PITCH = STRIDED ? few_pitch_b(BT) : few_pitch_a(BT), STAGE = STRIDED ? STEP * PITCH : BT * PITCH;
+    const int rowsTotal = STRIDED ? K : X, payload = STRIDED ? X : K;
+    if (payload < 4 || K < 4) return;
+    const long long size = (long long)(rowsTotal - 1) * ld + payload;
+    auto value = [&](long long e) { return (int)(e % 65521) + 1; };
+    const int nk = (K + STEP - 1) / STEP;
+    for (int x0 = 0; x0 < X; x0 += BT)
+        for (int t = 0; t < nk; ++t) {
+            const int k0 = t * STEP, left = X - x0;
+            const long long base = STRIDED ? (long long)k0 * ld + x0 : (long long)x0 * ld + k0;
+            std::vector<int> stage(STAGE / 4, -1);
+            for (int w = 0; w < 4; ++w)
+                for (int lane = 0; lane < 64; ++lane)
+                    for (int j = 0; j < 4; ++j) {
+                        int r = 0, c = 0, at = 0, sh = 0;
+                        long long off = 0;
+                        few_place_f32<BT, STRIDED>(j, w, lane, r, c, at);
+                        if (t + 1 < nk) off = ragged_offset<STRIDED, 4>(r, c, ld, left);
+                        else ragged_last<STRIDED, 4>(r, c, ld, left, K - k0, off, sh);
+                        if (base + off < 0 || base + off + 4 > size || at % 16 || at + 16 > STAGE) {
+                            std::printf("fp32 BT %d strided %d X %d K %d ld %d x0 %d step %d: read %lld of %lld, place %d\n", BT, STRIDED, X, K, ld, x0, t, base + off, size, at);
+                            std::exit(1);
+                        }
+                        for (int e = 0; e < 4; ++e) stage[at / 4 + e] = e + sh < 4 ? value(base + off + e + sh) : 0;
+                    }
+            for (int x = 0; x < BT && x0 + x < X; ++x)
+                for (int k = 0; k < STEP; ++k) {
+                    const int at = (STRIDED ? few_at_b(BT, k, x) : few_at_a(BT, x, k)) / 4;
+                    const long long from = STRIDED ? (long long)(k0 + k) * ld + x0 + x : (long long)(x0 + x) * ld + k0 + k;
+                    const int want = k0 + k < K ? value(from) : 0;
+                    if (stage[at] != want) {
+                        std::printf("fp32 BT %d strided %d X %d K %d ld %d: x %d k %d holds %d, not %d\n", BT, STRIDED, X, K, ld, x0 + x, k0 + k, stage[at], want);
+                        std::exit(1);
+                    }
+                    ++checked;
+                }
+        }
+}
+
 int main()
 {
+    for (int X : {1, 3, 4, 5, 15, 16, 17, 32, 33, 70})
+        for (int K : {4, 5, 31, 127, 128, 129, 255, 256, 257, 515, 1023})
+            for (int pad : {0, 1, 3}) {
+                run_f32<32, false>(X, K, K + pad);
+                run_f32<32, true>(X, K, X + pad);
+                run_f32<16, false>(X, K, K + pad);
+                run_f32<16, true>(X, K, X + pad);
+            }
+    struct { long long t16, t32; int K, tile; } few[] = {{256, 64, 256, 16}, {256, 64, 65, 16}, {256, 64, 64, 32}, {512, 140, 129, 16}, {512, 140, 128, 32}, {513, 140, 1000, 32},
+                                                          {1024, 256, 64, 32}, {1100, 257, 256, 0}, {1100, 257, 257, 32}, {2048, 512, 512, 32}, {2052, 513, 512, 0}};
+    for (auto &c : few)
+        if (few_tile_f32(c.t16, c.t32, c.K) != c.tile) {
+            std::printf("rule: %lld and %lld tiles, K %d\n", c.t16, c.t32, c.K);
+            return 1;
+        }
     for (int X : {1, 7, 8, 9, 31, 32, 33, 40, 65, 100})
         for (int K : {8, 9, 31, 63, 64, 65, 255, 256, 257, 263, 264, 511, 512, 513, 769, 1031})
             for (int pad : {0, 1, 3, 8}) {
