@@ -42,7 +42,7 @@ BOUND = {
     "c7_fused_tn_8192_chain": "mfma",
     "c8_fused_batched_512x512x64_bf16out": "hbm",
     "c11_fused_lower_8192_bias_relu": "mfma",
-    "c1_f32_256": ("f32_small_32x32_k4", 807, 256, ('bf16_layout.h', 'ge_device.h', 'gemm_f32_few.h', 'ragged_layout.h', 'small_layout.h'), "f9534648b2de2406"),
+    "c1_f32_256": "mfma",
     "c13_f32_8192x8192x2048": "mfma",
 }
 # 16-byte pieces read : written by the HBM-bound workloads, for the stream probe of the same mix
