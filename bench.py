@@ -69,7 +69,7 @@ _F32 = ("bf16_layout.h", "ge_device.h", "gemm_f32_fast.h")
 # workload -> (kernel configuration, FETCH_SIZE KiB, WRITE_SIZE KiB, source files, their hash)
 # TRAFFIC-BEGIN (rows written from the counter runs; see profiles/)
 TRAFFIC = {
-    "c1_f32_256": ("f32_small_32x32_k4", 807, 256, ('bf16_layout.h', 'ge_device.h', 'gemm_f32_few.h', 'ragged_layout.h', 'small_layout.h'), "f9534648b2de2406"),
+    "c1_f32_256": ("f32_small_32x32_k4", 807, 256, ('bf16_layout.h', 'ge_device.h', 'gemm_f32_few.h', 'ragged_layout.h', 'small_layout.h'), "ca11123253c48852"),
     "c2_bf16_4096": ("bf16_256x256x64_w4", 98447, 65536, _MAIN_W4, "22b85d300136d772"),
     "c3_bf16_8192_bias_gelu": ("bf16_256x256x64_w4", 792297, 262146, _MAIN_W4, "22b85d300136d772"),
     "c4_bf16_batched_512x512x64": ("bf16_256x256x32_w8", 16469, 262147, _MAIN_W8, "106d9e23471a6331"),

@@ -12,7 +12,9 @@
 #include "conv_rows.h"
 #include "gemm_bf16_fast.h"
 #include "gemm_fused.h"
+#include "gemm_small_launch.h"
 #include "ge_host.h"
+#include "small_layout.h"
 
 namespace {
 
@@ -272,9 +274,17 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
 
     // few output tiles and a long K (late layers: small images, many channels): K slices into the
     // library's workspace, summed in slice order by the second pass, which also runs the chain
-    const bool raw = pl.splitK > 1;
+    const bool sliced = pl.splitK > 1;
+    // few tiles: in smaller ones, with the sums of the plan (gemm_small.h); a workspace that is given is held to the plan's size all the same
+    const bool small = pl.tile == TILE_128 && opt_force_config() == FORCE_NONE &&
+                       ge::small_conv_takes((long long)ceil_div(M, 32) * ceil_div(a.Cout, 32), pl.splitK, (int)K, cp.c8);
+    const bool raw = sliced && !small;
     void *ws = nullptr;
     GemmParams pg = p;
+    if (small) {
+        st = check_unused_workspace(partial_bytes((int)M, a.Cout, 1, pl.splitK), a.workspace, a.workspace_bytes);
+        if (st != GE_OK) return st;
+    }
     if (raw) {
         st = acquire_workspace(partial_bytes((int)M, a.Cout, 1, pl.splitK), a.workspace, a.workspace_bytes, (hipStream_t)stream, &ws);
         if (st != GE_OK) return st;
@@ -293,13 +303,14 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
         g_last_config = raw ? "conv_bf16_256x256x32_w8_splitk" : "conv_bf16_256x256x32_w8";
         break;
     case TILE_128:
+        if (small) launch_small(p, hs);
+        else if (cp.c8) launch_conv_c8<128, 128, 2, 2>(pg, raw, grid, hs);
+        else launch_conv<128, 128, 2, 2>(pg, pl.edge, raw, grid, hs);
         if (cp.c8) {
-            launch_conv_c8<128, 128, 2, 2>(pg, raw, grid, hs);
-            g_last_config = raw ? "conv_bf16_c8_128x128x32_w4_splitk" : "conv_bf16_c8_128x128x32_w4";
+            g_last_config = sliced ? "conv_bf16_c8_128x128x32_w4_splitk" : "conv_bf16_c8_128x128x32_w4";
             break;
         }
-        launch_conv<128, 128, 2, 2>(pg, pl.edge, raw, grid, hs);
-        g_last_config = raw ? "conv_bf16_128x128x32_w4_splitk" : "conv_bf16_128x128x32_w4";
+        g_last_config = sliced ? "conv_bf16_128x128x32_w4_splitk" : "conv_bf16_128x128x32_w4";
         break;
     default:
         if (raw) GE_LAUNCH(ge::conv_bf16_generic_kernel<true>, grid, dim3(256), 0, hs, pg);

@@ -1,4 +1,4 @@
-// bf16 GEMM for few output tiles: 32 x BN tiles, 256 k to a step, operands of any alignment.
+// bf16 GEMM and convolution for few output tiles: 32 x 32 tiles, 256 k to a step, operands of any alignment.
 //
 // What bounds such a product on the larger tiles is neither bytes nor the matrix pipes: a block walks K alone on its CU, one barrier and
 // one trip through LDS after the other (0.28 us for each 64 k of a 64 x 64 tile, of which the multiplies are 0.05), and most CUs have
@@ -61,14 +61,53 @@ struct SmallChunks {
     }
 };
 
-// A stored M x K or (TA) K x M, B stored K x N or (TB) N x K; the run-time consumer chain with fp32 or (OUTBF16) bf16 output.  run: steps
+// The gathered rows of a convolution in the same places: row r of the tile is an output position, a chunk eight channels of one filter tap (channels are a
+// multiple of 8), the same ones for all of a lane's chunks.  Padding, positions beyond the last and k beyond the last read zeros, out of the resource's range.
+template <int NW>
+struct SmallConvRows {
+    static constexpr int NL = small_chunks<32, NW>();
+    typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
+    int ih0[NL], iw0[NL], k0;               // input row and column of tap (0, 0); k of the lane's chunk in the first step
+    unsigned off[NL];                       // byte offset of that element, modulo 2^32 (it may lie in the padding)
+    buffer_t rows;
+
+    __device__ __forceinline__ void init(const GemmParams &p, int m0, int w, int lane)
+    {
+        rows = __builtin_amdgcn_make_buffer_rsrc((void *)p.A, 0, (int)p.bytesA, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            int r, c, place;
+            small_place<32, NW, false>(j, w, lane, r, c, place);
+            const int m = m0 + r, pos = m % (p.convOH * p.convOW), img = m / (p.convOH * p.convOW), oh = pos / p.convOW, ow = pos % p.convOW;
+            const int row = oh * p.convSh - p.convPh;
+            ih0[j] = m < p.M ? row : -(1 << 24);
+            iw0[j] = ow * p.convSw - p.convPw;
+            off[j] = (unsigned)((img * p.convH + row) * p.convW + iw0[j]) * (unsigned)p.convCin * 2u;
+            k0 = c * 8;
+        }
+    }
+    __device__ __forceinline__ void load(const GemmParams &p, int t, i32x4_t (&v)[NL]) const
+    {
+        const int k = t * SMALL_STEP + k0, tap = (int)((unsigned)k / (unsigned)p.convCin), kh = (int)((unsigned)tap / (unsigned)p.convKW);
+        const int dIh = kh * p.convDh, dIw = (tap - kh * p.convKW) * p.convDw;
+        const unsigned tapOff = (unsigned)(((dIh * p.convW + dIw) * p.convCin + (k - tap * p.convCin)) * 2);
+#pragma unroll
+        for (int j = 0; j < NL; ++j) {
+            const bool inside = k < p.K && (unsigned)(ih0[j] + dIh) < (unsigned)p.convH && (unsigned)(iw0[j] + dIw) < (unsigned)p.convW;
+            v[j] = __builtin_bit_cast(i32x4_t, (u32x4_t)__builtin_amdgcn_raw_buffer_load_b128(rows, (int)(inside ? off[j] + tapOff : 0x80000000u), 0, 0));
+        }
+    }
+};
+
+// A stored M x K or (TA) K x M, or (CONV) the gathered rows of a convolution, B stored K x N or (TB) N x K; the run-time consumer chain with fp32 or (OUTBF16) bf16 output.  run: steps
 // whose sums form one chain (small_run).
 // DEPTH: steps on their way in registers (one: K is one step at most).
-template <int DEPTH, bool TA, bool TB, bool OUTBF16>
+template <int DEPTH, bool TA, bool TB, bool OUTBF16, bool CONV = false>
 __global__ void __launch_bounds__(256)
 gemm_bf16_small_kernel(const GemmParams p, int run)
 {
     constexpr int BM = 32, BN = 32, NW = 4, WN = 2, STAGE_A = BM * 512, STAGE_B = BN * 512, STAGES = DEPTH == 1 ? 1 : 2;
+    static_assert(!CONV || (!TA && TB), "rows along k, filters as N x K");
     using ChunksA = SmallChunks<BM, NW, TA>;
     using ChunksB = SmallChunks<BN, NW, !TB>;
     __shared__ __attribute__((aligned(1024))) char smem[STAGES * (STAGE_A + STAGE_B)];
@@ -83,9 +122,10 @@ gemm_bf16_small_kernel(const GemmParams p, int run)
     const char *gA = (const char *)p.A + 2 * ((long long)tc.b * p.strideA + (TA ? (long long)m0 : (long long)m0 * p.lda));
     const char *gB = (const char *)p.B + 2 * ((long long)tc.b * p.strideB + (TB ? (long long)n0 * p.ldb : (long long)n0));
     const long long stepA = (TA ? (long long)p.lda : 1ll) * SMALL_STEP * 2, stepB = (TB ? 1ll : (long long)p.ldb) * SMALL_STEP * 2;
-    ChunksA ca;
+    std::conditional_t<CONV, SmallConvRows<NW>, ChunksA> ca;
     ChunksB cb;
-    ca.init(p.lda, p.M - m0, kLast, w, lane);
+    if constexpr (CONV) ca.init(p, m0, w, lane);
+    else ca.init(p.lda, p.M - m0, kLast, w, lane);
     cb.init(p.ldb, p.N - n0, kLast, w, lane);
     i32x4_t va[DEPTH][ChunksA::NL], vb[DEPTH][ChunksB::NL];
     // (steps beyond the last are the last one again: no load behind a branch)
@@ -93,13 +133,14 @@ gemm_bf16_small_kernel(const GemmParams p, int run)
         constexpr int S = decltype(set)::value;
         const bool last = t + 1 >= nk;
         const int tt = last ? nk - 1 : t;
-        ca.load(gA + tt * stepA, last, va[S]);
+        if constexpr (CONV) ca.load(p, tt, va[S]);
+        else ca.load(gA + tt * stepA, last, va[S]);
         cb.load(gB + tt * stepB, last, vb[S]);
     };
     auto store = [&](auto set, bool last) __attribute__((always_inline)) {
         constexpr int S = decltype(set)::value;
         if (last) {
-            ca.settle_last(kLast, w, lane, va[S]);
+            if constexpr (!CONV) ca.settle_last(kLast, w, lane, va[S]);
             cb.settle_last(kLast, w, lane, vb[S]);
         }
         ChunksA::store(lds + S % STAGES * STAGE_A, w, lane, va[S]);

@@ -24,6 +24,13 @@ void launch_small_depth(const GemmParams &p, int run, dim3 grid, hipStream_t st)
     else                        launch_small_mode<DEPTH, false>(p, run, grid, st);
 }
 
+template <int DEPTH>
+void launch_small_conv_depth(const GemmParams &p, int run, dim3 grid, hipStream_t st)
+{
+    if (p.cType == ge::DT_BF16) GE_LAUNCH((ge::gemm_bf16_small_kernel<DEPTH, false, true, true, true>), grid, dim3(256), 0, st, p, run);
+    else                        GE_LAUNCH((ge::gemm_bf16_small_kernel<DEPTH, false, true, false, true>), grid, dim3(256), 0, st, p, run);
+}
+
 void launch_small(GemmParams p, hipStream_t st)
 {
     const int run = ge::small_run(p.splitK, p.kPerSlice);
@@ -31,8 +38,11 @@ void launch_small(GemmParams p, hipStream_t st)
     p.tilesN = ceil_div(p.N, 32);
     p.groupM = choose_group_m(p.tilesM, p.tilesN);
     const dim3 grid((unsigned)((long long)p.tilesM * p.tilesN * p.batch));
-    if (p.K <= ge::SMALL_STEP) launch_small_depth<1>(p, run, grid, st);
-    else                       launch_small_depth<2>(p, run, grid, st);
+    if (p.convKH > 0) {
+        if (p.K <= ge::SMALL_STEP) launch_small_conv_depth<1>(p, run, grid, st);
+        else                       launch_small_conv_depth<2>(p, run, grid, st);
+    } else if (p.K <= ge::SMALL_STEP) launch_small_depth<1>(p, run, grid, st);
+    else launch_small_depth<2>(p, run, grid, st);
 }
 
 }  // namespace ge_host

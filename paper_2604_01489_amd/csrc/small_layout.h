@@ -49,6 +49,18 @@ GE_HD constexpr bool small_tile_takes(long long tiles, int slices, int K, bool r
     return K > 128 ? tiles <= (ragged ? 2 : 3) * SMALL_CUS : !ragged && tiles <= 2 * SMALL_CUS;
 }
 
+// The same for a convolution whose plan names the 128 x 128 tile; c8: of the kernel for channels a multiple of 8 but not of 32.  Its gathered rows cost that tile 0.4 us for each
+// 32 k, so the lines lie further out.  us, plan's tile / small: 8 images of 14 x 14 x 256 -> 64, 1 x 1, 6.9 / 3.9; 14 of 13 x 13 x 256 -> 32, 3 x 3, in slices 11.9 / 9.4; of its time over 9000 drawn
+// calls, up to two tiles a CU: K = 64 0.78 to 0.91, 256 0.55 to 0.65, 576 0.56 to 0.70, 1152 0.46 to 0.58, in slices 2304 0.72 to 0.86 (4608 1.0 to 1.4), c8 0.38 to 0.9.  Three: 65 to 256 k 0.94
+// and 0.77, 1152 0.87, c8 0.70 to 0.85 (288 to 576 k 1.0 to 1.24); four: 129 to 256 k 0.87.
+GE_HD constexpr bool small_conv_takes(long long tiles, int slices, int K, bool c8)
+{
+    if (slices > 1) return tiles <= 2 * SMALL_CUS && K <= 2560;
+    if (tiles <= 2 * SMALL_CUS) return true;
+    if (K > 128 && K <= SMALL_STEP) return tiles <= 4 * SMALL_CUS;
+    return tiles <= 3 * SMALL_CUS && (K <= 128 ? K > 64 : K > 768 || c8);
+}
+
 // Steps whose sums form one chain before they are added to the others: a plan's K slice, so that the sums are as exact as in slices.
 GE_HD constexpr int small_run(int slices, int kPerSlice) { return slices > 1 ? (kPerSlice >= SMALL_STEP ? kPerSlice / SMALL_STEP : 1) : 0x7fffffff; }
 

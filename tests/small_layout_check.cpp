@@ -140,6 +140,14 @@ int main()
             std::printf("rule: %lld tiles, %d slices, K %d, ragged %d\n", c.tiles, c.slices, c.K, c.ragged);
             return 1;
         }
+    struct { long long tiles; int slices, K; bool c8, takes; } conv[] = {{512, 1, 27 * 8, true, true}, {512, 1, 64, false, true}, {513, 1, 64, false, false}, {513, 1, 72, false, true},
+        {1024, 1, 136, false, true}, {1025, 1, 136, true, false}, {768, 1, 288, false, false}, {768, 1, 288, true, true}, {768, 1, 1152, false, true}, {769, 1, 1152, true, false},
+        {512, 4, 2304, false, true}, {513, 4, 2304, false, false}, {20, 8, 4608, false, false}};
+    for (auto &c : conv)
+        if (small_conv_takes(c.tiles, c.slices, c.K, c.c8) != c.takes) {
+            std::printf("rule of convolutions: %lld tiles, %d slices, K %d, c8 %d\n", c.tiles, c.slices, c.K, c.c8);
+            return 1;
+        }
     if (small_run(1, 64) < 1 << 30 || small_run(3, 512) != 2 || small_run(3, 672) != 2 || small_run(8, 128) != 1) return 1;
     std::printf("small layout ok: %lld elements\n", checked);
     return 0;

@@ -9,6 +9,7 @@ import pytest
 from paper_2604_01489_amd import binding
 
 from gpu_util import run_case, run_fused_case
+from test_gpu_conv import run_conv_case
 
 LAYOUTS = [(False, False), (False, True), (True, False), (True, True)]
 
@@ -94,3 +95,43 @@ def test_a_workspace_that_was_too_small_still_is():
         binding.gemm_epilogue_bf16_ex(M, N, K, A, K, B, N, None, 1.0, "none", C, N, workspace=torch.empty(1024, device="cuda"))
     binding.gemm_epilogue_bf16_ex(M, N, K, A, K, B, N, None, 1.0, "none", C, N, workspace=torch.empty(need // 4, device="cuda"))
     torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,kw", [
+    ((1, 7, 5, 8, 32, 3, 3), dict(pad=(1, 1))),                                                    # a tap to a chunk; guarded kernel below a million multiply-adds
+    ((2, 15, 17, 24, 136, 3, 3), dict(pad=(1, 1), residual="bf16", out="bf16")),                    # one step of 216, taps that end inside a chunk's neighbours
+    ((9, 14, 13, 40, 72, 5, 4), dict(stride=(1, 2), pad=(2, 0), dil=(2, 1), act="gelu_tanh")),      # four steps, every way the geometry enters
+    ((2, 20, 20, 64, 64, 3, 3), dict(pad=(1, 1), out="bf16")),                                      # 576: three steps
+    ((3, 9, 9, 256, 40, 1, 1), dict(residual="f32", beta=-0.5, clamp=(-0.5, 0.5))),                 # one full step, no padding
+    ((4, 9, 9, 128, 96, 3, 3), dict(pad=(0, 2), stride=(3, 2), out="bf16")),                        # 1152: five
+    ((1, 12, 12, 256, 128, 3, 3), dict(pad=(1, 1), residual="bf16", out="bf16")),                   # 2304, in place of slices
+    ((1, 11, 9, 264, 96, 3, 3), dict(pad=(1, 1)))])                                                 # 2376 of channels a multiple of 8
+def test_convolutions(oracle, shape, kw):
+    outs = []
+    for option in (None, "128x128"):
+        binding.set_option("force_config", option)
+        kw2 = dict(kw)
+        outs.append(run_conv_case(oracle, shape, alpha=0.75, act=kw2.pop("act", "relu"), seed=sum(shape), **kw2))
+    assert outs[0].replace("_splitk", "") == outs[1].replace("_splitk", "") or "generic" in outs[0], outs
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,h,cin,cout", [(1, 14, 256, 96), (2, 9, 264, 128)])
+def test_convolutions_are_as_exact_as_slices(n, h, cin, cout):
+    """3 x 3, K of 2304 and 2376 in place of slices (the switch keeps the plan's tile and its slices).  18000 outputs and more: the norm of the errors is
+    steady to two percent."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(cin)
+    X, W = torch.randn(n, h, h, cin, device="cuda", generator=g).bfloat16(), torch.randn(cout, 3, 3, cin, device="cuda", generator=g).bfloat16()
+    x = torch.nn.functional.pad(X.double(), (0, 0, 1, 1, 1, 1))
+    ref = sum(x[:, i:i + h, j:j + h, :].reshape(-1, cin) @ W[:, i, j, :].double().t().contiguous() for i in range(3) for j in range(3))
+    err = {}
+    for option in (None, "128x128"):
+        binding.set_option("force_config", option)
+        Y = torch.empty(n, h, h, cout, device="cuda")
+        binding.conv2d_epilogue_bf16(X, W, Y, pad=(1, 1))
+        torch.cuda.synchronize()
+        assert binding.last_config().endswith("_splitk"), binding.last_config()
+        err[option] = float((Y.reshape(-1, cout).double() - ref).norm() / ref.norm())
+    assert err[None] <= 1.02 * err["128x128"], err
