@@ -39,8 +39,8 @@
  * (GE_ERR_WORKSPACE): run the call once on that stream before capturing, or
  * pass a workspace.  Calls on different streams use different buffers; calls
  * on one stream are ordered by it.  (Where the library itself would slice K, up
- * to 2560, for at most 256 tiles of 32 x 32, each workgroup adds up its tile's
- * slices and nothing is parked; the workspace query is the plan's all the same,
+ * to 2560, for at most 256 tiles of 32 x 32 (convolutions: 512), each workgroup adds
+ * up its tile's slices and nothing is parked; the workspace query is the plan's all the same,
  * and a workspace that is given must still be as large.)
  *
  * Errors.  Every call validates its arguments first and returns a status; on

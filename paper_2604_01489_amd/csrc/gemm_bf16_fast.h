@@ -112,9 +112,9 @@ __device__ __forceinline__ bool stage_residual_bf16(const GemmParams &p, int b, 
     return true;
 }
 
-template <int BM, int BN, int WM, int WN>
+template <int BM, int BN, int WM, int WN, int STAGES = BF16_STAGES>
 struct Bf16Tile {
-    static constexpr int BK = BF16_BK, NS = BF16_STAGES;
+    static constexpr int BK = BF16_BK, NS = STAGES;
     static constexpr int NW = WM * WN;
     static constexpr int THREADS = NW * 64;
     static constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -165,16 +165,19 @@ struct Bf16Tile {
 // are k-contiguous (measured: 8192^3 with both operands k-contiguous 0.85 -> 0.81 ms; with one
 // or none 0.75 -> 0.81 ms; the 3x3 convolution over 256 channels 0.139 -> 0.147 ms, so it is used
 // for the first only).  The K range of a block must be a multiple of 64 unless EDGE is 2.
+// NS: stages of 32 k.  Two: a block's K is 64 at most and comes in one load phase, in half the LDS, so that three or more blocks
+// share a CU and cover each other's loads, epilogues and stores (gemm_tile64_launch.h).  PER: waves of a SIMD that the registers are to leave room for (0: no matter).
 template <int BM, int BN, int WM, int WN, int EDGE, bool RAW, int ACT, bool TA = false, bool TB = false,
-          bool FUSED = false, bool OUTBF16 = false, int CONV = 0, bool K64 = false>
-__global__ void __launch_bounds__(WM * WN * 64)
+          bool FUSED = false, bool OUTBF16 = false, int CONV = 0, bool K64 = false, int NS = BF16_STAGES, int PER = 0>
+__global__ void __launch_bounds__(WM * WN * 64, PER)
 gemm_bf16_kernel(const GemmParams p)
 {
-    using T = Bf16Tile<BM, BN, WM, WN>;
+    using T = Bf16Tile<BM, BN, WM, WN, NS>;
     constexpr int BK = T::BK, NW = T::NW, TM = T::TM, TN = T::TN, LOADS = T::LOADS;
     constexpr bool PINGPONG = T::PINGPONG;
     constexpr bool KEDGE = EDGE == 2;
     constexpr bool A64 = K64 && !TA, B64 = K64 && TB;     // operands staged in 128-byte rows
+    static_assert(NS == 4 || (NS == 2 && !K64), "a ring of four stages, or all of K in two");
     static_assert(!(RAW && FUSED) && (FUSED || !OUTBF16), "partial tiles carry no epilogue; bf16 output is the fused one's");
     static_assert(!CONV || (!TA && TB && (FUSED || RAW) && !K64), "convolution: gathered k-contiguous A, filters as N x K, 32 k per step");
     static_assert((BM & (BM - 1)) == 0 && ((T::WTM / 32) & (T::WTM / 32 - 1)) == 0, "k-strided A stage");
@@ -343,7 +346,7 @@ gemm_bf16_kernel(const GemmParams p)
     const int nk64 = (kLen + 63) / 64;
     auto issue64 = [&](int t64, int stage) {
         GE_LDS char *dA = (GE_LDS char *)smem + stage * 2 * T::A_BYTES;
-        GE_LDS char *dB = (GE_LDS char *)smem + 4 * T::A_BYTES + stage * 2 * T::B_BYTES;
+        GE_LDS char *dB = (GE_LDS char *)smem + NS * T::A_BYTES + stage * 2 * T::B_BYTES;
         const int kLeft = kLen - t64 * 64;           // valid k in this tile (KEDGE only)
         if constexpr (A64) {
             const long long stepA = (long long)t64 * 128;
@@ -419,7 +422,7 @@ gemm_bf16_kernel(const GemmParams p)
             const int j = l < NLA ? 0 : l - NLA;
             unsigned v = voffB[j];
             if (KEDGE && kB[j] >= kLeft64) v = OOB_OFFSET;
-            lds_dma16(rB64, (unsigned)(size_t)((GE_LDS char *)smem + 4 * T::A_BYTES + stage * 2 * T::B_BYTES + (j * NW + w) * 1024), v);
+            lds_dma16(rB64, (unsigned)(size_t)((GE_LDS char *)smem + NS * T::A_BYTES + stage * 2 * T::B_BYTES + (j * NW + w) * 1024), v);
         }
     };
 
@@ -461,8 +464,8 @@ gemm_bf16_kernel(const GemmParams p)
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        if (B64) bAddr[j] = (unsigned)(size_t)(GE_LDS char *)smem + 4 * T::A_BYTES + (unsigned)a64_frag_offset(wn * T::WTN, lane, j);
-        else bAddr[j] = (unsigned)(size_t)(GE_LDS char *)smem + 4 * T::A_BYTES + (bBase ^ (unsigned)(j * 32));
+        if (B64) bAddr[j] = (unsigned)(size_t)(GE_LDS char *)smem + NS * T::A_BYTES + (unsigned)a64_frag_offset(wn * T::WTN, lane, j);
+        else bAddr[j] = (unsigned)(size_t)(GE_LDS char *)smem + NS * T::A_BYTES + (bBase ^ (unsigned)(j * 32));
         asm volatile("" : "+v"(bAddr[j]));
     }
     auto read_strided = [&](unsigned addr, int rowBytes) {
@@ -533,11 +536,11 @@ gemm_bf16_kernel(const GemmParams p)
     };
 
     GE_LDS char *const ldsBase = (GE_LDS char *)smem;
-    GE_LDS char *lA[4], *lB[4];
+    GE_LDS char *lA[NS], *lB[NS];
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
+    for (int st = 0; st < NS; ++st) {
         lA[st] = ldsBase + st * T::A_BYTES;
-        lB[st] = ldsBase + 4 * T::A_BYTES + st * T::B_BYTES;
+        lB[st] = ldsBase + NS * T::A_BYTES + st * T::B_BYTES;
     }
     // waves w and w+4 share a SIMD: they form the two phase groups
     const int group = w >> 2;
@@ -643,20 +646,20 @@ gemm_bf16_kernel(const GemmParams p)
             }
             if (PINGPONG && group == 0) asm volatile("s_barrier" ::: "memory");
         }
-    } else if (nk <= 4) {
-        // The whole K range fits the four stages (K <= 128, always bound by the C stores): one
+    } else if (NS == 2 || nk <= 4) {
+        // The whole K range fits the stages (K <= 128, always bound by the C stores): one
         // load phase, one barrier, then the multiply; no ring, no phase groups.
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < NS; ++t)
             if (t < nk) issue(t, lA[t], lB[t]);
         asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < NS; ++t)
             if (t < nk) {
                 read_frags(t);
                 mma();
             }
-    } else {
+    } else if constexpr (NS == 4) {
         issue(0, lA[0], lB[0]);
         issue(1, lA[1], lB[1]);
         issue(2, lA[2], lB[2]);

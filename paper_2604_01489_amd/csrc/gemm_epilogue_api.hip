@@ -21,6 +21,7 @@
 #include "gemm_ragged_launch.h"
 #include "gemm_skinny.h"
 #include "gemm_small_launch.h"
+#include "gemm_tile64_launch.h"
 #include "ge_host.h"
 #include "plan_rates.h"
 #include "small_layout.h"
@@ -532,6 +533,11 @@ ge_status_t run_bf16(int M, int N, int K, const uint16_t *A, int lda, const uint
     p.bytesB = 2 * (((long long)batch * K - 1) * ldb + N);
 
     const bool sliced = pl.splitK > 1, small = small_ok(pl, p, plan), raw = sliced && !small;
+    const Tile64 tile64 = small ? TILE64_NO : tile64_of(pl, p, plan);
+    if (small || tile64 != TILE64_NO) {          // the run-time consumer chain, with nothing beyond the plain operator's
+        p.clampLo = -INFINITY;
+        p.clampHi = INFINITY;
+    }
     void *ws = nullptr;
     if (small) {
         st = check_unused_workspace(partial_bytes(M, N, batch, pl.splitK), workspace, workspace_bytes);
@@ -579,10 +585,9 @@ ge_status_t run_bf16(int M, int N, int K, const uint16_t *A, int lda, const uint
         g_last_config = raw ? "bf16_256x256x32_w8_splitk" : "bf16_256x256x32_w8";
         break;
     case TILE_128:
-        if (small) {
-            p.clampLo = -INFINITY;   // as below
-            p.clampHi = INFINITY;
-            launch_small(p, hs);
+        if (small || tile64 != TILE64_NO) {
+            if (small) launch_small(p, hs);
+            else       launch_tile64(p, tile64, hs);
             err = ge_host::take_launch_error();
         } else {
             err = launch_fast<128, 128, 2, 2>(p, tile_edge(pl, K, 32), raw, (int)act, grid, hs);

@@ -13,6 +13,7 @@
 #include "gemm_fused_launch.h"
 #include "gemm_ragged_launch.h"
 #include "gemm_small_launch.h"
+#include "gemm_tile64_launch.h"
 #include "ge_host.h"
 
 namespace {
@@ -215,6 +216,7 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
     }
 
     const bool sliced = pl.splitK > 1, small = !fewRows && small_ok(pl, p, a.plan), raw = sliced && !small;
+    const Tile64 tile64 = fewRows || small ? TILE64_NO : tile64_of(pl, p, a.plan);
     void *ws = nullptr;
     GemmParams pg = p;                      // the GEMM pass: partial tiles go to the workspace
     if (small) {
@@ -243,6 +245,11 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
         set_config(a.M <= 16 ? "few_rows_16_k128" : "few_rows_32_k128", a.transA, a.transB, false);
     } else switch (pl.tile) {
     case TILE_256:
+        if (tile64 != TILE64_NO) {
+            launch_tile64(p, tile64, hs);
+            set_config(tile_k64(p, 256, grid) ? "256x256x64_w8" : "256x256x32_w8", a.transA, a.transB, false);
+            break;
+        }
         // both operands k-strided: every request is a whole line already and the four-wave
         // kernel has nothing to gain (measured at 8192^3: 0.812 against 0.806 ms)
         if (four_wave_ok(pl, a.K) && !(a.transA && !a.transB)) {
@@ -255,8 +262,9 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
         else set_config("256x256x32_w8", a.transA, a.transB, raw);
         break;
     case TILE_128:
-        if (small) {
-            launch_small(p, hs);
+        if (small || tile64 != TILE64_NO) {
+            if (small) launch_small(p, hs);
+            else       launch_tile64(p, tile64, hs);
             set_config(tile_k64(p, 128, grid) ? "128x128x64_w4" : "128x128x32_w4", a.transA, a.transB, sliced);
         } else if (launch_tile<128>(pg, pl, raw, grid, hs)) set_config("128x128x64_w4", a.transA, a.transB, raw);
         else set_config("128x128x32_w4", a.transA, a.transB, raw);

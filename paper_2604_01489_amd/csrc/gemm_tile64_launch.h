@@ -1,0 +1,30 @@
+// Two more tiles of gemm_bf16_kernel (gemm_bf16_fast.h) for calls whose plan names the 128 x 128 or the 256 x 256 one and takes no K slices: 64 x 128 where that
+// gives every block a CU of its own, and K <= 64 in one load phase and half the LDS, so that three and more blocks share a CU.  Same sums in the same order.
+//
+// 64 x 128: the 128 x 128 tile on fewer than 128 CUs spends 8.3 us beside its steps (0.17 to 0.21 us each), this one 5.0 and 0.15 to 0.17, as its epilogue is half as
+// long, and there are twice as many of them: B K x N, bf16 out, 1024 x 1536 x 1216 14.8 -> 10.6 us; of 870 drawn calls each 0.74 to 0.92 of the time.  More
+// blocks than CUs: 1.0 to 1.3 of it (1280 x 2560 x 1024, 400 blocks, 13.6 / 15.0).
+// K <= 64, bf16 out: 256 of 256 x 256 x 64 13.8 -> 11.5 us, 256 of 128 x 128 x 64 6.0 -> 5.4, 256 of 512 x 512 x 64, there on 128 x 128 tiles in place of 256 x 256 ones (64 x 128: 46.6), 49.6 -> 43.6;
+// with fp32 out, where the stores are all, 0.93 of the time up to a block a CU and 0.89 beyond four, between these none (0.96 to 0.99).
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "ge_device.h"
+#include "ge_host.h"
+#include "small_layout.h"
+
+namespace ge_host {
+
+// Which of them a call takes (small_layout.h).  The plan, and with it the configuration's name, stays as it is.
+using ge::Tile64;
+using ge::TILE64_NO;
+using ge::TILE64_RING;
+using ge::TILE64_SHORT_WIDE;
+Tile64 tile64_of(const Plan &pl, const ge::GemmParams &p, ge_plan_t plan);
+
+// For the storages of p.transA / p.transB and the output type of p.cType; p.tilesM, p.tilesN and p.groupM are set here.
+void launch_tile64(ge::GemmParams p, Tile64 kind, hipStream_t st);
+void launch_tile64_ring(const ge::GemmParams &p, dim3 grid, hipStream_t st);
+void launch_tile64_short(const ge::GemmParams &p, bool wide, dim3 grid, hipStream_t st);
+
+}  // namespace ge_host

@@ -38,19 +38,19 @@ GE_HD constexpr void small_place(int j, int w, int lane, int &r, int &c, int &at
 // Beyond that only what is over in one step of 256, which has no walk to wait in: more than 128 k, up to two tiles a CU beside the 64 x 64 tile
 // (0.83 to 0.97 of its time) or three beside the 128 x 128 one (0.7 to 0.98; four 1.1); more than 64 k, two beside the latter (0.8 to 0.94; K <= 64 1.02; 640^3, 400 tiles, 6.5 / 6.9).
 // In place of K slices, which cost a second launch and its round trip, where one walk over K is the shorter way: 512 x 512 x 2048, five slices, 10.9 / 8.9, 44 x 690 x
-// 1109 8.8 / 6.3; aligned operands, whose slices are the longer kernel's, up to 2560 (144 x 448 x 2688 9.8 / 9.8), the others up to 1792 (40 x 1678 x 2119 9.1 / 10.9).
+// 1109 8.8 / 6.3; aligned operands, whose slices are the longer kernel's, up to 2560 (144 x 448 x 2688 9.8 / 9.8), the others up to 1536 (36 x 71 x 1653 8.5 / 9.5; 40 x 1678 x 2119 9.1 / 10.9).
 constexpr int SMALL_CUS = 256;
 GE_HD constexpr bool small_tile_takes(long long tiles, int slices, int K, bool ragged)
 {
-    if (slices > 1) return tiles <= SMALL_CUS && K <= (ragged ? 1792 : 2560);
+    if (slices > 1) return tiles <= SMALL_CUS && K <= (ragged ? 1536 : 2560);
     if (ragged && K <= 64) return false;
     if (tiles <= SMALL_CUS) return true;
     if (K > SMALL_STEP || K <= 64) return false;
     return K > 128 ? tiles <= (ragged ? 2 : 3) * SMALL_CUS : !ragged && tiles <= 2 * SMALL_CUS;
 }
 
-// The same for a convolution whose plan names the 128 x 128 tile; c8: of the kernel for channels a multiple of 8 but not of 32.  Its gathered rows cost that tile 0.4 us for each
-// 32 k, so the lines lie further out.  us, plan's tile / small: 8 images of 14 x 14 x 256 -> 64, 1 x 1, 6.9 / 3.9; 14 of 13 x 13 x 256 -> 32, 3 x 3, in slices 11.9 / 9.4; of its time over 9000 drawn
+// The same for a convolution whose plan names the 128 x 128 tile; c8: of the kernel for channels a multiple of 8 but not of 32.  That tile's gathered
+// steps take 0.2 to 0.35 us each beside 8 us for its prologue and epilogue, more than in a product, so the lines lie further out.  us, plan's tile / small: 8 images of 14 x 14 x 256 -> 64, 1 x 1, 6.9 / 3.9; 14 of 13 x 13 x 256 -> 32, 3 x 3, in slices 11.9 / 9.4; of its time over 9000 drawn
 // calls, up to two tiles a CU: K = 64 0.78 to 0.91, 256 0.55 to 0.65, 576 0.56 to 0.70, 1152 0.46 to 0.58, in slices 2304 0.72 to 0.86 (4608 1.0 to 1.4), c8 0.38 to 0.9.  Three: 65 to 256 k 0.94
 // and 0.77, 1152 0.87, c8 0.70 to 0.85 (288 to 576 k 1.0 to 1.24); four: 129 to 256 k 0.87.
 GE_HD constexpr bool small_conv_takes(long long tiles, int slices, int K, bool c8)
@@ -59,6 +59,15 @@ GE_HD constexpr bool small_conv_takes(long long tiles, int slices, int K, bool c
     if (tiles <= 2 * SMALL_CUS) return true;
     if (K > 128 && K <= SMALL_STEP) return tiles <= 4 * SMALL_CUS;
     return tiles <= 3 * SMALL_CUS && (K <= 128 ? K > 64 : K > 768 || c8);
+}
+
+// Which of the tiles of gemm_tile64_launch.h (figures there) a product in one pass takes whose plan names the 128 x 128 tile (plan128) or the 256 x 256 one; blocks: its 64 x 128 tiles.
+enum Tile64 { TILE64_NO = 0, TILE64_RING = 1, TILE64_SHORT = 2, TILE64_SHORT_WIDE = 3 };
+GE_HD constexpr Tile64 tile64_kind(bool plan128, long long blocks, int K, bool bf16Out)
+{
+    if (K > 64) return plan128 && blocks <= SMALL_CUS ? TILE64_RING : TILE64_NO;
+    if (bf16Out) return blocks > 16 * SMALL_CUS ? TILE64_SHORT_WIDE : TILE64_SHORT;
+    return plan128 && (blocks <= SMALL_CUS || (blocks > 4 * SMALL_CUS && blocks <= 16 * SMALL_CUS)) ? TILE64_SHORT : TILE64_NO;
 }
 
 // Steps whose sums form one chain before they are added to the others: a plan's K slice, so that the sums are as exact as in slices.

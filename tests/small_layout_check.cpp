@@ -134,7 +134,7 @@ int main()
         {60, 1, 640, true, true}, {256, 1, 8192, false, true}, {257, 1, 257, false, false}, {257, 1, 256, false, true}, {768, 1, 136, false, true},
         {769, 1, 136, false, false}, {512, 1, 128, false, true}, {513, 1, 128, false, false}, {257, 1, 64, false, false}, {256, 1, 64, false, true}, {1, 1, 8, false, true},
         {4, 1, 64, true, false}, {4, 1, 65, true, true}, {512, 1, 136, true, true}, {513, 1, 136, true, false}, {257, 1, 128, true, false},
-        {72, 3, 1792, true, true}, {72, 3, 1793, true, false}, {72, 5, 2560, false, true}, {72, 5, 2568, false, false}, {257, 2, 2048, false, false}};
+        {72, 3, 1536, true, true}, {72, 3, 1537, true, false}, {72, 5, 2560, false, true}, {72, 5, 2568, false, false}, {257, 2, 2048, false, false}};
     for (auto &c : rule)
         if (small_tile_takes(c.tiles, c.slices, c.K, c.ragged) != c.takes) {
             std::printf("rule: %lld tiles, %d slices, K %d, ragged %d\n", c.tiles, c.slices, c.K, c.ragged);
@@ -146,6 +146,14 @@ int main()
     for (auto &c : conv)
         if (small_conv_takes(c.tiles, c.slices, c.K, c.c8) != c.takes) {
             std::printf("rule of convolutions: %lld tiles, %d slices, K %d, c8 %d\n", c.tiles, c.slices, c.K, c.c8);
+            return 1;
+        }
+    struct { bool plan128; long long blocks; int K; bool bf16; Tile64 kind; } tiles[] = {{true, 256, 65, true, TILE64_RING}, {true, 256, 5000, false, TILE64_RING}, {true, 257, 65, true, TILE64_NO},
+        {false, 100, 128, true, TILE64_NO}, {false, 4096, 64, true, TILE64_SHORT}, {false, 4097, 64, true, TILE64_SHORT_WIDE}, {false, 4096, 64, false, TILE64_NO},
+        {true, 256, 64, false, TILE64_SHORT}, {true, 257, 64, false, TILE64_NO}, {true, 1025, 64, false, TILE64_SHORT}, {true, 4097, 64, false, TILE64_NO}};
+    for (auto &c : tiles)
+        if (tile64_kind(c.plan128, c.blocks, c.K, c.bf16) != c.kind) {
+            std::printf("rule of the 64 x 128 tile: %lld blocks, K %d\n", c.blocks, c.K);
             return 1;
         }
     if (small_run(1, 64) < 1 << 30 || small_run(3, 512) != 2 || small_run(3, 672) != 2 || small_run(8, 128) != 1) return 1;
