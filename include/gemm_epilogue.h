@@ -425,7 +425,8 @@ const char *ge_status_string(ge_status_t status);
 /* Name of the kernel configuration the last successful call on this thread
  * launched ("bf16_256x256x64_w4", "bf16_256x256x32_w8", "f32_128x128x16_w4", "f32_ragged_64x64x32",
  * ...); for reports.  The names may change from one build to the next.  The tile is the plan's:
- * bf16 products of few tiles go to workgroups in 32 x 32 pieces of it under the same name. */
+ * bf16 products of few tiles go to workgroups in 32 x 32, 64 x 128 or (K up to 64)
+ * 128 x 128 pieces of it under the same name. */
 const char *ge_last_config(void);
 
 #ifdef __cplusplus

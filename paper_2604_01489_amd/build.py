@@ -22,7 +22,7 @@ MARSHAL_SOURCE = os.path.join(CSRC, "py_marshal.cpp")
 LIB_SOURCES = ["conv_halo_14_11.hip", "conv_halo_12_12.hip", "conv_api.hip", "gemm_fused_t256.hip", "gemm_fused_t256_edge.hip", "gemm_fused_t256_kedge.hip", "gemm_fused_t128.hip",
                "gemm_fused_t128_edge.hip", "gemm_fused_t128_kedge.hip",
                "gemm_fused_w4_e0.hip", "gemm_fused_w4_e1.hip", "gemm_fused_w4_e2.hip", "gemm_epilogue_api.hip",
-               "gemm_tile64.hip", "gemm_tile64_short.hip", "gemm_small.hip", "gemm_ragged_t128.hip", "gemm_ragged_t128_w8.hip", "gemm_ragged_t64.hip", "gemm_fused_api.hip", "gemm_symm_api.hip", "gemm_diag.hip", "gemm_rowsum.hip"]
+               "gemm_tile64.hip", "gemm_tile64_short.hip", "gemm_tile64_conv.hip", "gemm_small.hip", "gemm_ragged_t128.hip", "gemm_ragged_t128_w8.hip", "gemm_ragged_t64.hip", "gemm_fused_api.hip", "gemm_symm_api.hip", "gemm_diag.hip", "gemm_rowsum.hip"]
 PROBE_SOURCES = ["ge_probes.hip"]
 SOURCES = LIB_SOURCES + PROBE_SOURCES
 # packed fp32 instructions are kept off: some of their forms have misbehaved on this hardware

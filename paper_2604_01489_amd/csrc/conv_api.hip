@@ -13,6 +13,7 @@
 #include "gemm_bf16_fast.h"
 #include "gemm_fused.h"
 #include "gemm_small_launch.h"
+#include "gemm_tile64_launch.h"
 #include "ge_host.h"
 #include "small_layout.h"
 
@@ -278,6 +279,9 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
     // few tiles: in smaller ones, with the sums of the plan (gemm_small.h); a workspace that is given is held to the plan's size all the same
     const bool small = pl.tile == TILE_128 && opt_force_config() == FORCE_NONE &&
                        ge::small_conv_takes((long long)ceil_div(M, 32) * ceil_div(a.Cout, 32), pl.splitK, (int)K, cp.c8);
+    // few or short ones otherwise: gemm_tile64_launch.h
+    const Tile64 tile64 = sliced || small || pl.tile == TILE_GENERIC || opt_force_config() != FORCE_NONE ? TILE64_NO
+        : ge::conv_tile64_kind(pl.tile == TILE_128, (long long)ceil_div(M, 64) * ceil_div(a.Cout, 128), (int)K, a.y_type == GE_DTYPE_BF16, cp.c8);
     const bool raw = sliced && !small;
     void *ws = nullptr;
     GemmParams pg = p;
@@ -294,16 +298,18 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
     hipStream_t hs = (hipStream_t)stream;
     switch (pl.tile) {
     case TILE_256:
+        if (tile64 != TILE64_NO) launch_tile64_conv(p, tile64, cp.c8, hs);
+        else if (cp.c8) launch_conv_c8<256, 256, 2, 4>(pg, raw, grid, hs);
+        else launch_conv<256, 256, 2, 4>(pg, pl.edge, raw, grid, hs);
         if (cp.c8) {
-            launch_conv_c8<256, 256, 2, 4>(pg, raw, grid, hs);
             g_last_config = raw ? "conv_bf16_c8_256x256x32_w8_splitk" : "conv_bf16_c8_256x256x32_w8";
             break;
         }
-        launch_conv<256, 256, 2, 4>(pg, pl.edge, raw, grid, hs);
         g_last_config = raw ? "conv_bf16_256x256x32_w8_splitk" : "conv_bf16_256x256x32_w8";
         break;
     case TILE_128:
         if (small) launch_small(p, hs);
+        else if (tile64 != TILE64_NO) launch_tile64_conv(p, tile64, cp.c8, hs);
         else if (cp.c8) launch_conv_c8<128, 128, 2, 2>(pg, raw, grid, hs);
         else launch_conv<128, 128, 2, 2>(pg, pl.edge, raw, grid, hs);
         if (cp.c8) {

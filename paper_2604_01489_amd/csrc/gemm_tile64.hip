@@ -13,13 +13,18 @@ Tile64 tile64_of(const Plan &pl, const GemmParams &p, ge_plan_t plan)
 
 void launch_tile64_ring(const GemmParams &p, dim3 grid, hipStream_t st) { launch_tile64_mode<64, 1, 4, 4, 3>(p, grid, st); }
 
-void launch_tile64(GemmParams p, Tile64 kind, hipStream_t st)
+dim3 tile64_grid(GemmParams &p, bool wide)
 {
-    const bool wide = kind == TILE64_SHORT_WIDE;
     p.tilesM = ceil_div(p.M, wide ? 128 : 64);
     p.tilesN = ceil_div(p.N, 128);
     p.groupM = choose_group_m(p.tilesM, p.tilesN);
-    const dim3 grid((unsigned)((long long)p.tilesM * p.tilesN * p.batch));
+    return dim3((unsigned)((long long)p.tilesM * p.tilesN * p.batch));
+}
+
+void launch_tile64(GemmParams p, Tile64 kind, hipStream_t st)
+{
+    const bool wide = kind == TILE64_SHORT_WIDE;
+    const dim3 grid = tile64_grid(p, wide);
     if (kind == TILE64_RING) launch_tile64_ring(p, grid, st);
     else                     launch_tile64_short(p, wide, grid, st);
 }

@@ -3,8 +3,13 @@
 //
 // 64 x 128: the 128 x 128 tile on fewer than 128 CUs spends 8.3 us beside its steps (0.17 to 0.21 us each), this one 5.0 and 0.15 to 0.17, as its epilogue is half as
 // long, and there are twice as many of them: B K x N, bf16 out, 1024 x 1536 x 1216 14.8 -> 10.6 us; of 870 drawn calls each 0.74 to 0.92 of the time.  More
-// blocks than CUs: 1.0 to 1.3 of it (1280 x 2560 x 1024, 400 blocks, 13.6 / 15.0).
-// K <= 64, bf16 out: 256 of 256 x 256 x 64 13.8 -> 11.5 us, 256 of 128 x 128 x 64 6.0 -> 5.4, 256 of 512 x 512 x 64, there on 128 x 128 tiles in place of 256 x 256 ones (64 x 128: 46.6), 49.6 -> 43.6;
+// blocks than CUs: three of them are on a CU at once, where two of the larger tile are, and what that saves is the epilogue.  K <= 128, bf16 out, of 1300 drawn calls up to three to a CU
+// 0.88 to 0.92, a fourth 1.12, up to six 0.85 to 0.89; beside the 256 x 256 tile five 0.91; fp32 out 0.92 to 0.96 with single ones 1.05; K = 192 0.98, 1024 1.1 (1280 x 2560 x
+// 1024, 400 blocks, 13.6 / 15.0).
+// Convolutions: a block a CU 0.69 to 0.82 of the time (8 images of 56 x 56 x 128 -> 128, 3 x 3, stride 2, 15.3 -> 11.5 us); beyond, K <= 128 as above 0.80 to 0.91; channels a multiple of 8 only, up
+// to two blocks a CU K = 576 0.87, 1152 0.84 to 0.92, up to six K = 256 0.83 to 0.92 (else K = 256 0.95, 576 1.0); K <= 64 0.71 to 0.97.
+// K <= 64, bf16 out: 256 of 256 x 256 x 64 13.8 -> 11.5 us, 256 of 128 x 128 x 64 6.0 -> 5.4, 256 of 512 x 512 x 64, there on 128 x 128 tiles in place of 256 x 256 ones (64 x 128: 46.6), 49.6 -> 43.6, as
+// a fourth to a CU is (209 of 80 x 256 x 40 6.55 us, 64 x 128 6.80; convolutions 0.97);
 // with fp32 out, where the stores are all, 0.93 of the time up to a block a CU and 0.89 beyond four, between these none (0.96 to 0.99).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -24,6 +29,8 @@ Tile64 tile64_of(const Plan &pl, const ge::GemmParams &p, ge_plan_t plan);
 
 // For the storages of p.transA / p.transB and the output type of p.cType; p.tilesM, p.tilesN and p.groupM are set here.
 void launch_tile64(ge::GemmParams p, Tile64 kind, hipStream_t st);
+void launch_tile64_conv(ge::GemmParams p, Tile64 kind, bool c8, hipStream_t st);     // p.transA 0, p.transB 1
+dim3 tile64_grid(ge::GemmParams &p, bool wide);
 void launch_tile64_ring(const ge::GemmParams &p, dim3 grid, hipStream_t st);
 void launch_tile64_short(const ge::GemmParams &p, bool wide, dim3 grid, hipStream_t st);
 
