@@ -80,7 +80,7 @@ TRAFFIC = {
     "c9_diag_bf16_8192": ("diag_rows_vec4", 65964, 262666, ('gemm_diag.hip',), "95489dc912964713"),
     "c10_conv3x3_256_bf16out": ("conv_bf16_halo_3x3_w4_14_11", 60946, 50176, ('bf16_layout.h', 'conv_halo.h', 'conv_halo_launch.h', 'conv_halo_layout.h', 'ge_device.h', 'gemm_bf16_fast.h'), "b41bc798f4ef9cba"),
     "c11_fused_lower_8192_bias_relu": ("bf16_fused_256x256x64_w4_nn", 654644, 262144, _MAIN_W4, "22b85d300136d772"),
-    "c12_rowsum_linear_8192": ("rowsum_rows_wide", 133385, 4235, ('bf16_layout.h', 'ge_device.h', 'gemm_rowsum.hip'), "b52b9a7dbfd635dc"),
+    "c12_rowsum_linear_8192": ("rowsum_rows_wide", 133389, 4226, ('bf16_layout.h', 'ge_device.h', 'gemm_rowsum.hip'), "601e6dd4cc8e5692"),
     "c13_f32_8192x8192x2048": ("f32_128x128x16_w4", 783944, 262144, _F32, "2b99fdce10bb8826"),
     "c15_conv7x7_first_layer_bf16out": ("conv_bf16_rows_k32", 16594, 50176, ('bf16_layout.h', 'conv_rows.h', 'conv_rows_layout.h', 'ge_device.h'), "6c4db93c683436ae"),
     "c14_symm_lower_16384_n16": ("bf16_symm_lower_768x768_n16", 145628, 23552, ('bf16_layout.h', 'ge_device.h', 'gemm_symm.h', 'splitk_reduce.h', 'symm_layout.h'), "a541a86efb2a2fa5"),

@@ -53,15 +53,48 @@ __device__ inline float pair_sum(const float *t)
     else return pair_sum<n / 2>(t) + pair_sum<n / 2>(t + n / 2);
 }
 
+// sum of x[0..n) by the first 256 threads of one block: a thread adds every 256th element, then a fixed tree (x may be null: 0).  Eight loads are on their way at a time.
+__device__ inline void block_vector_sum(int n, const float *__restrict__ x, float *__restrict__ out)
+{
+    __shared__ float part[4];
+    float acc = 0.0f;
+    if (x != nullptr && threadIdx.x < 256)
+        for (unsigned i = threadIdx.x; i < (unsigned)n; i += 8 * 256) {
+            float t[8];
+#pragma unroll
+            for (unsigned u = 0; u < 8; ++u) t[u] = i + 256 * u < (unsigned)n ? x[i + 256 * u] : 0.0f;
+#pragma unroll
+            for (unsigned u = 0; u < 8; ++u) acc = i + 256 * u < (unsigned)n ? acc + t[u] : acc;
+        }
+    acc = wave_sum(acc);
+    if ((threadIdx.x & 63) == 0 && threadIdx.x < 256) part[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) out[0] = (part[0] + part[1]) + (part[2] + part[3]);
+}
+
+// A vector whose sum the first block of a row pass takes on (SUM).  In a launch of its own, with one load on its way at a time, it cost the parameter call on weights K x N
+// more than a launch (both calls, us, rows x inputs x outputs: 976 x 3156 x 1152 12.9 -> 11.0, 1024 x 1088 x 7805 20.5 -> 11.6; N x K, whose finish pass has the loads: 722 x 2276 x 7200 24.1 -> 19.1).
+struct VectorSum {
+    int n;
+    const float *x;
+    float *out;
+};
+
 // out[r] = scale * sum_c X[r,c] * v[c] + add[0]   (v == nullptr: ones; add == nullptr: 0)
 // One wave per row at a time, a lane takes 8 consecutive columns per step (16 bytes of X) when
 // VEC, single columns otherwise; v is staged in LDS once per block when it fits (`stage`), and a
 // block of 16 waves walks rows with the stride of the grid so that the staging is paid once per many rows.
-template <bool VEC>
+template <bool VEC, bool SUM>
 __global__ void __launch_bounds__(kRowWaves * 64)
 rows_dot_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, const float *__restrict__ v,
-                float scale, const float *__restrict__ add, float *__restrict__ out, int stage)
+                float scale, const float *__restrict__ add, float *__restrict__ out, int stage, VectorSum sum)
 {
+    constexpr int extra = SUM ? 1 : 0;
+    const int block = (int)blockIdx.x - extra;
+    if (SUM && block < 0) {
+        block_vector_sum(sum.n, sum.x, sum.out);
+        return;
+    }
     extern __shared__ float vs[];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (stage) {
@@ -70,7 +103,7 @@ rows_dot_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, con
     }
     const float *vv = stage ? vs : v;
     const float addv = add != nullptr ? add[0] : 0.0f;
-    for (long long r = (long long)blockIdx.x * kRowWaves + w; r < R; r += (long long)gridDim.x * kRowWaves) {
+    for (long long r = (long long)block * kRowWaves + w; r < R; r += (long long)((int)gridDim.x - extra) * kRowWaves) {
         const uint16_t *row = X + r * ldx;
         float acc = 0.0f;
         if (VEC) {
@@ -117,17 +150,22 @@ rows_dot_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, con
 // sweeps, a fixed butterfly inside each wave, then the wave sums of its group added in wave order.
 // ANY: rows at any address and of any length of at least 8; the chunk at a row's end is pulled back to end there and
 // shifted down, which puts zeros beyond (12096 x 2205 + 2752 x 2205: 26.1 us for both calls, 50.8 by the kernel above).
-template <int WAVES, int G, bool ANY>
+template <int WAVES, int G, bool ANY, bool SUM>
 __global__ void __launch_bounds__(WAVES * 64)
 rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx, const float *__restrict__ v,
-                     float scale, const float *__restrict__ add, float *__restrict__ out)
+                     float scale, const float *__restrict__ add, float *__restrict__ out, VectorSum sum)
 {
+    const int block = (int)blockIdx.x - (SUM ? 1 : 0);
+    if (SUM && block < 0) {
+        block_vector_sum(sum.n, sum.x, sum.out);
+        return;
+    }
     constexpr int WG = WAVES / G;                   // waves of a group
     constexpr int SWEEP = WG * 64 * 8;              // columns a group covers in one sweep
     __shared__ float part[G * kBlockRows][WG];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int g = w / WG, wg = w % WG;
-    const long long r0 = ((long long)blockIdx.x * G + g) * kBlockRows;
+    const long long r0 = ((long long)block * G + g) * kBlockRows;
     float acc[kBlockRows];
 #pragma unroll
     for (int u = 0; u < kBlockRows; ++u) acc[u] = 0.0f;
@@ -177,7 +215,7 @@ rows_dot_wide_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx
     }
     __syncthreads();
     if (threadIdx.x < G * kBlockRows) {
-        const long long r = (long long)blockIdx.x * G * kBlockRows + threadIdx.x;      // rows of a block are consecutive
+        const long long r = (long long)block * G * kBlockRows + threadIdx.x;      // rows of a block are consecutive
         if (r < R) {
             float t = 0.0f;
 #pragma unroll
@@ -267,19 +305,6 @@ cols_partial_kernel(int R, int C, const uint16_t *__restrict__ X, long long ldx,
     }
 }
 
-// sum of x[0..n) by one block: a thread adds every 256th element, then a fixed tree (x may be null: 0)
-__device__ inline void block_vector_sum(int n, const float *__restrict__ x, float *__restrict__ out)
-{
-    __shared__ float part[4];
-    float acc = 0.0f;
-    if (x != nullptr)
-        for (unsigned i = threadIdx.x; i < (unsigned)n; i += 256) acc += x[i];
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) out[0] = (part[0] + part[1]) + (part[2] + part[3]);
-}
-
 // s[c] = sum of the chunks' partial sums; the block past the last column block adds up the bias into
 // s[C].  A block covers 64 columns: 16 groups of 16 threads, a thread 4 consecutive columns (16 bytes per
 // load).  Group g adds up 64-row chunks g, g + 16, ... in ascending order, eight loads in flight at a time, a chunk
@@ -350,12 +375,6 @@ cols_finish_kernel(int C, int partials, const float *__restrict__ partial, float
     }
 }
 
-__global__ void __launch_bounds__(256)
-vector_sum_kernel(int n, const float *__restrict__ x, float *__restrict__ out)
-{
-    block_vector_sum(n, x, out);
-}
-
 bool vec_ok(const void *base, long long ld) { return (((uintptr_t)base) & 15u) == 0 && ld % 8 == 0; }
 
 bool rows_aligned(int C, const void *X, long long ldx) { return vec_ok(X, ldx) && C % 8 == 0; }
@@ -376,16 +395,18 @@ bool rows_wide(int R, int C, const void *X, long long ldx)
     return C >= 2048 || (double)R * C >= 8.0 * 1024 * 1024;
 }
 
-// rows of X times v (or ones), on `st`
+// rows of X times v (or ones), on `st`; SUM: and a vector's sum
+template <bool SUM>
 void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float *v, float scale, const float *add,
-                     float *out, hipStream_t st)
+                     float *out, hipStream_t st, VectorSum sum = VectorSum{0, nullptr, nullptr})
 {
+    constexpr unsigned extra = SUM ? 1 : 0;
     if (rows_wide(R, C, X, ldx)) {
         auto launch = [&](auto waves, auto groups) {
             constexpr int W = decltype(waves)::value, G = decltype(groups)::value;
-            const dim3 blocks((unsigned)ceil_div(R, G * kBlockRows)), threads(W * 64);
-            if (rows_aligned(C, X, ldx)) GE_LAUNCH((rows_dot_wide_kernel<W, G, false>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out);
-            else                         GE_LAUNCH((rows_dot_wide_kernel<W, G, true>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out);
+            const dim3 blocks((unsigned)ceil_div(R, G * kBlockRows) + extra), threads(W * 64);
+            if (rows_aligned(C, X, ldx)) GE_LAUNCH((rows_dot_wide_kernel<W, G, false, SUM>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out, sum);
+            else                         GE_LAUNCH((rows_dot_wide_kernel<W, G, true, SUM>), blocks, threads, 0, st, R, C, X, ldx, v, scale, add, out, sum);
         };
         using std::integral_constant;
         constexpr integral_constant<int, 4> four{};
@@ -397,8 +418,8 @@ void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float
         // 6475 x 1712 9.1 / 8.8, 8000 x 2000 10.4 / 10.0; 160 blocks 5000 x 1536 7.0 / 7.8).
         const long long of16 = C > 2048 ? ceil_div(R, 16) : ceil_div(R, 32);
         const bool one16 = rows_aligned(C, X, ldx) && C > 1024 && C <= 4096 && of16 <= kNumCU && of16 * 16 > kNumCU * (C > 2560 ? 8 : C > 2048 ? 9 : 12);
-        if (one16 && C > 2048) GE_LAUNCH((rows_dot_wide_kernel<16, 2, false>), dim3((unsigned)of16), dim3(1024), 0, st, R, C, X, ldx, v, scale, add, out);
-        else if (one16)        GE_LAUNCH((rows_dot_wide_kernel<16, 4, false>), dim3((unsigned)of16), dim3(1024), 0, st, R, C, X, ldx, v, scale, add, out);
+        if (one16 && C > 2048) GE_LAUNCH((rows_dot_wide_kernel<16, 2, false, SUM>), dim3((unsigned)of16 + extra), dim3(1024), 0, st, R, C, X, ldx, v, scale, add, out, sum);
+        else if (one16)        GE_LAUNCH((rows_dot_wide_kernel<16, 4, false, SUM>), dim3((unsigned)of16 + extra), dim3(1024), 0, st, R, C, X, ldx, v, scale, add, out, sum);
         else if (C > 2048 && R < kBlockRows * 2 * kNumCU) launch(integral_constant<int, 8>{}, integral_constant<int, 1>{});
         else if (C <= 512)                           launch(four, integral_constant<int, 4>{});
         else if (C <= 1024)                          launch(four, integral_constant<int, 2>{});
@@ -411,8 +432,8 @@ void launch_rows_dot(int R, int C, const uint16_t *X, long long ldx, const float
     const long long cap = 2ll * kNumCU;             // two blocks of 16 waves per CU; many rows per staging of v
     if (blocks > cap) blocks = cap;
     const dim3 threads(kRowWaves * 64);
-    if (vec_ok(X, ldx)) GE_LAUNCH(rows_dot_kernel<true>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out, stage);
-    else                GE_LAUNCH(rows_dot_kernel<false>, dim3((unsigned)blocks), threads, lds, st, R, C, X, ldx, v, scale, add, out, stage);
+    if (vec_ok(X, ldx)) GE_LAUNCH((rows_dot_kernel<true, SUM>), dim3((unsigned)blocks + extra), threads, lds, st, R, C, X, ldx, v, scale, add, out, stage, sum);
+    else                GE_LAUNCH((rows_dot_kernel<false, SUM>), dim3((unsigned)blocks + extra), threads, lds, st, R, C, X, ldx, v, scale, add, out, stage, sum);
 }
 
 }  // namespace
@@ -441,8 +462,7 @@ extern "C" ge_status_t gemm_rowsum_params_bf16_ex(int N, int K, const uint16_t *
     hipStream_t st = (hipStream_t)stream;
     if (!transB) {
         // B is K x N: s[k] is the sum of row k
-        launch_rows_dot(K, N, B, ldb, nullptr, 1.0f, nullptr, params, st);
-        GE_LAUNCH(vector_sum_kernel, dim3(1), dim3(256), 0, st, N, bias, params + K);
+        launch_rows_dot<true>(K, N, B, ldb, nullptr, 1.0f, nullptr, params, st, VectorSum{N, bias, params + K});
         g_last_config = "rowsum_params_rows";
     } else {
         // B is stored N x K: s[k] is the sum of column k, in two passes through the workspace.  A caller's buffer (or the
@@ -487,7 +507,7 @@ extern "C" ge_status_t gemm_rowsum_bf16(int M, int K, const uint16_t *A, int lda
     if (M < 1 || K < 1) return GE_ERR_SHAPE;
     if (lda < K) return GE_ERR_LD;
     if ((((uintptr_t)A) & 1u) || (((uintptr_t)params) & 3u) || (((uintptr_t)y) & 3u)) return GE_ERR_ALIGN;
-    launch_rows_dot(M, K, A, lda, params, alpha, params + K, y, (hipStream_t)stream);
+    launch_rows_dot<false>(M, K, A, lda, params, alpha, params + K, y, (hipStream_t)stream);
     g_last_config = rows_wide(M, K, A, lda) ? (rows_aligned(K, A, lda) ? "rowsum_rows_wide" : "rowsum_rows_wide_any")
                                  : vec_ok(A, lda) ? "rowsum_rows_vec8" : "rowsum_rows_generic";
     return ge_host::take_launch_error() == hipSuccess ? GE_OK : GE_ERR_LAUNCH;
