@@ -7,7 +7,7 @@
 // 0.88 to 0.92, a fourth 1.12, up to six 0.85 to 0.89; beside the 256 x 256 tile five 0.91; fp32 out 0.92 to 0.96 with single ones 1.05; K = 192 0.98, 1024 1.1 (1280 x 2560 x
 // 1024, 400 blocks, 13.6 / 15.0).
 // Convolutions: a block a CU 0.69 to 0.82 of the time (8 images of 56 x 56 x 128 -> 128, 3 x 3, stride 2, 15.3 -> 11.5 us); beyond, K <= 128 as above 0.80 to 0.91; channels a multiple of 8 only, up
-// to two blocks a CU K = 576 0.87, 1152 0.84 to 0.92, up to six K = 256 0.83 to 0.92 (else K = 256 0.95, 576 1.0); K <= 64 0.71 to 0.97.
+// to two blocks a CU K = 576 0.87, up to one and a half 1152 0.85 (490 blocks of K = 720 17.6 / 18.6), up to six K = 256 0.83 to 0.92 (else K = 256 0.95, 576 1.0); K <= 64 0.71 to 0.97.
 // K <= 64, bf16 out: 256 of 256 x 256 x 64 13.8 -> 11.5 us, 256 of 128 x 128 x 64 6.0 -> 5.4, 256 of 512 x 512 x 64, there on 128 x 128 tiles in place of 256 x 256 ones (64 x 128: 46.6), 49.6 -> 43.6, as
 // a fourth to a CU is (209 of 80 x 256 x 40 6.55 us, 64 x 128 6.80; convolutions 0.97);
 // with fp32 out, where the stores are all, 0.93 of the time up to a block a CU and 0.89 beyond four, between these none (0.96 to 0.99).

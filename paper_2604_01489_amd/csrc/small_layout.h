@@ -79,7 +79,7 @@ GE_HD constexpr Tile64 tile64_kind(bool plan128, long long blocks, int K, bool b
 // A convolution's: with a chunk's tap per lane (c8) the larger tile's steps are dearer.
 GE_HD constexpr Tile64 conv_tile64_kind(bool plan128, long long blocks, int K, bool bf16Out, bool c8)
 {
-    return tile64_kind(plan128, blocks, K, bf16Out, !c8 ? 128 : blocks <= 2 * SMALL_CUS ? 1152 : 256);
+    return tile64_kind(plan128, blocks, K, bf16Out, !c8 ? 128 : 2 * blocks <= 3 * SMALL_CUS ? 1152 : blocks <= 2 * SMALL_CUS ? 576 : 256);
 }
 
 // Steps whose sums form one chain before they are added to the others: a plan's K slice, so that the sums are as exact as in slices.

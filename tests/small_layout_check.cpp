@@ -158,7 +158,7 @@ int main()
             std::printf("rule of the 64 x 128 tile: %lld blocks, K %d\n", c.blocks, c.K);
             return 1;
         }
-    if (conv_tile64_kind(true, 512, 1152, true, true) != TILE64_RING || conv_tile64_kind(true, 512, 1160, true, true) != TILE64_NO || conv_tile64_kind(true, 513, 264, true, true) != TILE64_NO ||
+    if (conv_tile64_kind(true, 384, 1152, true, true) != TILE64_RING || conv_tile64_kind(true, 384, 1160, true, true) != TILE64_NO || conv_tile64_kind(true, 512, 576, true, true) != TILE64_RING || conv_tile64_kind(true, 385, 584, true, true) != TILE64_NO || conv_tile64_kind(true, 513, 264, true, true) != TILE64_NO ||
         conv_tile64_kind(true, 768, 256, true, true) != TILE64_RING || conv_tile64_kind(true, 257, 160, true, false) != TILE64_NO || conv_tile64_kind(true, 256, 4608, false, false) != TILE64_RING) {
         std::printf("rule of the 64 x 128 tile for convolutions\n");
         return 1;
