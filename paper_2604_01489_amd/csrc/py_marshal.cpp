@@ -13,10 +13,12 @@
 #include <ATen/PythonTorchFunctionTLS.h>
 
 #include "../../include/gemm_epilogue.h"
+#include "py_call.h"
 
 namespace {
 
-struct Decline {};                       // thrown where binding.py's own code has to take the call
+using ge_py::Decline;
+using ge_py::without_gil;
 
 int to_int(PyObject *o)
 {
@@ -114,30 +116,13 @@ void *stream_handle(PyObject *stream, PyObject *raw)
     return p;
 }
 
-// The body of a method: its status as an int, or None where it declines.
 template <typename F>
 PyObject *guarded(Py_ssize_t given, Py_ssize_t wanted, F body)
 {
-    if (given != wanted) {
-        PyErr_Format(PyExc_TypeError, "%zd arguments expected, %zd given", wanted, given);
-        return nullptr;
-    }
-    try {
-        if (at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;
-        return PyLong_FromLong(body());
-    } catch (...) {                      // Decline, and what torch throws of a tensor without storage
-        PyErr_Clear();
-        Py_RETURN_NONE;
-    }
-}
-
-template <typename F>
-long without_gil(F call) noexcept        // (nothing that the entry point could throw is handed to binding.py's own code, which would call it again)
-{
-    PyThreadState *state = PyEval_SaveThread();
-    const long status = (long)call();
-    PyEval_RestoreThread(state);
-    return status;
+    return ge_py::guarded(given, wanted, [&] {
+        if (at::impl::torch_function_mode_enabled()) throw Decline{};
+        return body();
+    });
 }
 
 // (entry point, raw stream queries, M, N, K, A, lda, B, ldb, bias, alpha, act, C, ldc, batch, stream)

@@ -1,5 +1,10 @@
 """The binding's native marshalling (csrc/py_marshal.cpp): declines what it does not take, so that binding.py's own code raises what it always has, and
 gives the library the same arguments as that code for what it takes."""
+import os
+import subprocess
+import sys
+import sysconfig
+
 import numpy as np
 import pytest
 
@@ -24,6 +29,29 @@ def test_declines_on_the_host():
         _plain(good[:-1])
     with pytest.raises(ValueError):
         binding.gemm_epilogue_f32(*good[:-1])
+
+
+def test_a_call_that_outlives_the_interpreter(tmp_path):
+    """A daemon thread that comes back from the library while the interpreter shuts down is ended by it there, as it is in a call through ctypes: the
+    process ends with its own status and does not abort.  (The last object of the module to go keeps the interpreter in its shutdown until the thread is back.)"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    probe = str(tmp_path / "py_call_probe.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", probe,
+                    os.path.join(root, "tests", "py_call_probe.cpp")], check=True)
+    code = """
+import threading, time, sys
+sys.path.insert(0, %r)
+import py_call_probe
+assert py_call_probe.call(0) == 7 and py_call_probe.call(-1) is None
+class Last:
+    def __del__(self, sleep=time.sleep): sleep(1.5)
+last = Last()
+threading.Thread(target=py_call_probe.call, args=(700000,), daemon=True).start()
+time.sleep(0.2)
+print("done", flush=True)
+""" % str(tmp_path)
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=60)
+    assert res.stdout == "done\n" and res.returncode == 0, (res.returncode, res.stdout, res.stderr)
 
 
 def _calls():
