@@ -8,7 +8,8 @@ calls raise.
 
 The calls that launch kernels go through native marshalling (``_marshal``, csrc/py_marshal.cpp) where every
 argument is what it takes; it returns None, before it has called anything, where one is not, and the code
-below, which says what a call does with its arguments, takes it from the start.
+below, which says what a call does with its arguments, takes it from the start.  It takes every call where the module
+is missing, or was built for another torch: ``load`` then warns.
 """
 from __future__ import annotations
 
@@ -93,10 +94,9 @@ def load():
     # hands over (every launch then fails with "no device").
     import torch  # noqa: F401
     path = os.environ.get("GE_LIBRARY", LIB_PATH)     # another build of the same library, for A/B timing
-    for needed in (path, MARSHAL_PATH):
-        if not os.path.exists(needed):
-            raise FileNotFoundError(
-                f"{needed} is missing: run `python -m paper_2604_01489_amd.build` first")
+    if not os.path.exists(path):
+        raise FileNotFoundError(
+            f"{path} is missing: run `python -m paper_2604_01489_amd.build` first")
     lib = ctypes.CDLL(path)
     c_int, c_void, c_float, c_size = ctypes.c_int, ctypes.c_void_p, ctypes.c_float, ctypes.c_size_t
     common = [c_int, c_int, c_int, c_void, c_int, c_void, c_int, c_void, c_float, c_int,
@@ -142,17 +142,31 @@ def load():
     lib.conv2d_epilogue_workspace_bytes.argtypes = [ctypes.POINTER(ConvArgs)]
     lib.ge_set_option.restype = c_int
     lib.ge_set_option.argtypes = [ctypes.c_char_p, ctypes.c_char_p]
-    spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
-    native = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(native)
     for name in ("gemm_epilogue_bf16", "gemm_epilogue_f32", "gemm_epilogue_bf16_fused", "conv2d_epilogue_bf16",
                  "gemm_rowsum_params_bf16_ex", "gemm_rowsum_bf16"):
         _entry[name] = ctypes.cast(getattr(lib, name), c_void).value
     if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
         _raw = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
-    _native = native
+    try:
+        _native = load_marshal()
+    except ImportError as err:
+        import warnings
+        warnings.warn(f"no native marshalling, every call costs 2.5 to 4.5 us more on the host ({err}): "
+                      "run `python -m paper_2604_01489_amd.build`", RuntimeWarning, stacklevel=2)
     _lib = lib
     return lib
+
+
+def load_marshal():
+    """The native marshalling, or ImportError: there is none, or it was built for another torch than this one."""
+    import torch
+    spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    built_for = getattr(native, "built_for", None)
+    if built_for != torch.__version__:
+        raise ImportError(f"{MARSHAL_PATH} was built for torch {built_for}, this is {torch.__version__}")
+    return native
 
 
 def load_probes():

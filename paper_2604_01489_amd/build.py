@@ -42,11 +42,12 @@ def _includes(path, seen):
 
 
 def build_marshal(verbose: bool = False) -> str:
-    """The extension module: host code only, against torch's headers and the libraries that ``import torch`` loads."""
+    """The extension module: host code only, against torch's headers and the libraries that ``import torch`` loads, and for that torch alone."""
     import torch
     top = os.path.dirname(torch.__file__)
     lib = os.path.join(top, "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           f'-DGE_TORCH_VERSION="{torch.__version__}"',
            "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(top, "include"), "-o", MARSHAL, MARSHAL_SOURCE,
            "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath," + lib]
     if verbose:
@@ -85,7 +86,12 @@ def build_library(verbose: bool = False, extra_flags=(), incremental: bool = Fal
     def marshal():
         deps = _includes(MARSHAL_SOURCE, set())
         if not incremental or not os.path.exists(MARSHAL) or any(os.path.getmtime(d) > os.path.getmtime(MARSHAL) for d in deps):
-            build_marshal(verbose)
+            try:
+                build_marshal(verbose)
+            except (OSError, RuntimeError) as err:       # no g++, or no headers: the library is whole without it
+                if os.path.exists(MARSHAL):
+                    os.remove(MARSHAL)
+                sys.stderr.write(f"{err}\nno native marshalling: the binding's Python code takes every call\n")
 
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
         marshalled = pool.submit(marshal)

@@ -31,6 +31,32 @@ def test_declines_on_the_host():
         binding.gemm_epilogue_f32(*good[:-1])
 
 
+def _fresh(monkeypatch):
+    for name, value in (("_lib", None), ("_native", None), ("_entry", {}), ("_raw", None)):
+        monkeypatch.setattr(binding, name, value)
+
+
+def test_the_library_loads_without_it(monkeypatch, tmp_path):
+    """No module, something else in its place, or one for another torch: a warning, and binding.py's own code takes every call."""
+    import torch
+    broken = tmp_path / "broken.so"
+    broken.write_bytes(b"no module")
+    t = torch.zeros(64, 64)
+    for what, value in ((binding, str(tmp_path / "missing.so")), (binding, str(broken)), (torch, "0.0")):
+        with monkeypatch.context() as m:
+            _fresh(m)
+            m.setattr(what, "MARSHAL_PATH" if what is binding else "__version__", value)
+            with pytest.warns(RuntimeWarning, match="no native marshalling"):
+                assert binding.status_string(0) == "ok"
+            assert binding._native is None
+            with pytest.raises(ValueError):
+                binding.gemm_epilogue_f32(64, 64, 64, t, 64, t, 64, None, 1.0, "none", t, 64)
+    with monkeypatch.context() as m:
+        _fresh(m)
+        binding.load()
+        assert binding._native is not None
+
+
 def test_a_call_that_outlives_the_interpreter(tmp_path):
     """A daemon thread that comes back from the library while the interpreter shuts down is ended by it there, as it is in a call through ctypes: the
     process ends with its own status and does not abort.  (The last object of the module to go keeps the interpreter in its shutdown until the thread is back.)"""
