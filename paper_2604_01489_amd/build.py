@@ -17,6 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgemm_epilogue.so")
 PROBES_LIB = os.path.join(HERE, "libge_probes.so")
 MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+MARSHAL_STAMP = os.path.join(HERE, "_build", "marshal_torch_version")
 MARSHAL_SOURCE = os.path.join(CSRC, "py_marshal.cpp")
 # the longest compiles first (the pool takes the sources in this order)
 LIB_SOURCES = ["conv_halo_14_11.hip", "conv_halo_12_12.hip", "conv_api.hip", "gemm_fused_t256.hip", "gemm_fused_t256_edge.hip", "gemm_fused_t256_kedge.hip", "gemm_fused_t128.hip",
@@ -41,10 +42,15 @@ def _includes(path, seen):
     return seen
 
 
+def _newer(built, deps):
+    return os.path.exists(built) and all(os.path.getmtime(d) <= os.path.getmtime(built) for d in deps)
+
+
 def build_marshal(verbose: bool = False) -> str:
     """The extension module: host code only, against torch's headers and the libraries that ``import torch`` loads, and for that torch alone."""
     import torch
     top = os.path.dirname(torch.__file__)
+    os.makedirs(os.path.dirname(MARSHAL_STAMP), exist_ok=True)
     lib = os.path.join(top, "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
            f'-DGE_TORCH_VERSION="{torch.__version__}"',
@@ -56,7 +62,16 @@ def build_marshal(verbose: bool = False) -> str:
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("g++ failed on py_marshal.cpp")
+    with open(MARSHAL_STAMP, "w") as f:
+        f.write(torch.__version__)
     return MARSHAL
+
+
+def marshal_is_current() -> bool:
+    """Newer than what it is compiled from, and for the torch that is installed (as the build noted: a module that is loaded to be asked stays loaded)."""
+    import torch
+    return (_newer(MARSHAL, _includes(MARSHAL_SOURCE, set())) and os.path.exists(MARSHAL_STAMP) and
+            open(MARSHAL_STAMP).read() == torch.__version__)
 
 
 def build_library(verbose: bool = False, extra_flags=(), incremental: bool = False) -> str:
@@ -70,10 +85,8 @@ def build_library(verbose: bool = False, extra_flags=(), incremental: bool = Fal
 
     def compile_one(src):
         obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
-        if incremental and not extra_flags and os.path.exists(obj):
-            deps = _includes(os.path.join(CSRC, src), set())
-            if all(os.path.getmtime(d) <= os.path.getmtime(obj) for d in deps):
-                return obj
+        if incremental and not extra_flags and _newer(obj, _includes(os.path.join(CSRC, src), set())):
+            return obj
         cmd = ["hipcc", *compile_flags, *extra_flags, "-c", "-o", obj, os.path.join(CSRC, src)]
         if verbose:
             print(" ".join(cmd), flush=True)
@@ -84,14 +97,14 @@ def build_library(verbose: bool = False, extra_flags=(), incremental: bool = Fal
         return obj
 
     def marshal():
-        deps = _includes(MARSHAL_SOURCE, set())
-        if not incremental or not os.path.exists(MARSHAL) or any(os.path.getmtime(d) > os.path.getmtime(MARSHAL) for d in deps):
-            try:
-                build_marshal(verbose)
-            except (OSError, RuntimeError) as err:       # no g++, or no headers: the library is whole without it
-                if os.path.exists(MARSHAL):
-                    os.remove(MARSHAL)
-                sys.stderr.write(f"{err}\nno native marshalling: the binding's Python code takes every call\n")
+        if incremental and marshal_is_current():
+            return
+        try:
+            build_marshal(verbose)
+        except (OSError, RuntimeError) as err:       # no g++, or no headers: the library is whole without it
+            if os.path.exists(MARSHAL):
+                os.remove(MARSHAL)
+            sys.stderr.write(f"{err}\nno native marshalling: the binding's Python code takes every call\n")
 
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
         marshalled = pool.submit(marshal)
@@ -110,13 +123,13 @@ def build_library(verbose: bool = False, extra_flags=(), incremental: bool = Fal
 
 
 def library_is_current() -> bool:
-    if not all(os.path.exists(f) for f in (LIB, PROBES_LIB, MARSHAL)):
-        return False
-    t = min(os.path.getmtime(f) for f in (LIB, PROBES_LIB, MARSHAL))
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)]
-    inc = os.path.join(os.path.dirname(HERE), "include")
-    deps += [os.path.join(inc, f) for f in os.listdir(inc)]
-    return all(os.path.getmtime(d) <= t for d in deps)
+    """Whether the two HIP libraries are newer than the sources that each is made of."""
+    def deps(sources):
+        seen = set()
+        for src in sources:
+            _includes(os.path.join(CSRC, src), seen)
+        return seen
+    return _newer(LIB, deps(LIB_SOURCES)) and _newer(PROBES_LIB, deps(PROBE_SOURCES))
 
 
 if __name__ == "__main__":

@@ -15,7 +15,36 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 def lib():
     if not build.library_is_current():
         build.build_library()
+    elif not build.marshal_is_current():
+        build.build_marshal()
     return binding.load()
+
+
+def test_what_is_built_is_measured_against_its_own_sources(monkeypatch, tmp_path):
+    """An incremental build compiles the module only where one of its own sources changed: neither it nor the libraries are out of date for the others'."""
+    files = {"a.hip": '#include "a.h"\n', "a.h": "", "p.hip": "", "m.cpp": '#include "m.h"\n', "m.h": "", "stamp": "t1", "a.so": "", "p.so": "", "m.so": ""}
+    for i, (name, text) in enumerate(files.items()):
+        (tmp_path / name).write_text(text)
+        os.utime(tmp_path / name, (i, i))
+    at = lambda name: str(tmp_path / name)
+    for name, value in (("CSRC", str(tmp_path)), ("LIB", at("a.so")), ("PROBES_LIB", at("p.so")), ("MARSHAL", at("m.so")), ("MARSHAL_SOURCE", at("m.cpp")),
+                        ("MARSHAL_STAMP", at("stamp")), ("LIB_SOURCES", ["a.hip"]), ("PROBE_SOURCES", ["p.hip"])):
+        monkeypatch.setattr(build, name, value, raising=False)
+    import torch
+    monkeypatch.setattr(torch, "__version__", "t1")
+    state = lambda: (build.library_is_current(), build.marshal_is_current())
+    assert state() == (True, True)
+    for edited, built, now in (("a.h", "a.so", (False, True)), ("p.hip", "p.so", (False, True)), ("m.h", "m.so", (True, False)), ("m.cpp", "m.so", (True, False))):
+        os.utime(at(edited), (100, 100))
+        assert state() == now, edited
+        os.utime(at(built), (101, 101))
+        assert state() == (True, True), built
+        os.utime(at(edited), (1, 1))
+        os.utime(at(built), (50, 50))
+    monkeypatch.setattr(torch, "__version__", "t2")
+    assert state() == (True, False)
+    os.remove(at("m.so"))
+    assert state() == (True, False)
 
 
 def declared_in(header_file):
