@@ -38,10 +38,11 @@
  * stream that is being captured is refused such a first allocation
  * (GE_ERR_WORKSPACE): run the call once on that stream before capturing, or
  * pass a workspace.  Calls on different streams use different buffers; calls
- * on one stream are ordered by it.  (Where the library itself would slice K, up
- * to 2560, for at most 256 tiles of 32 x 32 (convolutions: 512), each workgroup adds
- * up its tile's slices and nothing is parked; the workspace query is the plan's all the same,
- * and a workspace that is given must still be as large.)
+ * on one stream are ordered by it.  (Some calls of few output tiles for which the
+ * plan slices K add up a tile's slices in one workgroup and park nothing.  Which these are is
+ * this build's choice and nothing to count on: the workspace query is the plan's all the same, a workspace
+ * that is given must be as large, and the stream's buffer grows to it; only in a capture, where it cannot, such a
+ * call goes without.)
  *
  * Errors.  Every call validates its arguments first and returns a status; on
  * any status other than GE_OK nothing was enqueued and C is untouched.

@@ -286,7 +286,7 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
     void *ws = nullptr;
     GemmParams pg = p;
     if (small) {
-        st = check_unused_workspace(partial_bytes((int)M, a.Cout, 1, pl.splitK), a.workspace, a.workspace_bytes);
+        st = reserve_workspace(partial_bytes((int)M, a.Cout, 1, pl.splitK), a.workspace, a.workspace_bytes, (hipStream_t)stream);
         if (st != GE_OK) return st;
     }
     if (raw) {

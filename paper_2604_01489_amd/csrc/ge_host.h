@@ -97,8 +97,10 @@ ge_status_t make_plan_bf16_for(int M, int N, int K, int batch, bool fast, ge_pla
 // Whether the call goes to workgroups in the 32 x 32 tiles of gemm_small.h, with the sums of the plan: few of them (small_layout.h), the library's own choice of
 // slices, panels within 31-bit byte offsets.  The plan, and with it the configuration's name, stays as it is.
 bool small_ok(const Plan &pl, const GemmParams &p, ge_plan_t plan);
-// Such a call needs no workspace; one that is given is held to the plan's size, as before there were such calls.
-ge_status_t check_unused_workspace(size_t need, const void *user, size_t user_bytes);
+// Such a call needs no workspace, but asks for its slices' all the same where it can, as before there were such calls: one that is given is held to the plan's size,
+// and the library's buffer of the stream grows to it, on which a smaller sliced call may count that is captured afterwards (256 x 256 x 4096 behind 512 x 512 x
+// 2048).  In a capture the call goes without.
+ge_status_t reserve_workspace(size_t need, void *user, size_t user_bytes, hipStream_t stream);
 size_t partial_bytes(int M, int N, int batch, int splitK);
 int choose_group_m(int tilesM, int tilesN);
 // The four-wave kernel (gemm_bf16_w4.h) takes launches of 256 x 256 tiles whose blocks walk a K range

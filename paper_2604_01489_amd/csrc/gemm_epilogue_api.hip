@@ -341,11 +341,6 @@ bool small_ok(const Plan &pl, const GemmParams &p, ge_plan_t plan)
     return ge::small_tile_takes((long long)ceil_div(p.M, 32) * ceil_div(p.N, 32) * p.batch, pl.splitK, p.K, pl.tile == TILE_RAGGED_64);
 }
 
-ge_status_t check_unused_workspace(size_t need, const void *user, size_t user_bytes)
-{
-    return user && need && (user_bytes < need || ((uintptr_t)user & 255u)) ? GE_ERR_WORKSPACE : GE_OK;
-}
-
 size_t partial_bytes(int M, int N, int batch, int splitK)
 {
     return splitK <= 1 ? 0 : (size_t)splitK * (size_t)batch * (size_t)M * (size_t)N * sizeof(float);
@@ -431,6 +426,14 @@ ge_status_t acquire_workspace(size_t need, void *user, size_t user_bytes, hipStr
     }
     *out = ptr;
     return GE_OK;
+}
+
+ge_status_t reserve_workspace(size_t need, void *user, size_t user_bytes, hipStream_t stream)
+{
+    void *unused = nullptr;
+    if (need == 0 || acquire_workspace(need, user, user_bytes, stream, &unused) == GE_OK) return GE_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return !user && hipStreamIsCapturing(stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone ? GE_OK : GE_ERR_WORKSPACE;
 }
 
 template <int EDGE>
@@ -540,7 +543,7 @@ ge_status_t run_bf16(int M, int N, int K, const uint16_t *A, int lda, const uint
     }
     void *ws = nullptr;
     if (small) {
-        st = check_unused_workspace(partial_bytes(M, N, batch, pl.splitK), workspace, workspace_bytes);
+        st = reserve_workspace(partial_bytes(M, N, batch, pl.splitK), workspace, workspace_bytes, (hipStream_t)stream);
         if (st != GE_OK) return st;
     }
     if (raw) {

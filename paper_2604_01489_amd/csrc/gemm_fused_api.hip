@@ -220,7 +220,7 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
     void *ws = nullptr;
     GemmParams pg = p;                      // the GEMM pass: partial tiles go to the workspace
     if (small) {
-        st = check_unused_workspace(partial_bytes(a.M, a.N, a.batch, pl.splitK), a.workspace, a.workspace_bytes);
+        st = reserve_workspace(partial_bytes(a.M, a.N, a.batch, pl.splitK), a.workspace, a.workspace_bytes, (hipStream_t)stream);
         if (st != GE_OK) return st;
     }
     if (raw) {

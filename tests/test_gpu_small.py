@@ -98,6 +98,39 @@ def test_a_workspace_that_was_too_small_still_is():
 
 
 @pytest.mark.gpu
+def test_a_sliced_call_captured_behind_one_that_slices_no_longer():
+    """The first call adds up its slices in its workgroups, and the stream's buffer grows to them all the same: the capture of a call that parks less finds room."""
+    import torch
+    g, side = torch.Generator(device="cuda").manual_seed(3), torch.cuda.Stream()
+
+    def operands(M, N, K):
+        return [torch.randn(s, device="cuda", generator=g).bfloat16() for s in ((M, K), (K, N))] + [torch.empty(M, N, device="cuda") for _ in range(2)]
+    for conv in (False, True):
+        assert binding.load().ge_release_workspace() == 0                      # no buffer left of an earlier test
+        A, B, C, _ = operands(512, 512, 2048)
+        if conv:
+            X, W = torch.randn(4, 14, 14, 256, device="cuda", generator=g).bfloat16(), torch.randn(256, 3, 3, 256, device="cuda", generator=g).bfloat16()
+            Y = torch.empty(4, 14, 14, 256, device="cuda")
+        A2, B2, C2, eager = operands(256, 256, 4096)
+        binding.gemm_epilogue_bf16(256, 256, 4096, A2, 4096, B2, 256, None, 1.0, "none", eager, 256)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            if conv: binding.conv2d_epilogue_bf16(X, W, Y, pad=(1, 1))
+            else: binding.gemm_epilogue_bf16(512, 512, 2048, A, 2048, B, 512, None, 1.0, "none", C, 512)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            binding.gemm_epilogue_bf16(256, 256, 4096, A2, 4096, B2, 256, None, 1.0, "none", C2, 256, stream=side)
+        for _ in range(3):
+            C2.fill_(-1.0)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(C2, eager)
+        del graph
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("shape,kw", [
     ((1, 7, 5, 8, 32, 3, 3), dict(pad=(1, 1))),                                                    # a tap to a chunk; guarded kernel below a million multiply-adds
     ((2, 15, 17, 24, 136, 3, 3), dict(pad=(1, 1), residual="bf16", out="bf16")),                    # one step of 216, taps that end inside a chunk's neighbours
