@@ -56,7 +56,7 @@ def test_any_alignment(oracle, transA, transB, M, N, K, kw):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K,kw", [(44, 690, 1109, dict()), (131, 67, 1536, dict(misalign=1)), (512, 512, 2048, dict()), (144, 440, 2560, dict())])
+@pytest.mark.parametrize("M,N,K,kw", [(44, 690, 1109, dict()), (131, 67, 1536, dict(misalign=1)), (512, 512, 2048, dict()), (144, 440, 2552, dict())])     # (2560 takes slices)
 def test_in_place_of_k_slices(oracle, M, N, K, kw):
     """In runs of steps no longer than the plan's slices: as exact as these, and nothing goes to a workspace, so a capture needs none."""
     import torch
