@@ -276,9 +276,10 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
     // few output tiles and a long K (late layers: small images, many channels): K slices into the
     // library's workspace, summed in slice order by the second pass, which also runs the chain
     const bool sliced = pl.splitK > 1;
+    const bool bareF32 = a.y_type == GE_DTYPE_F32 && !a.R;
     // few tiles: in smaller ones, with the sums of the plan (gemm_small.h); a workspace that is given is held to the plan's size all the same
     const bool small = pl.tile == TILE_128 && opt_force_config() == FORCE_NONE &&
-                       ge::small_conv_takes((long long)ceil_div(M, 32) * ceil_div(a.Cout, 32), pl.splitK, (int)K, cp.c8);
+                       ge::small_conv_takes((long long)ceil_div(M, 32) * ceil_div(a.Cout, 32), pl.splitK, (int)K, cp.c8, bareF32);
     // few or short ones otherwise: gemm_tile64_launch.h
     const Tile64 tile64 = sliced || small || pl.tile == TILE_GENERIC || opt_force_config() != FORCE_NONE ? TILE64_NO
         : ge::conv_tile64_kind(pl.tile == TILE_128, (long long)ceil_div(M, 64) * ceil_div(a.Cout, 128), (int)K, a.y_type == GE_DTYPE_BF16, cp.c8);

@@ -54,10 +54,13 @@ GE_HD constexpr bool small_tile_takes(long long tiles, int slices, int K, bool r
 // The same for a convolution whose plan names the 128 x 128 tile; c8: of the kernel for channels a multiple of 8 but not of 32.  That tile's gathered
 // steps take 0.2 to 0.35 us each beside 8 us for its prologue and epilogue, more than in a product, so the lines lie further out.  us, plan's tile / small: 8 images of 14 x 14 x 256 -> 64, 1 x 1, 6.9 / 3.9; 14 of 13 x 13 x 256 -> 32, 3 x 3, in slices 11.9 / 9.4; of its time over 9000 drawn
 // calls, up to two tiles a CU: K = 64 0.78 to 0.91, 256 0.55 to 0.65, 576 0.56 to 0.70, 1152 0.46 to 0.58, in slices 2304 0.72 to 0.86 (4608 1.0 to 1.4), c8 0.38 to 0.9.  Three: 65 to 256 k 0.94
-// and 0.77, 1152 0.87, c8 0.70 to 0.85 (288 to 576 k 1.0 to 1.24); four: 129 to 256 k 0.87.
-GE_HD constexpr bool small_conv_takes(long long tiles, int slices, int K, bool c8)
+// and 0.77, 1152 0.87, c8 0.70 to 0.85 (288 to 576 k 1.0 to 1.24); four: 129 to 256 k 0.87.  These with bf16 out; fp32 out without a residual (bareF32), whose stores are
+// twice as many, beside the larger tile's in one round of them: a second tile a CU from 48 k on (48 0.97, 64 1.00; 32 1.05: 3724 x 128 x 32 4.7 / 5.1; 16 1.03), a third from 129 on
+// (128 1.04: 6125 x 128 x 128 5.8 / 6.1; channels of 8, 80 k, 1.05), as with bf16 out beyond that; what stays takes the 64 x 128 tile (0.84 to 0.87).  With a residual as with bf16 out (32 k 0.90, 128 0.91).
+GE_HD constexpr bool small_conv_takes(long long tiles, int slices, int K, bool c8, bool bareF32)
 {
     if (slices > 1) return tiles <= 2 * SMALL_CUS && K <= 2560;
+    if (bareF32 && tiles > SMALL_CUS && K <= (tiles > 2 * SMALL_CUS ? 128 : 47)) return false;
     if (tiles <= 2 * SMALL_CUS) return true;
     if (K > 128 && K <= SMALL_STEP) return tiles <= 4 * SMALL_CUS;
     return tiles <= 3 * SMALL_CUS && (K <= 128 ? K > 64 : K > 768 || c8);

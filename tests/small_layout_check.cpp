@@ -142,14 +142,16 @@ int main()
                 std::printf("rule: %lld tiles, %d slices, K %d, ragged %d, bare fp32 %d\n", c.tiles, c.slices, c.K, c.ragged, bare);
                 return 1;
             }
-    struct { long long tiles; int slices, K; bool c8, takes; } conv[] = {{512, 1, 27 * 8, true, true}, {512, 1, 64, false, true}, {513, 1, 64, false, false}, {513, 1, 72, false, true},
+    struct { long long tiles; int slices, K; bool c8, takes; int bareF32 = -1; } conv[] = {{256, 1, 32, false, true}, {257, 1, 40, true, true, 0}, {512, 1, 32, false, true, 0}, {257, 1, 48, true, true},
+        {768, 1, 128, false, true, 0}, {513, 1, 136, false, true}, {512, 1, 27 * 8, true, true}, {512, 1, 64, false, true}, {513, 1, 64, false, false}, {513, 1, 72, false, true, 0},
         {1024, 1, 136, false, true}, {1025, 1, 136, true, false}, {768, 1, 288, false, false}, {768, 1, 288, true, true}, {768, 1, 1152, false, true}, {769, 1, 1152, true, false},
         {512, 4, 2304, false, true}, {513, 4, 2304, false, false}, {20, 8, 4608, false, false}};
     for (auto &c : conv)
-        if (small_conv_takes(c.tiles, c.slices, c.K, c.c8) != c.takes) {
-            std::printf("rule of convolutions: %lld tiles, %d slices, K %d, c8 %d\n", c.tiles, c.slices, c.K, c.c8);
-            return 1;
-        }
+        for (bool bare : {false, true})
+            if (small_conv_takes(c.tiles, c.slices, c.K, c.c8, bare) != (bare && c.bareF32 >= 0 ? c.bareF32 != 0 : c.takes)) {
+                std::printf("rule of convolutions: %lld tiles, %d slices, K %d, c8 %d, bare fp32 %d\n", c.tiles, c.slices, c.K, c.c8, bare);
+                return 1;
+            }
     struct { bool plan128; long long blocks; int K; bool bf16; Tile64 kind; } tiles[] = {{true, 256, 65, true, TILE64_RING}, {true, 256, 5000, false, TILE64_RING}, {true, 257, 65, false, TILE64_NO},
         {true, 768, 128, true, TILE64_RING}, {true, 257, 129, true, TILE64_NO}, {true, 769, 72, true, TILE64_NO}, {true, 1025, 72, true, TILE64_RING}, {true, 1537, 72, true, TILE64_NO},
         {false, 1280, 128, true, TILE64_RING}, {false, 1281, 72, true, TILE64_NO},
