@@ -282,7 +282,7 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
                        ge::small_conv_takes((long long)ceil_div(M, 32) * ceil_div(a.Cout, 32), pl.splitK, (int)K, cp.c8, bareF32);
     // few or short ones otherwise: gemm_tile64_launch.h
     const Tile64 tile64 = sliced || small || pl.tile == TILE_GENERIC || opt_force_config() != FORCE_NONE ? TILE64_NO
-        : ge::conv_tile64_kind(pl.tile == TILE_128, (long long)ceil_div(M, 64) * ceil_div(a.Cout, 128), (int)K, a.y_type == GE_DTYPE_BF16, cp.c8);
+        : ge::conv_tile64_kind(pl.tile == TILE_128, (long long)ceil_div(M, 64) * ceil_div(a.Cout, 128), (int)K, a.y_type == GE_DTYPE_BF16, ceil_div(M, 64) % 2 != 0, cp.c8);
     const bool raw = sliced && !small;
     void *ws = nullptr;
     GemmParams pg = p;

@@ -8,7 +8,7 @@ Tile64 tile64_of(const Plan &pl, const GemmParams &p, ge_plan_t plan)
     if ((pl.tile != TILE_128 && pl.tile != TILE_256) || pl.splitK > 1 || plan == GE_PLAN_SPLITK || p.triA != ge::TRI_NONE || opt_force_config() != FORCE_NONE || opt_eight_waves() ||
         opt_stage_k32())
         return TILE64_NO;
-    return ge::tile64_kind(pl.tile == TILE_128, (long long)ceil_div(p.M, 64) * ceil_div(p.N, 128) * p.batch, p.K, p.cType == ge::DT_BF16);
+    return ge::tile64_kind(pl.tile == TILE_128, (long long)ceil_div(p.M, 64) * ceil_div(p.N, 128) * p.batch, p.K, p.cType == ge::DT_BF16, ceil_div(p.M, 64) % 2 != 0);
 }
 
 void launch_tile64_ring(const GemmParams &p, dim3 grid, hipStream_t st) { launch_tile64_mode<64, 1, 4, 4, 3>(p, grid, st); }

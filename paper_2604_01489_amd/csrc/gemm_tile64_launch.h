@@ -10,7 +10,11 @@
 // to two blocks a CU K = 576 0.87, up to one and a half 1152 0.85 (490 blocks of K = 720 17.6 / 18.6), up to six K = 256 0.83 to 0.92 (else K = 256 0.95, 576 1.0); K <= 64 0.71 to 0.97.
 // K <= 64, bf16 out: 256 of 256 x 256 x 64 13.8 -> 11.5 us, 256 of 128 x 128 x 64 6.0 -> 5.4, 256 of 512 x 512 x 64, there on 128 x 128 tiles in place of 256 x 256 ones (64 x 128: 46.6), 49.6 -> 43.6, as
 // a fourth to a CU is (209 of 80 x 256 x 40 6.55 us, 64 x 128 6.80; convolutions 0.97);
-// with fp32 out, where the stores are all, 0.93 of the time up to a block a CU and 0.89 beyond four, between these none (0.96 to 0.99).
+// with fp32 out, where the stores are all, 0.93 of the time up to a block a CU, between one and four none (0.96 to 0.99), the fifth 0.84 to 0.91.  Beyond that where half of the larger
+// tile's last row of blocks is padding (64-row tiles odd in number), up to sixteen: 0.81 to 0.94, results that come from memory 0.87 to 0.97 (1500 drawn calls each).  Rows of whole larger tiles
+// only gain while the 256 MB cache holds what is written (0.88 to 0.97 up to ten a CU); from memory 0.96 to 1.03, with a residual 0.97 to 1.08, one call in three by more than 3 %.
+// bf16 out beyond sixteen to a CU, 128 x 128 against 64 x 128, 470 drawn calls: up to 6000 blocks 1.05, with a residual 1.08 to 1.09; up to 10000 1.00, 1.06; 256 of 512 x 512 x 64, 8192
+// blocks, 43.6 / 46.6: the line is drawn for full tiles, the others (either way faster than the ring of four stages, 0.79 to 0.94) would gain on the narrower one.
 #pragma once
 #include <hip/hip_runtime.h>
 

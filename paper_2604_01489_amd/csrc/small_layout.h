@@ -67,9 +67,9 @@ GE_HD constexpr bool small_conv_takes(long long tiles, int slices, int K, bool c
 }
 
 // Which of the tiles of gemm_tile64_launch.h (figures there) a product in one pass takes whose plan names the 128 x 128 tile (plan128) or the 256 x 256 one; blocks: its 64 x 128 tiles;
-// upTo: the K up to which it takes the 64 x 128 tile beyond one block a CU.
+// oddRows: their rows are odd in number; upTo: the K up to which it takes the 64 x 128 tile beyond one block a CU.
 enum Tile64 { TILE64_NO = 0, TILE64_RING = 1, TILE64_SHORT = 2, TILE64_SHORT_WIDE = 3 };
-GE_HD constexpr Tile64 tile64_kind(bool plan128, long long blocks, int K, bool bf16Out, int upTo = 128)
+GE_HD constexpr Tile64 tile64_kind(bool plan128, long long blocks, int K, bool bf16Out, bool oddRows, int upTo = 128)
 {
     // three are on a CU at once, or two of 128 x 128: what four to a CU take twice, those take in one round
     const bool third = blocks <= 3 * SMALL_CUS, fourth = !third && blocks <= 4 * SMALL_CUS;
@@ -78,13 +78,13 @@ GE_HD constexpr Tile64 tile64_kind(bool plan128, long long blocks, int K, bool b
         return bf16Out && K <= upTo && (plan128 ? !fourth && blocks <= 6 * SMALL_CUS : !third && blocks <= 5 * SMALL_CUS) ? TILE64_RING : TILE64_NO;
     }
     if (bf16Out) return fourth || blocks > 16 * SMALL_CUS ? TILE64_SHORT_WIDE : TILE64_SHORT;
-    return plan128 && (blocks <= SMALL_CUS || (blocks > 4 * SMALL_CUS && blocks <= 16 * SMALL_CUS)) ? TILE64_SHORT : TILE64_NO;
+    return plan128 && (blocks <= SMALL_CUS || (blocks > 4 * SMALL_CUS && blocks <= (oddRows ? 16 : 5) * SMALL_CUS)) ? TILE64_SHORT : TILE64_NO;
 }
 
 // A convolution's: with a chunk's tap per lane (c8) the larger tile's steps are dearer.
-GE_HD constexpr Tile64 conv_tile64_kind(bool plan128, long long blocks, int K, bool bf16Out, bool c8)
+GE_HD constexpr Tile64 conv_tile64_kind(bool plan128, long long blocks, int K, bool bf16Out, bool oddRows, bool c8)
 {
-    return tile64_kind(plan128, blocks, K, bf16Out, !c8 ? 128 : 2 * blocks <= 3 * SMALL_CUS ? 1152 : blocks <= 2 * SMALL_CUS ? 576 : 256);
+    return tile64_kind(plan128, blocks, K, bf16Out, oddRows, !c8 ? 128 : 2 * blocks <= 3 * SMALL_CUS ? 1152 : blocks <= 2 * SMALL_CUS ? 576 : 256);
 }
 
 // Steps whose sums form one chain before they are added to the others: a plan's K slice, so that the sums are as exact as in slices.

@@ -152,21 +152,24 @@ int main()
                 std::printf("rule of convolutions: %lld tiles, %d slices, K %d, c8 %d, bare fp32 %d\n", c.tiles, c.slices, c.K, c.c8, bare);
                 return 1;
             }
-    struct { bool plan128; long long blocks; int K; bool bf16; Tile64 kind; } tiles[] = {{true, 256, 65, true, TILE64_RING}, {true, 256, 5000, false, TILE64_RING}, {true, 257, 65, false, TILE64_NO},
+    struct { bool plan128; long long blocks; int K; bool bf16; Tile64 kind, even = (Tile64)-1; } tiles[] = {{true, 1280, 64, false, TILE64_SHORT}, {true, 1281, 64, false, TILE64_SHORT, TILE64_NO}, {true, 4096, 64, false, TILE64_SHORT, TILE64_NO},
+        {true, 256, 65, true, TILE64_RING}, {true, 256, 5000, false, TILE64_RING}, {true, 257, 65, false, TILE64_NO},
         {true, 768, 128, true, TILE64_RING}, {true, 257, 129, true, TILE64_NO}, {true, 769, 72, true, TILE64_NO}, {true, 1025, 72, true, TILE64_RING}, {true, 1537, 72, true, TILE64_NO},
         {false, 1280, 128, true, TILE64_RING}, {false, 1281, 72, true, TILE64_NO},
         {false, 100, 128, true, TILE64_NO}, {true, 768, 64, true, TILE64_SHORT}, {true, 769, 64, true, TILE64_SHORT_WIDE}, {true, 1024, 64, true, TILE64_SHORT_WIDE}, {false, 4096, 64, true, TILE64_SHORT}, {false, 4097, 64, true, TILE64_SHORT_WIDE}, {false, 4096, 64, false, TILE64_NO},
         {true, 256, 64, false, TILE64_SHORT}, {true, 257, 64, false, TILE64_NO}, {true, 1025, 64, false, TILE64_SHORT}, {true, 4097, 64, false, TILE64_NO}};
     for (auto &c : tiles)
-        if (tile64_kind(c.plan128, c.blocks, c.K, c.bf16) != c.kind) {
-            std::printf("rule of the 64 x 128 tile: %lld blocks, K %d\n", c.blocks, c.K);
+        for (bool odd : {false, true})
+            if (tile64_kind(c.plan128, c.blocks, c.K, c.bf16, odd) != (!odd && c.even != (Tile64)-1 ? c.even : c.kind)) {
+                std::printf("rule of the 64 x 128 tile: %lld blocks, K %d, odd %d\n", c.blocks, c.K, odd);
+                return 1;
+            }
+    for (bool odd : {false, true})
+        if (conv_tile64_kind(true, 384, 1152, true, odd, true) != TILE64_RING || conv_tile64_kind(true, 384, 1160, true, odd, true) != TILE64_NO || conv_tile64_kind(true, 512, 576, true, odd, true) != TILE64_RING || conv_tile64_kind(true, 385, 584, true, odd, true) != TILE64_NO || conv_tile64_kind(true, 513, 264, true, odd, true) != TILE64_NO ||
+            conv_tile64_kind(true, 768, 256, true, odd, true) != TILE64_RING || conv_tile64_kind(true, 257, 160, true, odd, false) != TILE64_NO || conv_tile64_kind(true, 256, 4608, false, odd, false) != TILE64_RING) {
+            std::printf("rule of the 64 x 128 tile for convolutions\n");
             return 1;
         }
-    if (conv_tile64_kind(true, 384, 1152, true, true) != TILE64_RING || conv_tile64_kind(true, 384, 1160, true, true) != TILE64_NO || conv_tile64_kind(true, 512, 576, true, true) != TILE64_RING || conv_tile64_kind(true, 385, 584, true, true) != TILE64_NO || conv_tile64_kind(true, 513, 264, true, true) != TILE64_NO ||
-        conv_tile64_kind(true, 768, 256, true, true) != TILE64_RING || conv_tile64_kind(true, 257, 160, true, false) != TILE64_NO || conv_tile64_kind(true, 256, 4608, false, false) != TILE64_RING) {
-        std::printf("rule of the 64 x 128 tile for convolutions\n");
-        return 1;
-    }
     if (small_run(1, 64) < 1 << 30 || small_run(3, 512) != 2 || small_run(3, 672) != 2 || small_run(8, 128) != 1) return 1;
     std::printf("small layout ok: %lld elements\n", checked);
     return 0;
