@@ -406,7 +406,8 @@ ge_status_t ge_release_workspace(void);
 /*
  * Switches for timing runs and tests; none changes a result contract.
  *   "force_config"  "256x256" | "128x128" | "generic": block tile of the bf16 kernels
- *                   ("generic" also for fp32: its kernels for any alignment), whatever the planner would pick
+ *                   ("generic" also for fp32: its kernels for any alignment), whatever the planner would pick;
+ *                   any of them keeps calls of few tiles or a short K from the kernels for these, in fp32 as well
  *   "waves"         "8": full 256 x 256 tiles stay on the eight-wave kernel ("4": default)
  *   "stage_k"       "32": no 64-k load phases in the eight-wave kernel ("64": default)
  *   "conv_halo"     "off": 3 x 3 convolutions stay on the gathering kernel; "on": the
@@ -425,9 +426,8 @@ const char *ge_status_string(ge_status_t status);
 
 /* Name of the kernel configuration the last successful call on this thread
  * launched ("bf16_256x256x64_w4", "bf16_256x256x32_w8", "f32_128x128x16_w4", "f32_ragged_64x64x32",
- * ...); for reports.  The names may change from one build to the next.  The tile is the plan's:
- * bf16 products of few tiles go to workgroups in 32 x 32, 64 x 128 or (K up to 64)
- * 128 x 128 pieces of it under the same name. */
+ * ...); for reports.  The names may change from one build to the next.  "_splitk": K slices in a launch
+ * of their own and a second pass. */
 const char *ge_last_config(void);
 
 #ifdef __cplusplus

@@ -297,27 +297,30 @@ extern "C" ge_status_t conv2d_epilogue_bf16(const ge_conv_args_t *args, void *st
     }
     const dim3 grid((unsigned)((long long)pl.tilesM * pl.tilesN * pl.splitK));
     hipStream_t hs = (hipStream_t)stream;
-    switch (pl.tile) {
+    if (small) {
+        launch_small(p, hs);
+        g_last_config = cp.c8 ? "conv_bf16_c8_small_32x32x256" : "conv_bf16_small_32x32x256";
+    } else if (tile64 != TILE64_NO) {
+        launch_tile64_conv(p, tile64, cp.c8, hs);
+        g_last_config = tile64_config(tile64, cp.c8 ? TILE64_CONV_C8 : TILE64_CONV);
+    } else switch (pl.tile) {
     case TILE_256:
-        if (tile64 != TILE64_NO) launch_tile64_conv(p, tile64, cp.c8, hs);
-        else if (cp.c8) launch_conv_c8<256, 256, 2, 4>(pg, raw, grid, hs);
-        else launch_conv<256, 256, 2, 4>(pg, pl.edge, raw, grid, hs);
         if (cp.c8) {
+            launch_conv_c8<256, 256, 2, 4>(pg, raw, grid, hs);
             g_last_config = raw ? "conv_bf16_c8_256x256x32_w8_splitk" : "conv_bf16_c8_256x256x32_w8";
             break;
         }
+        launch_conv<256, 256, 2, 4>(pg, pl.edge, raw, grid, hs);
         g_last_config = raw ? "conv_bf16_256x256x32_w8_splitk" : "conv_bf16_256x256x32_w8";
         break;
     case TILE_128:
-        if (small) launch_small(p, hs);
-        else if (tile64 != TILE64_NO) launch_tile64_conv(p, tile64, cp.c8, hs);
-        else if (cp.c8) launch_conv_c8<128, 128, 2, 2>(pg, raw, grid, hs);
-        else launch_conv<128, 128, 2, 2>(pg, pl.edge, raw, grid, hs);
         if (cp.c8) {
-            g_last_config = sliced ? "conv_bf16_c8_128x128x32_w4_splitk" : "conv_bf16_c8_128x128x32_w4";
+            launch_conv_c8<128, 128, 2, 2>(pg, raw, grid, hs);
+            g_last_config = raw ? "conv_bf16_c8_128x128x32_w4_splitk" : "conv_bf16_c8_128x128x32_w4";
             break;
         }
-        g_last_config = sliced ? "conv_bf16_128x128x32_w4_splitk" : "conv_bf16_128x128x32_w4";
+        launch_conv<128, 128, 2, 2>(pg, pl.edge, raw, grid, hs);
+        g_last_config = raw ? "conv_bf16_128x128x32_w4_splitk" : "conv_bf16_128x128x32_w4";
         break;
     default:
         if (raw) GE_LAUNCH(ge::conv_bf16_generic_kernel<true>, grid, dim3(256), 0, hs, pg);

@@ -95,7 +95,7 @@ ge_status_t make_plan_bf16(int M, int N, int K, int batch, bool fast, ge_plan_t 
 ge_status_t make_plan_bf16_for(int M, int N, int K, int batch, bool fast, ge_plan_t plan, int split_k, int ldc, bool f32Out, Plan *out,
                                bool skinny = false, bool ragged = false);
 // Whether the call goes to workgroups in the 32 x 32 tiles of gemm_small.h, with the sums of the plan: few of them (small_layout.h), the library's own choice of
-// slices, panels within 31-bit byte offsets.  The plan, and with it the configuration's name, stays as it is.
+// slices, panels within 31-bit byte offsets.  The plan, and with it the workspace query, stays as it is.
 bool small_ok(const Plan &pl, const GemmParams &p, ge_plan_t plan);
 // Such a call needs no workspace, but asks for its slices' all the same where it can, as before there were such calls: one that is given is held to the plan's size,
 // and the library's buffer of the stream grows to it, on which a smaller sliced call may count that is captured afterwards (256 x 256 x 4096 behind 512 x 512 x

@@ -555,6 +555,12 @@ ge_status_t run_bf16(int M, int N, int K, const uint16_t *A, int lda, const uint
     const dim3 grid((unsigned)((long long)pl.tilesM * pl.tilesN * batch * pl.splitK));
     hipStream_t hs = (hipStream_t)stream;
     hipError_t err;
+    if (small || tile64 != TILE64_NO) {
+        if (small) launch_small(p, hs);
+        else       launch_tile64(p, tile64, hs);
+        g_last_config = small ? "bf16_small_32x32x256" : tile64_config(tile64, TILE64_PLAIN);
+        return ge_host::take_launch_error() != hipSuccess ? GE_ERR_LAUNCH : GE_OK;
+    }
     switch (pl.tile) {
     case TILE_SKINNY: {
         const dim3 sgrid((unsigned)((long long)pl.tilesM * pl.splitK), (unsigned)batch);
@@ -589,25 +595,18 @@ ge_status_t run_bf16(int M, int N, int K, const uint16_t *A, int lda, const uint
         g_last_config = raw ? "bf16_256x256x32_w8_splitk" : "bf16_256x256x32_w8";
         break;
     case TILE_128:
-        if (small || tile64 != TILE64_NO) {
-            if (small) launch_small(p, hs);
-            else       launch_tile64(p, tile64, hs);
-            err = ge_host::take_launch_error();
-        } else {
-            err = launch_fast<128, 128, 2, 2>(p, tile_edge(pl, K, 32), raw, (int)act, grid, hs);
-        }
-        g_last_config = sliced ? "bf16_128x128x32_w4_splitk" : "bf16_128x128x32_w4";
+        err = launch_fast<128, 128, 2, 2>(p, tile_edge(pl, K, 32), raw, (int)act, grid, hs);
+        g_last_config = raw ? "bf16_128x128x32_w4_splitk" : "bf16_128x128x32_w4";
         break;
     case TILE_RAGGED_128:
     case TILE_RAGGED_64:
         p.clampLo = -INFINITY;       // the run-time consumer chain, with nothing beyond the plain operator's
         p.clampHi = INFINITY;
-        if (small)                           launch_small(p, hs);
-        else if (pl.tile == TILE_RAGGED_128) launch_ragged_128(p, raw, grid, hs);
-        else                                 launch_ragged_64(p, raw, grid, hs);
+        if (pl.tile == TILE_RAGGED_128) launch_ragged_128(p, raw, grid, hs);
+        else                            launch_ragged_64(p, raw, grid, hs);
         err = ge_host::take_launch_error();
         g_last_config = pl.tile == TILE_RAGGED_128 ? (raw ? "bf16_ragged_128x128x64_splitk" : "bf16_ragged_128x128x64")
-                                                   : (sliced ? "bf16_ragged_64x64x64_splitk" : "bf16_ragged_64x64x64");
+                                                   : (raw ? "bf16_ragged_64x64x64_splitk" : "bf16_ragged_64x64x64");
         break;
     default:
         if (raw) GE_LAUNCH(ge::gemm_bf16_generic_kernel<true>, grid, dim3(256), 0, hs, p);
@@ -766,7 +765,7 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
     }
     // few tiles and no slices: smaller ones (gemm_f32_few.h), for rows of a chunk or more and panels within 31-bit byte offsets; one step of the
     // direct-to-LDS kernel (K <= 16) is over as soon (5 x 40 x 8 3.1 us, 3.2 there)
-    const int few = raw || elementwise || (fast && K <= 16) || opt_force_config() == FORCE_GENERIC || K < 4 || N < 4 || (long long)lda * 128 + 1024 >= (1ll << 31) || (long long)ldb * 1024 + 1024 >= (1ll << 31) ? 0
+    const int few = raw || elementwise || (fast && K <= 16) || opt_force_config() != FORCE_NONE || K < 4 || N < 4 || (long long)lda * 128 + 1024 >= (1ll << 31) || (long long)ldb * 1024 + 1024 >= (1ll << 31) ? 0
                   : ge::few_tile_f32((long long)ceil_div(M, 16) * ceil_div(N, 16) * batch, (long long)ceil_div(M, 32) * ceil_div(N, 32) * batch, K);
     const bool edge = (M % bm) || (N % bm) || (K % 16);
     auto launch_few = [&](GemmParams pg) {
@@ -817,8 +816,7 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
                                             {"f32_ragged_128x128x32", "f32_ragged_128x128x32_splitk", "f32_ragged_128x128x32_splitk_passes"},
                                             {"f32_elements_64x64x32", "f32_elements_64x64x32_splitk", "f32_elements_64x64x32_splitk_passes"}};
     g_last_config = names[elementwise ? 4 : (fast ? 0 : 2) + (big ? 1 : 0)][!raw ? 0 : perPass == p.splitK ? 1 : 2];
-    // (few tiles in whole 32s and 256 k went by this name when they had a kernel of their own)
-    if (few && fast && M % 32 == 0 && N % 32 == 0 && K % 256 == 0 && t64 <= 64) g_last_config = "f32_small_32x32_k4";
+    if (few) g_last_config = few == 16 ? "f32_few_16x16x256" : "f32_few_32x32x128";
     if (!raw) {
         if (few) launch_few(p);
         else     launch_tiles(p);

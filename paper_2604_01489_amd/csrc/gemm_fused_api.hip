@@ -115,18 +115,13 @@ ge_status_t plan_of(const ge_fused_args_t &a, Plan *out)
                               a.c_type == GE_DTYPE_F32, out, false, ragged(a));
 }
 
-bool tile_k64(const GemmParams &p, int tile, dim3 grid)
+template <int BM>
+bool launch_tile(const GemmParams &p, const Plan &pl, bool raw, dim3 grid, hipStream_t st)
 {
     // 128 x 128 blocks: only where more than one block shares a CU (measured with both operands along
     // k, bf16 out: 4096x2048x2048, 512 blocks, 33 us with 64 k per load phase against 44 us with 32;
     // 2048^3, 256 blocks, 27 against 22 us; 2048x2048x8192 81 against 66 us)
-    return stage_k64(p.transA != 0, p.transB != 0) && (tile == 256 || grid.x > (unsigned)kNumCU);
-}
-
-template <int BM>
-bool launch_tile(const GemmParams &p, const Plan &pl, bool raw, dim3 grid, hipStream_t st)
-{
-    const bool k64 = tile_k64(p, BM, grid);
+    const bool k64 = stage_k64(p.transA != 0, p.transB != 0) && (BM == 256 || grid.x > (unsigned)kNumCU);
     const int edge = tile_edge(pl, p.K, k64 ? 64 : 32);
     if (BM == 256) {
         if (edge == 2) fused_tile_256_kedge(p, k64, raw, grid, st);
@@ -243,13 +238,14 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
             else      GE_LAUNCH((ge::gemm_few_rows_kernel<32, 4>), fgrid, dim3(256), 0, hs, p);
         }
         set_config(a.M <= 16 ? "few_rows_16_k128" : "few_rows_32_k128", a.transA, a.transB, false);
+    } else if (small) {
+        launch_small(p, hs);
+        set_config("small_32x32x256", a.transA, a.transB, false);
+    } else if (tile64 != TILE64_NO) {
+        launch_tile64(p, tile64, hs);
+        set_config(tile64_config(tile64, TILE64_PLAIN) + sizeof "bf16_" - 1, a.transA, a.transB, false);
     } else switch (pl.tile) {
     case TILE_256:
-        if (tile64 != TILE64_NO) {
-            launch_tile64(p, tile64, hs);
-            set_config(tile_k64(p, 256, grid) ? "256x256x64_w8" : "256x256x32_w8", a.transA, a.transB, false);
-            break;
-        }
         // both operands k-strided: every request is a whole line already and the four-wave
         // kernel has nothing to gain (measured at 8192^3: 0.812 against 0.806 ms)
         if (four_wave_ok(pl, a.K) && !(a.transA && !a.transB)) {
@@ -262,11 +258,7 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
         else set_config("256x256x32_w8", a.transA, a.transB, raw);
         break;
     case TILE_128:
-        if (small || tile64 != TILE64_NO) {
-            if (small) launch_small(p, hs);
-            else       launch_tile64(p, tile64, hs);
-            set_config(tile_k64(p, 128, grid) ? "128x128x64_w4" : "128x128x32_w4", a.transA, a.transB, sliced);
-        } else if (launch_tile<128>(pg, pl, raw, grid, hs)) set_config("128x128x64_w4", a.transA, a.transB, raw);
+        if (launch_tile<128>(pg, pl, raw, grid, hs)) set_config("128x128x64_w4", a.transA, a.transB, raw);
         else set_config("128x128x32_w4", a.transA, a.transB, raw);
         break;
     case TILE_RAGGED_128:
@@ -274,9 +266,8 @@ extern "C" ge_status_t gemm_epilogue_bf16_fused(const ge_fused_args_t *args, voi
         set_config("ragged_128x128x64", a.transA, a.transB, raw);
         break;
     case TILE_RAGGED_64:
-        if (small) launch_small(p, hs);
-        else       launch_ragged_64(pg, raw, grid, hs);
-        set_config("ragged_64x64x64", a.transA, a.transB, sliced);
+        launch_ragged_64(pg, raw, grid, hs);
+        set_config("ragged_64x64x64", a.transA, a.transB, raw);
         break;
     default:
         if (raw) GE_LAUNCH(ge::gemm_bf16_fused_generic_kernel<true>, grid, dim3(256), 0, hs, pg);

@@ -11,6 +11,14 @@ Tile64 tile64_of(const Plan &pl, const GemmParams &p, ge_plan_t plan)
     return ge::tile64_kind(pl.tile == TILE_128, (long long)ceil_div(p.M, 64) * ceil_div(p.N, 128) * p.batch, p.K, p.cType == ge::DT_BF16, ceil_div(p.M, 64) % 2 != 0);
 }
 
+const char *tile64_config(Tile64 kind, int family)
+{
+    static const char *const names[3][3] = {{"bf16_64x128x32_w4", "bf16_64x128_k64_w4", "bf16_128x128_k64_w4"},
+                                            {"conv_bf16_64x128x32_w4", "conv_bf16_64x128_k64_w4", "conv_bf16_128x128_k64_w4"},
+                                            {"conv_bf16_c8_64x128x32_w4", "conv_bf16_c8_64x128_k64_w4", "conv_bf16_c8_128x128_k64_w4"}};
+    return names[family][kind - TILE64_RING];
+}
+
 void launch_tile64_ring(const GemmParams &p, dim3 grid, hipStream_t st) { launch_tile64_mode<64, 1, 4, 4, 3>(p, grid, st); }
 
 dim3 tile64_grid(GemmParams &p, bool wide)

@@ -24,12 +24,14 @@
 
 namespace ge_host {
 
-// Which of them a call takes (small_layout.h).  The plan, and with it the configuration's name, stays as it is.
+// Which of them a call takes (small_layout.h), whatever tile its plan names.
 using ge::Tile64;
 using ge::TILE64_NO;
 using ge::TILE64_RING;
 using ge::TILE64_SHORT_WIDE;
 Tile64 tile64_of(const Plan &pl, const ge::GemmParams &p, ge_plan_t plan);
+enum { TILE64_PLAIN = 0, TILE64_CONV = 1, TILE64_CONV_C8 = 2 };
+const char *tile64_config(Tile64 kind, int family);     // its configuration's name
 
 // For the storages of p.transA / p.transB and the output type of p.cType; p.tilesM, p.tilesN and p.groupM are set here.
 void launch_tile64(ge::GemmParams p, Tile64 kind, hipStream_t st);

@@ -220,3 +220,21 @@ def run_fused_case(oracle, M, N, K, *, batch=1, transA=False, transB=False, alph
     rel = compare(got, ref, f"{cfg} fused {M}x{N}x{K}x{batch}", bf16_out=(out == "bf16"))
     del keepA, keepB
     return got, ref, rel, cfg
+
+
+def takes_small(cfg):
+    """Whether ``cfg`` is one of the kernels for few tiles or a short K, which a forced configuration keeps calls from."""
+    return any(name in cfg for name in ("small_32x32", "few_16x16", "few_32x32", "64x128", "128x128_k64"))
+
+
+def both_kernels(run, plan, small=True):
+    """``run()``, which returns the configuration, on the kernel that the call takes by itself (one for few tiles or a short K, where ``small``) and, by the
+    switch that keeps it there, on the tile of its plan."""
+    from paper_2604_01489_amd import binding
+    cfg = run()
+    assert takes_small(cfg) if small else cfg == plan, (cfg, plan)
+    if small:
+        binding.set_option("force_config", "128x128")
+        cfg = run()
+        binding.set_option("force_config", None)
+        assert cfg == plan, (cfg, plan)

@@ -6,7 +6,7 @@ import pytest
 
 from paper_2604_01489_amd import binding
 
-from gpu_util import compare, to_device, torch_device
+from gpu_util import both_kernels, compare, to_device, torch_device
 
 pytestmark = pytest.mark.gpu
 
@@ -48,8 +48,8 @@ def run_conv_case(oracle, shape, *, stride=(1, 1), pad=(0, 0), dil=(1, 1), alpha
 
 
 def test_conv_3x3_tiles_128(oracle):
-    run_conv_case(oracle, (2, 20, 20, 64, 64, 3, 3), pad=(1, 1), act="relu", seed=1, expect="conv_bf16_128x128x32_w4")
-    run_conv_case(oracle, (1, 16, 16, 32, 128, 3, 3), pad=(1, 1), seed=2, expect="conv_bf16_128x128x32_w4")   # 256 x 128: full tiles
+    both_kernels(lambda: run_conv_case(oracle, (2, 20, 20, 64, 64, 3, 3), pad=(1, 1), act="relu", seed=1), "conv_bf16_128x128x32_w4")
+    both_kernels(lambda: run_conv_case(oracle, (1, 16, 16, 32, 128, 3, 3), pad=(1, 1), seed=2), "conv_bf16_128x128x32_w4")   # 256 x 128: full tiles
 
 
 def test_conv_3x3_tiles_256(oracle, monkeypatch):
@@ -72,11 +72,10 @@ def test_conv_3x3_tiles_256(oracle, monkeypatch):
     ((1, 1), (3, 3), (2, 2), (3, 3)),
 ])
 def test_conv_geometry(oracle, stride, pad, dil, k):
-    run_conv_case(oracle, (2, 17, 23, 32, 72, k[0], k[1]), stride=stride, pad=pad, dil=dil, act="relu",
-                  seed=10 + k[0] + 3 * k[1], expect="conv_bf16_128x128x32_w4")
-    cfg = run_conv_case(oracle, (1, 17, 23, 128, 40, k[0], k[1]), stride=stride, pad=pad, dil=dil, out="bf16",
-                        seed=12 + k[0] + 3 * k[1])
-    assert cfg in ("conv_bf16_128x128x32_w4", "conv_bf16_128x128x32_w4_splitk")     # K slices where K is long
+    both_kernels(lambda: run_conv_case(oracle, (2, 17, 23, 32, 72, k[0], k[1]), stride=stride, pad=pad, dil=dil, act="relu", seed=10 + k[0] + 3 * k[1]),
+                 "conv_bf16_128x128x32_w4")
+    both_kernels(lambda: run_conv_case(oracle, (1, 17, 23, 128, 40, k[0], k[1]), stride=stride, pad=pad, dil=dil, out="bf16",
+                                       seed=12 + k[0] + 3 * k[1]).replace("_splitk", ""), "conv_bf16_128x128x32_w4")     # K slices where K is long
 
 
 @pytest.mark.parametrize("out", ["f32", "bf16"])
@@ -270,8 +269,7 @@ def test_conv_split_k_for_few_tiles_and_long_k(oracle, monkeypatch):
     summed in slice order by the second pass, which also runs the consumer chain."""
     cfg = run_conv_case(oracle, (1, 8, 8, 512, 256, 3, 3), pad=(1, 1), act="relu", residual="bf16", out="bf16", seed=40)
     assert cfg == "conv_bf16_128x128x32_w4_splitk"
-    cfg = run_conv_case(oracle, (4, 9, 9, 256, 512, 3, 3), pad=(1, 1), act="gelu_tanh", alpha=0.5, seed=41)
-    assert cfg == "conv_bf16_128x128x32_w4_splitk"
+    both_kernels(lambda: run_conv_case(oracle, (4, 9, 9, 256, 512, 3, 3), pad=(1, 1), act="gelu_tanh", alpha=0.5, seed=41), "conv_bf16_128x128x32_w4_splitk")
     cfg = run_conv_case(oracle, (1, 7, 7, 200, 100, 3, 3), pad=(1, 1), stride=(2, 2), act="relu", clamp=(0.0, 1.0), seed=42)
     assert cfg == "conv_bf16_generic_64x64x32_splitk"
     binding.set_option("force_config", "256x256")            # the 256 x 256 kernel's partial tiles

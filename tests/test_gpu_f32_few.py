@@ -1,5 +1,5 @@
-"""fp32 products of few tiles in tiles of 16 x 16 or 32 x 32 (csrc/gemm_f32_few.h).  The names of the configurations are the plan's: which sizes take which tile is asserted
-by the host model (small_layout_check.cpp)."""
+"""fp32 products of few tiles in tiles of 16 x 16 or 32 x 32 (csrc/gemm_f32_few.h).  Which sizes take which tile is asserted by the host model (small_layout_check.cpp), that these
+take it by the configuration's name."""
 import pytest
 
 from paper_2604_01489_amd import binding
@@ -26,8 +26,10 @@ pytestmark = pytest.mark.gpu
     (480, 1056, 1023, dict(misalign=1))])               # 32: eight, two tiles to a CU
 @pytest.mark.parametrize("act", ["none", "gelu_tanh"])
 def test_few_tiles(oracle, M, N, K, kw, act):
-    outs = [run_case(oracle, "f32", M, N, K, alpha=0.5, act=act, seed=M + N + K, **kw)[0].tobytes() for _ in range(2)]
-    assert outs[0] == outs[1]
+    t16 = -(-M // 16) * -(-N // 16) * kw.get("batch", 1)
+    kernel = "f32_64x64x16_w4" if K <= 16 else "f32_few_16x16x256" if K > 64 and t16 <= (512 if K > 128 else 256) else "f32_few_32x32x128"
+    outs = [run_case(oracle, "f32", M, N, K, alpha=0.5, act=act, seed=M + N + K, **kw) for _ in range(2)]
+    assert outs[0][0].tobytes() == outs[1][0].tobytes() and outs[0][3] == kernel, outs[0][3]
 
 
 @pytest.mark.parametrize("M,N,K", [(256, 256, 256), (256, 250, 1000), (512, 512, 512), (500, 500, 1000), (255, 938, 347), (512, 500, 60)])

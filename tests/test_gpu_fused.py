@@ -9,7 +9,7 @@ import pytest
 
 from paper_2604_01489_amd import binding
 
-from gpu_util import run_case, run_fused_case
+from gpu_util import both_kernels, takes_small, run_case, run_fused_case
 
 pytestmark = pytest.mark.gpu
 
@@ -41,9 +41,8 @@ def test_layouts_tile_256(oracle, transA, transB, monkeypatch):
 @pytest.mark.parametrize("transA,transB", LAYOUTS)
 def test_layouts_tile_128(oracle, transA, transB):
     for M, N, K in [(128, 128, 192), (136, 248, 200), (8, 8, 8), (64, 384, 40)]:
-        _, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=transB, act="relu", with_row_scale=True,
-                                      seed=3 * M + K)
-        assert cfg == f"bf16_fused_128x128x{stage_k(transA, transB, shared_cu=False)}_w4_{NAME[transA, transB]}"
+        both_kernels(lambda: run_fused_case(oracle, M, N, K, transA=transA, transB=transB, act="relu", with_row_scale=True, seed=3 * M + K)[3],
+                     f"bf16_fused_128x128x{stage_k(transA, transB, shared_cu=False)}_w4_{NAME[transA, transB]}")
     # more blocks than CUs (17 x 17 full and ragged tiles): 64 k per load phase where both operands run along k
     for M, N, K in [(2176, 2176, 192), (2184, 2168, 200)]:
         _, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=transB, act="relu", with_row_scale=True,
@@ -104,8 +103,13 @@ def test_triangular_a(oracle, structure, transA, transB):
                   seed=50 + M + K, a_structure=structure, plan="direct", **extra)      # one pass, the same order of sums
         got, _, _, cfg = run_fused_case(oracle, M, N, K, **kw)
         plain, _, _, cfg2 = run_fused_case(oracle, M, N, K, hint=False, **kw)
-        assert cfg == cfg2
-        assert np.array_equal(got, plain), f"{cfg}: the promise changed the result"
+        assert cfg == cfg2 or takes_small(cfg2)
+        assert np.array_equal(got, plain), f"{cfg}, {cfg2}: the promise changed the result"
+        if takes_small(cfg2):                                # and on the tile that the promise keeps
+            binding.set_option("force_config", "128x128")
+            plain, _, _, cfg2 = run_fused_case(oracle, M, N, K, hint=False, **kw)
+            binding.set_option("force_config", None)
+            assert cfg == cfg2 and np.array_equal(got, plain), (cfg, cfg2)
     # batched, and the promise is not compatible with K slices
     run_fused_case(oracle, 512, 256, 512, batch=3, transA=transA, transB=transB, residual="bf16", out="bf16",
                    seed=60, a_structure=structure)
@@ -157,8 +161,8 @@ def test_plain_operator_is_the_special_case(oracle):
         got_p, _, _, cfg_p = run_case(oracle, "bf16", M, N, K, alpha=0.5, act="gelu_tanh", seed=5)
         assert cfg_f == cfg_p and not cfg_f.startswith("bf16_fused")
         assert np.array_equal(got_f, got_p)
-    _, _, _, cfg = run_fused_case(oracle, 512, 512, 256, alpha=0.5, act="gelu_tanh", clamp=(-1.0, 1.0), seed=5)
-    assert cfg == f"bf16_fused_128x128x{stage_k(False, False)}_w4_nn"
+    both_kernels(lambda: run_fused_case(oracle, 512, 512, 256, alpha=0.5, act="gelu_tanh", clamp=(-1.0, 1.0), seed=5)[3],
+                 f"bf16_fused_128x128x{stage_k(False, False)}_w4_nn")
 
 
 def test_diagonal_times_dense(oracle):

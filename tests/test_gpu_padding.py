@@ -23,15 +23,16 @@ def _same(run, kernel):
     outs = []
     for poison in (False, True):
         outs.append(run(poison))
-        assert kernel in binding.last_config(), binding.last_config()
+        assert kernel in binding.last_config(), (kernel, binding.last_config())
     torch.cuda.synchronize()
     assert torch.isfinite(outs[0]).all()
     assert torch.equal(outs[0], outs[1])
 
 
 @pytest.mark.parametrize("transA,transB", [(False, False), (False, True), (True, False), (True, True)])
-@pytest.mark.parametrize("M,N,K,pad,out", [(259, 261, 257, 5, "f32"), (2051, 2049, 9, 3, "bf16"), (131, 67, 2051, 1, "f32")])
-def test_bf16_any_alignment(M, N, K, pad, out, transA, transB):
+@pytest.mark.parametrize("M,N,K,pad,out,kernel", [(259, 261, 257, 5, "f32", "ragged_64x64"), (2051, 2049, 9, 3, "bf16", "ragged_128x128"), (131, 67, 2051, 1, "f32", "ragged"),
+                                                  (259, 261, 257, 5, "bf16", "small_32x32"), (131, 67, 701, 1, "f32", "small_32x32")])
+def test_bf16_any_alignment(M, N, K, pad, out, kernel, transA, transB):
     import torch
     dt = torch.bfloat16
     rowsA, colsA, rowsB, colsB = (K, M, N, K) if transA and transB else (K, M, K, N) if transA else (M, K, N, K) if transB else (M, K, K, N)
@@ -42,10 +43,10 @@ def test_bf16_any_alignment(M, N, K, pad, out, transA, transB):
         binding.gemm_epilogue_bf16_fused(M, N, K, A, colsA + pad, B, colsB + pad, C, N, transA=transA, transB=transB, act="relu",
                                          row_scale=torch.ones(M, device="cuda"))
         return C
-    _same(run, "ragged")
+    _same(run, kernel)
 
 
-@pytest.mark.parametrize("M,N,K,kernel", [(257, 513, 35, "f32_ragged_64x64x32"), (1921, 2046, 33, "f32_ragged_128x128x32"), (130, 257, 2075, "splitk"),
+@pytest.mark.parametrize("M,N,K,kernel", [(257, 513, 35, "f32_few_32x32"), (67, 131, 301, "f32_few_16x16"), (901, 903, 301, "f32_ragged_64x64x32"), (1921, 2046, 33, "f32_ragged_128x128x32"), (130, 257, 2075, "splitk"),
                                           (300, 3, 50, "f32_elements"), (130, 515, 3, "f32_elements")])
 def test_f32_any_alignment(M, N, K, kernel):
     import torch

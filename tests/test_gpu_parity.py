@@ -7,7 +7,7 @@ import pytest
 
 from paper_2604_01489_amd import binding
 
-from gpu_util import run_case
+from gpu_util import both_kernels, run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -25,8 +25,7 @@ pytestmark = pytest.mark.gpu
 def test_bf16_fast_256(oracle, M, N, K, monkeypatch):
     """The 256 x 256 kernel on shapes the oracle finishes quickly: forced through the library's switch, since
     the planning rule gives so few tiles to the 128 x 128 kernel (checked first, on the same inputs)."""
-    _, _, _, cfg = run_case(oracle, "bf16", M, N, K, alpha=0.5, act="gelu_tanh", seed=M + N + K)
-    assert cfg == "bf16_128x128x32_w4"
+    both_kernels(lambda: run_case(oracle, "bf16", M, N, K, alpha=0.5, act="gelu_tanh", seed=M + N + K)[3], "bf16_128x128x32_w4")
     binding.set_option("force_config", "256x256")
     binding.set_option("waves", "8")         # the four-wave kernel has its own tests
     _, _, _, cfg = run_case(oracle, "bf16", M, N, K, alpha=0.5, act="gelu_tanh", seed=M + N + K)
@@ -37,8 +36,7 @@ def test_bf16_fast_256(oracle, M, N, K, monkeypatch):
     (128, 128, 64), (128, 128, 192), (128, 384, 128), (200, 136, 72), (8, 8, 8), (1, 8, 8), (131, 248, 200),
 ])
 def test_bf16_fast_128(oracle, M, N, K):
-    _, _, _, cfg = run_case(oracle, "bf16", M, N, K, alpha=1.25, act="relu", seed=M * 3 + N + K)
-    assert cfg == "bf16_128x128x32_w4"
+    both_kernels(lambda: run_case(oracle, "bf16", M, N, K, alpha=1.25, act="relu", seed=M * 3 + N + K)[3], "bf16_128x128x32_w4")
 
 
 @pytest.mark.parametrize("act", ["none", "relu", "gelu_tanh"])
@@ -75,18 +73,16 @@ def test_f32(oracle, M, N, K):
 
 def test_f32_fast_kernels(oracle):
     """direct-to-LDS fp32 kernels: 64x64 and 128x128 tiles, full and ragged, several K tiles"""
-    _, _, _, cfg = run_case(oracle, "f32", 256, 256, 272, act="none", with_bias=False, seed=30)
-    assert cfg == "f32_64x64x16_w4"
+    both_kernels(lambda: run_case(oracle, "f32", 256, 256, 272, act="none", with_bias=False, seed=30)[3], "f32_64x64x16_w4")
+    for M, N, K in [(1024, 1024, 512), (1000, 1000, 300)]:                 # more tiles than the kernel for few takes: full, and over every edge
+        both_kernels(lambda: run_case(oracle, "f32", M, N, K, alpha=0.5, act="gelu_tanh", seed=M + K)[3], "f32_64x64x16_w4", small=False)
     _, _, _, cfg = run_case(oracle, "f32", 1024, 2048, 64, alpha=0.5, act="gelu_tanh", seed=31)
     assert cfg == "f32_128x128x16_w4"
     _, _, _, cfg = run_case(oracle, "f32", 1100, 1900, 68, alpha=0.5, act="relu", seed=32, lda=72, ldb=1904, ldc=1901)
     assert cfg == "f32_128x128x16_w4"
-    _, _, _, cfg = run_case(oracle, "f32", 300, 96, 40, alpha=1.0, act="none", seed=33)
-    assert cfg == "f32_64x64x16_w4"
-    _, _, _, cfg = run_case(oracle, "f32", 72, 200, 20, batch=5, act="relu", seed=34)
-    assert cfg == "f32_64x64x16_w4"
-    _, _, _, cfg = run_case(oracle, "f32", 129, 130, 31, act="none", seed=35)
-    assert cfg == "f32_ragged_128x128x32"
+    both_kernels(lambda: run_case(oracle, "f32", 300, 96, 40, alpha=1.0, act="none", seed=33)[3], "f32_64x64x16_w4")
+    both_kernels(lambda: run_case(oracle, "f32", 72, 200, 20, batch=5, act="relu", seed=34)[3], "f32_64x64x16_w4")
+    both_kernels(lambda: run_case(oracle, "f32", 129, 130, 31, act="none", seed=35)[3], "f32_ragged_128x128x32")
 
 
 def test_f32_k_slices(oracle):
@@ -104,19 +100,18 @@ def test_f32_k_slices(oracle):
     assert cfg == "f32_64x64x16_w4_splitk"
     outs = [run_case(oracle, "f32", 256, 256, 4096, alpha=0.5, act="gelu_tanh", seed=40)[0].tobytes() for _ in range(2)]
     assert outs[0] == outs[1]
-    _, _, _, cfg = run_case(oracle, "f32", 256, 256, 528, act="none", seed=45)       # K too short to slice
-    assert cfg == "f32_64x64x16_w4"
+    both_kernels(lambda: run_case(oracle, "f32", 256, 256, 528, act="none", seed=45)[3], "f32_64x64x16_w4")       # K too short to slice
 
 
 def test_f32_small_products(oracle):
-    """Small fp32 products (the 256^3 workload's class): 32 x 32 tiles whose four waves share K and add their partial
-    tiles through LDS in wave order; one chunk of 64 k per wave, two and three (the prefetch's both buffers);
-    batches, padded leading dimensions, every activation; exact on integers; repeatable bit for bit."""
-    small = "f32_small_32x32_k4"
+    """Small fp32 products (the 256^3 workload's class) in 16 x 16 tiles whose four waves share K and add their partial
+    tiles through LDS in wave order, or 32 x 32 ones; one step of K, two and three;
+    batches, padded leading dimensions, every activation; repeatable bit for bit."""
+    small = "f32_few_16x16x256"
     _, _, _, cfg = run_case(oracle, "f32", 256, 256, 256, act="none", with_bias=False, seed=50)
     assert cfg == small
     _, _, _, cfg = run_case(oracle, "f32", 512, 512, 512, alpha=0.5, act="gelu_tanh", seed=51)
-    assert cfg == small
+    assert cfg == "f32_few_32x32x128"
     _, _, _, cfg = run_case(oracle, "f32", 32, 64, 768, alpha=0.25, act="relu", seed=52, lda=772, ldb=68, ldc=65)
     assert cfg == small
     _, _, _, cfg = run_case(oracle, "f32", 64, 96, 256, batch=3, act="relu", seed=53)
@@ -124,7 +119,7 @@ def test_f32_small_products(oracle):
     outs = [run_case(oracle, "f32", 256, 256, 256, alpha=0.5, act="gelu_tanh", seed=54)[0].tobytes() for _ in range(2)]
     assert outs[0] == outs[1]
     _, _, _, cfg = run_case(oracle, "f32", 256, 264, 256, act="none", seed=55)       # N not a multiple of 32
-    assert cfg == "f32_64x64x16_w4"
+    assert cfg == small
 
 
 def test_f32_layouts(oracle):

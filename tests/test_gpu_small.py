@@ -1,5 +1,5 @@
-"""Products of few output tiles in tiles of 32 x 32 (csrc/gemm_small.h).  The names of the configurations are the plan's and do not tell: which sizes take
-the kernel is asserted by the host model (small_layout_check.cpp), and a test switch that keeps the plan's own kernel gives the other side."""
+"""Products of few output tiles in tiles of 32 x 32 (csrc/gemm_small.h).  Which sizes take the kernel is asserted by the host model (small_layout_check.cpp), that these do by the
+configuration's name, and a test switch that keeps the plan's own kernel gives the other side."""
 import os
 import subprocess
 
@@ -39,9 +39,10 @@ def test_aligned(oracle, transA, transB, M, N, K, kw):
         outs = []
         for option in (None, "128x128"):
             binding.set_option("force_config", option)
-            got, _, _, _ = run_fused_case(oracle, M, N, K, transA=transA, transB=transB, alpha=0.75, with_row_scale=True, act="gelu_tanh", out=out,
-                                          plan="direct", seed=M + K, **kw)
+            got, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=transB, alpha=0.75, with_row_scale=True, act="gelu_tanh", out=out,
+                                            plan="direct", seed=M + K, **kw)
             outs.append(got)
+            assert ("small_32x32" if option is None else "128x128") in cfg, cfg
         assert np.array_equal(outs[0], outs[1])
         binding.set_option("force_config", None)
 
@@ -52,7 +53,15 @@ def test_aligned(oracle, transA, transB, M, N, K, kw):
                                       (193, 129, 513, dict(misalign=3, batch=2, residual="f32")), (100, 333, 900, dict(pad=(0, 0, 1, 1)))])
 def test_any_alignment(oracle, transA, transB, M, N, K, kw):
     for out in ("f32", "bf16"):
-        run_fused_case(oracle, M, N, K, transA=transA, transB=transB, alpha=0.5, with_row_scale=True, act="relu", out=out, plan="direct", seed=M + N, **kw)
+        outs = []
+        bare = out == "f32" and "residual" not in kw and 256 < K <= 320           # stays on the 64 x 64 tile
+        for option in (None, "128x128"):
+            binding.set_option("force_config", option)
+            got, _, _, cfg = run_fused_case(oracle, M, N, K, transA=transA, transB=transB, alpha=0.5, with_row_scale=True, act="relu", out=out, plan="direct", seed=M + N, **kw)
+            outs.append(got)
+            assert ("small_32x32" if option is None and not bare else "ragged_64x64") in cfg, cfg
+        binding.set_option("force_config", None)
+        assert np.array_equal(outs[0], outs[1])
 
 
 @pytest.mark.gpu
@@ -68,6 +77,7 @@ def test_in_place_of_k_slices(oracle, M, N, K, kw):
     for plan in ("auto", "splitk"):
         binding.gemm_epilogue_bf16_ex(M, N, K, A, K, B, N, None, 1.0, "none", C, N, plan=plan)
         torch.cuda.synchronize()
+        assert binding.last_config() == "bf16_small_32x32x256" if plan == "auto" else binding.last_config().endswith("_splitk"), binding.last_config()
         err[plan] = float((C.double() - ref).norm() / ref.norm())
     # 30000 outputs and more: the norm of the errors is steady to two percent
     assert err["auto"] <= 1.02 * err["splitk"], err
@@ -132,7 +142,7 @@ def test_a_sliced_call_captured_behind_one_that_slices_no_longer():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,kw", [
-    ((1, 7, 5, 8, 32, 3, 3), dict(pad=(1, 1))),                                                    # a tap to a chunk; guarded kernel below a million multiply-adds
+    ((4, 17, 15, 8, 40, 3, 3), dict(pad=(1, 1))),                                                  # a tap to a chunk
     ((2, 15, 17, 24, 136, 3, 3), dict(pad=(1, 1), residual="bf16", out="bf16")),                    # one step of 216, taps that end inside a chunk's neighbours
     ((9, 14, 13, 40, 72, 5, 4), dict(stride=(1, 2), pad=(2, 0), dil=(2, 1), act="gelu_tanh")),      # four steps, every way the geometry enters
     ((2, 20, 20, 64, 64, 3, 3), dict(pad=(1, 1), out="bf16")),                                      # 576: three steps
@@ -146,7 +156,7 @@ def test_convolutions(oracle, shape, kw):
         binding.set_option("force_config", option)
         kw2 = dict(kw)
         outs.append(run_conv_case(oracle, shape, alpha=0.75, act=kw2.pop("act", "relu"), seed=sum(shape), **kw2))
-    assert outs[0].replace("_splitk", "") == outs[1].replace("_splitk", "") or "generic" in outs[0], outs
+    assert "small_32x32" in outs[0] and "128x128" in outs[1], outs
 
 
 @pytest.mark.gpu
@@ -165,6 +175,6 @@ def test_convolutions_are_as_exact_as_slices(n, h, cin, cout):
         Y = torch.empty(n, h, h, cout, device="cuda")
         binding.conv2d_epilogue_bf16(X, W, Y, pad=(1, 1))
         torch.cuda.synchronize()
-        assert binding.last_config().endswith("_splitk"), binding.last_config()
+        assert "small_32x32" in binding.last_config() if option is None else binding.last_config().endswith("_splitk"), binding.last_config()
         err[option] = float((Y.reshape(-1, cout).double() - ref).norm() / ref.norm())
     assert err[None] <= 1.02 * err["128x128"], err

@@ -41,37 +41,42 @@ def test_bf16_kernels_at_any_distance(M, N, K, out):
     import torch
     A, B, ref = _operands(M, N, K, torch.bfloat16)
     dtype = torch.float32 if out == "f32" else torch.bfloat16
-    names = []
-    for ldc in (N, LIMIT, LIMIT + 8):
-        C = _buffer(M, ldc, N, dtype)
-        binding.gemm_epilogue_bf16_fused(M, N, K, A, K, B, N, C, ldc)
-        names.append(binding.last_config())
-        torch.cuda.synchronize()
-        # fp32 sums of K products of N(0, 1) values; half a bf16 step
-        _check(C, M, ldc, N, ref, 2e-6 if out == "f32" else 2.0 ** -9)
-        del C
-    assert len(set(names)) == 1 and "128x128" in names[0], names
+    for option, tile in ((None, "small_32x32"), ("128x128", "128x128")):
+        binding.set_option("force_config", option)
+        names = []
+        for ldc in (N, LIMIT, LIMIT + 8):
+            C = _buffer(M, ldc, N, dtype)
+            binding.gemm_epilogue_bf16_fused(M, N, K, A, K, B, N, C, ldc)
+            names.append(binding.last_config())
+            torch.cuda.synchronize()
+            # fp32 sums of K products of N(0, 1) values; half a bf16 step
+            _check(C, M, ldc, N, ref, 2e-6 if out == "f32" else 2.0 ** -9)
+            del C
+        assert len(set(names)) == 1 and tile in names[0], names
 
 
 @pytest.mark.parametrize("M,N,K", [(64, 128, 48), (64, 64, 256)])
 def test_f32_kernels_at_any_distance(M, N, K):
     import torch
     A, B, ref = _operands(M, N, K, torch.float32)
-    names = []
-    for ldc in (N, LIMIT, LIMIT + 1):
-        C = _buffer(M, ldc, N, torch.float32)
-        binding.gemm_epilogue_f32(M, N, K, A, K, B, N, None, 1.0, "none", C, ldc)
-        names.append(binding.last_config())
-        torch.cuda.synchronize()
-        _check(C, M, ldc, N, ref, 2e-6)
-        del C
-    assert len(set(names)) == 1 and names[0] in ("f32_64x64x16_w4", "f32_small_32x32_k4"), names
+    for option, kernel in ((None, "f32_few_"), ("128x128", "f32_64x64x16_w4")):
+        binding.set_option("force_config", option)
+        names = []
+        for ldc in (N, LIMIT, LIMIT + 1):
+            C = _buffer(M, ldc, N, torch.float32)
+            binding.gemm_epilogue_f32(M, N, K, A, K, B, N, None, 1.0, "none", C, ldc)
+            names.append(binding.last_config())
+            torch.cuda.synchronize()
+            _check(C, M, ldc, N, ref, 2e-6)
+            del C
+        assert len(set(names)) == 1 and names[0].startswith(kernel), names
 
 
-# tiles on the edge, fp32: the offsets at their largest, and the guarded kernels from there on
+# tiles on the edge, fp32: the offsets at their largest (on the tile of the plan: the kernels for few tiles store through 64-bit addresses), and the guarded kernels from there on
+@pytest.mark.parametrize("own", [True, False])
 @pytest.mark.parametrize("ldc,past", [(LIMIT - 1, False), (LIMIT, True)])
 @pytest.mark.parametrize("M,N,K,dtype,aligned", [(96, 136, 64, "bf16", True), (96, 200, 900, "bf16", False), (96, 68, 48, "f32", True), (96, 67, 33, "f32", False)])
-def test_edge_tiles_near_the_limit(M, N, K, dtype, aligned, ldc, past):
+def test_edge_tiles_near_the_limit(M, N, K, dtype, aligned, ldc, past, own):
     import torch
     td = torch.bfloat16 if dtype == "bf16" else torch.float32
     A, B, ref = _operands(M, N, K, td)
@@ -80,13 +85,15 @@ def test_edge_tiles_near_the_limit(M, N, K, dtype, aligned, ldc, past):
     Bs = torch.zeros(K * N + shift, device="cuda", dtype=td)
     Bs[shift:] = B.reshape(-1)
     call = binding.gemm_epilogue_bf16 if dtype == "bf16" else binding.gemm_epilogue_f32
+    binding.set_option("force_config", None if own else "128x128")
     call(M, N, K, A, K, Bs[shift:], N, None, 1.0, "none", C, ldc)
     name = binding.last_config()
     torch.cuda.synchronize()
     _check(C, M, ldc, N, ref, 2e-6)
+    small = own and not past
     if dtype == "bf16":
-        assert name == ("bf16_generic_64x64x32" if past else "bf16_128x128x32_w4" if aligned else "bf16_ragged_64x64x64"), name
+        assert name == ("bf16_small_32x32x256" if small else "bf16_generic_64x64x32" if past else "bf16_128x128x32_w4" if aligned else "bf16_ragged_64x64x64"), name
+    elif small:
+        assert name.startswith("f32_few_"), name
     else:
         assert name == ("f32_elements_64x64x32" if past else "f32_64x64x16_w4" if aligned else "f32_ragged_128x128x32"), name
-
-

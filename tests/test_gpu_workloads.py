@@ -136,7 +136,7 @@ def test_c7_fused_tn_chain(oracle):
 
 def test_c8_fused_batched_bf16out(oracle):
     C, cfg = _run_fused_workload(oracle, "c8_fused_batched_512x512x64_bf16out", 512, batches_wanted=6)
-    assert cfg in ("bf16_fused_256x256x32_w8_nn", "bf16_fused_128x128x32_w4_nn")      # the planner's measured per-round costs decide
+    assert cfg == "bf16_fused_128x128_k64_w4_nn"
     assert float(C.float().min()) >= 0.0
 
 
