@@ -175,7 +175,7 @@ double plan_cost_us(int M, int N, int K, int batch, int tile, int slices)
 // alignment: 130 x 70 x 1500, 13.7 M, 48.4 / 11.0; 513 x 515 x 33, 8.7 M, 7.5 / 5.2; 33 x 33 x 4096, 4.5 M, 27.7 / 8.4; 221 x 155 x
 // 44, 1.5 M, 7.6 / 5.1), and products of aligned operands with few large tiles as well (small_tile_pays; 128 / 64 tile: 128 x 128 x 512 6.9 / 5.6,
 // 200 x 200 x 400 7.4 / 5.3, 72 x 72 x 2040 22.1 / 12.7).  Not where the two cross: up to the line it is the shorter call too (128 x 128 x 64, on the line,
-// 7.8 / 3.4; 100 x 100 x 100 10.4 / 4.5; 33 x 35 x 700 35.6 / 7.4), and so it is for K slices that the caller asks for up to kRaggedMinSliced; the
+// 7.8 / 3.4; 100 x 100 x 100 10.4 / 4.5; 33 x 35 x 700 35.6 / 7.4; all of these on the 64 x 64 tile, from which gemm_small.h takes most), and so it is for K slices that the caller asks for up to kRaggedMinSliced; the
 // configuration that these calls report is the guarded kernel's, which tests of that kernel count on.
 constexpr double kRaggedMinWork = 1024.0 * 1024, kRaggedMinSliced = 16.0 * 1024 * 1024;
 
@@ -212,7 +212,8 @@ bool small_tile_pays(int M, int N, int K, int batch, double otherCost)
 }
 // Products shorter than this stay on the larger tiles: there both are a launch and little else, and the line is not where they
 // cross (us, 128 tile / this one: 736 x 320 x 320 5.8 / 5.0, 512 x 512 x 256 5.4 / 5.0, 1024 x 512 x 352 6.1 / 5.4, 520 x 776 x 128
-// 5.1 / 4.8; above the line 1024 x 1024 x 1024 11.1 / 8.9).
+// 5.1 / 4.8; above the line 1024 x 1024 x 1024 11.1 / 8.9).  Of these the line decides little by now: where they are few tiles the 32 x 32 or the 64 x 128 one takes them from whichever
+// plan they have (512 x 512 x 256, 1024 x 512 x 352).
 constexpr int kSmallTileMinK = 384;
 
 bool ragged_ok(int M, int N, int K, int batch, int lda, bool transA, int ldb, bool transB, int ldc, bool plain)
@@ -733,12 +734,10 @@ ge_status_t gemm_epilogue_f32(int M, int N, int K, const float *A, int lda, cons
         least = choose_split(t128, K, 512);
         // Operands of any alignment: the tile whose rounds of blocks on the CUs take the matrix pipe less time (a 128 tile is
         // four of the small one, at 1.1 times its rate; 64 against 128, us: 1023 x 771 x 2049 48 / 57, 1501^3 82 / 114, 2001 x
-        // 2003 x 401 45 / 42).  Two kinds of few tiles keep the large one though it is the slower, which is what they report and tests of that tile
-        // count on: those of one or two 32-k steps (129 x 130 x 31 3.6 / 6.0, 100 x 333 x 64 4.3 / 8.2), and fewer than 16 tiles in slices (130 x 257 x
-        // 2075 10.3 / 15.2, 67 x 45 x 2051 7.9 / 13.5, 191 x 255 x 4097 13.1 / 20.1).
-        // The others are the small tile's (100 x 333 x 900 22 / 66, 255 x 255 x 1001 24 / 73, 129 x 130 x 300 9.6 / 25.6, 320 x 320 x 4095
-        // 16.4 / 49.7).
-        big = !elementwise && ((t64 < 32 && K <= 64) || (t64 < 16 && least > 1) ||
+        // 2003 x 401 45 / 42).  Fewer than 16 tiles in slices keep the large one though it is the slower, which is what they report and tests of that tile
+        // count on (130 x 257 x 2075 10.3 / 15.2, 67 x 45 x 2051 7.9 / 13.5, 191 x 255 x 4097 13.1 / 20.1).  Without slices few tiles go to gemm_f32_few.h, whichever this is.
+        // The others are the small tile's (255 x 255 x 1001 in slices 24 / 73, 320 x 320 x 4095 16.4 / 49.7).
+        big = !elementwise && ((t64 < 16 && least > 1) ||
                                (double)((t128 + kNumCU - 1) / kNumCU) * 3.6 <= (double)((t64 + kNumCU - 1) / kNumCU));
     }
     slice_k(K, 16, least > 1 ? f32_slices(big ? 128 : 64, big ? t128 : t64, outputs, K, least, elementwise) : 1, &p.splitK, &p.kPerSlice);

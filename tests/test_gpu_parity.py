@@ -82,7 +82,7 @@ def test_f32_fast_kernels(oracle):
     assert cfg == "f32_128x128x16_w4"
     both_kernels(lambda: run_case(oracle, "f32", 300, 96, 40, alpha=1.0, act="none", seed=33)[3], "f32_64x64x16_w4")
     both_kernels(lambda: run_case(oracle, "f32", 72, 200, 20, batch=5, act="relu", seed=34)[3], "f32_64x64x16_w4")
-    both_kernels(lambda: run_case(oracle, "f32", 129, 130, 31, act="none", seed=35)[3], "f32_ragged_128x128x32")
+    both_kernels(lambda: run_case(oracle, "f32", 129, 130, 31, act="none", seed=35)[3], "f32_ragged_64x64x32")
 
 
 def test_f32_k_slices(oracle):

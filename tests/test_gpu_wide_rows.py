@@ -96,4 +96,4 @@ def test_edge_tiles_near_the_limit(M, N, K, dtype, aligned, ldc, past, own):
     elif small:
         assert name.startswith("f32_few_"), name
     else:
-        assert name == ("f32_elements_64x64x32" if past else "f32_64x64x16_w4" if aligned else "f32_ragged_128x128x32"), name
+        assert name == ("f32_elements_64x64x32" if past else "f32_64x64x16_w4" if aligned else "f32_ragged_64x64x32"), name
