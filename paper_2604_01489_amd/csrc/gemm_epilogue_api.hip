@@ -339,8 +339,9 @@ bool small_ok(const Plan &pl, const GemmParams &p, ge_plan_t plan)
     if ((pl.tile != TILE_128 && pl.tile != TILE_RAGGED_64) || p.triA != ge::TRI_NONE || plan == GE_PLAN_SPLITK || opt_force_config() != FORCE_NONE) return false;
     // 256 rows along k, or 32 along M or N
     if ((long long)p.lda * (p.transA ? 512 : 64) + 1024 >= (1ll << 31) || (long long)p.ldb * (p.transB ? 64 : 512) + 1024 >= (1ll << 31)) return false;
-    return ge::small_tile_takes((long long)ceil_div(p.M, 32) * ceil_div(p.N, 32) * p.batch, pl.splitK, p.K, pl.tile == TILE_RAGGED_64,
-                                p.cType == ge::DT_F32 && p.R == nullptr);
+    const bool oddA = ((uintptr_t)p.A & 2u) != 0 || (p.lda & 1), oddB = ((uintptr_t)p.B & 2u) != 0 || (p.ldb & 1);
+    return ge::small_tile_takes((long long)ceil_div(p.M, 32) * ceil_div(p.N, 32) * p.batch, pl.splitK, p.K, pl.tile == TILE_RAGGED_64, p.transA != 0,
+                                p.cType == ge::DT_F32 && ge::small_odd_rows(p.transA != 0, oddA, oddB, p.R != nullptr));
 }
 
 size_t partial_bytes(int M, int N, int batch, int splitK)

@@ -31,21 +31,27 @@ GE_HD constexpr void small_place(int j, int w, int lane, int &r, int &c, int &at
     }
 }
 
+// Whether rows at odd elements make fp32 results of any alignment and 257 to 320 k, the first of a second step of 256, the slower ones in 32 x 32 tiles: every chunk of them costs
+// twice the look-ups, and the second step brings in as many as the first.  1800 drawn calls, of the time on the 64 x 64 tile with and without such rows: without a residual, A stored K x M odd 1.03 to
+// 1.07, else 0.95 to 0.99, M x K with both odd 1.03, else 0.95 to 1.00 (199 x 465 x 273, A K x M, B N x K, 5.3 / 5.8; 277 x 842 x 269 5.3 / 5.7; 38 x 618 x 320 5.35 / 4.9); with one, A K x M with both odd 1.02 and
+// 1.00, else 0.94 to 0.99.  (bf16 out 0.95 to 1.00, in one call of thirty above 1.03, to 1.08.)
+GE_HD constexpr bool small_odd_rows(bool transA, bool oddA, bool oddB, bool residual) { return transA ? oddA && (oddB || !residual) : oddA && oddB && !residual; }
+
 // Whether a product whose plan names the 128 x 128 tile or (ragged) the 64 x 64 one of gemm_ragged.h goes to workgroups in 32 x 32 tiles: tiles of those,
-// K slices of the plan, K; bareF32: fp32 out and no residual.  Up to one tile to a CU it does: us, plan's tile / small, 192 x 312 x 640 6.5 / 5.0, 264 x 232 x 1920 12.5 / 8.6 (B N x K,
+// K slices of the plan, K; oddRows: fp32 out with rows as above.  Up to one tile to a CU it does: us, plan's tile / small, 192 x 312 x 640 6.5 / 5.0, 264 x 232 x 1920 12.5 / 8.6 (B N x K,
 // bf16 out, 11.9 / 7.7), 72 x 1096 x 1160 9.0 / 6.2, 200^3 5.8 / 3.7, 512^3 5.8 / 4.9; over 21000 drawn calls 0.72 of the time on average.  Not where the 64 x 64 tile has
-// one 64-k step, for which it has a kernel of its own (533 x 416 x 47 3.6 / 4.0), or five and fp32 goes out without a residual (257 to 320 k, of 1800 drawn calls
-// 1.00 with three in ten above 1.03: 277 x 842 x 269 5.3 / 5.7, A stored K x M, B N x K 199 x 465 x 273 5.3 / 5.8; with a residual 0.95 to 0.96, bf16 out 0.90 to 0.94, six steps 0.93).
+// one 64-k step, for which it has a kernel of its own (533 x 416 x 47 3.6 / 4.0).
 // Beyond that only what is over in one step of 256, which has no walk to wait in: more than 128 k, up to two tiles a CU beside the 64 x 64 tile
-// (0.83 to 0.97 of its time) or three beside the 128 x 128 one (0.7 to 0.98; four 1.1); more than 64 k, two beside the latter (0.8 to 0.94; K <= 64 1.02; 640^3, 400 tiles, 6.5 / 6.9).
+// (0.83 to 0.98 of its time) or three beside the 128 x 128 one (0.7 to 0.98; four 1.1); more than 64 k, two beside the latter (0.8 to 0.94; K <= 64 1.02; 640^3, 400 tiles, 6.5 / 6.9).
 // In place of K slices, which cost a second launch and its round trip, where one walk over K is the shorter way: 512 x 512 x 2048, four slices, 10.9 / 8.9, 44 x 690 x
-// 1109 8.8 / 6.3; aligned operands, whose slices are the longer kernel's, up to four slices, short of 2560 k (1900 drawn calls from 2496 on 0.79 to 0.87; 250 of 2560, five, 0.99 to 1.04: 280 x 168 with A stored
-// K x M 10.8 / 12.4, 24 x 24 8.9 / 9.6), the others up to 1536 (36 x 71 x 1653 8.5 / 9.5; 40 x 1678 x 2119 9.1 / 10.9).
+// 1109 8.8 / 6.3; aligned operands, whose slices are the longer kernel's, up to four of them (1900 drawn calls of 2496 to 2552 k 0.79 to 0.87, A K x M in one of a hundred 1.03 to 1.09), and five where
+// their second pass has much to add up (26000 drawn calls of 2560 k: A M x K up to 64 tiles 1.00 to 1.06, then 0.86 to 0.97; A K x M up to 192 0.97 to 1.05 with single ones 1.2, then 0.94 to 0.95; 24 x 24 8.9 / 9.6, 280 x
+// 168 with A K x M 10.8 / 12.4, 128 x 1464 12.5 / 10.3); the others up to 1536 (36 x 71 x 1653 8.5 / 9.5; 40 x 1678 x 2119 9.1 / 10.9).
 constexpr int SMALL_CUS = 256;
-GE_HD constexpr bool small_tile_takes(long long tiles, int slices, int K, bool ragged, bool bareF32)
+GE_HD constexpr bool small_tile_takes(long long tiles, int slices, int K, bool ragged, bool transA, bool oddRows)
 {
-    if (slices > 1) return tiles <= SMALL_CUS && (ragged ? K <= 1536 : K < 2560);
-    if (ragged && (K <= 64 || (bareF32 && K > SMALL_STEP && K <= 320))) return false;
+    if (slices > 1) return tiles <= SMALL_CUS && (ragged ? K <= 1536 : K < 2560 || (K == 2560 && tiles > (transA ? 192 : 64)));
+    if (ragged && (K <= 64 || (oddRows && K > SMALL_STEP && K <= 320))) return false;
     if (tiles <= SMALL_CUS) return true;
     if (K > SMALL_STEP || K <= 64) return false;
     return K > 128 ? tiles <= (ragged ? 2 : 3) * SMALL_CUS : !ragged && tiles <= 2 * SMALL_CUS;

@@ -129,19 +129,23 @@ int main()
                 run<false>(X, K, K + pad);
                 run<true>(X, K, X + pad);
             }
-    // tiles, slices of the plan, K, 64 x 64 tile of the plan, whether the kernel takes it; and whether with fp32 out and no residual, where that differs
-    struct { long long tiles; int slices, K; bool ragged, takes; int bareF32 = -1; } rule[] = {
+    // tiles, slices of the plan, K, 64 x 64 tile of the plan, whether the kernel takes it; and whether with rows that are slow to it, or with A stored K x M, where that differs
+    struct { long long tiles; int slices, K; bool ragged, takes; int oddRows = -1, transA = -1; } rule[] = {
         {60, 1, 640, true, true}, {256, 1, 8192, false, true}, {257, 1, 257, false, false}, {257, 1, 256, false, true}, {768, 1, 136, false, true},
         {769, 1, 136, false, false}, {512, 1, 128, false, true}, {513, 1, 128, false, false}, {257, 1, 64, false, false}, {256, 1, 64, false, true}, {1, 1, 8, false, true},
         {4, 1, 64, true, false}, {4, 1, 65, true, true}, {512, 1, 136, true, true}, {513, 1, 136, true, false}, {257, 1, 128, true, false},
-        {72, 3, 1536, true, true}, {72, 3, 1537, true, false}, {72, 4, 2552, false, true}, {72, 5, 2560, false, false}, {4, 1, 256, true, true}, {4, 1, 257, true, true, 0}, {256, 1, 320, true, true, 0}, {4, 1, 321, true, true},
+        {72, 3, 1536, true, true}, {72, 3, 1537, true, false}, {72, 4, 2552, false, true}, {65, 5, 2560, false, true, -1, 0}, {64, 5, 2560, false, false}, {193, 5, 2560, false, true}, {192, 5, 2560, false, true, -1, 0}, {4, 1, 256, true, true}, {4, 1, 257, true, true, 0}, {256, 1, 320, true, true, 0}, {4, 1, 321, true, true},
         {257, 1, 256, true, true}, {4, 1, 300, false, true}, {257, 2, 2048, false, false}};
     for (auto &c : rule)
-        for (bool bare : {false, true})
-            if (small_tile_takes(c.tiles, c.slices, c.K, c.ragged, bare) != (bare && c.bareF32 >= 0 ? c.bareF32 != 0 : c.takes)) {
-                std::printf("rule: %lld tiles, %d slices, K %d, ragged %d, bare fp32 %d\n", c.tiles, c.slices, c.K, c.ragged, bare);
-                return 1;
-            }
+        for (bool odd : {false, true})
+            for (bool transA : {false, true})
+                if (small_tile_takes(c.tiles, c.slices, c.K, c.ragged, transA, odd) != (odd && c.oddRows >= 0 ? c.oddRows != 0 : transA && c.transA >= 0 ? c.transA != 0 : c.takes)) {
+                    std::printf("rule: %lld tiles, %d slices, K %d, ragged %d, odd rows %d, A K x M %d\n", c.tiles, c.slices, c.K, c.ragged, odd, transA);
+                    return 1;
+                }
+    // rows at odd elements: M x K both (6), K x M A's (3, 7), with a residual both (15)
+    for (int bits = 0; bits < 16; ++bits)
+        if (small_odd_rows(bits & 1, bits & 2, bits & 4, bits & 8) != (bits == 3 || bits == 6 || bits == 7 || bits == 15)) return 1;
     struct { long long tiles; int slices, K; bool c8, takes; int bareF32 = -1; } conv[] = {{256, 1, 32, false, true}, {257, 1, 40, true, true, 0}, {512, 1, 32, false, true, 0}, {257, 1, 48, true, true},
         {768, 1, 128, false, true, 0}, {513, 1, 136, false, true}, {512, 1, 27 * 8, true, true}, {512, 1, 64, false, true}, {513, 1, 64, false, false}, {513, 1, 72, false, true, 0},
         {1024, 1, 136, false, true}, {1025, 1, 136, true, false}, {768, 1, 288, false, false}, {768, 1, 288, true, true}, {768, 1, 1152, false, true}, {769, 1, 1152, true, false},
