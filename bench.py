@@ -69,14 +69,14 @@ _F32 = ("bf16_layout.h", "ge_device.h", "gemm_f32_fast.h")
 # workload -> (kernel configuration, FETCH_SIZE KiB, WRITE_SIZE KiB, source files, their hash)
 # TRAFFIC-BEGIN (rows written from the counter runs; see profiles/)
 TRAFFIC = {
-    "c1_f32_256": ("f32_few_16x16x256", 807, 256, ('bf16_layout.h', 'ge_device.h', 'gemm_f32_few.h', 'ragged_layout.h', 'small_layout.h'), "ca02b34cf01675a0"),
+    "c1_f32_256": ("f32_few_16x16x256", 807, 256, ('bf16_layout.h', 'ge_device.h', 'gemm_f32_few.h', 'ragged_layout.h', 'small_layout.h'), "1f78df3650b6df68"),
     "c2_bf16_4096": ("bf16_256x256x64_w4", 98447, 65536, _MAIN_W4, "22b85d300136d772"),
     "c3_bf16_8192_bias_gelu": ("bf16_256x256x64_w4", 792297, 262146, _MAIN_W4, "22b85d300136d772"),
     "c4_bf16_batched_512x512x64": ("bf16_256x256x32_w8", 16479, 262162, _MAIN_W8, "18418acf8263dcf2"),
     "c5_bf16_splitk_1024x1024x65536": ("bf16_256x256x64_w4_splitk", 131219, 65536, _MAIN_W4, "22b85d300136d772"),
     "c6_fused_nt_8192_bias_gelu_bf16out": ("bf16_fused_256x256x64_w4_nt", 790443, 131174, _MAIN_W4, "22b85d300136d772"),
     "c7_fused_tn_8192_chain": ("bf16_fused_256x256x32_w8_tn", 852380, 131072, _MAIN_W8, "18418acf8263dcf2"),
-    "c8_fused_batched_512x512x64_bf16out": ("bf16_fused_128x128_k64_w4_nn", 16480, 131072, _MAIN_W8 + ("gemm_tile64_launch.h", "gemm_tile64_short.hip", "gemm_tile64_tiles.h", "small_layout.h"), "e64a60444940f845"),
+    "c8_fused_batched_512x512x64_bf16out": ("bf16_fused_128x128_k64_w4_nn", 16480, 131072, _MAIN_W8 + ("gemm_tile64_launch.h", "gemm_tile64_short.hip", "gemm_tile64_tiles.h", "small_layout.h"), "df7c4665837cff5f"),
     "c9_diag_bf16_8192": ("diag_rows_vec4", 65964, 262666, ('gemm_diag.hip',), "95489dc912964713"),
     "c10_conv3x3_256_bf16out": ("conv_bf16_halo_3x3_w4_14_11", 60946, 50176, ('bf16_layout.h', 'conv_halo.h', 'conv_halo_launch.h', 'conv_halo_layout.h', 'ge_device.h', 'gemm_bf16_fast.h'), "b41bc798f4ef9cba"),
     "c11_fused_lower_8192_bias_relu": ("bf16_fused_256x256x64_w4_nn", 654644, 262144, _MAIN_W4, "22b85d300136d772"),

@@ -16,6 +16,9 @@ traffic of every kernel of the call counted (a split plan pays for its partial t
                                                                (--write: into csrc/plan_rates.h; --json: the record)
     python -m paper_2604_01489_amd.tune --write-rates FILE     csrc/plan_rates.h from such a record
 
+Calls of few tiles or a short K go from their plan to kernels that no structure of the search names, and that a forced
+tile keeps them from: these are timed as the library's own choice alone.
+
 It is a tool for checking the fixed planning rules (and for callers who want to pass ``plan`` and
 ``split_k`` to ``gemm_epilogue_bf16_ex`` themselves), not part of the hot path.
 """
